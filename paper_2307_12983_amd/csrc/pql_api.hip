@@ -71,6 +71,9 @@ const char* kernel_name(int kid) {
         case KID_CHAIN_POLICY: return "chain_policy_kernel";
         case KID_CHAIN_ACT: return "chain_act_kernel";
         case KID_FUSED_ACT16: return "fused_act16_kernel";
+        case KID_SPLIT_WEIGHTS: return "split_weights_kernel";
+        case KID_SPLIT_CRITIC: return "split_critic_kernel";
+        case KID_SPLIT_POLICY: return "split_policy_kernel";
         default: return "?";
     }
 }
@@ -254,35 +257,78 @@ struct Layout {
     size_t mu2a, logp, epsb, dOut, p_sc, p_lp;                        // stochastic policy: outputs, log pi, draws, gradient, partials
     size_t sqp;                                                       // per-workgroup sums of squared gradients
     size_t xn;                                                        // standardised Actor observations
+    size_t split;                                                     // weights in fragment order (row-tile kernels on fp16 pairs)
     size_t total;
 };
 
-// The row-tile fused kernels apply when every hidden layer is a multiple of 32 and at most
-// FUSED_MAXW wide, the action vector fits one MFMA tile and the tile's LDS footprint fits a CU.
-bool fused_ok(const pql_config* c) {
-    int hmax = 0;
-    for (int l = 0; l < c->n_hidden; ++l) {
-        if (c->hidden[l] % 32 != 0 || c->hidden[l] > FUSED_MAXW) return false;
-        hmax = c->hidden[l] > hmax ? c->hidden[l] : hmax;
-    }
-    const int aw = actor_out(c);                  // the policy's output columns share one 32-column tile
-    if (aw > FUSED_MAX_ACT || c->obs_dim > 1024) return false;
-    if (distributional(c) && hmax < 64) return false;   // the dlogits of a row tile borrow 64 columns of an activation tile
-    return fused_lds_bytes(c->obs_dim, aw, hmax) <= 160 * 1024;
-}
-// The row-tile chain kernels take networks with a layer too wide for the kernels above (up to 512 columns),
-// scalar critics and a deterministic policy, once the batch has a row tile for at least half the compute
-// units (below that the LDS-tiled kernels, which spread one layer over more workgroups, are the better fit).
-constexpr int CHAIN_MIN_TILES = 128;
-bool chain_ok(const pql_config* c, int rows) {
-    if (fused_ok(c) || distributional(c) || c->stochastic_policy) return false;
-    if ((rows + FUSED_BM - 1) / FUSED_BM < CHAIN_MIN_TILES) return false;
-    return chain_shape_ok(c->obs_dim, c->act_dim, c->hidden, c->n_hidden);
-}
 int max_hidden(const pql_config* c) {
     int hmax = 0;
     for (int l = 0; l < c->n_hidden; ++l) hmax = c->hidden[l] > hmax ? c->hidden[l] : hmax;
     return hmax;
+}
+// Which kernels take an update of `rows` batch rows.  Layers up to 256 columns wide in multiples of 32: the fused row-tile
+// kernels, whatever the batch.  A widest layer of 512, scalar critics, deterministic policy, and a row tile for at least
+// half the compute units: the chain kernels.  Other shapes (any widths up to 1024) run in one launch per step as well,
+// between two bounds.  Below, the launch has too few workgroups: each streams all weights by itself (about 50 GB/s), where a
+// launch per layer spreads them over the chip.  Measured per critic update, one launch against a launch per layer:
+// 1024-512-256 at 64 / 520 / 2048 / 8000 rows 399 / 415 / 450 / 685 us against 276 / 309 / 466 / 1029; 512-512-512
+// 290 / 304 / 342 / 498 against 260 / 276 / 400 / 839; 300-136-128 118 / 123 / 130 / 187 against 147 / 154 / 174 / 260: the
+// line is at 2048 rows, and at no batch for critics of up to 2^18 weights.  Above (256 row tiles), every layer's launch has
+// enough work of its own, unless the variant has steps that only the one-launch kernels have on the 16-bit matrix cores.
+constexpr int CHAIN_MIN_TILES = 128;
+constexpr int LAYERED_MIN_TILES = 256;
+constexpr int SPLIT_MIN_TILES = 64;
+constexpr int64_t SPLIT_ANY_TILES_WEIGHTS = 1 << 18;
+bool chain_shape_ok(const pql_config* c) {
+    if (distributional(c) || c->stochastic_policy) return false;
+    for (int l = 0; l < c->n_hidden; ++l)
+        if (c->hidden[l] % 32 != 0 || (c->hidden[l] > 256 && c->hidden[l] != 512)) return false;
+    return c->hidden[c->n_hidden - 1] <= 256;
+}
+bool split_ok(const pql_config* c) {
+    return split_shape_ok(c->obs_dim, c->act_dim, actor_out(c), c->hidden, c->n_hidden, distributional(c));
+}
+bool fused_ok(const pql_config* c) {
+    for (int l = 0; l < c->n_hidden; ++l)
+        if (c->hidden[l] % 32 != 0 || c->hidden[l] > FUSED_MAXW) return false;
+    return split_ok(c);
+}
+enum Family : int { FAM_LAYERED = -1, FAM_FUSED = SPLIT_FUSED, FAM_CHAIN = SPLIT_CHAIN, FAM_SPLIT = SPLIT_OTHER };
+int family(const pql_config* c, int rows) {
+    if (!split_ok(c)) return FAM_LAYERED;
+    if (fused_ok(c)) return FAM_FUSED;
+    const int tiles = (rows + FUSED_BM - 1) / FUSED_BM;
+    if (tiles >= CHAIN_MIN_TILES && chain_shape_ok(c)) return FAM_CHAIN;
+    if (tiles < SPLIT_MIN_TILES && pql_critic_param_count(c) > SPLIT_ANY_TILES_WEIGHTS) return FAM_LAYERED;
+    const bool plain = !distributional(c) && !c->stochastic_policy;
+    return tiles < LAYERED_MIN_TILES || (!plain && max_hidden(c) <= 512) ? FAM_SPLIT : FAM_LAYERED;
+}
+// The Actor step where fused_act16_kernel (16-row tiles, up to 4096 environments) does not apply: the row-tile kernels on
+// prepared weights for the shapes of the fused and chain kernels, else layer by layer.
+int act_family(const pql_config* c, int rows) {
+    if (fused_ok(c)) return FAM_FUSED;
+    const bool narrow = split_shape_ok(c->obs_dim, c->act_dim, actor_out(c), c->hidden, c->n_hidden);
+    return narrow && chain_shape_ok(c) && (rows + FUSED_BM - 1) / FUSED_BM >= CHAIN_MIN_TILES ? FAM_CHAIN : FAM_LAYERED;
+}
+// Floats of prepared weights that one call can need (the critic step's or the policy step's, whichever is larger).
+size_t split_floats(const pql_config* c) {
+    const int L = c->n_hidden, o = c->obs_dim, a = c->act_dim, aw = actor_out(c);
+    size_t pi = up(split_mat_floats(o, c->hidden[0])), q = up(split_mat_floats(o + a, c->hidden[0])), qT = 0;
+    size_t waT = up(split_mat_floats(aw, c->hidden[L - 1]));
+    for (int l = 1; l < L; ++l) {
+        const size_t f = up(split_mat_floats(c->hidden[l - 1], c->hidden[l])), b = up(split_mat_floats(c->hidden[l], c->hidden[l - 1]));
+        pi += f; q += f; qT += b; waT += b;
+    }
+    pi += up(split_mat_floats(c->hidden[L - 1], aw));
+    size_t vec = up((size_t)c->hidden[L - 1] + 31);       // output weights of a scalar critic, padded
+    if (distributional(c)) {
+        q += up(split_mat_floats(c->hidden[L - 1], c->num_atoms));
+        qT += up(split_mat_floats(c->num_atoms, c->hidden[L - 1]));
+        vec = 0;
+    }
+    const size_t critic = pi + 4 * q + 2 * qT + 4 * vec;
+    const size_t policy = pi + waT + 2 * (q + qT + up(split_mat_floats(c->hidden[0], a)) + vec);
+    return critic > policy ? critic : policy;
 }
 
 inline long dw_tiles(int M, int N) { return (long)((M + 63) / 64) * ((N + 63) / 64); }
@@ -311,7 +357,8 @@ size_t splitk_floats(const pql_config* c, int B) {
     return sc > sa ? sc : sa;
 }
 
-void make_layout(const pql_config* c, Layout& w) {
+// with_split = false: without room for prepared weights (the calls then take the other kernels).
+void make_layout(const pql_config* c, Layout& w, bool with_split = true) {
     std::memset(&w, 0, sizeof(w));
     const int L = c->n_hidden;
     const size_t B = (size_t)c->max_batch;
@@ -327,10 +374,22 @@ void make_layout(const pql_config* c, Layout& w) {
         w.dA[l] = take(B * h);
         w.colA[l] = take(crow * h);
         for (int i = 0; i < 2; ++i) {
-            w.hT[i][l] = take(B * h);
             w.hQ[i][l] = take(B * h);
             w.dQ[i][l] = take(B * h);
             w.colQ[i][l] = take(crow * h);
+        }
+    }
+    // the target critics' activations (layer-by-layer path) and the prepared weights (row-tile kernels on fp16 pairs) are
+    // never needed by the same call: they share their place
+    {
+        const size_t at = off;
+        for (int l = 1; l <= L; ++l)
+            for (int i = 0; i < 2; ++i) w.hT[i][l] = take(B * (size_t)c->hidden[l - 1]);
+        w.split = 0;
+        if (with_split && split_ok(c)) {
+            w.split = at;
+            const size_t need = split_floats(c);
+            if (off - at < need) off = at + up(need);
         }
     }
     w.colA[L + 1] = take(crow * (size_t)actor_out(c));
@@ -395,6 +454,22 @@ void make_cache_layout(const pql_config* c, CacheLayout& w) {
     for (int l = 1; l <= L; ++l) w.waT[l] = take((size_t)c->hidden[l - 1] * (l < L ? c->hidden[l] : actor_out(c)));
     w.total = off;
 }
+
+// Collects the matrices a call needs in fragment order; their places run through the workspace block for them.  Sources
+// are named by the parameter vector they lie in (`from`) and an offset.
+struct SplitPrep {
+    SplitPrepArgs args;
+    float* block;
+    int at;
+    explicit SplitPrep(float* b) : block(b), at(0) { args.n = 0; args.dst = b; args.src[0] = args.src[1] = args.src[2] = nullptr; }
+    const float* add(int from, int64_t src, int64_t bias, int K, int N, int kind) {
+        SplitPrepArgs::Mat& m = args.m[args.n++];
+        m.src = (int)src; m.bias = (int)bias; m.dst = at; m.K = (uint16_t)K; m.N = (uint16_t)N;
+        m.kind = (uint8_t)kind; m.from = (uint8_t)from; m.pad_ = 0;
+        at += (int)up(kind == SPLIT_VECTOR ? (size_t)(N + 31) / 32 * 32 : split_mat_floats(K, N));
+        return block + m.dst;
+    }
+};
 
 inline int vec_ok(const float* p, int ld) { return ((((uintptr_t)p) & 15) == 0 && (ld % 4) == 0) ? 1 : 0; }
 
@@ -805,6 +880,38 @@ static GemmProb critic_layer(pql_ctx* c, const float* params, int l, const float
     return p;
 }
 
+static void fill_shape(const pql_ctx* c, SplitShape& p) {
+    p.o = c->cfg.obs_dim; p.a = c->cfg.act_dim; p.L = c->L;
+    for (int l = 0; l < c->L; ++l) p.H[l] = c->cfg.hidden[l];
+}
+// The policy's layers 0..L and a critic's hidden layers 0..L-1 in fragment order (`base`: where the critic begins).
+static void add_policy(const pql_ctx* c, SplitPrep& prep, int from, const float** out) {
+    for (int l = 0; l <= c->L; ++l) {
+        const int K = l == 0 ? c->cfg.obs_dim : c->cfg.hidden[l - 1], N = l < c->L ? c->cfg.hidden[l] : actor_out(&c->cfg);
+        out[l] = prep.add(from, c->a_w[l], c->a_b[l], K, N, SPLIT_PLAIN);
+    }
+}
+static void add_critic(const pql_ctx* c, SplitPrep& prep, int from, int64_t base, const float** out) {
+    for (int l = 0; l < c->L; ++l) {
+        const int K = l == 0 ? c->cfg.obs_dim + c->cfg.act_dim : c->cfg.hidden[l - 1], N = c->cfg.hidden[l];
+        out[l] = prep.add(from, base + c->c_w[l], base + c->c_b[l], K, N, SPLIT_PLAIN);
+    }
+    if (distributional(&c->cfg))
+        out[c->L] = prep.add(from, base + c->c_w[c->L], SPLIT_NO_BIAS, c->cfg.hidden[c->L - 1], c->cfg.num_atoms, SPLIT_PLAIN);
+}
+// The transposes of its layers 1..L-1 (with distributional critics also L) for the backward products.
+static void add_critic_back(const pql_ctx* c, SplitPrep& prep, int from, int64_t base, const float** out) {
+    for (int l = 1; l < c->L; ++l)
+        out[l] = prep.add(from, base + c->c_w[l], SPLIT_NO_BIAS, c->cfg.hidden[l], c->cfg.hidden[l - 1], SPLIT_TRANSPOSED);
+    if (distributional(&c->cfg))
+        out[c->L] = prep.add(from, base + c->c_w[c->L], SPLIT_NO_BIAS, c->cfg.num_atoms, c->cfg.hidden[c->L - 1], SPLIT_TRANSPOSED);
+}
+// The output weights of a scalar critic, padded with zeros to whole tiles.
+static const float* add_output(const pql_ctx* c, SplitPrep& prep, int from, int64_t base) {
+    if (distributional(&c->cfg)) return nullptr;
+    return prep.add(from, base + c->c_w[c->L], SPLIT_NO_BIAS, 1, c->cfg.hidden[c->L - 1], SPLIT_VECTOR);
+}
+
 int32_t pql_actor_act(pql_ctx* c, const float* actor_params, const float* obs, int32_t num, float sigma_min,
                       float sigma_max, float* act_out, void* workspace, void* stream) {
     if (!c) return PQL_ERR_NULL;
@@ -817,8 +924,7 @@ int32_t pql_actor_act(pql_ctx* c, const float* actor_params, const float* obs, i
     float* ws = (float*)workspace;
     Layout w;
     make_layout(&c->cfg, w);
-    const bool chain = chain_ok(&c->cfg, num);
-    if (fused_ok(&c->cfg) || chain) {
+    if (fused_ok(&c->cfg)) {
         FusedActArgs fa;
         std::memset(&fa, 0, sizeof(fa));
         fa.B = num; fa.o = c->cfg.obs_dim; fa.a = c->cfg.act_dim; fa.L = c->L; fa.hmax = max_hidden(&c->cfg);
@@ -833,9 +939,34 @@ int32_t pql_actor_act(pql_ctx* c, const float* actor_params, const float* obs, i
         fa.noise.key0 = (uint32_t)(c->cfg.seed & 0xffffffffu); fa.noise.key1 = (uint32_t)(c->cfg.seed >> 32);
         fa.noise.ctr2 = (uint32_t)((uint64_t)c->acts & 0xffffffffu); fa.noise.ctr3 = (uint32_t)((uint64_t)c->acts >> 32);
         fa.sac = fused_sac(c, 2u, c->acts, nullptr);
-        // up to 4096 environments the 32-row tiles leave compute units idle: 16-row tiles where that kernel applies
-        const hipError_t fe = chain ? chain_act_launch(fa, st) : (act16_ok(fa) ? fused_act16_launch(fa, st) : fused_act_launch(fa, st));
-        if (fe != hipSuccess) return E.hip(fe, "pql_actor_act");
+        if (act16_ok(fa)) {
+            const hipError_t fe = fused_act16_launch(fa, st);
+            if (fe != hipSuccess) return E.hip(fe, "pql_actor_act");
+            c->acts += 1;
+            return PQL_OK;
+        }
+    }
+    const int fam = act_family(&c->cfg, num);
+    if (fam != FAM_LAYERED) {
+        SplitActArgs sa;
+        std::memset(&sa, 0, sizeof(sa));
+        fill_shape(c, sa.shape);
+        SplitPrep prep(ws + w.split);
+        prep.args.src[0] = actor_params;
+        add_policy(c, prep, 0, sa.pi);
+        sa.B = num; sa.pi_bias = actor_params + c->a_b[c->L];
+        sa.obs = obs; sa.act_out = act_out;
+        if (c->obs_norm) {
+            const ObsStatsView ov = obs_stats_view(c->obs_norm, c->cfg.obs_dim);
+            sa.nmean = ov.mean_f; sa.nrstd = ov.rstd_f;
+        }
+        sa.noise.act_dim = c->cfg.act_dim; sa.noise.sigma_rows = num; sa.noise.sigma_min = sigma_min; sa.noise.sigma_max = sigma_max;
+        sa.noise.key0 = (uint32_t)(c->cfg.seed & 0xffffffffu); sa.noise.key1 = (uint32_t)(c->cfg.seed >> 32);
+        sa.noise.ctr2 = (uint32_t)((uint64_t)c->acts & 0xffffffffu); sa.noise.ctr3 = (uint32_t)((uint64_t)c->acts >> 32);
+        sa.sac = fused_sac(c, 2u, c->acts, nullptr);
+        hipError_t se = split_weights_launch(prep.args, fam == FAM_CHAIN ? KID_CHAIN_ACT : KID_FUSED_ACT, st);
+        if (se == hipSuccess) se = split_act_launch(sa, fam, st);
+        if (se != hipSuccess) return E.hip(se, "pql_actor_act");
         c->acts += 1;
         return PQL_OK;
     }
@@ -890,12 +1021,11 @@ static int32_t critic_update_check(pql_ctx* c, const float* critic_params, const
 // memory of at least pql_workspace_bytes(cfg) bytes, 256-byte aligned, whoever owns it.
 static int32_t critic_update_run(pql_ctx* c, float* critic_params, const float* critic_target_params,
                                  const float* actor_target_params, float* adam_m, float* adam_v, float* grads_out,
-                                 pql_batch batch, int32_t B, pql_adam opt, float* loss_out, void* workspace, void* stream) {
+                                 pql_batch batch, int32_t B, pql_adam opt, float* loss_out, void* workspace, void* stream,
+                                 const Layout& w) {
     Err E{c};
     hipStream_t st = (hipStream_t)stream;
     float* ws = (float*)workspace;
-    Layout w;
-    make_layout(&c->cfg, w);
     const int L = c->L, o = c->cfg.obs_dim, ad = c->cfg.act_dim, HL = c->cfg.hidden[L - 1];
     const int64_t Pc = c->c_total;
     hipError_t e;
@@ -907,63 +1037,46 @@ static int32_t critic_update_run(pql_ctx* c, float* critic_params, const float* 
     const bool dist = distributional(&c->cfg);
     // Transposed weights: from the caller's cache when it holds those of this parameter vector (then the
     // optimiser kernel refreshes them at the end of the call), else transposed into the workspace here.
+    const int fam = w.split != 0 ? family(&c->cfg, B) : FAM_LAYERED;
     const bool cached = c->wcache != nullptr && c->wcache_critic == critic_params;
     CacheLayout cl;
     make_cache_layout(&c->cfg, cl);
     auto WT = [&](int i, int l) { return cached ? c->wcache + cl.wT[i][l] : ws + w.wT[i][l]; };
     auto WOT = [&](int i) { return cached ? c->wcache + cl.woT[i] : ws + w.woT[i]; };
-    const bool chain = chain_ok(&c->cfg, B);
-    if (fused_ok(&c->cfg) || chain) {
-        // One launch per row tile: target path, forward, heads and backward data path.
-        TransposeArgs tr;
-        tr.n = 0;
-        FusedCriticArgs fa;
-        std::memset(&fa, 0, sizeof(fa));
-        fa.B = B; fa.o = o; fa.a = ad; fa.L = L; fa.nwg = (B + FUSED_BM - 1) / FUSED_BM; fa.hmax = max_hidden(&c->cfg);
-        for (int l = 0; l < L; ++l) fa.H[l] = c->cfg.hidden[l];
-        for (int l = 0; l <= L; ++l) {
-            fa.pi.w[l] = actor_target_params + c->a_w[l]; fa.pi.b[l] = actor_target_params + c->a_b[l];
-            for (int i = 0; i < 2; ++i) {
-                fa.qt[i].w[l] = critic_target_params + i * Pc + c->c_w[l]; fa.qt[i].b[l] = critic_target_params + i * Pc + c->c_b[l];
-                fa.q[i].w[l] = critic_params + i * Pc + c->c_w[l];        fa.q[i].b[l] = critic_params + i * Pc + c->c_b[l];
-            }
-        }
+    if (fam != FAM_LAYERED) {
+        // The weights into fragment order, then one launch per row tile: target path, forward, heads, backward data path.
+        SplitCriticArgs sa;
+        std::memset(&sa, 0, sizeof(sa));
+        fill_shape(c, sa.shape);
+        sa.B = B;
+        SplitPrep prep(ws + w.split);
+        prep.args.src[0] = actor_target_params; prep.args.src[1] = critic_target_params; prep.args.src[2] = critic_params;
+        add_policy(c, prep, 0, sa.pi);
+        sa.pi_bias = actor_target_params + c->a_b[L];
         for (int i = 0; i < 2; ++i) {
-            for (int l = 1; l < L; ++l) {
-                if (!cached) {
-                    TransposeArgs::Mat& mt = tr.m[tr.n++];
-                    mt.src = critic_params + i * Pc + c->c_w[l]; mt.dst = ws + w.wT[i][l];
-                    mt.rows = c->cfg.hidden[l - 1]; mt.cols = c->cfg.hidden[l];
-                }
-                fa.wT[i][l] = WT(i, l);
-            }
-            for (int l = 1; l <= L; ++l) {
-                fa.hQ[i][l] = ws + w.hQ[i][l]; fa.dQ[i][l] = ws + w.dQ[i][l]; fa.colQ[i][l] = ws + w.colQ[i][l];
-            }
-            fa.q_out[i] = ws + w.q[i];
-            fa.p_dw[i] = ws + w.p_dw[i]; fa.p_dbh[i] = ws + w.p_dbh[i]; fa.p_db[i] = ws + w.p_db[i];
+            const float *qt = critic_target_params + i * Pc, *q = critic_params + i * Pc;
+            add_critic(c, prep, 1, i * Pc, sa.qt[i]);
+            add_critic(c, prep, 2, i * Pc, sa.q[i]);
+            add_critic_back(c, prep, 2, i * Pc, sa.qT[i]);
+            sa.wo_t[i] = add_output(c, prep, 1, i * Pc);
+            sa.wo_q[i] = add_output(c, prep, 2, i * Pc);
+            sa.bo_t[i] = qt + c->c_b[L]; sa.bo_q[i] = q + c->c_b[L];
+            for (int l = 1; l <= L; ++l) { sa.h[i][l] = ws + w.hQ[i][l]; sa.d[i][l] = ws + w.dQ[i][l]; sa.col[i][l] = ws + w.colQ[i][l]; }
+            sa.q_out[i] = ws + w.q[i];
+            if (dist) { sa.dlg[i] = ws + w.lgQ[i]; sa.p_dbo[i] = ws + w.p_dbo[i]; }
+            sa.p_dw[i] = ws + w.p_dw[i]; sa.p_dbh[i] = ws + w.p_dbh[i]; sa.p_db[i] = ws + w.p_db[i];
         }
-        fa.obs = batch.obs; fa.act = batch.act; fa.ret = batch.ret; fa.next_obs = batch.next_obs; fa.boot = batch.boot;
-        fa.y = ws + w.y; fa.p_loss = ws + w.p_loss;
-        fa.sac = fused_sac(c, 4u, c->critic_t, c->temperature_v);
-        if (dist) {
-            fa.atoms = c->cfg.num_atoms; fa.v_min = c->cfg.v_min; fa.v_max = c->cfg.v_max;
-            for (int i = 0; i < 2; ++i) {
-                if (!cached) {
-                    TransposeArgs::Mat& mt = tr.m[tr.n++];
-                    mt.src = critic_params + i * Pc + c->c_w[L]; mt.dst = ws + w.woT[i]; mt.rows = HL; mt.cols = fa.atoms;
-                }
-                fa.woT[i] = WOT(i); fa.dlg[i] = ws + w.lgQ[i]; fa.p_dbo[i] = ws + w.p_dbo[i];
-            }
-        }
-        if ((e = transpose_launch(tr, st)) != hipSuccess) return E.hip(e, who);
-        if ((e = chain ? chain_critic_launch(fa, st) : fused_critic_launch(fa, st)) != hipSuccess) return E.hip(e, who);
-        head_parts = fa.nwg;
-        for (int i = 0; i < 2; ++i) {
+        sa.obs = batch.obs; sa.act = batch.act; sa.ret = batch.ret; sa.next_obs = batch.next_obs; sa.boot = batch.boot;
+        sa.y = ws + w.y; sa.p_loss = ws + w.p_loss;
+        if (dist) { sa.atoms = c->cfg.num_atoms; sa.v_min = c->cfg.v_min; sa.v_max = c->cfg.v_max; }
+        sa.sac = fused_sac(c, 4u, c->critic_t, c->temperature_v);
+        if ((e = split_weights_launch(prep.args, KID_SPLIT_WEIGHTS, st)) != hipSuccess) return E.hip(e, who);
+        if ((e = split_critic_launch(sa, fam, st)) != hipSuccess) return E.hip(e, who);
+        head_parts = (B + FUSED_BM - 1) / FUSED_BM;
+        for (int i = 0; i < 2; ++i)
             for (int l = 1; l < L; ++l)
-                red(adm, i * Pc + c->c_b[l - 1], ws + w.colQ[i][l], c->cfg.hidden[l - 1], fa.nwg, c->cfg.hidden[l - 1]);
-            if (dist) red(adm, i * Pc + c->c_b[L - 1], ws + w.colQ[i][L], HL, fa.nwg, HL);
-        }
+                red(adm, i * Pc + c->c_b[l - 1], ws + w.colQ[i][l], c->cfg.hidden[l - 1], head_parts, c->cfg.hidden[l - 1]);
+        for (int i = 0; i < 2 && dist; ++i) red(adm, i * Pc + c->c_b[L - 1], ws + w.colQ[i][L], HL, head_parts, HL);
     } else {
         // 1. lagged policy pi^v on s' (hidden layers) together with the online critics on (s, a)
         for (int l = 1; l <= L; ++l) {
@@ -1161,8 +1274,10 @@ int32_t pql_critic_update(pql_ctx* c, float* critic_params, const float* critic_
                                            grads_out, batch, B, opt, loss_out);
     if (rc != PQL_OK) return rc;
     if (((uintptr_t)workspace) & 255) return E.fail(PQL_ERR_ALIGNMENT, "pql_critic_update: workspace not 256-byte aligned");
+    Layout w;
+    make_layout(&c->cfg, w);
     return critic_update_run(c, critic_params, critic_target_params, actor_target_params, adam_m, adam_v, grads_out, batch,
-                             B, opt, loss_out, workspace, stream);
+                             B, opt, loss_out, workspace, stream, w);
 }
 
 // ---- the same step on the library's own scratch --------------------------------------------
@@ -1182,6 +1297,8 @@ int32_t pql_critic_update_static(pql_ctx* c, float* critic_params, const float* 
     if (rc != PQL_OK) return rc;
     Layout w;
     make_layout(&c->cfg, w);
+    // a configuration that fits without the prepared weights only runs on the kernels that need none
+    if (w.total * sizeof(float) > STATIC_SCRATCH_BYTES) make_layout(&c->cfg, w, false);
     if (w.total * sizeof(float) > STATIC_SCRATCH_BYTES) {
         char msg[192];
         std::snprintf(msg, sizeof(msg), "pql_critic_update_static: this configuration needs %zu bytes of scratch, the static "
@@ -1193,7 +1310,7 @@ int32_t pql_critic_update_static(pql_ctx* c, float* critic_params, const float* 
     const hipError_t e = static_scratch_address(&ws);
     if (e != hipSuccess) return E.hip(e, "pql_critic_update_static: scratch address");
     return critic_update_run(c, critic_params, critic_target_params, actor_target_params, adam_m, adam_v, grads_out, batch,
-                             B, opt, loss_out, ws, stream);
+                             B, opt, loss_out, ws, stream, w);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1225,6 +1342,7 @@ int32_t pql_actor_update(pql_ctx* c, float* actor_params, const float* critic_pa
     const float* d_top = sac ? ws + w.dOut : ws + w.dPre;       // gradient at that layer
     int logp_parts = (B + SAC_ROWS - 1) / SAC_ROWS;             // partial sums of log pi (stochastic policy)
     // Transposed weights from the caller's cache where it holds those of these parameter vectors
+    const int fam = w.split != 0 ? family(&c->cfg, B) : FAM_LAYERED;
     const bool cached_q = c->wcache != nullptr && c->wcache_critic == critic_params;
     const bool cached_a = c->wcache != nullptr && c->wcache_actor == actor_params;
     CacheLayout cl;
@@ -1233,52 +1351,41 @@ int32_t pql_actor_update(pql_ctx* c, float* actor_params, const float* critic_pa
     auto W1AT = [&](int i) { return cached_q ? c->wcache + cl.w1aT[i] : ws + w.w1aT[i]; };
     auto WOT = [&](int i) { return cached_q ? c->wcache + cl.woT[i] : ws + w.woT[i]; };
     auto WAT = [&](int l) { return cached_a ? c->wcache + cl.waT[l] : ws + w.waT[l]; };
-    const bool chain = chain_ok(&c->cfg, B);
-    if (fused_ok(&c->cfg) || chain) {
-        TransposeArgs tr;
-        tr.n = 0;
-        FusedPolicyArgs fa;
-        std::memset(&fa, 0, sizeof(fa));
-        fa.B = B; fa.o = o; fa.a = ad; fa.L = L; fa.nwg = (B + FUSED_BM - 1) / FUSED_BM; fa.hmax = max_hidden(&c->cfg);
-        for (int l = 0; l < L; ++l) fa.H[l] = c->cfg.hidden[l];
-        for (int l = 0; l <= L; ++l) {
-            fa.pi.w[l] = actor_params + c->a_w[l]; fa.pi.b[l] = actor_params + c->a_b[l];
-            for (int i = 0; i < 2; ++i) { fa.q[i].w[l] = critic_params + i * Pc + c->c_w[l]; fa.q[i].b[l] = critic_params + i * Pc + c->c_b[l]; }
-        }
-        auto add_tr = [&](const float* src, float* dst, int rows, int cols) {
-            TransposeArgs::Mat& mt = tr.m[tr.n++];
-            mt.src = src; mt.dst = dst; mt.rows = rows; mt.cols = cols;
-        };
-        for (int i = 0; i < 2; ++i) {
-            for (int l = 1; l < L; ++l) {
-                if (!cached_q) add_tr(critic_params + i * Pc + c->c_w[l], ws + w.wT[i][l], c->cfg.hidden[l - 1], c->cfg.hidden[l]);
-                fa.wT[i][l] = WT(i, l);
-            }
-            if (!cached_q) add_tr(critic_params + i * Pc + c->c_w[0] + (int64_t)o * H1, ws + w.w1aT[i], ad, H1);
-            fa.w1aT[i] = W1AT(i);
-            for (int l = 1; l <= L; ++l) fa.hQ[i][l] = ws + w.hQ[i][l];
-            fa.q_out[i] = ws + w.q[i];
-            if (distributional(&c->cfg)) {
-                if (!cached_q) add_tr(critic_params + i * Pc + c->c_w[L], ws + w.woT[i], HL, c->cfg.num_atoms);
-                fa.woT[i] = WOT(i);
-            }
-        }
-        if (distributional(&c->cfg)) { fa.atoms = c->cfg.num_atoms; fa.v_min = c->cfg.v_min; fa.v_max = c->cfg.v_max; }
+    if (fam != FAM_LAYERED) {
+        SplitPolicyArgs sa;
+        std::memset(&sa, 0, sizeof(sa));
+        fill_shape(c, sa.shape);
+        sa.B = B;
+        SplitPrep prep(ws + w.split);
+        prep.args.src[0] = actor_params; prep.args.src[1] = critic_params;
+        add_policy(c, prep, 0, sa.pi);
+        sa.pi_bias = actor_params + c->a_b[L];
         for (int l = 1; l <= L; ++l) {
-            if (!cached_a) add_tr(actor_params + c->a_w[l], ws + w.waT[l], c->cfg.hidden[l - 1], l < L ? c->cfg.hidden[l] : aw);
-            fa.waT[l] = WAT(l);
-            fa.hA[l] = ws + w.hA[l]; fa.dA[l] = ws + w.dA[l]; fa.colA[l] = ws + w.colA[l];
+            const int K = l < L ? c->cfg.hidden[l] : aw;
+            sa.waT[l] = prep.add(0, c->a_w[l], SPLIT_NO_BIAS, K, c->cfg.hidden[l - 1], SPLIT_TRANSPOSED);
+            sa.hA[l] = ws + w.hA[l]; sa.dA[l] = ws + w.dA[l]; sa.colA[l] = ws + w.colA[l];
         }
-        fa.colA[L + 1] = ws + w.colA[L + 1];
-        fa.obs = obs; fa.dPre = const_cast<float*>(d_top); fa.p_loss = ws + w.p_loss;
-        fa.sac = fused_sac(c, 5u, c->actor_t, c->temperature);
-        fa.p_logp = sac ? ws + w.p_lp : nullptr;
-        if ((e = transpose_launch(tr, st)) != hipSuccess) return E.hip(e, who);
-        if ((e = chain ? chain_policy_launch(fa, st) : fused_policy_launch(fa, st)) != hipSuccess) return E.hip(e, who);
-        loss_parts = fa.nwg;
-        logp_parts = fa.nwg;
-        red(adm, c->a_b[L], ws + w.colA[L + 1], aw, fa.nwg, aw);
-        for (int l = 1; l <= L; ++l) red(adm, c->a_b[l - 1], ws + w.colA[l], c->cfg.hidden[l - 1], fa.nwg, c->cfg.hidden[l - 1]);
+        sa.colA[L + 1] = ws + w.colA[L + 1];
+        for (int i = 0; i < 2; ++i) {
+            const float* q = critic_params + i * Pc;
+            add_critic(c, prep, 1, i * Pc, sa.q[i]);
+            add_critic_back(c, prep, 1, i * Pc, sa.qT[i]);
+            sa.w1aT[i] = prep.add(1, i * Pc + c->c_w[0] + (int64_t)o * H1, SPLIT_NO_BIAS, H1, ad, SPLIT_TRANSPOSED);
+            sa.wo[i] = add_output(c, prep, 1, i * Pc);
+            sa.bo[i] = q + c->c_b[L];
+            for (int l = 1; l <= L; ++l) sa.h[i][l] = ws + w.hQ[i][l];
+            sa.q_out[i] = ws + w.q[i];
+        }
+        sa.obs = obs; sa.dPre = const_cast<float*>(d_top); sa.p_loss = ws + w.p_loss;
+        sa.sac = fused_sac(c, 5u, c->actor_t, c->temperature);
+        sa.p_logp = sac ? ws + w.p_lp : nullptr;
+        if (distributional(&c->cfg)) { sa.atoms = c->cfg.num_atoms; sa.v_min = c->cfg.v_min; sa.v_max = c->cfg.v_max; }
+        if ((e = split_weights_launch(prep.args, KID_SPLIT_WEIGHTS, st)) != hipSuccess) return E.hip(e, who);
+        if ((e = split_policy_launch(sa, fam, st)) != hipSuccess) return E.hip(e, who);
+        loss_parts = (B + FUSED_BM - 1) / FUSED_BM;
+        logp_parts = loss_parts;
+        red(adm, c->a_b[L], ws + w.colA[L + 1], aw, loss_parts, aw);
+        for (int l = 1; l <= L; ++l) red(adm, c->a_b[l - 1], ws + w.colA[l], c->cfg.hidden[l - 1], loss_parts, c->cfg.hidden[l - 1]);
     } else {
         // 1. a = pi(s), or the reparameterised sample a = tanh(mu + sigma eps)
         if ((e = actor_hidden_forward(c, actor_params, obs, B, ws, w, st)) != hipSuccess) return E.hip(e, who);

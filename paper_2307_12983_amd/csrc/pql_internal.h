@@ -21,7 +21,8 @@ enum KernelId : int {
     KID_FUSED_ACT = 24, KID_TRANSPOSE = 25, KID_ADAM_CLIP = 26, KID_OBS_STATS = 27, KID_OBS_MERGE = 28,
     KID_NORMALIZE = 29, KID_DIST_CRITIC = 30, KID_DIST_POLICY = 31, KID_SAC_SAMPLE = 32, KID_SAC_GRAD = 33,
     KID_SAC_ALPHA = 34, KID_MFMA_PROBE = 35, KID_LAYER_ROWTILE = 36, KID_NARROW_ROWTILE = 37, KID_CHAIN_CRITIC = 38,
-    KID_CHAIN_POLICY = 39, KID_CHAIN_ACT = 40, KID_FUSED_ACT16 = 41, KID_COUNT = 42
+    KID_CHAIN_POLICY = 39, KID_CHAIN_ACT = 40, KID_FUSED_ACT16 = 41, KID_SPLIT_WEIGHTS = 42, KID_SPLIT_CRITIC = 43,
+    KID_SPLIT_POLICY = 44, KID_COUNT = 45
 };
 const char* kernel_name(int kid);
 bool prof_active();
@@ -310,52 +311,6 @@ struct FusedNet {                   // per layer l = 0..L: weights W_l[in][out] 
     const float* b[PQL_MAX_HIDDEN + 1];
 };
 
-struct FusedCriticArgs {
-    int B, o, a, L, nwg, hmax;
-    int H[PQL_MAX_HIDDEN];
-    FusedNet pi;                    // lagged policy pi^v
-    FusedNet qt[2];                 // target critics
-    FusedNet q[2];                  // online critics
-    const float* wT[2][PQL_MAX_HIDDEN + 1];   // [i][l]: transpose of W_l of online critic i, l = 1..L-1
-    const float *obs, *act, *ret, *next_obs, *boot;
-    float* hQ[2][PQL_MAX_HIDDEN + 1];          // [i][l], l = 1..L-1: hidden activations (layer numbers from 1)
-    float* dQ[2][PQL_MAX_HIDDEN + 1];          // [i][l], l = 1..L: deltas
-    float* colQ[2][PQL_MAX_HIDDEN + 1];        // [i][l], l = 1..L-1: bias-gradient partials [nwg][H_l]
-    float* y; float* q_out[2];
-    float* p_dw[2]; float* p_dbh[2]; float* p_db[2]; float* p_loss;
-    FusedSac sac;                   // on: a' is a sample of pi^v and y carries the entropy term
-    // distributional critics (atoms >= 2): the last layer has `atoms` outputs
-    int atoms; float v_min, v_max;
-    const float* woT[2];            // transpose of the online critics' output weights: [atoms][H_L]
-    float* dlg[2];                  // [B][atoms] dLoss/dlogits (for the weight-gradient GEMM)
-    float* p_dbo[2];                // [nwg][atoms] partial sums of the output-bias gradient
-};
-hipError_t fused_critic_launch(const FusedCriticArgs& a, hipStream_t stream);
-size_t fused_lds_bytes(int o, int a, int hmax);
-
-struct FusedPolicyArgs {
-    int B, o, a, L, nwg, hmax;
-    int H[PQL_MAX_HIDDEN];
-    FusedNet pi;                    // policy being updated
-    FusedNet q[2];                  // online critics (read-only)
-    const float* wT[2][PQL_MAX_HIDDEN + 1];   // [i][l]: transpose of critic W_l, l = 1..L-1
-    const float* w1aT[2];                      // transpose of the action rows of critic W_0: [H_1][a]
-    const float* waT[PQL_MAX_HIDDEN + 1];      // [l]: transpose of policy W_l, l = 1..L
-    const float* obs;
-    float* hA[PQL_MAX_HIDDEN + 1];             // [l], l = 1..L: policy activations
-    float* dA[PQL_MAX_HIDDEN + 1];             // [l], l = 1..L: policy deltas
-    float* colA[PQL_MAX_HIDDEN + 2];           // [l], l = 1..L+1: bias-gradient partials [nwg][width]
-    float* hQ[2][PQL_MAX_HIDDEN + 1];          // [i][l], l = 1..L-1: critic activations (scratch for L > 2)
-    float* dPre;                               // [B][a] (stochastic policy: [B][2a]): delta at the policy's output layer
-    float* q_out[2];
-    float* p_loss;                             // [nwg]
-    FusedSac sac;                              // on: reparameterised sample, log-density terms in the gradient
-    float* p_logp;                             // [nwg] partial sums of log pi (stochastic policy)
-    int atoms; float v_min, v_max;             // distributional critics (atoms >= 2)
-    const float* woT[2];                       // transpose of the critics' output weights: [atoms][H_L]
-};
-hipError_t fused_policy_launch(const FusedPolicyArgs& a, hipStream_t stream);
-
 struct FusedActArgs {
     int B, o, a, L, hmax;
     int H[PQL_MAX_HIDDEN];
@@ -367,18 +322,98 @@ struct FusedActArgs {
     GemmNoise noise;
     FusedSac sac;                   // on: the action is a sample of the policy, `noise` is unused
 };
-hipError_t fused_act_launch(const FusedActArgs& a, hipStream_t stream);
 // The same step on 16-row tiles (pql_act16.hip), for up to 4096 environments.
 bool act16_ok(const FusedActArgs& a);
 hipError_t fused_act16_launch(const FusedActArgs& a, hipStream_t stream);
 
-// Row-tile chains for networks with layers up to 512 columns wide (pql_chain.hip): same argument blocks,
-// scalar critics and deterministic policy only.
-bool chain_shape_ok(int o, int a, const int* H, int L);
-size_t chain_lds_bytes(int o, int a, const int* H, int L);
-hipError_t chain_critic_launch(const FusedCriticArgs& a, hipStream_t stream);
-hipError_t chain_policy_launch(const FusedPolicyArgs& a, hipStream_t stream);
-hipError_t chain_act_launch(const FusedActArgs& a, hipStream_t stream);
+// ---- row-tile kernels on fp16 pairs (pql_split.hip) -----------------------------------------
+constexpr int SPLIT_MAXW = 1024;             // widest layer and input
+constexpr size_t SPLIT_LDS = 160 * 1024;
+enum SplitKind : int { SPLIT_PLAIN = 0, SPLIT_TRANSPOSED = 1, SPLIT_VECTOR = 2 };
+// Matrices (K x N) to bring into fragment order: element (k, n) is src[k * N + n], or src[n * K + k] (transposed); a vector
+// of N floats is only padded with zeros to a multiple of 32.  Records are kept small and their first workgroups apart: a
+// workgroup finds its record with one load per lane, not by walking the list.
+// Most entries: critic step with PQL_MAX_HIDDEN = 8 layers and distributional critics: policy 9, four critics 9 each, 8
+// transposes for each online critic.
+constexpr int SPLIT_MAX_MATS = 9 + 4 * 9 + 2 * 8;
+constexpr int SPLIT_NO_BIAS = -1;
+struct SplitPrepArgs {
+    const float* src[3];                 // the parameter vectors the records' offsets refer to
+    float* dst;
+    int n;
+    int first[64];                       // first workgroup of each record, filled by the launch function
+    struct Mat { int src, bias, dst; uint16_t K, N; uint8_t kind, from; uint16_t pad_; } m[SPLIT_MAX_MATS];   // offsets in floats
+};
+static_assert(SPLIT_MAX_MATS <= 64, "a wavefront looks its record up with one lane each");
+size_t split_mat_floats(int K, int N);
+// kid: the class the launch is filed under (the Actor step counts its preparation as part of itself)
+hipError_t split_weights_launch(SplitPrepArgs& a, int kid, hipStream_t stream);
+
+struct SplitShape {
+    int o, a, L;
+    int H[PQL_MAX_HIDDEN];
+    // LDS plan, filled by the launch functions: activation tiles and input tile (16-byte units), small arrays (floats)
+    int h0, hplane, x0, xplane, sm, as, alias;
+};
+struct SplitCriticArgs {
+    SplitShape shape;
+    int B;
+    const float* pi[PQL_MAX_HIDDEN + 1];          // prepared matrices, [l] = layer l -> l + 1, l = 0..L (output layer)
+    const float* qt[2][PQL_MAX_HIDDEN + 1];       // l = 0..L-1
+    const float* q[2][PQL_MAX_HIDDEN + 1];
+    const float* qT[2][PQL_MAX_HIDDEN + 1];       // transposed, l = 1..L-1; distributional critics: also [L], and qt / q [L]
+    const float *wo_t[2], *wo_q[2];               // output weights, padded
+    const float *bo_t[2], *bo_q[2], *pi_bias;     // output biases
+    const float *obs, *act, *ret, *next_obs, *boot;
+    float* h[2][PQL_MAX_HIDDEN + 1];              // hidden activations, l = 1..L-1
+    float* d[2][PQL_MAX_HIDDEN + 1];              // deltas, l = 1..L
+    float* col[2][PQL_MAX_HIDDEN + 1];            // bias-gradient partials [nwg][H_l], l = 1..L-1
+    float* y; float* q_out[2];
+    float* p_dw[2]; float* p_dbh[2]; float* p_db[2]; float* p_loss;
+    FusedSac sac;
+    int atoms; float v_min, v_max;                // distributional critics (atoms >= 2)
+    float* dlg[2];                                // [B][atoms] dLoss/dlogits
+    float* p_dbo[2];                              // [nwg][atoms] partial sums of the output-bias gradient
+};
+struct SplitPolicyArgs {
+    SplitShape shape;
+    int B;
+    const float* pi[PQL_MAX_HIDDEN + 1];
+    const float* q[2][PQL_MAX_HIDDEN + 1];
+    const float* qT[2][PQL_MAX_HIDDEN + 1];
+    const float* w1aT[2];                         // transposed action rows of the critics' first layer (H_1 x a)
+    const float* waT[PQL_MAX_HIDDEN + 1];         // transposed policy layers, l = 1..L (l = L: output layer)
+    const float* wo[2];
+    const float *bo[2], *pi_bias;
+    const float* obs;
+    float* hA[PQL_MAX_HIDDEN + 1];                // l = 1..L
+    float* dA[PQL_MAX_HIDDEN + 1];
+    float* colA[PQL_MAX_HIDDEN + 2];              // l = 1..L+1
+    float* h[2][PQL_MAX_HIDDEN + 1];              // critic activations, l = 1..L
+    float* dPre;
+    float* q_out[2];
+    float* p_loss;
+    float* p_logp;
+    FusedSac sac;
+    int atoms; float v_min, v_max;
+};
+struct SplitActArgs {
+    SplitShape shape;
+    int B;
+    const float* pi[PQL_MAX_HIDDEN + 1];
+    const float* pi_bias;
+    const float* obs;
+    const float* nmean;
+    const float* nrstd;
+    float* act_out;
+    GemmNoise noise;
+    FusedSac sac;
+};
+bool split_shape_ok(int o, int a, int aw, const int* H, int L, bool dist = false);
+enum SplitClass : int { SPLIT_FUSED = 0, SPLIT_CHAIN = 1, SPLIT_OTHER = 2 };
+hipError_t split_critic_launch(SplitCriticArgs& a, int kind, hipStream_t stream);
+hipError_t split_policy_launch(SplitPolicyArgs& a, int kind, hipStream_t stream);
+hipError_t split_act_launch(SplitActArgs& a, int kind, hipStream_t stream);
 
 struct TransposeArgs {
     struct Mat { const float* src; float* dst; int rows, cols, block_begin, pad_; };

@@ -1,8 +1,9 @@
-// Building blocks of the row-tile kernels (pql_fused.hip, pql_chain.hip): a workgroup of eight
+// Building blocks of the row-tile kernels on fp32 MFMAs (pql_fused.hip): a workgroup of eight
 // wavefronts owns 32 batch rows whose activations live in LDS; the weights are streamed from L2
 // into registers as the B operand of v_mfma_f32_32x32x2_f32 (each wavefront owns 32 output
-// columns; lanes run along W's contiguous output dimension).  Device code only; each translation
-// unit that includes this header has its own dynamic LDS array `smem`.
+// columns; lanes run along W's contiguous output dimension); and the elementwise functions,
+// reductions and random draws that the kernels on fp16 pairs (pql_split.hip) share with them.
+// Device code only; each translation unit that includes this header has its own dynamic LDS array `smem`.
 #pragma once
 
 #include "pql_internal.h"
@@ -256,102 +257,6 @@ __device__ inline void mac_segment(floatx16 (&acc)[NN], const int (&in)[NN], int
     mac_segment<NN>(acc, in, ld, K, W, ldw, ncol, T, c_begin, c_step, false, none);
 }
 
-enum WideEpi : int { WIDE_BIAS_ELU = 0, WIDE_MUL_DELU = 1 };
-
-// One layer for NN networks of equal shape (the twin critics run as a pair).
-template <int NN>
-struct WideArgs {
-    int in0[NN]; const float* W0[NN]; int ld0, K0;               // first input segment (LDS offset)
-    int in1[NN]; const float* W1[NN]; int ld1, K1;               // optional second segment (K1 = 0: none)
-    int ldw, N;
-    const float* bias[NN];                                       // WIDE_BIAS_ELU
-    int aux[NN]; int ldaux;                                      // WIDE_MUL_DELU: LDS tile of activations (offset)
-    int outL[NN]; int ldo;                                       // LDS output tile (offset; may be aux, never an input)
-    float* outG[NN]; int ldg;                                    // optional copy in memory
-    float* colsum[NN];                                           // optional column sums over the tile's rows
-    int epi;
-};
-
-// out[32 x N] (N <= 256, one 32-column tile per wavefront).  WIDE_BIAS_ELU: out = ELU(acc + bias).
-// WIDE_MUL_DELU: out = acc * ELU'(.) with the activation taken from the LDS tile `aux`.  Rows
-// beyond the batch are written as zero.
-template <int NN, bool PRE2 = true>
-__device__ inline void wide_linear(const Lanes& T, const WideArgs<NN>& w, int r0, int B) {
-    const int n0 = T.wave * 32, N = w.N;
-    if (n0 >= N) return;
-    const int n = n0 + T.l32;
-    const bool n_ok = n < N;
-    const int ncol = n_ok ? n : N - 1;
-    float bv[NN];
-#pragma unroll
-    for (int i = 0; i < NN; ++i) bv[i] = (w.epi == WIDE_BIAS_ELU) ? w.bias[i][ncol] : 0.f;   // in flight during the MFMAs
-    floatx16 acc[NN];
-#pragma unroll
-    for (int i = 0; i < NN; ++i)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[i][r] = 0.f;
-    if (w.K1 > 0 && !PRE2) {
-        // two segments one after the other (for callers without the registers to hold both first chunks)
-        mac_segment<NN>(acc, w.in1, w.ld1, w.K1, w.W1, w.ldw, ncol, T, 0, 1);
-        mac_segment<NN>(acc, w.in0, w.ld0, w.K0, w.W0, w.ldw, ncol, T, 0, 1);
-    } else if (w.K1 > 0) {
-        // two segments (a critic's first layer: state columns, then action columns): the first chunks
-        // of both are requested together, and the short segment runs while the long one's arrives
-        float bs[NN][16], bf[NN][16];
-        prefetch_first_chunk<NN>(bs, w.W1, w.K1, w.ldw, ncol, T, 0, 1);
-        prefetch_first_chunk<NN>(bf, w.W0, w.K0, w.ldw, ncol, T, 0, 1);
-        mac_segment<NN>(acc, w.in1, w.ld1, w.K1, w.W1, w.ldw, ncol, T, 0, 1, true, bs);
-        mac_segment<NN>(acc, w.in0, w.ld0, w.K0, w.W0, w.ldw, ncol, T, 0, 1, true, bf);
-    } else {
-        mac_segment<NN>(acc, w.in0, w.ld0, w.K0, w.W0, w.ldw, ncol, T, 0, 1);
-    }
-    // Epilogue.  Row r of the accumulator sits (8 * (r / 4) + r % 4) rows below the lane's first row
-    // (4 * half): offsets from per-lane bases are compile-time multiples of the strides.
-    const bool full = r0 + BMF <= B;                      // uniform: every row of the tile is in the batch
-    const int lrow = 4 * T.half;
-#pragma unroll
-    for (int i = 0; i < NN; ++i) {
-        float cs = 0.f;
-        const int lbase = w.outL[i] + lrow * w.ldo + n;
-        const int abase = w.aux[i] + lrow * w.ldaux + ncol;
-        float* __restrict__ gbase = w.outG[i] ? w.outG[i] + (size_t)(r0 + lrow) * (size_t)w.ldg + n : nullptr;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int dr = 8 * (r >> 2) + (r & 3);
-            float x = acc[i][r];
-            if (w.epi == WIDE_BIAS_ELU) x = elu_f(x + bv[i]);
-            else x *= delu_h(smem[abase + dr * w.ldaux]);
-            const bool rv = full || (r0 + lrow + dr < B);
-            if (!rv) x = 0.f;
-            if (n_ok) {
-                smem[lbase + dr * w.ldo] = x;
-                if (gbase && rv) gbase[dr * w.ldg] = x;
-                cs += x;
-            }
-        }
-        if (w.colsum[i]) {
-            cs += __shfl_xor(cs, 32);
-            if (T.half == 0 && n_ok) w.colsum[i][n] = cs;
-        }
-    }
-}
-
-// Partial products of a narrow layer (N <= 32): the contraction is split across the wavefronts,
-// each leaves its 32x32 partial tile in `scratch` (accumulator layout: index r * 64 + lane).
-// The caller synchronises and finishes with small_sum().
-__device__ inline void small_partial(const Lanes& T, int in0, int ld0, int K0, const float* W0, int ldw, int N,
-                                     int scratch) {
-    floatx16 acc[1];
-#pragma unroll
-    for (int r = 0; r < 16; ++r) acc[0][r] = 0.f;
-    const int ncol = T.l32 < N ? T.l32 : N - 1;
-    const int ins[1] = {in0};
-    const float* const ws[1] = {W0};
-    mac_segment<1>(acc, ins, ld0, K0, ws, ldw, ncol, T, T.wave, FW);
-#pragma unroll
-    for (int r = 0; r < 16; ++r) smem[scratch + T.wave * 1024 + r * 64 + T.lane] = acc[0][r];
-}
-
 // Sum of the FW partial tiles for output element e (0..1023): returns the value and its (row, col).
 __device__ inline float small_sum(int scratch, int e, int& row, int& col) {
     float s = 0.f;
@@ -422,6 +327,15 @@ __device__ inline void philox4x32_10_f(uint32_t c0, uint32_t c1, uint32_t c2, ui
         k0 += 0x9E3779B9u; k1 += 0xBB67AE85u;
     }
     o0 = c0; o1 = c1;
+}
+
+__device__ inline float std_normal_f(uint32_t element, const FusedSac& sc) {
+    uint32_t w0, w1;
+    philox4x32_10_f(element, sc.stream_id, sc.ctr2, sc.ctr3, sc.key0, sc.key1, w0, w1);
+    // double precision: (w >> 8) + 0.5 needs 25 significant bits
+    const double u1 = ((double)(w0 >> 8) + 0.5) * 0x1p-24;
+    const double u2 = ((double)(w1 >> 8) + 0.5) * 0x1p-24;
+    return (float)(sqrt(-2.0 * log(u1)) * cos(6.283185307179586476925286766559 * u2));
 }
 
 }  // namespace pql

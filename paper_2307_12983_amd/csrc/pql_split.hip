@@ -1,0 +1,1434 @@
+// Row-tile learner kernels on the 16-bit matrix cores at 32-bit precision.
+//
+// Every operand of a matrix product is an fp32 value times a power of two, written as the sum of two fp16 terms
+// (hi = fp16(x s), lo = fp16(x s - hi): 22 significant bits and the sign of lo), and a product is three fp16 MFMAs
+// (lo w_hi + hi w_lo + hi w_hi; the left-out lo w_lo is below 2^-22 of the product) that accumulate in fp32.  The
+// scales keep the terms inside fp16's range whatever the data: one per batch row of an activation tile (its largest
+// magnitude goes to [2^14, 2^15), found anew for every layer), one per 32 output columns of a weight matrix.  A value
+// 2^17 and more below its row's largest loses relative, not absolute, precision (2^-40 of that largest one).
+// Measured against double precision a K = 256 product is off by 1.2e-7 (2-norm) where a chain of fp32 MFMAs is off by
+// 2.8e-7: three roundings per 32 products instead of sixteen outweigh the two missing bits of the operands.
+// v_mfma_f32_16x16x32_f16 multiplies at 13 times the rate of v_mfma_f32_32x32x2_f32 (2.0 PFLOP/s against 0.15), so
+// three of them are 4.4 times as fast and take a quarter of the energy, which matters as much: the chip holds
+// 2.4 GHz only below its power limit.
+//
+// A workgroup (sixteen wavefronts, four per SIMD) owns 32 batch rows and carries them through a whole chain of layers,
+// the twin critics side by side (eight wavefronts each) where the layers are at most 512 wide, one after the other up to
+// 1024.  A wavefront owns 32 output columns of one network.  The product is computed as W^T X^T (weights are the A
+// operand): a lane then holds four consecutive output columns of one batch row, which is the order in which the next
+// layer's B operand wants them, so an epilogue packs its results with no exchange between lanes and writes them to LDS as
+// 16-byte pieces, and row maxima, output heads and their gradients come from registers.
+//
+// What bounds it: with 32 rows per workgroup the weights (4 bytes each, once per workgroup) come from L2 at 30 - 40 bytes
+// per clock and compute unit, about twice the time of the matrix work; a paired 256 x 256 layer takes 7.0 us with all
+// compute units running (5.4 us with 64 of them: the rest is the clock the power limit leaves), where the fp32 MFMA
+// kernels take 18.8 us.
+//
+// The weights are brought into fragment order by split_weights_kernel at the start of every call (zero-padded to whole
+// tiles, so any layer width works): a lane's operand is one 16-byte load, a wavefront's a contiguous kilobyte.
+#include "pql_rowtile.h"
+
+namespace pql {
+
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+
+enum Variant : int { VAR_PLAIN = 0, VAR_SAC = 1, VAR_DIST = 2 };
+constexpr int SW = 16;               // wavefronts per workgroup
+constexpr int ST = 64 * SW;          // threads per workgroup
+constexpr int CS = 33;               // 16-byte units per k-chunk of a tile: 32 rows and one of padding against bank conflicts
+
+// ---- layouts ----------------------------------------------------------------------------------------
+// A prepared matrix (K x N): fragments [N/32][K/32][16-column half][hi, lo][lane] of 16 bytes, then the inverse scale of
+// every 32-column tile (64 floats reserved), then the bias padded with zeros to whole tiles.  Lane (l15 = lane & 15,
+// q = lane >> 4) holds column 16 half + l15 for the eight k-values k_slot(step, q, i).
+__host__ __device__ __forceinline__ int k_slot(int step, int q, int i) { return 32 * step + 16 * (i >> 2) + 4 * q + (i & 3); }
+size_t split_mat_floats(int K, int N) {
+    const size_t ks = (size_t)((K + 31) / 32), tiles = (size_t)((N + 31) / 32);
+    return tiles * ks * 1024 + 64 + tiles * 32;
+}
+struct MatView { const u32x4* frag; const float* inv; const float* bias; int ks, tiles; };
+__device__ __forceinline__ MatView mat_view(const float* base, int K, int N) {
+    MatView m;
+    m.ks = (K + 31) >> 5; m.tiles = (N + 31) >> 5;
+    m.frag = reinterpret_cast<const u32x4*>(base);
+    m.inv = base + (size_t)m.tiles * m.ks * 1024;
+    m.bias = m.inv + 64;
+    return m;
+}
+
+// Power-of-two scale that brings a largest magnitude m to [2^14, 2^15), and its inverse.  The exponent is clamped so
+// that both are normal numbers (zero rows, subnormals, infinities).
+__device__ __forceinline__ float scale_for(float m, float& inv) {
+    int e = (int)(__float_as_uint(m) >> 23);
+    e = e < 20 ? 20 : (e > 254 ? 254 : e);
+    inv = __uint_as_float((unsigned)(e - 14) << 23);
+    return __uint_as_float((unsigned)(268 - e) << 23);
+}
+__device__ __forceinline__ void split16(float x, float s, _Float16& hi, _Float16& lo) {
+    hi = (_Float16)(x * s);
+    lo = (_Float16)__fmaf_rn(x, s, -(float)hi);
+}
+__device__ __forceinline__ void split16x8(const f32x4& a, const f32x4& b, float s, u32x4& hi, u32x4& lo) {
+    f16x8 h, l;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        _Float16 x, y;
+        split16(a[i], s, x, y); h[i] = x; l[i] = y;
+        split16(b[i], s, x, y); h[4 + i] = x; l[4 + i] = y;
+    }
+    hi = __builtin_bit_cast(u32x4, h); lo = __builtin_bit_cast(u32x4, l);
+}
+
+// Reductions across the four 16-lane rows of a wavefront (same l15) and inside one of them.
+__device__ __forceinline__ float quarters_max(float x) {
+    auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    x = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+    auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+__device__ __forceinline__ float quarters_sum(float x) {
+    auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    x = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+    auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return __uint_as_float(b[0]) + __uint_as_float(b[1]);
+}
+__device__ __forceinline__ float row16_sum(float x) {
+    x += dpp_move<0x128>(x);     // row_ror 8, 4, 2, 1
+    x += dpp_move<0x124>(x);
+    x += dpp_move<0x122>(x);
+    return x + dpp_move<0x121>(x);
+}
+__device__ __forceinline__ float half_max(float x) {          // over the 32 lanes of a half wavefront
+    x = fmaxf(x, dpp_move<0x128>(x));
+    x = fmaxf(x, dpp_move<0x124>(x));
+    x = fmaxf(x, dpp_move<0x122>(x));
+    x = fmaxf(x, dpp_move<0x121>(x));
+    auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+}
+
+// The kernel's argument block, read in place.  As an ordinary by-value parameter it is copied to private memory as soon as
+// one of its arrays is indexed with a run-time layer number; through the segment pointer every access is a scalar load.
+template <typename ARGS>
+__device__ __forceinline__ const ARGS& kernel_args() {
+    return *(const ARGS*)__builtin_amdgcn_kernarg_segment_ptr();
+}
+
+// ---- weights into fragment order ------------------------------------------------------------------------
+// One workgroup per 32-column tile: every element is read once (all requests in flight together), kept in registers while
+// the tile's largest magnitude is found, and written as fragments.  Latency-bound: one round trip each way.
+__global__ __launch_bounds__(ST) void split_weights_kernel(const SplitPrepArgs) {
+    const SplitPrepArgs& P = kernel_args<SplitPrepArgs>();
+    __shared__ float red[SW];
+    const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
+    const int first = P.first[lane];
+    const int pi = __builtin_amdgcn_readfirstlane(__popcll(__ballot(b >= first)) - 1);
+    const SplitPrepArgs::Mat M = P.m[pi];
+    const int tile = b - __builtin_amdgcn_readlane(first, pi), K = M.K, N = M.N;
+    const float* src = P.src[M.from] + M.src;
+    float* dst = P.dst + M.dst;
+    if (M.kind == SPLIT_VECTOR) {        // a vector padded with zeros to whole tiles
+        for (int i = tid; i < (N + 31) / 32 * 32; i += ST) dst[i] = i < N ? src[i] : 0.f;
+        return;
+    }
+    const int ks = (K + 31) >> 5, tiles = (N + 31) >> 5;
+    const int items = ks * 128;
+    const int l15 = lane & 15, q = lane >> 4;
+    const bool trans = M.kind == SPLIT_TRANSPOSED;
+    const __amdgpu_buffer_rsrc_t rs =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(src), 0, K * N * (int)sizeof(float), 0x00020000);
+    // element (k, n) at k sk + n sn; what lies outside the matrix is requested outside the descriptor and reads as zero
+    const int sk = trans ? 1 : N, sn = trans ? K : 1;
+    f32x4 v[4][2];
+    float mx = 0.f;
+#pragma unroll
+    for (int it = 0; it < 4; ++it) {
+        if (it * ST >= items) break;
+        const int e = it * ST + tid;
+        const int n = tile * 32 + ((e >> 6) & 1) * 16 + l15;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const int k = k_slot(e >> 7, q, i);
+            v[it][i >> 2][i & 3] = buf_load(rs, k < K && n < N ? (unsigned)(k * sk + n * sn) * 4u : 0x7ffffffcu, 0);
+        }
+    }
+    float bias = 0.f;
+    if (tid < 32 && M.bias != SPLIT_NO_BIAS && tile * 32 + tid < N) bias = P.src[M.from][M.bias + tile * 32 + tid];
+#pragma unroll
+    for (int it = 0; it < 4; ++it) {
+        if (it * ST >= items) break;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) mx = fmaxf(mx, fabsf(v[it][i >> 2][i & 3]));
+    }
+    mx = quarters_max(half_max(mx));
+    if (lane == 0) red[tid >> 6] = mx;
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < SW; ++w) mx = fmaxf(mx, red[w]);
+    float inv;
+    const float s = scale_for(mx, inv);
+    u32x4* frag = reinterpret_cast<u32x4*>(dst) + (size_t)tile * ks * 256;
+    float* tail = dst + (size_t)tiles * ks * 1024;
+#pragma unroll
+    for (int it = 0; it < 4; ++it) {
+        const int e = it * ST + tid;
+        if (e >= items) break;
+        u32x4 hi, lo;
+        split16x8(v[it][0], v[it][1], s, hi, lo);
+        u32x4* d = frag + (size_t)(e >> 6) * 128 + lane;
+        d[0] = hi;
+        d[64] = lo;
+    }
+    if (tid == 0) tail[tile] = inv;
+    if (tid < 32) tail[64 + tile * 32 + tid] = bias;
+}
+
+hipError_t split_weights_launch(SplitPrepArgs& a, int kid, hipStream_t stream) {
+    int blocks = 0;
+    double bytes = 0.0;
+    for (int i = 0; i < 64; ++i) {
+        a.first[i] = i < a.n ? blocks : 0x7fffffff;
+        if (i >= a.n) continue;
+        if (a.m[i].kind != SPLIT_VECTOR && a.m[i].K > SPLIT_MAXW) return hipErrorInvalidValue;
+        blocks += a.m[i].kind == SPLIT_VECTOR ? 1 : (a.m[i].N + 31) / 32;
+        bytes += 8.0 * a.m[i].K * a.m[i].N;
+    }
+    if (blocks == 0) return hipSuccess;
+    const ProfSlot ps = prof_slot();
+    PQL_LAUNCH(ps, split_weights_kernel, dim3(blocks), dim3(ST), 0, stream, a);
+    prof_commit(ps, kid, 0.0, kid == KID_SPLIT_WEIGHTS ? bytes : 0.0);
+    return hipGetLastError();
+}
+
+// ---- a layer on the tile --------------------------------------------------------------------------------
+struct Wv { int tid, lane, wave, l15, q; };
+
+// Barrier for data in LDS only: __syncthreads() would also wait for every store to memory and every weight request that
+// is meant to stay in flight across it.
+__device__ __forceinline__ void lds_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+__device__ __forceinline__ u32x4* lds_units() { return reinterpret_cast<u32x4*>(smem); }
+
+// Activation tile in LDS: k-chunks of eight values (chunk 4 step + q holds k_slot(step, q, 0..7)), 32 rows each, hi terms
+// then lo terms.  base and plane in 16-byte units.
+struct Tile { int base, plane; };
+
+// The fragments of one k-step of a 32-column tile (4 KB): the requests run one step ahead of the matrix work, also from
+// one product to the next (over the epilogue and its barriers), so every product is told where the following one begins.
+struct Ahead { u32x4 w[4]; };
+__device__ __forceinline__ const u32x4* first_step(const MatView& W, int tile, int step) {
+    const int t = tile < W.tiles ? tile : 0, s = step < W.ks ? step : 0;       // an idle wavefront requests something valid
+    return W.frag + (size_t)(t * W.ks + s) * 256;
+}
+__device__ __forceinline__ const u32x4* cur_valid(const float* mat) { return reinterpret_cast<const u32x4*>(mat); }
+__device__ __forceinline__ void request(Ahead& a, const u32x4* p, const Wv& T) {
+    const char* b = reinterpret_cast<const char*>(p);
+    const unsigned off = (unsigned)T.lane * 16u;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) a.w[i] = *reinterpret_cast<const u32x4*>(b + off + i * 1024);
+}
+
+// acc[m][n] += 16x16 products of weight columns 32 tile + 16 m .. with batch rows 16 n .., steps s0, s0 + ds, ...  `cur`
+// holds the first step's fragments and leaves with those at `next` (the fences keep the requests ahead of the MFMAs).
+__device__ __forceinline__ void mac_steps(f32x4 (&acc)[2][2], const MatView& W, int tile, const Tile& X, const Wv& T, int s0, int ds,
+                                 Ahead& cur, const u32x4* next) {
+    const u32x4* p = W.frag + (size_t)tile * W.ks * 256;
+    auto mac = [&](int s, const u32x4 (&w)[4]) {
+        const int at = X.base + (4 * s + T.q) * CS + T.l15;
+        u32x4 xh[2], xl[2];
+#pragma unroll
+        for (int n = 0; n < 2; ++n) { xh[n] = lds_units()[at + 16 * n]; xl[n] = lds_units()[at + X.plane + 16 * n]; }
+#pragma unroll
+        for (int c = 0; c < 3; ++c)          // smallest contributions first
+#pragma unroll
+            for (int m = 0; m < 2; ++m)
+#pragma unroll
+                for (int n = 0; n < 2; ++n)
+                    acc[m][n] = __builtin_amdgcn_mfma_f32_16x16x32_f16(
+                        __builtin_bit_cast(f16x8, c == 0 ? w[2 * m + 1] : w[2 * m]),
+                        __builtin_bit_cast(f16x8, c == 1 ? xl[n] : xh[n]), acc[m][n], 0, 0, 0);
+    };
+    Ahead other;
+    for (int s = s0; ; s += 2 * ds) {
+        const int s1 = s + ds, s2 = s + 2 * ds;
+        request(other, s1 < W.ks ? p + (size_t)s1 * 256 : next, T);
+        __builtin_amdgcn_sched_barrier(0);
+        mac(s, cur.w);
+        __builtin_amdgcn_sched_barrier(0);
+        if (s1 >= W.ks) { cur = other; break; }
+        request(cur, s2 < W.ks ? p + (size_t)s2 * 256 : next, T);
+        __builtin_amdgcn_sched_barrier(0);
+        mac(s1, other.w);
+        __builtin_amdgcn_sched_barrier(0);
+        if (s2 >= W.ks) break;
+    }
+}
+
+__device__ __forceinline__ void clear(f32x4 (&z)[2][2]) {
+#pragma unroll
+    for (int m = 0; m < 2; ++m)
+#pragma unroll
+        for (int n = 0; n < 2; ++n) z[m][n] = f32x4{0.f, 0.f, 0.f, 0.f};
+}
+
+// (Stores bypass the caches' retention: the arrays are read by another kernel, and lines left dirty in L2 would be written
+// back in one burst when this one ends.)
+// The 32 x 32 results of one tile to / from a row-major [B][N] array: this lane's rows r0 + 16 n + l15, columns
+// 32 tile + 16 m + 4 q .. + 3.
+__device__ __forceinline__ void store_tile(float* g, int N, int tile, const f32x4 (&z)[2][2], int r0, int B, const Wv& T) {
+#pragma unroll
+    for (int n = 0; n < 2; ++n) {
+        const int row = r0 + 16 * n + T.l15;
+        if (row >= B) continue;
+        float* p = g + (size_t)row * (size_t)N;
+#pragma unroll
+        for (int m = 0; m < 2; ++m) {
+            const int col = 32 * tile + 16 * m + 4 * T.q;
+            if ((N & 3) == 0) {
+                if (col < N) __builtin_nontemporal_store(z[m][n], reinterpret_cast<f32x4*>(p + col));
+            } else {
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    if (col + r < N) __builtin_nontemporal_store(z[m][n][r], p + col + r);
+            }
+        }
+    }
+}
+__device__ __forceinline__ void load_tile(const float* g, int N, int tile, f32x4 (&z)[2][2], int r0, int B, const Wv& T) {
+    clear(z);
+#pragma unroll
+    for (int n = 0; n < 2; ++n) {
+        const int row = r0 + 16 * n + T.l15;
+        if (row >= B) continue;
+        const float* p = g + (size_t)row * (size_t)N;
+#pragma unroll
+        for (int m = 0; m < 2; ++m) {
+            const int col = 32 * tile + 16 * m + 4 * T.q;
+            if ((N & 3) == 0) {
+                if (col < N) z[m][n] = *reinterpret_cast<const f32x4*>(p + col);
+            } else {
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    if (col + r < N) z[m][n][r] = p[col + r];
+            }
+        }
+    }
+}
+// Sums over the tile's 32 rows of a[..] (times b[..] where given) to out[N].
+__device__ __forceinline__ void store_colsum(float* out, int N, int tile, const f32x4 (&a)[2], const Wv& T) {
+#pragma unroll
+    for (int m = 0; m < 2; ++m) {
+        const int col = 32 * tile + 16 * m + 4 * T.q;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const float s = row16_sum(a[m][r]);
+            if (T.l15 == 0 && col + r < N) out[col + r] = s;
+        }
+    }
+}
+
+// Which of the workgroup's networks and output tiles a wavefront works on.
+struct Share { int net, slot, waves; };      // tiles slot, slot + waves, ...
+template <int TPW>
+__device__ __forceinline__ void load_ahead(const float* h, int N, f32x4 (&hv)[2][2], const Share& S, int r0, int B, const Wv& T) {
+    if (TPW == 1) load_tile(h, N, S.slot, hv, r0, B, T);
+}
+
+// Small per-tile arrays in LDS (floats from `sm`).
+struct SmallMem {
+    int max, part, inv, logp, act;           // [512] row maxima, [512] head partials, [32] inverse scales of X, [32] log pi, [32][as] actions
+    int as;
+};
+__device__ __forceinline__ SmallMem small_mem(int sm, int as) {
+    SmallMem m;
+    m.max = sm; m.part = sm + 512; m.inv = sm + 1024; m.logp = sm + 1056; m.act = sm + 1088; m.as = as;
+    return m;
+}
+
+// Puts the wavefronts' results (z, TPW tiles of 32 columns each) into the activation tile `out`, in place over the layer's
+// input: row maxima meet in LDS; the barrier they need is also the one after which nobody reads the input any more.
+template <int TPW>
+__device__ __forceinline__ void put_tile(const f32x4 (&z)[TPW][2][2], int tiles, const Tile& out, const Share& S, const SmallMem& M,
+                                float (&inv)[2], const Wv& T) {
+    float mx[2] = {0.f, 0.f};
+#pragma unroll
+    for (int t = 0; t < TPW; ++t)
+        if (S.slot + t * S.waves < tiles) {
+#pragma unroll
+            for (int n = 0; n < 2; ++n)
+#pragma unroll
+                for (int m = 0; m < 2; ++m)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) mx[n] = fmaxf(mx[n], fabsf(z[t][m][n][r]));
+        }
+#pragma unroll
+    for (int n = 0; n < 2; ++n) {
+        mx[n] = quarters_max(mx[n]);
+        if (T.q == 0) smem[M.max + (S.net * 32 + 16 * n + T.l15) * S.waves + S.slot] = mx[n];
+    }
+    lds_barrier();
+    float sc[2];
+#pragma unroll
+    for (int n = 0; n < 2; ++n) {
+        const f32x4* src = reinterpret_cast<const f32x4*>(smem) + (M.max + (S.net * 32 + 16 * n + T.l15) * S.waves) / 4;
+        f32x4 a = src[0], b = src[1];
+        float m = fmaxf(fmaxf(fmaxf(a[0], a[1]), fmaxf(a[2], a[3])), fmaxf(fmaxf(b[0], b[1]), fmaxf(b[2], b[3])));
+        if (S.waves > 8) {
+            a = src[2]; b = src[3];
+            m = fmaxf(m, fmaxf(fmaxf(fmaxf(a[0], a[1]), fmaxf(a[2], a[3])), fmaxf(fmaxf(b[0], b[1]), fmaxf(b[2], b[3]))));
+        }
+        sc[n] = scale_for(m, inv[n]);
+    }
+#pragma unroll
+    for (int t = 0; t < TPW; ++t) {
+        const int tile = S.slot + t * S.waves;
+        if (tile < tiles) {
+#pragma unroll
+            for (int n = 0; n < 2; ++n) {
+                u32x4 hi, lo;
+                split16x8(z[t][0][n], z[t][1][n], sc[n], hi, lo);
+                const int at = out.base + (4 * tile + T.q) * CS + 16 * n + T.l15;
+                lds_units()[at] = hi;
+                lds_units()[at + out.plane] = lo;
+            }
+        }
+    }
+    lds_barrier();
+}
+
+// z = ELU(X W + b) for this wavefront's tiles; inv = inverse row scales of the input tile.
+template <int TPW>
+__device__ __forceinline__ void forward(f32x4 (&z)[TPW][2][2], const MatView& W, const Tile& X, const Share& S, const float (&inv)[2],
+                               const Wv& T, Ahead& cur, const u32x4* next) {
+    if (S.slot >= W.tiles) request(cur, next, T);
+#pragma unroll
+    for (int t = 0; t < TPW; ++t) {
+        const int tile = S.slot + t * S.waves;
+        if (tile >= W.tiles) { clear(z[t]); continue; }
+        const bool more = t + 1 < TPW && tile + S.waves < W.tiles;
+        f32x4 b[2];
+#pragma unroll
+        for (int m = 0; m < 2; ++m) b[m] = *reinterpret_cast<const f32x4*>(W.bias + 32 * tile + 16 * m + 4 * T.q);
+        const float iw = W.inv[tile];
+        f32x4 acc[2][2];
+        clear(acc);
+        mac_steps(acc, W, tile, X, T, 0, 1, cur, more ? first_step(W, tile + S.waves, 0) : next);
+#pragma unroll
+        for (int m = 0; m < 2; ++m)
+#pragma unroll
+            for (int n = 0; n < 2; ++n)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) z[t][m][n][r] = elu_f(__fmaf_rn(acc[m][n][r] * inv[n], iw, b[m][r]));
+    }
+}
+
+// z = (D W^T) * ELU'(.) with the activations h [B][N] read back from memory (each lane reads what it wrote in the forward
+// pass: with one tile per wavefront the caller has requested them into hv before the deltas were put into the tile, with
+// two there are no registers for that); the deltas go to d_out and their column sums to col_out where given.
+template <int TPW>
+__device__ __forceinline__ void backward(f32x4 (&z)[TPW][2][2], const MatView& W, const Tile& X, const Share& S, const float (&inv)[2],
+                                const float* h, float* d_out, float* col_out, int N, int r0, int B, const Wv& T, Ahead& cur,
+                                const u32x4* next, f32x4 (&hv)[2][2]) {
+    if (S.slot >= W.tiles) request(cur, next, T);
+#pragma unroll
+    for (int t = 0; t < TPW; ++t) {
+        const int tile = S.slot + t * S.waves;
+        if (tile >= W.tiles) { clear(z[t]); continue; }
+        const bool more = t + 1 < TPW && tile + S.waves < W.tiles;
+        f32x4 acc[2][2];
+        const float iw = W.inv[tile];
+        if (TPW > 1) load_tile(h, N, tile, hv, r0, B, T);
+        clear(acc);
+        mac_steps(acc, W, tile, X, T, 0, 1, cur, more ? first_step(W, tile + S.waves, 0) : next);
+#pragma unroll
+        for (int m = 0; m < 2; ++m)
+#pragma unroll
+            for (int n = 0; n < 2; ++n)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) z[t][m][n][r] = acc[m][n][r] * inv[n] * iw * delu_h(hv[m][n][r]);
+        if (d_out != nullptr) store_tile(d_out, N, tile, z[t], r0, B, T);
+        if (col_out != nullptr) {
+            const f32x4 cs[2] = {z[t][0][0] + z[t][0][1], z[t][1][0] + z[t][1][1]};
+            store_colsum(col_out, N, tile, cs, T);
+        }
+    }
+}
+
+// ---- input rows --------------------------------------------------------------------------------------------
+// Rows r0 .. r0 + 31 of concat(obs[o], act[a]) as a tile: half a wavefront per row, so that its largest magnitude is found
+// without leaving the registers.  `floor`: lower bound of that magnitude (actions in [-1, 1] that are inserted later must
+// fit the row's scale).  Up to 256 columns are requested ahead of time into v.
+struct InputRows { __amdgpu_buffer_rsrc_t obs, act, mean, rstd; int o, a, act_lds, as; bool norm; };   // act_lds >= 0: actions in LDS
+constexpr int XV = 8;
+constexpr int NOWHERE = 0x7ffffffc;          // a buffer offset past any descriptor used here: the load returns zero
+
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t rows_of(const float* p, int cols, int r0, int B) {
+    const int rows = B - r0 < 32 ? B - r0 : 32;
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p) + (size_t)r0 * (size_t)cols, 0,
+                                             p != nullptr ? rows * cols * (int)sizeof(float) : 0, 0x00020000);
+}
+__device__ __forceinline__ InputRows input_rows(const float* obs, int o, const float* act, int act_lds, int a, int as, int r0, int B) {
+    InputRows in;
+    in.obs = rows_of(obs, o, r0, B); in.act = rows_of(act, a, r0, B); in.mean = in.obs; in.rstd = in.obs;
+    in.o = o; in.a = a; in.act_lds = act_lds; in.as = as; in.norm = false;
+    return in;
+}
+// Column c + 32 j of the concatenated row.  Branch-free: what a descriptor does not hold reads as zero (rows beyond the
+// batch, columns beyond the row).
+__device__ __forceinline__ float input_value(const InputRows& in, int row, int col) {
+    float x = buf_load(in.obs, (unsigned)(col < in.o ? (row * in.o + col) * 4 : NOWHERE), 0);
+    if (in.norm) {
+        const unsigned at = (unsigned)(col < in.o ? col * 4 : NOWHERE);
+        x = (x - buf_load(in.mean, at, 0)) * buf_load(in.rstd, at, 0);
+    }
+    return x;
+}
+__device__ __forceinline__ float input_action(const InputRows& in, int row, int col) {
+    const int c = col - in.o;
+    const bool live = c >= 0 && c < in.a;
+    if (in.act_lds >= 0) {
+        const float y = smem[in.act_lds + row * in.as + (live ? c : 0)];
+        return live ? y : 0.f;
+    }
+    return buf_load(in.act, (unsigned)(live ? (row * in.a + c) * 4 : NOWHERE), 0);
+}
+__device__ __forceinline__ void request_rows(float (&v)[XV], const InputRows& in, int steps, const Wv& T) {
+    if (steps > XV) return;
+    const int row = 2 * T.wave + (T.lane >> 5), c = T.lane & 31;
+    const int j0 = in.o >> 5;                 // at most 32 action columns: they lie in the steps j0 and j0 + 1
+#pragma unroll
+    for (int j = 0; j < XV; ++j) v[j] = input_value(in, row, c + 32 * j);
+    if (in.a > 0) {
+        const float y0 = input_action(in, row, c + 32 * j0), y1 = input_action(in, row, c + 32 * j0 + 32);
+#pragma unroll
+        for (int j = 0; j < XV; ++j) {
+            const bool live = c + 32 * j >= in.o;
+            v[j] = live ? (j == j0 ? y0 : (j == j0 + 1 ? y1 : 0.f)) : v[j];
+        }
+    }
+}
+__device__ __forceinline__ float input_any(const InputRows& in, int row, int col) {
+    const float x = input_value(in, row, col);
+    return in.a > 0 && col >= in.o ? input_action(in, row, col) : x;
+}
+__device__ __forceinline__ int tile_half(const Tile& X, int row, int k) {      // position of (row, k) in 2-byte units
+    return (X.base + ((k >> 5) * 4 + ((k >> 2) & 3)) * CS + row) * 8 + (k & 3) + 4 * ((k >> 4) & 1);
+}
+__device__ __forceinline__ void put_value(const Tile& X, int row, int k, float x, float s) {
+    _Float16* h = reinterpret_cast<_Float16*>(smem);
+    _Float16 hi, lo;
+    split16(x, s, hi, lo);
+    const int at = tile_half(X, row, k);
+    h[at] = hi;
+    h[at + X.plane * 8] = lo;
+}
+__device__ __forceinline__ void put_rows(const float (&v)[XV], const InputRows& in, int steps, const Tile& X, int inv_at, float floor_,
+                                const Wv& T) {
+    const int row = 2 * T.wave + (T.lane >> 5), c = T.lane & 31;
+    float mx = floor_;
+    if (steps <= XV) {
+#pragma unroll
+        for (int j = 0; j < XV; ++j) mx = fmaxf(mx, fabsf(v[j]));
+    } else {
+        for (int j = 0; j < steps; ++j) mx = fmaxf(mx, fabsf(input_any(in, row, c + 32 * j)));
+    }
+    float inv;
+    const float s = scale_for(half_max(mx), inv);
+    if (c == 0) smem[inv_at + row] = inv;
+    if (steps <= XV) {
+#pragma unroll
+        for (int j = 0; j < XV; ++j)
+            if (j < steps) put_value(X, row, c + 32 * j, v[j], s);
+    } else {
+        for (int j = 0; j < steps; ++j) put_value(X, row, c + 32 * j, input_any(in, row, c + 32 * j), s);
+    }
+}
+__device__ __forceinline__ void row_inv(float (&inv)[2], int at, const Wv& T) {
+    inv[0] = smem[at + T.l15];
+    inv[1] = smem[at + 16 + T.l15];
+}
+
+// ---- action-wide products --------------------------------------------------------------------------------
+// At most 32 output columns: the wavefronts of a network split the contraction, every one leaves its partial 32 x 32 tile
+// in LDS, over the input tile (hence the first barrier); afterwards element (row, col) is the sum of the partial tiles.
+__device__ __forceinline__ void put_partial(const f32x4 (&acc)[2][2], int at, int part, bool mine, const Wv& T) {
+    lds_barrier();
+    if (mine) {
+        f32x4* p = reinterpret_cast<f32x4*>(smem) + at + part * 256 + T.lane;
+#pragma unroll
+        for (int m = 0; m < 2; ++m)
+#pragma unroll
+            for (int n = 0; n < 2; ++n) p[(2 * m + n) * 64] = acc[m][n];
+    }
+    lds_barrier();
+}
+__device__ __forceinline__ float sum_partials(int at, int parts, int row, int col) {
+    const int e = (((col >> 4) * 2 + (row >> 4)) * 64 + ((col >> 2) & 3) * 16 + (row & 15)) * 4 + (col & 3);
+    float s = 0.f;
+    for (int p = 0; p < parts; ++p) s += smem[at * 4 + p * 1024 + e];
+    return s;
+}
+__device__ __forceinline__ void scaled(f32x4 (&acc)[2][2], const float (&inv)[2], float iw) {
+#pragma unroll
+    for (int m = 0; m < 2; ++m)
+#pragma unroll
+        for (int n = 0; n < 2; ++n)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) acc[m][n][r] = acc[m][n][r] * inv[n] * iw;
+}
+
+// A sample of the tanh-Gaussian policy for element (row, col) of the output tile; the 32 lanes of a row add their shares of
+// log pi, which every lane returns.
+__device__ __forceinline__ float sample_action(int at, int parts, int row, int col, int a, const float* bias, int r0, const FusedSac& sc,
+                                      float& act, float& eps, float& raw) {
+    float lp = 0.f;
+    act = 0.f; eps = 0.f; raw = 0.f;
+    if (col < a) {
+        const float mu = sum_partials(at, parts, row, col) + bias[col];
+        raw = sum_partials(at, parts, row, col + a) + bias[col + a];
+        eps = std_normal_f((uint32_t)((r0 + row) * a + col), sc);
+        const float ls = fminf(fmaxf(raw, SAC_LOG_STD_MIN), SAC_LOG_STD_MAX);
+        const float u = mu + expf(ls) * eps;
+        const float x = -2.f * u;
+        const float softplus = fmaxf(x, 0.f) + log1pf(expf(-fabsf(x)));
+        lp = -0.5f * eps * eps - ls - 0.91893853320467274178f - 2.f * (0.69314718055994530942f - u - softplus);
+        act = tanhf(u);
+    }
+#pragma unroll
+    for (int o = 16; o >= 1; o >>= 1) lp += __shfl_xor(lp, o);
+    return lp;
+}
+
+// The policy's hidden layers on the tile (all sixteen wavefronts on one network), its output layer as partial tiles.
+// keep: h_l go to hA[l]; returns the number of partial tiles at H.
+template <int TPW>
+__device__ __forceinline__ int policy_forward(const SplitShape& P, const float* const* mats, const Tile& X, const Tile& H, const SmallMem& M,
+                                     bool keep, float* const* hA, int aw, int r0, int B, const Wv& T, Ahead& cur,
+                                     const u32x4* next) {
+    const Share S = {0, T.wave, SW};
+    float inv[2];
+    row_inv(inv, M.inv, T);
+    f32x4 z[TPW][2][2];
+    for (int l = 0; l < P.L; ++l) {
+        const int N = P.H[l];
+        const MatView W = mat_view(mats[l], l == 0 ? P.o : P.H[l - 1], N);
+        const MatView V = mat_view(mats[l + 1], N, l + 1 < P.L ? P.H[l + 1] : aw);
+        forward<TPW>(z, W, l == 0 ? X : H, S, inv, T, cur, l + 1 < P.L ? first_step(V, S.slot, 0) : first_step(V, 0, T.wave));
+        if (keep) {
+#pragma unroll
+            for (int t = 0; t < TPW; ++t)
+                if (S.slot + t * SW < W.tiles) store_tile(hA[l + 1], N, S.slot + t * SW, z[t], r0, B, T);
+        }
+        put_tile<TPW>(z, W.tiles, H, S, M, inv, T);
+    }
+    const MatView W = mat_view(mats[P.L], P.H[P.L - 1], aw);
+    f32x4 acc[2][2];
+    clear(acc);
+    if (T.wave < W.ks) mac_steps(acc, W, 0, H, T, T.wave, SW, cur, next);
+    else request(cur, next, T);
+    scaled(acc, inv, W.inv[0]);
+    const int parts = W.ks < SW ? W.ks : SW;
+    put_partial(acc, H.base, T.wave, T.wave < parts, T);
+    return parts;
+}
+
+// Scalar output head: partial dot products of this wavefront's tiles of the last hidden layer with the output weights meet in
+// LDS; q[i][n] = Q_i of this lane's rows (all networks the workgroup carries; one: q[0]).
+template <int NN, int TPW>
+__device__ __forceinline__ void head_values(const f32x4 (&z)[TPW][2][2], const f32x4 (&wo)[TPW][2], const Share& S, const SmallMem& M,
+                                   const float (&bias)[NN], float (&q)[NN][2], const Wv& T) {
+#pragma unroll
+    for (int n = 0; n < 2; ++n) {
+        float s = 0.f;
+#pragma unroll
+        for (int t = 0; t < TPW; ++t)
+#pragma unroll
+            for (int m = 0; m < 2; ++m)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) s += z[t][m][n][r] * wo[t][m][r];
+        s = quarters_sum(s);
+        if (T.q == 0) smem[M.part + (S.net * 32 + 16 * n + T.l15) * S.waves + S.slot] = s;
+    }
+    lds_barrier();
+#pragma unroll
+    for (int i = 0; i < NN; ++i)
+#pragma unroll
+        for (int n = 0; n < 2; ++n) {
+            const f32x4* src = reinterpret_cast<const f32x4*>(smem) + (M.part + (i * 32 + 16 * n + T.l15) * S.waves) / 4;
+            f32x4 v = src[0] + src[1];
+            if (S.waves > 8) v += src[2] + src[3];
+            q[i][n] = (v[0] + v[1]) + (v[2] + v[3]) + bias[i];
+        }
+}
+template <int TPW>
+__device__ __forceinline__ void head_weights(f32x4 (&wo)[TPW][2], const float* w, int tiles, const Share& S, const Wv& T) {
+#pragma unroll
+    for (int t = 0; t < TPW; ++t)
+#pragma unroll
+        for (int m = 0; m < 2; ++m) {
+            const int tile = S.slot + t * S.waves;
+            wo[t][m] = tile < tiles ? *reinterpret_cast<const f32x4*>(w + 32 * tile + 16 * m + 4 * T.q) : f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+}
+
+// Hidden layers of the critics on (X): leaves z = h_L in registers.  h_l of layers l <= kept go to h[net][l].
+template <int NN, int TPW>
+__device__ __forceinline__ void critic_forward(f32x4 (&z)[TPW][2][2], const SplitShape& P, const float* const (*mats)[PQL_MAX_HIDDEN + 1],
+                                      int net, const Tile& X, const Tile& H, const Share& S, const SmallMem& M, int kept,
+                                      float* const (*h)[PQL_MAX_HIDDEN + 1], int r0, int B, const Wv& T, Ahead& cur,
+                                      const u32x4* next, float (&xv)[XV], const InputRows& following, bool fetch) {
+    float inv[2];
+    row_inv(inv, M.inv, T);
+    for (int l = 0; l < P.L; ++l) {
+        const int N = P.H[l];
+        const MatView W = mat_view(mats[net][l], l == 0 ? P.o + P.a : P.H[l - 1], N);
+        const u32x4* n = next;
+        if (l + 1 < P.L) n = first_step(mat_view(mats[net][l + 1], N, P.H[l + 1]), S.slot, 0);
+        forward<TPW>(z, W, l == 0 ? X : H, S, inv, T, cur, n);
+        if (l == 0 && fetch) request_rows(xv, following, (P.o + P.a + 31) >> 5, T);    // the next chain's input
+        if (l < kept) {
+#pragma unroll
+            for (int t = 0; t < TPW; ++t)
+                if (S.slot + t * S.waves < W.tiles) store_tile(h[net][l + 1], N, S.slot + t * S.waves, z[t], r0, B, T);
+        }
+        if (l < P.L - 1) put_tile<TPW>(z, W.tiles, H, S, M, inv, T);
+    }
+}
+
+// ---- distributional critics (PQL-D) on the tile ------------------------------------------------------------------------
+// Logits of a network from its last hidden tile: atoms <= 64 columns in two 32-column tiles, the wavefronts of a network take
+// one tile and every fourth k-step; the partial tiles go to LDS over the activations.  A row is then handled by one
+// wavefront, lane = atom.
+constexpr int DIST_PARTS = 8;        // partial tiles per network: (k-step mod 4) * 2 + tile
+__device__ __forceinline__ void put_logits(const MatView& W, const Tile& H, int at, const Share& S, const float (&inv)[2], const Wv& T,
+                                  Ahead& cur, const u32x4* next) {
+    const int tile = S.slot & 1, part = S.slot >> 1;
+    f32x4 acc[2][2];
+    clear(acc);
+    if (tile < W.tiles && part < W.ks) {
+        mac_steps(acc, W, tile, H, T, part, 4, cur, next);
+        scaled(acc, inv, W.inv[tile]);
+    } else {
+        request(cur, next, T);
+    }
+    put_partial(acc, at, S.net * DIST_PARTS + S.slot, true, T);
+}
+__device__ __forceinline__ float logit(int at, int net, int row, int k) {
+    const int col = k & 31;
+    const int e = (((col >> 4) * 2 + (row >> 4)) * 64 + ((col >> 2) & 3) * 16 + (row & 15)) * 4 + (col & 3);
+    const int p = at * 4 + (net * DIST_PARTS + (k >> 5)) * 1024 + e;
+    return (smem[p] + smem[p + 2048]) + (smem[p + 4096] + smem[p + 6144]);
+}
+__device__ __forceinline__ float wave_max(float x) {
+    x = fmaxf(x, dpp_move<0x128>(x));
+    x = fmaxf(x, dpp_move<0x124>(x));
+    x = fmaxf(x, dpp_move<0x122>(x));
+    return quarters_max(fmaxf(x, dpp_move<0x121>(x)));
+}
+// Softmax over the lanes < atoms (lane = atom): returns p and, through logp, log p (0 for idle lanes).
+__device__ __forceinline__ float lane_softmax(float x, bool live, float& logp) {
+    const float mx = wave_max(live ? x : -3.0e38f);
+    const float e = live ? expf(x - mx) : 0.f;
+    const float s = wsum(e);
+    logp = live ? (x - mx) - logf(s) : 0.f;
+    return e / s;
+}
+// The gradients at the logits (two rows per wavefront, both networks) as a two-step tile per network at `at`, each row with
+// its own scale (inverse scales to smem[inv_at + 32 net + row]).
+__device__ __forceinline__ Tile logit_tile(int at, int net) { return Tile{at + net * 2 * 8 * CS, 8 * CS}; }
+__device__ __forceinline__ void put_dlogits(const float (&dl)[2][2], int at, int inv_at, const Wv& T) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int rr = 0; rr < 2; ++rr) {
+            const int row = 2 * T.wave + rr;
+            float inv;
+            const float s = scale_for(wave_max(fabsf(dl[i][rr])), inv);
+            put_value(logit_tile(at, i), row, T.lane, dl[i][rr], s);
+            if (T.lane == 0) smem[inv_at + 32 * i + row] = inv;
+        }
+}
+
+__device__ __forceinline__ Wv wave_of() {
+    Wv T;
+    T.tid = threadIdx.x; T.lane = T.tid & 63; T.wave = __builtin_amdgcn_readfirstlane(T.tid >> 6);
+    T.l15 = T.lane & 15; T.q = T.lane >> 4;
+    return T;
+}
+
+// =============================================================================================
+// V-learner step on one row tile (Algorithm 3; Section 3.2 for the lagged target policy): a' = pi^v(s'),
+// t_i = Q'_i(s', a'), y = ret + boot * min(t_1, t_2); q_i = Q_i(s, a); loss partials, output deltas, and the deltas of
+// every hidden layer of both critics.  NN networks side by side, TPW output tiles per wavefront.
+// =============================================================================================
+template <int NN, int TPW, int VAR>
+__device__ __forceinline__ void critic_step(const SplitCriticArgs& A) {
+    constexpr bool SAC = VAR == VAR_SAC, DIST = VAR == VAR_DIST;
+    const Wv T = wave_of();
+    const SplitShape& P = A.shape;
+    const int B = A.B, L = P.L, a = P.a, HL = P.H[L - 1];
+    const int r0 = blockIdx.x * 32, wg = blockIdx.x, nwg = gridDim.x;
+    const int aw = SAC ? 2 * a : a;
+    const Share S = NN == 2 ? Share{T.wave >> 3, T.wave & 7, 8} : Share{0, T.wave, SW};
+    const Tile X = {P.x0, P.xplane}, H0 = {P.h0, P.hplane};
+    const Tile H = {P.h0 + S.net * 2 * P.hplane, P.hplane};
+    const SmallMem M = small_mem(P.sm, P.as);
+    const int steps = (P.o + a + 31) >> 5;
+    float xv[XV];
+    InputRows in = input_rows(A.next_obs, P.o, nullptr, -1, a, P.as, r0, B);
+    request_rows(xv, in, steps, T);
+    Ahead cur;
+    request(cur, first_step(mat_view(A.pi[0], P.o, P.H[0]), T.wave, 0), T);
+    auto critic_begin = [&](const float* const (&mats)[2][PQL_MAX_HIDDEN + 1], int net) {
+        return first_step(mat_view(mats[net][0], P.o + a, P.H[0]), S.slot, 0);
+    };
+    float ret[2], boot[2];
+#pragma unroll
+    for (int n = 0; n < 2; ++n) {
+        const int row = r0 + 16 * n + T.l15;
+        ret[n] = row < B ? A.ret[row] : 0.f;
+        boot[n] = row < B ? A.boot[row] : 0.f;
+    }
+    put_rows(xv, in, steps, X, M.inv, 1.f, T);
+    lds_barrier();
+    // ---- a' from the lagged policy
+    {
+        const int parts = policy_forward<NN == 2 ? (TPW + 1) / 2 : TPW>(P, A.pi, X, H0, M, false, nullptr, aw, r0, B, T,
+                                                                             cur, critic_begin(A.qt, S.net));
+        const int row = T.tid >> 5, col = T.tid & 31;
+        float act = 0.f;
+        if (SAC) {      // a' ~ pi^v(.|s') with its log-density (soft target)
+            float eps, raw;
+            const float lp = sample_action(H0.base, parts, row, col, a, A.pi_bias, r0, A.sac, act, eps, raw);
+            if (col == 0) smem[M.logp + row] = lp;
+        } else if (col < a) {
+            act = tanhf(sum_partials(H0.base, parts, row, col) + A.pi_bias[col]);
+        }
+        if (col < a) {
+            if (P.alias) smem[M.act + row * M.as + col] = act;
+            else put_value(X, row, P.o + col, act, __uint_as_float(0x7F000000u - __float_as_uint(smem[M.inv + row])));
+        }
+        lds_barrier();
+        if (SAC) {      // y = ret + boot (min Q' - alpha log pi): the entropy term joins the reward part here
+            const float alpha = expf(A.sac.log_alpha[0]);
+#pragma unroll
+            for (int n = 0; n < 2; ++n) ret[n] = ret[n] - boot[n] * (alpha * smem[M.logp + 16 * n + T.l15]);
+        }
+    }
+    // ---- target critics, y
+    f32x4 z[TPW][2][2], wo[TPW][2];
+    const int tilesL = (HL + 31) >> 5;
+    float y[2], mass[2];                     // TD target of this lane's rows / projected target distribution of this wavefront's (lane = atom)
+    const int atoms = DIST ? A.atoms : 2;
+    const bool live = T.lane < atoms;
+    const float dz = (A.v_max - A.v_min) / (float)(atoms - 1), zk = A.v_min + (float)T.lane * dz;
+    auto dist_begin = [&](const float* const (&mats)[2][PQL_MAX_HIDDEN + 1]) {
+        return first_step(mat_view(mats[S.net][L], HL, atoms), S.slot & 1, S.slot >> 1);
+    };
+    const InputRows online = input_rows(A.obs, P.o, A.act, -1, a, P.as, r0, B);
+    {
+        float tq[2][2];
+        for (int ni = 0; ni < (NN == 2 ? 1 : 2); ++ni) {
+            const int net = NN == 2 ? S.net : ni;
+            if (P.alias) {      // the input tile shares its place with the activations: bring the rows in again
+                if (ni > 0) lds_barrier();
+                in.act_lds = M.act;
+                request_rows(xv, in, steps, T);
+                put_rows(xv, in, steps, X, M.inv, 1.f, T);
+                lds_barrier();
+            }
+            if (!DIST) head_weights<TPW>(wo, A.wo_t[net], tilesL, S, T);
+            const bool last = NN == 2 || ni == 1;
+            critic_forward<NN, TPW>(z, P, A.qt, net, X, H, S, M, 0, nullptr, r0, B, T, cur,
+                                    DIST ? dist_begin(A.qt) : (last ? critic_begin(A.q, S.net) : critic_begin(A.qt, 1)), xv, online,
+                                    last);
+            if (DIST) {
+                // the target critic with the smaller mean supplies the next-state distribution; its atoms move to
+                // clip(ret + boot z) and are projected back onto the support (lane k gathers atom k's mass)
+                float inv[2];
+                put_tile<TPW>(z, tilesL, H, S, M, inv, T);
+                put_logits(mat_view(A.qt[net][L], HL, atoms), H, H0.base, S, inv, T, cur, critic_begin(A.q, S.net));
+                const float b0 = live ? A.bo_t[0][T.lane] : 0.f, b1 = live ? A.bo_t[1][T.lane] : 0.f;
+#pragma unroll
+                for (int rr = 0; rr < 2; ++rr) {
+                    const int row = 2 * T.wave + rr;
+                    float unused;
+                    const float t0 = lane_softmax(logit(H0.base, 0, row, T.lane) + b0, live, unused);
+                    const float t1 = lane_softmax(logit(H0.base, 1, row, T.lane) + b1, live, unused);
+                    const float pn = wsum(t0 * zk) <= wsum(t1 * zk) ? t0 : t1;
+                    const bool rv = r0 + row < B;
+                    const float rt = rv ? A.ret[r0 + row] : 0.f, bt = rv ? A.boot[r0 + row] : 0.f;
+                    const float pos = (fminf(fmaxf(rt + bt * zk, A.v_min), A.v_max) - A.v_min) / dz;
+                    float mm = 0.f;
+                    for (int j = 0; j < atoms; ++j)         // j is wave-uniform: lane j's values come as scalars
+                        mm += lane_value(pn, j) * fminf(fmaxf(1.f - fabsf(lane_value(pos, j) - (float)T.lane), 0.f), 1.f);
+                    mass[rr] = live ? mm : 0.f;
+                }
+                continue;
+            }
+            float bias[NN], q[NN][2];
+#pragma unroll
+            for (int i = 0; i < NN; ++i) bias[i] = A.bo_t[NN == 2 ? i : net][0];
+            head_values<NN, TPW>(z, wo, S, M, bias, q, T);
+#pragma unroll
+            for (int n = 0; n < 2; ++n) {
+                if (NN == 2) { tq[0][n] = q[0][n]; tq[1][n] = q[NN - 1][n]; }
+                else if (ni == 0) tq[0][n] = q[0][n];
+                else tq[1][n] = q[0][n];
+            }
+        }
+#pragma unroll
+        for (int n = 0; n < 2 && !DIST; ++n) {
+            y[n] = ret[n] + boot[n] * fminf(tq[0][n], tq[1][n]);
+            const int row = r0 + 16 * n + T.l15;
+            if (T.wave == 0 && T.q == 0 && row < B) A.y[row] = y[n];
+        }
+    }
+    // ---- online critics: forward, head, backward data path
+    const float invB = 1.f / (float)B;
+    in = online;
+    for (int ni = 0; ni < (NN == 2 ? 1 : 2); ++ni) {
+        const int net = NN == 2 ? S.net : ni;
+        if (NN == 2 || P.alias || ni == 0) {
+            if (ni > 0) request_rows(xv, in, steps, T);       // (else requested during the target critics)
+            lds_barrier();     // the head partials of the networks before have been read, and so has their input
+            put_rows(xv, in, steps, X, M.inv, 0.f, T);
+        }
+        lds_barrier();
+        if (!DIST) head_weights<TPW>(wo, A.wo_q[net], tilesL, S, T);
+        const u32x4* after = NN == 1 && ni == 0 ? critic_begin(A.q, 1) : cur_valid(A.q[0][0]);
+        const u32x4* back = L > 1 ? first_step(mat_view(A.qT[net][L - 1], HL, P.H[L - 2]), S.slot, 0) : after;
+        critic_forward<NN, TPW>(z, P, A.q, net, X, H, S, M, DIST ? L : L - 1, A.h, r0, B, T, cur, DIST ? dist_begin(A.q) : back, xv, in,
+                                false);
+        if (DIST) {
+            // cross-entropy against the projected target, dLoss/dlogits, and through the output layer to h_L
+            float inv[2];
+            const MatView WT = mat_view(A.qT[net][L], atoms, HL);
+            put_tile<TPW>(z, tilesL, H, S, M, inv, T);
+            put_logits(mat_view(A.q[net][L], HL, atoms), H, H0.base, S, inv, T, cur, first_step(WT, S.slot, 0));
+            float dl[2][2], lsum[2] = {0.f, 0.f}, dsum[2] = {0.f, 0.f};
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                const float b = live ? A.bo_q[i][T.lane] : 0.f;
+#pragma unroll
+                for (int rr = 0; rr < 2; ++rr) {
+                    const int row = 2 * T.wave + rr;
+                    const bool rv = r0 + row < B;
+                    float lp;
+                    const float p = lane_softmax(logit(H0.base, i, row, T.lane) + b, live, lp);
+                    const float sum = wsum(mass[rr]), ce = wsum(mass[rr] * lp);
+                    if (rv) lsum[i] -= ce;
+                    dl[i][rr] = (rv && live) ? (p * sum - mass[rr]) * invB : 0.f;
+                    dsum[i] += dl[i][rr];
+                    if (rv && live) A.dlg[i][(size_t)(r0 + row) * atoms + T.lane] = dl[i][rr];
+                }
+            }
+            lds_barrier();                                   // the partial tiles have been read
+            put_dlogits(dl, H0.base, M.part, T);
+            float* sums = &smem[(H0.base + 4 * 8 * CS) * 4];  // [2][16][64] output-bias gradients, behind the two tiles
+            sums[T.wave * 64 + T.lane] = dsum[0];
+            sums[(SW + T.wave) * 64 + T.lane] = dsum[1];
+            if (T.lane == 0) { smem[M.part + 64 + T.wave] = lsum[0]; smem[M.part + 80 + T.wave] = lsum[1]; }
+            lds_barrier();
+            if (T.tid < 128) {
+                const int i = T.tid >> 6, k = T.tid & 63;
+                float s = 0.f;
+                for (int w = 0; w < SW; ++w) s += sums[(i * SW + w) * 64 + k];
+                if (k < atoms) A.p_dbo[i][(size_t)wg * atoms + k] = s;
+            } else if (T.tid < 130) {
+                const int i = T.tid - 128;
+                float s = 0.f;
+                for (int w = 0; w < SW; ++w) s += smem[M.part + 64 + 16 * i + w];
+                A.p_loss[i * nwg + wg] = s;
+            }
+            row_inv(inv, M.part + 32 * net, T);
+            f32x4 hl[2][2];
+            load_ahead<TPW>(A.h[net][L], HL, hl, S, r0, B, T);
+            backward<TPW>(z, WT, logit_tile(H0.base, net), S, inv, A.h[net][L], A.d[net][L], A.col[net][L] + (size_t)wg * HL, HL, r0, B, T,
+                          cur, back, hl);
+        } else {
+        float bias[NN], q[NN][2];
+#pragma unroll
+        for (int i = 0; i < NN; ++i) bias[i] = A.bo_q[NN == 2 ? i : net][0];
+        head_values<NN, TPW>(z, wo, S, M, bias, q, T);
+        float d[2], loss = 0.f, db = 0.f;
+#pragma unroll
+        for (int n = 0; n < 2; ++n) {
+            const int row = r0 + 16 * n + T.l15;
+            const bool rv = row < B;
+            const float qv = NN == 2 ? (S.net == 0 ? q[0][n] : q[NN - 1][n]) : q[0][n];
+            const float e = rv ? qv - y[n] : 0.f;
+            d[n] = 2.f * e * invB;
+            loss += e * e;
+            db += d[n];
+            if (S.slot == 0 && T.q == 0 && rv) A.q_out[net][row] = qv;
+        }
+        if (S.slot == 0) {
+            loss = row16_sum(loss);
+            db = row16_sum(db);
+            if (T.lane == 0) { A.p_loss[net * nwg + wg] = loss; A.p_db[net][wg] = db; }
+        }
+#pragma unroll
+        for (int t = 0; t < TPW; ++t) {
+            const int tile = S.slot + t * S.waves;
+            if (tile >= tilesL) continue;
+            f32x4 dw[2], cs[2];
+#pragma unroll
+            for (int m = 0; m < 2; ++m)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    dw[m][r] = d[0] * z[t][m][0][r] + d[1] * z[t][m][1][r];
+#pragma unroll
+                    for (int n = 0; n < 2; ++n) z[t][m][n][r] = d[n] * wo[t][m][r] * delu_h(z[t][m][n][r]);
+                    cs[m][r] = z[t][m][0][r] + z[t][m][1][r];
+                }
+            store_tile(A.d[net][L], HL, tile, z[t], r0, B, T);
+            store_colsum(A.p_dw[net] + (size_t)wg * HL, HL, tile, dw, T);
+            store_colsum(A.p_dbh[net] + (size_t)wg * HL, HL, tile, cs, T);
+        }
+        }
+        float inv[2];
+        f32x4 hv[2][2];
+        for (int l = L; l >= 2; --l) {
+            const int Hl = P.H[l - 1], Hp = P.H[l - 2];
+            load_ahead<TPW>(A.h[net][l - 1], Hp, hv, S, r0, B, T);
+            put_tile<TPW>(z, (Hl + 31) >> 5, H, S, M, inv, T);
+            const MatView W = mat_view(A.qT[net][l - 1], Hl, Hp);
+            backward<TPW>(z, W, H, S, inv, A.h[net][l - 1], A.d[net][l - 1], A.col[net][l - 1] + (size_t)wg * Hp, Hp, r0, B, T, cur,
+                          l > 2 ? first_step(mat_view(A.qT[net][l - 2], Hp, P.H[l - 3]), S.slot, 0) : after, hv);
+        }
+    }
+}
+
+// =============================================================================================
+// P-learner step on one row tile (Algorithm 2: maximise min_i Q_i(s, pi(s))): a = pi(s), both critics on (s, a), the
+// gradient -1/B through the smaller critic down to its action input, through tanh' and back through the policy.
+// =============================================================================================
+template <int NN, int TPW, int VAR>
+__device__ __forceinline__ void policy_step(const SplitPolicyArgs& A) {
+    constexpr bool SAC = VAR == VAR_SAC, DIST = VAR == VAR_DIST;
+    const Wv T = wave_of();
+    const SplitShape& P = A.shape;
+    constexpr int TPA = NN == 2 ? (TPW + 1) / 2 : TPW;       // the policy's tiles per wavefront
+    const int B = A.B, L = P.L, a = P.a, HL = P.H[L - 1], H1 = P.H[0];
+    const int r0 = blockIdx.x * 32, wg = blockIdx.x;
+    const int aw = SAC ? 2 * a : a;
+    const Share S = NN == 2 ? Share{T.wave >> 3, T.wave & 7, 8} : Share{0, T.wave, SW};
+    const Tile X = {P.x0, P.xplane}, H0 = {P.h0, P.hplane};
+    const Tile H = {P.h0 + S.net * 2 * P.hplane, P.hplane};
+    const SmallMem M = small_mem(P.sm, P.as);
+    const int atoms = DIST ? A.atoms : 2;
+    const int steps = (P.o + a + 31) >> 5;
+    const int row = T.tid >> 5, col = T.tid & 31;            // this thread's element of an action-wide tile
+    float xv[XV];
+    InputRows in = input_rows(A.obs, P.o, nullptr, -1, a, P.as, r0, B);
+    request_rows(xv, in, steps, T);
+    Ahead cur;
+    request(cur, first_step(mat_view(A.pi[0], P.o, P.H[0]), T.wave, 0), T);
+    auto critic_begin = [&](int net) { return first_step(mat_view(A.q[net][0], P.o + a, P.H[0]), S.slot, 0); };
+    // the first of the backward products of critic `net`: from its last hidden layer down, or its action gradient
+    auto action_begin = [&](int net) { return first_step(mat_view(A.w1aT[net], H1, a), 0, S.slot); };
+    auto back_begin = [&](int net) {
+        return L > 1 ? first_step(mat_view(A.qT[net][L - 1], HL, P.H[L - 2]), S.slot, 0) : action_begin(net);
+    };
+    put_rows(xv, in, steps, X, M.inv, 1.f, T);
+    lds_barrier();
+    float act = 0.f, eps = 0.f, raw = 0.f, logp = 0.f;
+    {
+        const int parts = policy_forward<TPA>(P, A.pi, X, H0, M, true, A.hA, aw, r0, B, T, cur, critic_begin(S.net));
+        if (SAC) logp = sample_action(H0.base, parts, row, col, a, A.pi_bias, r0, A.sac, act, eps, raw);
+        else if (col < a) act = tanhf(sum_partials(H0.base, parts, row, col) + A.pi_bias[col]);
+        if (col < a) {
+            if (P.alias) smem[M.act + row * M.as + col] = act;
+            else put_value(X, row, P.o + col, act, __uint_as_float(0x7F000000u - __float_as_uint(smem[M.inv + row])));
+        }
+        lds_barrier();
+    }
+    // ---- both critics on (s, a)
+    f32x4 z[TPW][2][2], wo[TPW][2];
+    const int tilesL = (HL + 31) >> 5;
+    float qv[2][2];
+    for (int ni = 0; ni < (NN == 2 ? 1 : 2); ++ni) {
+        const int net = NN == 2 ? S.net : ni;
+        if (P.alias) {
+            if (ni > 0) lds_barrier();
+            in.act_lds = M.act;
+            request_rows(xv, in, steps, T);
+            put_rows(xv, in, steps, X, M.inv, 1.f, T);
+            lds_barrier();
+        }
+        if (!DIST) head_weights<TPW>(wo, A.wo[net], tilesL, S, T);
+        critic_forward<NN, TPW>(z, P, A.q, net, X, H, S, M, NN == 2 && !DIST ? L - 1 : L, A.h, r0, B, T, cur,
+                                DIST ? first_step(mat_view(A.q[net][L], HL, atoms), S.slot & 1, S.slot >> 1)
+                                     : (NN == 1 && ni == 0 ? critic_begin(1) : back_begin(S.net)), xv, in, false);
+        if (DIST) continue;
+        float bias[NN], q[NN][2];
+#pragma unroll
+        for (int i = 0; i < NN; ++i) bias[i] = A.bo[NN == 2 ? i : net][0];
+        head_values<NN, TPW>(z, wo, S, M, bias, q, T);
+#pragma unroll
+        for (int n = 0; n < 2; ++n) {
+            if (NN == 2) { qv[0][n] = q[0][n]; qv[1][n] = q[NN - 1][n]; }
+            else if (ni == 0) qv[0][n] = q[0][n];
+            else qv[1][n] = q[0][n];
+        }
+    }
+    const float invB = 1.f / (float)B;
+    float pick0[2], pick1[2], loss = 0.f;
+    if (DIST) {
+        // Q_i = mean of critic i's distribution; the smaller one receives dJ/dlogit_k = -(1/B) p_k (z_k - Q), and from
+        // there through its output layer to h_L
+        const int net = S.net;
+        const bool live = T.lane < atoms;
+        const float zk = A.v_min + (float)T.lane * ((A.v_max - A.v_min) / (float)(atoms - 1));
+        float inv[2];
+        const MatView WT = mat_view(A.qT[net][L], atoms, HL);
+        put_tile<TPW>(z, tilesL, H, S, M, inv, T);
+        put_logits(mat_view(A.q[net][L], HL, atoms), H, H0.base, S, inv, T, cur, first_step(WT, S.slot, 0));
+        const float b0 = live ? A.bo[0][T.lane] : 0.f, b1 = live ? A.bo[1][T.lane] : 0.f;
+        float dl[2][2];
+#pragma unroll
+        for (int rr = 0; rr < 2; ++rr) {
+            const int tr = 2 * T.wave + rr;
+            const bool rv = r0 + tr < B;
+            float unused;
+            const float p0 = lane_softmax(logit(H0.base, 0, tr, T.lane) + b0, live, unused);
+            const float p1 = lane_softmax(logit(H0.base, 1, tr, T.lane) + b1, live, unused);
+            const float q0 = wsum(p0 * zk), q1 = wsum(p1 * zk);
+            const bool first = q0 <= q1;
+            if (rv) loss += first ? q0 : q1;
+            if (T.lane == 0 && rv) { A.q_out[0][r0 + tr] = q0; A.q_out[1][r0 + tr] = q1; }
+            dl[0][rr] = (rv && live && first) ? -invB * p0 * (zk - q0) : 0.f;
+            dl[1][rr] = (rv && live && !first) ? -invB * p1 * (zk - q1) : 0.f;
+        }
+        lds_barrier();                                       // the partial tiles have been read
+        put_dlogits(dl, H0.base, M.part, T);
+        if (T.lane == 0) smem[M.part + 64 + T.wave] = loss;
+        lds_barrier();
+        if (T.tid == 0) {
+            float s = 0.f;
+            for (int w = 0; w < SW; ++w) s += smem[M.part + 64 + w];
+            A.p_loss[wg] = s;
+        }
+        row_inv(inv, M.part + 32 * net, T);
+        f32x4 hl[2][2];
+        load_ahead<TPW>(A.h[net][L], HL, hl, S, r0, B, T);
+        backward<TPW>(z, WT, logit_tile(H0.base, net), S, inv, A.h[net][L], nullptr, nullptr, HL, r0, B, T, cur, back_begin(net), hl);
+    }
+#pragma unroll
+    for (int n = 0; n < 2 && !DIST; ++n) {
+        const int rr = r0 + 16 * n + T.l15;
+        const bool rv = rr < B, first = qv[0][n] <= qv[1][n];
+        pick0[n] = rv && first ? -invB : 0.f;
+        pick1[n] = rv && !first ? -invB : 0.f;
+        if (rv) loss += first ? qv[0][n] : qv[1][n];
+        if (T.wave == 0 && T.q == 0 && rv) { A.q_out[0][rr] = qv[0][n]; A.q_out[1][rr] = qv[1][n]; }
+    }
+    if (!DIST && T.wave == 0) {
+        loss = row16_sum(loss);
+        if (T.lane == 0) A.p_loss[wg] = loss;
+    }
+    // ---- down to the critics' action input
+    f32x4 da[2][2];
+    clear(da);
+    float inv[2];
+    for (int ni = 0; ni < (NN == 2 ? 1 : 2); ++ni) {
+        const int net = NN == 2 ? S.net : ni;
+        if (NN == 1) {
+            head_weights<TPW>(wo, A.wo[net], tilesL, S, T);
+#pragma unroll
+            for (int t = 0; t < TPW; ++t)
+                if (S.slot + t * S.waves < tilesL) load_tile(A.h[net][L], HL, S.slot + t * S.waves, z[t], r0, B, T);
+                else clear(z[t]);
+        }
+#pragma unroll
+        for (int t = 0; t < TPW; ++t)
+#pragma unroll
+            for (int m = 0; m < 2; ++m)
+#pragma unroll
+                for (int n = 0; n < 2 && !DIST; ++n)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        z[t][m][n][r] = (net == 0 ? pick0[n] : pick1[n]) * wo[t][m][r] * delu_h(z[t][m][n][r]);
+        f32x4 hv[2][2];
+        for (int l = L; l >= 2; --l) {
+            const int Hl = P.H[l - 1], Hp = P.H[l - 2];
+            load_ahead<TPW>(A.h[net][l - 1], Hp, hv, S, r0, B, T);
+            put_tile<TPW>(z, (Hl + 31) >> 5, H, S, M, inv, T);
+            const MatView W = mat_view(A.qT[net][l - 1], Hl, Hp);
+            backward<TPW>(z, W, H, S, inv, A.h[net][l - 1], nullptr, nullptr, Hp, r0, B, T, cur,
+                          l > 2 ? first_step(mat_view(A.qT[net][l - 2], Hp, P.H[l - 3]), S.slot, 0) : action_begin(net), hv);
+        }
+        put_tile<TPW>(z, (H1 + 31) >> 5, H, S, M, inv, T);
+        const MatView W = mat_view(A.w1aT[net], H1, a);
+        const u32x4* after = NN == 1 && ni == 0 ? back_begin(1) : first_step(mat_view(A.waT[L], aw, HL), T.wave, 0);
+        f32x4 acc[2][2];
+        clear(acc);
+        if (S.slot < W.ks) mac_steps(acc, W, 0, H, T, S.slot, S.waves, cur, after);
+        else request(cur, after, T);
+        scaled(acc, inv, W.inv[0]);
+#pragma unroll
+        for (int m = 0; m < 2; ++m)
+#pragma unroll
+            for (int n = 0; n < 2; ++n) da[m][n] += acc[m][n];
+    }
+    const int ks1 = (H1 + 31) >> 5;
+    const int per = ks1 < S.waves ? ks1 : S.waves;           // partial tiles per network
+    put_partial(da, H0.base, S.net * per + S.slot, S.slot < per, T);
+    float g = 0.f, g2 = 0.f;                                 // gradient at the output layer: column col, and a + col (raw)
+    {
+        const bool rv = r0 + row < B;
+        const float s = col < a ? sum_partials(H0.base, NN * per, row, col) : 0.f;
+        if (!SAC) {
+            g = (col < a && rv) ? s * (1.f - act * act) : 0.f;
+        } else if (col < a && rv) {
+            // J = mean(alpha log pi - min Q): dJ/dmu = dJ/du = g + (alpha/B) 2a; dJ/draw = dJ/du sigma eps - alpha/B
+            // inside the clip of log sigma, 0 outside
+            const float ab = expf(A.sac.log_alpha[0]) / (float)B;
+            const float ls = fminf(fmaxf(raw, SAC_LOG_STD_MIN), SAC_LOG_STD_MAX);
+            g = s * (1.f - act * act) + ab * 2.f * act;
+            g2 = (raw > SAC_LOG_STD_MIN && raw < SAC_LOG_STD_MAX) ? g * expf(ls) * eps - ab : 0.f;
+        }
+        if (col < a && rv) {
+            A.dPre[(size_t)(r0 + row) * aw + col] = g;
+            if (SAC) A.dPre[(size_t)(r0 + row) * aw + a + col] = g2;
+        }
+    }
+    lds_barrier();                                         // the partial tiles have been read
+    // one k-step of 32 columns at the place of the activations, with its own row scales; column sums for the output bias
+    const Tile D = {P.h0, 4 * CS};
+    float* sums = &smem[P.h0 * 4 + 2 * 4 * CS * 4];          // [32][33] behind that tile
+    {
+        float inv_d;
+        const float s = scale_for(half_max(fmaxf(fabsf(g), fabsf(g2))), inv_d);
+        if (col == 0) smem[M.inv + row] = inv_d;
+        if (!SAC || col < a || col >= aw) put_value(D, row, col, g, s);
+        if (SAC && col < a) put_value(D, row, a + col, g2, s);
+        if (!SAC || col < a) sums[row * 33 + col] = g;
+        if (SAC && col < a) sums[row * 33 + a + col] = g2;
+    }
+    lds_barrier();
+    if (T.tid < aw) {
+        float s = 0.f;
+        for (int r = 0; r < 32; ++r) s += sums[r * 33 + T.tid];
+        A.colA[L + 1][(size_t)wg * aw + T.tid] = s;
+    }
+    if (SAC) {
+        const float lp = col == 0 && r0 + row < B ? logp : 0.f;
+        if (col == 0) smem[M.logp + row] = lp;
+        lds_barrier();
+        if (T.tid == 0) {
+            float s = 0.f;
+            for (int r = 0; r < 32; ++r) s += smem[M.logp + r];
+            A.p_logp[wg] = s;
+        }
+    }
+    // ---- back through the policy
+    {
+        const Share SA = {0, T.wave, SW};
+        f32x4 za[TPA][2][2], hv[2][2];
+        row_inv(inv, M.inv, T);
+        load_ahead<TPA>(A.hA[L], HL, hv, SA, r0, B, T);
+        for (int l = L; l >= 1; --l) {
+            const int N = P.H[l - 1];
+            const MatView W = mat_view(A.waT[l], l == L ? aw : P.H[l], N);
+            backward<TPA>(za, W, l == L ? D : H0, SA, inv, A.hA[l], A.dA[l], A.colA[l] + (size_t)wg * N, N, r0, B, T, cur,
+                          l > 1 ? first_step(mat_view(A.waT[l - 1], N, P.H[l - 2]), T.wave, 0) : cur_valid(A.pi[0]), hv);
+            if (l > 1) {
+                load_ahead<TPA>(A.hA[l - 1], P.H[l - 2], hv, SA, r0, B, T);
+                put_tile<TPA>(za, W.tiles, H0, SA, M, inv, T);
+            }
+        }
+    }
+}
+
+// =============================================================================================
+// Actor step on one row tile (Section 3.3, Algorithm 1): a = clip(pi(s) + sigma_i * eps, -1, 1).
+// =============================================================================================
+template <int TPW, int VAR>
+__device__ __forceinline__ void act_step(const SplitActArgs& A) {
+    constexpr bool SAC = VAR == VAR_SAC;
+    const Wv T = wave_of();
+    const SplitShape& P = A.shape;
+    const int B = A.B, a = P.a, r0 = blockIdx.x * 32;
+    const int aw = SAC ? 2 * a : a;
+    const Tile X = {P.x0, P.xplane}, H = {P.h0, P.hplane};
+    const SmallMem M = small_mem(P.sm, P.as);
+    const int steps = (P.o + 31) >> 5;
+    float xv[XV];
+    InputRows in = input_rows(A.obs, P.o, nullptr, -1, 0, P.as, r0, B);
+    if (A.nmean != nullptr) {
+        in.norm = true;
+        in.mean = rows_of(A.nmean, P.o, 0, 1); in.rstd = rows_of(A.nrstd, P.o, 0, 1);
+    }
+    request_rows(xv, in, steps, T);
+    Ahead cur;
+    request(cur, first_step(mat_view(A.pi[0], P.o, P.H[0]), T.wave, 0), T);
+    put_rows(xv, in, steps, X, M.inv, 0.f, T);
+    lds_barrier();
+    const int parts = policy_forward<TPW>(P, A.pi, X, H, M, false, nullptr, aw, r0, B, T, cur, cur_valid(A.pi[0]));
+    const int row = T.tid >> 5, col = T.tid & 31, env = r0 + row;
+    if (SAC) {
+        float act, eps, raw;
+        (void)sample_action(H.base, parts, row, col, a, A.pi_bias, r0, A.sac, act, eps, raw);
+        if (col < a && env < B) A.act_out[(size_t)env * a + col] = act;
+    } else if (col < a && env < B) {
+        const GemmNoise& nz = A.noise;
+        uint32_t w0, w1;
+        philox4x32_10_f((uint32_t)(env * a + col), 2u, nz.ctr2, nz.ctr3, nz.key0, nz.key1, w0, w1);
+        // double precision: (w >> 8) + 0.5 needs 25 significant bits
+        const double u1 = ((double)(w0 >> 8) + 0.5) * 0x1p-24;
+        const double u2 = ((double)(w1 >> 8) + 0.5) * 0x1p-24;
+        const double e = sqrt(-2.0 * log(u1)) * cos(6.283185307179586476925286766559 * u2);
+        double sigma = (double)nz.sigma_min;
+        if (nz.sigma_rows > 1)
+            sigma += ((double)env / (double)(nz.sigma_rows - 1)) * ((double)nz.sigma_max - (double)nz.sigma_min);
+        const float x = tanhf(sum_partials(H.base, parts, row, col) + A.pi_bias[col]) + (float)(sigma * e);
+        A.act_out[(size_t)env * a + col] = fminf(fmaxf(x, -1.f), 1.f);
+    }
+}
+
+// ---- host side ------------------------------------------------------------------------------------------------
+// LDS plan of a shape: the activation tiles of `nets` networks, the input tile behind them or, where that does not fit, in
+// their place, and the small arrays.  Returns the bytes, 0 if the shape does not fit at all.
+static size_t plan_lds(SplitShape& p, int nets, int in_cols, bool dist = false) {
+    int w = 0;
+    for (int l = 0; l < p.L; ++l) w = p.H[l] > w ? p.H[l] : w;
+    p.hplane = (w + 31) / 32 * 4 * CS;
+    p.xplane = (in_cols + 31) / 32 * 4 * CS;
+    p.as = p.a | 1;
+    const int h_units = nets * 2 * p.hplane;
+    const size_t small = sizeof(float) * (size_t)(1088 + 32 * p.as);
+    // the policy step's output-layer tile and its column sums also live in the place of the activations
+    // (distributional critics: sixteen partial tiles of logits)
+    const int least = dist ? 2 * DIST_PARTS * 256 : 2 * 4 * CS + 32 * 33 / 4;
+    p.h0 = 0; p.x0 = h_units < least ? least : h_units; p.alias = 0;
+    size_t units = (size_t)p.x0 + 2 * (size_t)p.xplane;
+    if (units * 16 + small > SPLIT_LDS) {
+        p.x0 = 0; p.alias = 1;
+        units = (size_t)(h_units > 2 * p.xplane ? h_units : 2 * p.xplane);
+        if (units < (size_t)least) units = (size_t)least;
+    }
+    p.sm = (int)units * 4;
+    const size_t bytes = units * 16 + small;
+    return bytes <= SPLIT_LDS ? bytes : 0;
+}
+static int widest(const SplitShape& p) {
+    int w = 0;
+    for (int l = 0; l < p.L; ++l) w = p.H[l] > w ? p.H[l] : w;
+    return w;
+}
+
+bool split_shape_ok(int o, int a, int aw, const int* H, int L, bool dist) {
+    if (aw > FUSED_MAX_ACT || o + a > SPLIT_MAXW) return false;
+    SplitShape p;
+    p.o = o; p.a = a; p.L = L;
+    for (int l = 0; l < L; ++l) {
+        if (H[l] > SPLIT_MAXW) return false;
+        p.H[l] = H[l];
+    }
+    if (dist && widest(p) > 512) return false;
+    return plan_lds(p, widest(p) <= 512 ? 2 : 1, o + a, dist) != 0;
+}
+
+// ---- kernels ------------------------------------------------------------------------------------------------------
+// fused_*: every layer at most 256 wide; chain_*: a widest layer of 512 (two output tiles per wavefront); split_*: the
+// other shapes, layers above 512 with the critics one after the other.
+template <int VAR>
+__global__ __launch_bounds__(ST) void fused_critic_kernel(const SplitCriticArgs) { critic_step<2, 1, VAR>(kernel_args<SplitCriticArgs>()); }
+template <int VAR>
+__global__ __launch_bounds__(ST) void chain_critic_kernel(const SplitCriticArgs) { critic_step<2, 2, VAR>(kernel_args<SplitCriticArgs>()); }
+template <int NN, int TPW, int VAR>
+__global__ __launch_bounds__(ST) void split_critic_kernel(const SplitCriticArgs) { critic_step<NN, TPW, VAR>(kernel_args<SplitCriticArgs>()); }
+template <int VAR>
+__global__ __launch_bounds__(ST) void fused_policy_kernel(const SplitPolicyArgs) { policy_step<2, 1, VAR>(kernel_args<SplitPolicyArgs>()); }
+template <int VAR>
+__global__ __launch_bounds__(ST) void chain_policy_kernel(const SplitPolicyArgs) { policy_step<2, 2, VAR>(kernel_args<SplitPolicyArgs>()); }
+template <int NN, int TPW, int VAR>
+__global__ __launch_bounds__(ST) void split_policy_kernel(const SplitPolicyArgs) { policy_step<NN, TPW, VAR>(kernel_args<SplitPolicyArgs>()); }
+template <int VAR>
+__global__ __launch_bounds__(ST) void fused_act_kernel(const SplitActArgs) { act_step<1, VAR>(kernel_args<SplitActArgs>()); }
+template <int VAR>
+__global__ __launch_bounds__(ST) void chain_act_kernel(const SplitActArgs) { act_step<1, VAR>(kernel_args<SplitActArgs>()); }
+
+#define SPLIT_LAUNCH(KERNEL, KID)                                                                                  \
+    do {                                                                                                           \
+        static LdsLimit configured;                                                                                \
+        const hipError_t le = set_lds_limit(reinterpret_cast<const void*>(KERNEL), lds, configured);               \
+        if (le != hipSuccess) return le;                                                                           \
+        const ProfSlot ps = prof_slot();                                                                           \
+        PQL_LAUNCH(ps, (KERNEL), dim3((a.B + 31) / 32), dim3(ST), lds, stream, a);                                 \
+        prof_commit(ps, KID, flops, 0.0);                                                                          \
+        return hipGetLastError();                                                                                  \
+    } while (0)
+// Picks the kernel of one step: class, shape and policy variant are fixed at compile time.
+#define SPLIT_PICK(STEP, VAR)                                                                                      \
+    do {                                                                                                           \
+        if (kind == SPLIT_FUSED) SPLIT_LAUNCH((fused_##STEP##_kernel<VAR>), fused_kid);                            \
+        if (kind == SPLIT_CHAIN && VAR == VAR_PLAIN) SPLIT_LAUNCH((chain_##STEP##_kernel<VAR_PLAIN>), chain_kid);  \
+        if (w <= 256) SPLIT_LAUNCH((split_##STEP##_kernel<2, 1, VAR>), split_kid);                                 \
+        if (w <= 512) SPLIT_LAUNCH((split_##STEP##_kernel<2, 2, VAR>), split_kid);                                 \
+        if (VAR != VAR_DIST) SPLIT_LAUNCH((split_##STEP##_kernel<1, 2, VAR == VAR_DIST ? VAR_PLAIN : VAR>), split_kid); \
+    } while (0)
+
+static bool kind_fits(int kind, int w) {
+    return kind == SPLIT_FUSED ? w <= 256 : (kind == SPLIT_CHAIN ? w <= 512 : true);
+}
+
+hipError_t split_critic_launch(SplitCriticArgs& a, int kind, hipStream_t stream) {
+    SplitShape& p = a.shape;
+    const int w = widest(p), aw = a.sac.on ? 2 * p.a : p.a;
+    if (!split_shape_ok(p.o, p.a, aw, p.H, p.L) || !kind_fits(kind, w) || (a.atoms >= 2 && (w > 512 || a.sac.on))) return hipErrorInvalidValue;
+    const size_t lds = plan_lds(p, w <= 512 ? 2 : 1, p.o + p.a, a.atoms >= 2);
+    const double outs = a.atoms >= 2 ? (double)a.atoms : 1.0;
+    double pa = (double)p.o * p.H[0], pc = (double)(p.o + p.a) * p.H[0], pb = 0.0;
+    for (int l = 1; l < p.L; ++l) { const double x = (double)p.H[l - 1] * p.H[l]; pa += x; pc += x; pb += x; }
+    pa += (double)p.H[p.L - 1] * aw; pc += p.H[p.L - 1] * outs; pb += p.H[p.L - 1] * outs;
+    const double flops = 2.0 * a.B * (pa + 4.0 * pc + 2.0 * pb);
+    const int fused_kid = KID_FUSED_CRITIC, chain_kid = KID_CHAIN_CRITIC, split_kid = KID_SPLIT_CRITIC;
+    if (a.sac.on) SPLIT_PICK(critic, VAR_SAC);
+    if (a.atoms >= 2) SPLIT_PICK(critic, VAR_DIST);
+    SPLIT_PICK(critic, VAR_PLAIN);
+    return hipErrorInvalidValue;
+}
+
+hipError_t split_policy_launch(SplitPolicyArgs& a, int kind, hipStream_t stream) {
+    SplitShape& p = a.shape;
+    const int w = widest(p), aw = a.sac.on ? 2 * p.a : p.a;
+    if (!split_shape_ok(p.o, p.a, aw, p.H, p.L) || !kind_fits(kind, w) || (a.atoms >= 2 && (w > 512 || a.sac.on))) return hipErrorInvalidValue;
+    const size_t lds = plan_lds(p, w <= 512 ? 2 : 1, p.o + p.a, a.atoms >= 2);
+    const double outs = a.atoms >= 2 ? (double)a.atoms : 1.0;
+    double pa = (double)p.o * p.H[0], pc = (double)(p.o + p.a) * p.H[0], pb = (double)p.a * p.H[0], pab = 0.0;
+    for (int l = 1; l < p.L; ++l) { const double x = (double)p.H[l - 1] * p.H[l]; pa += x; pc += x; pb += x; pab += x; }
+    pa += (double)p.H[p.L - 1] * aw; pab += (double)p.H[p.L - 1] * aw; pc += p.H[p.L - 1] * outs; pb += p.H[p.L - 1] * outs;
+    const double flops = 2.0 * a.B * (pa + 2.0 * pc + 2.0 * pb + pab);
+    const int fused_kid = KID_FUSED_POLICY, chain_kid = KID_CHAIN_POLICY, split_kid = KID_SPLIT_POLICY;
+    if (a.sac.on) SPLIT_PICK(policy, VAR_SAC);
+    if (a.atoms >= 2) SPLIT_PICK(policy, VAR_DIST);
+    SPLIT_PICK(policy, VAR_PLAIN);
+    return hipErrorInvalidValue;
+}
+
+hipError_t split_act_launch(SplitActArgs& a, int kind, hipStream_t stream) {
+    SplitShape& p = a.shape;
+    const int w = widest(p), aw = a.sac.on ? 2 * p.a : p.a;
+    if (!split_shape_ok(p.o, p.a, aw, p.H, p.L) || w > 512) return hipErrorInvalidValue;
+    const size_t lds = plan_lds(p, 1, p.o);
+    double pa = (double)p.o * p.H[0] + (double)p.H[p.L - 1] * aw;
+    for (int l = 1; l < p.L; ++l) pa += (double)p.H[l - 1] * p.H[l];
+    const double flops = 2.0 * a.B * pa;
+    if (kind == SPLIT_FUSED) {
+        if (a.sac.on) SPLIT_LAUNCH(fused_act_kernel<VAR_SAC>, KID_FUSED_ACT);
+        SPLIT_LAUNCH(fused_act_kernel<VAR_PLAIN>, KID_FUSED_ACT);
+    }
+    if (a.sac.on) SPLIT_LAUNCH(chain_act_kernel<VAR_SAC>, KID_CHAIN_ACT);
+    SPLIT_LAUNCH(chain_act_kernel<VAR_PLAIN>, KID_CHAIN_ACT);
+}
+
+}  // namespace pql

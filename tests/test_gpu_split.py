@@ -1,0 +1,111 @@
+"""The row-tile kernels on fp16 pairs (pql_split.hip) at the sizes where they can go wrong: widths that fill no tile, inputs
+of more than 256 columns (brought in twice), an input tile that shares its place with the activations, layers above 512
+(critics one after the other), one hidden layer, last row tiles of one row, and values far from 1, against the CPU oracle.
+
+Tolerances: a product of fp16 pairs is off by at most 3 * 2^-22 of |x| |w|, so a layer by 7e-7 of its largest term sum, and
+the fp32 sums behind it are those of the other kernels: gradients and losses within 1e-5 of a tensor's largest value
+(measured below 4e-6) instead of the 1e-4 that holds everywhere."""
+import numpy as np
+import pytest
+
+from oracle import pql_oracle as O
+from paper_2307_12983_amd import workloads as W
+
+from parity_util import assert_params_close, fill_both, oracle_batch, oracle_learner, oracle_ring, rel_err
+
+pytestmark = pytest.mark.gpu
+TOL = 1e-5
+
+
+def session(w):
+    import torch
+    from paper_2307_12983_amd.session import LearnerSession
+    if not torch.cuda.is_available():
+        pytest.fail("no GPU visible: the gpu-marked tests need a real MI355X")
+    return LearnerSession(w)
+
+
+def workload(hidden, o, a, batch, **kw):
+    return W.WORKLOADS["tiny"].replace(name="split", obs_dim=o, act_dim=a, num_envs=37, capacity=37 * 9, batch=batch,
+                                       hidden=hidden, index=90, **kw)
+
+
+CASES = {
+    "single_two_pass_input": workload((1024, 40), 230, 32, 2049),
+    "pair_shared_input_tile": workload((512, 512), 250, 10, 2050),
+    "pair_two_tiles_odd": workload((300, 136, 24), 33, 1, 65),
+    "odd_widths_sac": workload((100, 200), 45, 11, 31, sac=True),
+    "one_layer_sac": workload((40,), 7, 3, 33, sac=True),
+    "one_layer_atoms": workload((24,), 7, 3, 33, num_atoms=51),
+    "few_atoms_wide": workload((512, 72), 19, 5, 97, num_atoms=11, v_min=-2.0, v_max=3.0),
+    "deep": workload((40, 72, 100, 24, 200, 8, 64, 33), 5, 2, 64),
+}
+
+
+@pytest.mark.parametrize("case", list(CASES))
+def test_gradients_at_the_edges(case):
+    w = CASES[case]
+    print(case, w.hidden, "B", w.batch, flush=True)
+    s, ring = session(w), oracle_ring(w)
+    fill_both(s, ring, w, w.nstep + 3)
+    L = oracle_learner(w, s.actor_init, s.critic_init)
+    s.sample(w.batch)
+    batch = oracle_batch(ring, w, w.batch, 0, None)
+    s.ctx.pql_profile_begin(64)
+    s.critic_update(w.batch)
+    losses, g = L.critic_update(batch)
+    s.actor_update(None, w.batch)
+    names = {k["name"] for k in s.ctx.pql_profile_end()}
+    assert {"split_weights_kernel", "split_critic_kernel", "split_policy_kernel"} <= names
+    _, ga = L.actor_update(batch["obs"])
+    assert rel_err(s.critic_loss.cpu().numpy(), losses) <= TOL
+    e = assert_params_close(s.c_g.cpu().numpy(), g, w.critic_dims(), 2, TOL, "critic grad")
+    ea = assert_params_close(s.a_g.cpu().numpy(), ga, w.actor_dims(), 1, TOL, "actor grad")
+    print(case, "critic grad", e, "actor grad", ea, flush=True)
+
+
+@pytest.mark.parametrize("hidden", [(256, 256), (512, 96), (40, 100)])
+def test_rows_and_weights_of_very_different_size(hidden):
+    """Every row of a batch has its own scale, every 32 columns of a matrix theirs: states between 1e-2 and 1e6 in one batch,
+    layers scaled by 1e3 and 1e-4, Q row by row to 1e-5 of the row's own value; a row of NaN and one of infinity stay alone."""
+    import torch
+    from test_gpu_parity import workspace_rows
+    w = workload(hidden, 20, 4, 96)
+    s = session(w)
+    rng = np.random.default_rng(3)
+    c = s.critic_init.astype(np.float64)
+    dims = w.critic_dims()
+    half, off = c.size // 2, 0
+    for l, (i, o) in enumerate(dims):
+        for h in (0, half):
+            c[h + off:h + off + i * o] *= (1e3, 1e-4, 1.0)[l % 3]
+        off += i * o + o
+    c = c.astype(np.float32)
+    B = w.batch
+    scale = 10.0 ** (np.arange(B) % 9 - 2)
+    obs = (rng.standard_normal((B, w.obs_dim)) * scale[:, None]).astype(np.float32)
+    act = rng.uniform(-1, 1, (B, w.act_dim)).astype(np.float32)
+
+    def run(obs):
+        s.critic.copy_(torch.from_numpy(c))
+        s.critic_target.copy_(torch.from_numpy(c))
+        s.batch.obs[:B].copy_(torch.from_numpy(obs))
+        s.batch.next_obs[:B].copy_(torch.from_numpy(obs))
+        s.batch.act[:B].copy_(torch.from_numpy(act))
+        s.batch.ret[:B].zero_()
+        s.batch.boot[:B].zero_()
+        s.critic_update(B)
+        return [workspace_rows(s, 1 + i, B) for i in (0, 1)]
+
+    q = run(obs)
+    for i, p in enumerate(O.split_twin(c)):
+        ref = O.critic_forward(p, dims, obs, act)
+        err = np.abs(q[i] - ref) / np.maximum(np.abs(ref), np.abs(ref).min())
+        print(hidden, "critic", i, "worst row", int(err.argmax()), "%.2e" % err.max(), flush=True)
+        assert err.max() <= 10 * TOL         # (a row's Q can cancel to a tenth of its terms)
+    bad = obs.copy()
+    bad[5], bad[40] = np.nan, np.inf
+    others = np.setdiff1d(np.arange(B), [5, 40])
+    for x, y in zip(run(bad), q):
+        assert np.isnan(x[5]) and not np.isfinite(x[40])
+        assert np.array_equal(x[others], y[others])
