@@ -18,6 +18,7 @@
 // C[8*(r/4) + 4*(l/32) + r%4][l%32].  The k index inside a group of 8 is assigned as
 // k = 4*(l/32) + i for the i-th of four consecutive MFMAs, so a lane's four A values (or B
 // values) are contiguous in a k-contiguous tile and can be read with one 16-byte LDS load.
+#include "pql_pairs.h"
 #include "pql_internal.h"
 
 namespace pql {
@@ -356,21 +357,57 @@ int gemm_tile_n(int tile) { return tile == TILE_128x128 ? 128 : (tile == TILE_12
 int gemm_waves_m(int tile) { return tile == TILE_128x32 ? 4 : 2; }
 
 // =============================================================================================
-// Weight gradients of small layers, dW[M x N] = A^T B over a range of batch rows (the K dimension),
-// 64 x 64 output tile per workgroup.  Both operands are row-major activations [rows x ld] whose
-// contiguous dimension is the MFMA's M resp. N dimension, so the lanes of a wavefront can take
-// their A and B fragments straight from memory (coalesced 128-byte row pieces through buffer
-// descriptors: a scalar row offset plus one lane offset, rows past the range read as zero): no LDS
-// staging and no barrier inside the loop.  The four wavefronts of a workgroup each take a quarter
-// of the split's rows of the same tile (rows in chunks of 8, the next chunk requested while the
-// current one feeds the matrix core); the partial tiles meet in LDS at the end.
+// Weight gradients, dW[M x N] = A^T B over a range of batch rows (the K dimension), 64 x 64 output tile per workgroup, on
+// the fp16 matrix cores at 32-bit precision.  Both operands are row-major activations [rows x ld] whose contiguous dimension
+// is the MFMA's M resp. N dimension, so the lanes of a wavefront take their A and B fragments straight from memory (coalesced
+// 128-byte row pieces through buffer descriptors: a scalar row offset plus one lane offset, rows past the range read as
+// zero): no LDS staging and no barrier inside the loop.  The four wavefronts of a workgroup each take a quarter of the
+// split's rows of the same tile (rows in chunks of 16); the partial tiles meet in LDS at the end.
+//
+// A lane holds eight rows of one column of each operand; it writes them as fp16 pairs (pql_pairs.h) scaled by a power of two
+// of that column's own, which stays the same over the rows as the contraction needs it to.  The scale comes from the first
+// chunk with room for values 2^8 larger; a chunk that holds a larger one still rescales the sums (rare: the check is eight
+// comparisons).  Products: lo hi + hi lo + hi hi, v_mfma_f32_32x32x16_f16, fp32 sums; with three roundings per 16 rows where the
+// fp32 MFMAs of a 32x32x2 kernel make eight, the result is the closer one.
 // TM = 32-row tiles of the output per wavefront (1 for outputs of at most 32 rows).
 // =============================================================================================
 __device__ inline float tn_load(__amdgpu_buffer_rsrc_t r, int voff, int soff) {
     return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, voff, soff, 0));
 }
 
-constexpr int TNS = 4;            // MFMA steps (2 rows each) per chunk of the streaming weight-gradient kernel
+constexpr int TNS = 8;            // row pairs per chunk: one MFMA contracts the chunk's 16 rows
+
+// One column's scale: s and its inverse, and the largest magnitude that s still fits.
+struct ColumnScale { float s, inv, limit; };
+
+// Eight values of a column as pairs.
+__device__ __forceinline__ void tn_split(const float (&x)[TNS], float s, u32x4 (&t)[2]) {
+    unsigned h[4], l[4];
+#pragma unroll
+    for (int p = 0; p < 4; ++p) split16x2<false>(x[2 * p], x[2 * p + 1], s, h[p], l[p]);
+    t[0] = u32x4{h[0], h[1], h[2], h[3]};
+    t[1] = u32x4{l[0], l[1], l[2], l[3]};
+}
+__device__ __forceinline__ float tn_max(const float (&x)[TNS]) {
+    float m = fabsf(x[0]);
+#pragma unroll
+    for (int i = 1; i < TNS; ++i) m = fmaxf(m, fabsf(x[i]));
+    return m;
+}
+// New scale of a column whose chunk exceeds the old one's limit (the halves of the wavefront hold the same column); returns
+// the factor by which the sums so far are to be multiplied.
+__device__ __forceinline__ float tn_rescale(ColumnScale& c, float m) {
+    auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(m), __float_as_uint(m), false, false);
+    m = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+    if (!(m > c.limit)) return 1.f;
+    const float old = c.inv;
+    c.s = scale_for<7>(m, c.inv);
+    c.limit = 32768.f * c.inv;
+    return old * c.s;
+}
+__device__ __forceinline__ floatx16 mfma_f16(u32x4 a, u32x4 b, floatx16 c) {
+    return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
+}
 
 // Quarter Q of a wavefront's TM x 2 accumulator tiles: registers f in [Q * NQ, (Q + 1) * NQ), NQ = TM * 8.
 template <int TM, int Q>
@@ -404,7 +441,7 @@ __device__ inline void tn_sum_store(const floatx16 (&acc)[TM][2], float (*red)[4
 }
 
 template <int TM>
-__device__ inline void tn_stream_tile(const GemmProb& P, int split, int m0, int n0, float (*red)[4096]) {
+__device__ inline void tn_stream_tile(const GemmProb& P, int split, int m0, int n0, float (*red)[4096], float (*rows)[64]) {
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l32 = lane & 31, half = lane >> 5;
@@ -434,44 +471,94 @@ __device__ inline void tn_stream_tile(const GemmProb& P, int split, int m0, int 
         for (int j = 0; j < 2; ++j)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-    float a0[TM][TNS], b0[2][TNS], a1[TM][TNS], b1[2][TNS];
-    auto load = [&](int c, float (&a)[TM][TNS], float (&b)[2][TNS]) {
+    float xa[TM][TNS], xb[2][TNS];
+    ColumnScale ca[TM], cb[2];
+#pragma unroll
+    for (int i = 0; i < TM; ++i) ca[i] = ColumnScale{1.f, 1.f, 0.f};
+#pragma unroll
+    for (int j = 0; j < 2; ++j) cb[j] = ColumnScale{1.f, 1.f, 0.f};
+    // factors of the output rows (columns of A) to all lanes that hold a part of them; only this wavefront's own LDS words
+    auto spread = [&](const float (&f)[TM], float (&out)[TM][16]) {
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+            if (half == 0) rows[wave][32 * i + l32] = f[i];
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) out[i][r] = rows[wave][32 * i + 8 * (r >> 2) + 4 * half + (r & 3)];
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
+    };
+    auto multiply = [&](const float (&fa)[TM], const float (&fb)[2]) {
+        float fr[TM][16];
+        spread(fa, fr);
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[i][j][r] *= fr[i][r] * fb[j];
+    };
+    auto load_a = [&](int c, int i) {
         const int row = 2 * TNS * (c < nch ? c : 0);          // relative to the wavefront's first row
 #pragma unroll
-        for (int st = 0; st < TNS; ++st) {
-#pragma unroll
-            for (int i = 0; i < TM; ++i) a[i][st] = tn_load(ra, va[i], (row + 2 * st) * lda * (int)sizeof(float));
-#pragma unroll
-            for (int j = 0; j < 2; ++j) b[j][st] = tn_load(rb, vb[j], (row + 2 * st) * ldb * (int)sizeof(float));
-        }
+        for (int st = 0; st < TNS; ++st) xa[i][st] = tn_load(ra, va[i], (row + 2 * st) * lda * (int)sizeof(float));
     };
-    auto mac = [&](const float (&a)[TM][TNS], const float (&b)[2][TNS]) {
+    auto load_b = [&](int c) {
+        const int row = 2 * TNS * (c < nch ? c : 0);
 #pragma unroll
         for (int st = 0; st < TNS; ++st)
 #pragma unroll
-            for (int i = 0; i < TM; ++i)
-#pragma unroll
-                for (int j = 0; j < 2; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i][st], b[j][st], acc[i][j], 0, 0, 0);
+            for (int j = 0; j < 2; ++j) xb[j][st] = tn_load(rb, vb[j], (row + 2 * st) * ldb * (int)sizeof(float));
     };
     if (nch > 0) {
-        load(0, a0, b0);
-        int left = nch, c = 0;
-        // the fences keep the next chunk's requests ahead of the current chunk's MFMAs
-        while (true) {
-            load(c + 1, a1, b1);
+        load_b(0);
+#pragma unroll
+        for (int i = 0; i < TM; ++i) load_a(0, i);
+        for (int c = 0; c < nch; ++c) {
+            float ma[TM], mb[2];
+            bool over = false;
+#pragma unroll
+            for (int j = 0; j < 2; ++j) { mb[j] = tn_max(xb[j]); over |= mb[j] > cb[j].limit; }
+#pragma unroll
+            for (int i = 0; i < TM; ++i) { ma[i] = tn_max(xa[i]); over |= ma[i] > ca[i].limit; }
+            if (__ballot(over) != 0) {
+                float fa[TM], fb[2];
+#pragma unroll
+                for (int i = 0; i < TM; ++i) fa[i] = tn_rescale(ca[i], ma[i]);
+#pragma unroll
+                for (int j = 0; j < 2; ++j) fb[j] = tn_rescale(cb[j], mb[j]);
+                multiply(fa, fb);
+            }
+            // a value's registers are free once it is split: the same value of the next chunk is requested into
+            // them at once (the fences keep the requests there) and has this chunk's matrix work to arrive
+            u32x4 tb[2][2], ta[2];
+#pragma unroll
+            for (int j = 0; j < 2; ++j) tn_split(xb[j], cb[j].s, tb[j]);
             __builtin_amdgcn_sched_barrier(0);
-            mac(a0, b0);
+            load_b(c + 1);
             __builtin_amdgcn_sched_barrier(0);
-            if (--left == 0) break;
-            ++c;
-            load(c + 1, a0, b0);
-            __builtin_amdgcn_sched_barrier(0);
-            mac(a1, b1);
-            __builtin_amdgcn_sched_barrier(0);
-            if (--left == 0) break;
-            ++c;
+#pragma unroll
+            for (int i = 0; i < TM; ++i) {
+                tn_split(xa[i], ca[i].s, ta);
+                __builtin_amdgcn_sched_barrier(0x008);
+                load_a(c + 1, i);
+                __builtin_amdgcn_sched_barrier(0x008);
+#pragma unroll
+                for (int j = 0; j < 2; ++j) acc[i][j] = mfma_f16(ta[1], tb[j][0], acc[i][j]);
+#pragma unroll
+                for (int j = 0; j < 2; ++j) acc[i][j] = mfma_f16(ta[0], tb[j][1], acc[i][j]);
+#pragma unroll
+                for (int j = 0; j < 2; ++j) acc[i][j] = mfma_f16(ta[0], tb[j][0], acc[i][j]);
+            }
         }
+        float fa[TM], fb[2];
+#pragma unroll
+        for (int i = 0; i < TM; ++i) fa[i] = ca[i].inv;
+#pragma unroll
+        for (int j = 0; j < 2; ++j) fb[j] = cb[j].inv;
+        multiply(fa, fb);
     }
     // The four partial tiles meet in LDS.  Every wavefront owns a quarter of the tile's accumulator registers
     // (flattened as f = (i * 2 + j) * 16 + r): it parks the other three quarters in LDS (slot = source wavefront,
@@ -491,6 +578,7 @@ __device__ inline void tn_stream_tile(const GemmProb& P, int split, int m0, int 
 
 __global__ __launch_bounds__(NTHREADS, 3) void gemm_tn_stream_kernel(const GemmGroup g) {
     __shared__ float red[3][4096];
+    __shared__ float rows[4][64];
     const int bid = xcd_remap(blockIdx.x, gridDim.x);
     int pi = 0;
     for (int i = 1; i < g.nprob; ++i)
@@ -502,8 +590,8 @@ __global__ __launch_bounds__(NTHREADS, 3) void gemm_tn_stream_kernel(const GemmG
     local -= split * per_split;
     const int tile_m = local / P.tiles_n, tile_n = local % P.tiles_n;
     const int m0 = tile_m * 64, n0 = tile_n * 64;
-    if (P.M - m0 <= 32) tn_stream_tile<1>(P, split, m0, n0, red);
-    else                tn_stream_tile<2>(P, split, m0, n0, red);
+    if (P.M - m0 <= 32) tn_stream_tile<1>(P, split, m0, n0, red, rows);
+    else                tn_stream_tile<2>(P, split, m0, n0, red, rows);
 }
 
 template <int MODE>
