@@ -1,20 +1,20 @@
 // Row-tile learner kernels on the 16-bit matrix cores at 32-bit precision.
 //
 // Every operand of a matrix product is an fp32 value times a power of two, written as the sum of two fp16 terms
-// (hi = fp16(x s), lo = fp16(x s - hi): 22 significant bits and the sign of lo), and a product is three fp16 MFMAs
-// (lo w_hi + hi w_lo + hi w_hi; the left-out lo w_lo is below 2^-22 of the product) that accumulate in fp32.  The
-// scales keep the terms inside fp16's range whatever the data: one per batch row of an activation tile (its largest
-// magnitude goes to [2^14, 2^15), found anew for every layer), one per 32 output columns of a weight matrix.  A value
-// 2^17 and more below its row's largest loses relative, not absolute, precision (2^-40 of that largest one).
+// (hi = fp16(x s), lo = fp16(2^11 (x s - hi)): 22 significant bits and the sign of lo), and a product is three fp16 MFMAs
+// (lo w_hi + hi w_lo with sums of their own, hi w_hi; the left-out lo w_lo is below 2^-22 of the product) with fp32 sums.
+// The scales keep the terms inside fp16's range whatever the data: one per batch row of an activation tile (its largest
+// magnitude goes to [2^14, 2^15), found anew for every layer), one per 32 output columns of a weight matrix.  Values down
+// to 2^-28 of their row's largest keep their relative precision, smaller ones are off by 2^-50 of that largest one.
 // Measured against double precision a K = 256 product is off by 1.2e-7 (2-norm) where a chain of fp32 MFMAs is off by
-// 2.8e-7: three roundings per 32 products instead of sixteen outweigh the two missing bits of the operands.
+// 2.8e-7: one rounding of the large sums per 32 products instead of sixteen outweighs the two missing bits of the operands.
 // v_mfma_f32_16x16x32_f16 multiplies at 13 times the rate of v_mfma_f32_32x32x2_f32 (2.0 PFLOP/s against 0.15), so
 // three of them are 4.4 times as fast and take a quarter of the energy, which matters as much: the chip holds
 // 2.4 GHz only below its power limit.
 //
-// A workgroup (sixteen wavefronts, four per SIMD) owns 32 batch rows and carries them through a whole chain of layers,
-// the twin critics side by side (eight wavefronts each) where the layers are at most 512 wide, one after the other up to
-// 1024.  A wavefront owns 32 output columns of one network.  The product is computed as W^T X^T (weights are the A
+// A workgroup (eight wavefronts, two per SIMD) owns 32 batch rows and carries them through a whole chain of layers, the
+// twin critics side by side (four wavefronts each) where the layers are at most 512 wide, one after the other up to 1024.
+// (Sixteen wavefronts of 128 registers spilled: 132 us for the update at 256-256 and batch 8192.)  A wavefront owns 32 output columns of one network.  The product is computed as W^T X^T (weights are the A
 // operand): a lane then holds four consecutive output columns of one batch row, which is the order in which the next
 // layer's B operand wants them, so an epilogue packs its results with no exchange between lanes and writes them to LDS as
 // 16-byte pieces, and row maxima, output heads and their gradients come from registers.
@@ -26,17 +26,16 @@
 //
 // The weights are brought into fragment order by split_weights_kernel at the start of every call (zero-padded to whole
 // tiles, so any layer width works): a lane's operand is one 16-byte load, a wavefront's a contiguous kilobyte.
+#include "pql_pairs.h"
 #include "pql_rowtile.h"
 
 namespace pql {
 
-typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
-
 enum Variant : int { VAR_PLAIN = 0, VAR_SAC = 1, VAR_DIST = 2 };
-constexpr int SW = 16;               // wavefronts per workgroup
+constexpr int SW = 8;                // wavefronts per workgroup
 constexpr int ST = 64 * SW;          // threads per workgroup
+constexpr int PT = 1024;             // threads per workgroup of the preparation
+constexpr int PREP_ITEMS = SPLIT_MAXW / 256;   // pieces of eight values per thread
 constexpr int CS = 33;               // 16-byte units per k-chunk of a tile: 32 rows and one of padding against bank conflicts
 
 // ---- layouts ----------------------------------------------------------------------------------------
@@ -58,27 +57,15 @@ __device__ __forceinline__ MatView mat_view(const float* base, int K, int N) {
     return m;
 }
 
-// Power-of-two scale that brings a largest magnitude m to [2^14, 2^15), and its inverse.  The exponent is clamped so
-// that both are normal numbers (zero rows, subnormals, infinities).
-__device__ __forceinline__ float scale_for(float m, float& inv) {
-    int e = (int)(__float_as_uint(m) >> 23);
-    e = e < 20 ? 20 : (e > 254 ? 254 : e);
-    inv = __uint_as_float((unsigned)(e - 14) << 23);
-    return __uint_as_float((unsigned)(268 - e) << 23);
-}
-__device__ __forceinline__ void split16(float x, float s, _Float16& hi, _Float16& lo) {
-    hi = (_Float16)(x * s);
-    lo = (_Float16)__fmaf_rn(x, s, -(float)hi);
-}
 __device__ __forceinline__ void split16x8(const f32x4& a, const f32x4& b, float s, u32x4& hi, u32x4& lo) {
-    f16x8 h, l;
+    unsigned h[4], l[4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        _Float16 x, y;
-        split16(a[i], s, x, y); h[i] = x; l[i] = y;
-        split16(b[i], s, x, y); h[4 + i] = x; l[4 + i] = y;
+    for (int i = 0; i < 2; ++i) {
+        split16x2<true>(a[2 * i], a[2 * i + 1], s, h[i], l[i]);
+        split16x2<true>(b[2 * i], b[2 * i + 1], s, h[2 + i], l[2 + i]);
     }
-    hi = __builtin_bit_cast(u32x4, h); lo = __builtin_bit_cast(u32x4, l);
+    hi = u32x4{h[0], h[1], h[2], h[3]};
+    lo = u32x4{l[0], l[1], l[2], l[3]};
 }
 
 // Reductions across the four 16-lane rows of a wavefront (same l15) and inside one of them.
@@ -119,9 +106,9 @@ __device__ __forceinline__ const ARGS& kernel_args() {
 // ---- weights into fragment order ------------------------------------------------------------------------
 // One workgroup per 32-column tile: every element is read once (all requests in flight together), kept in registers while
 // the tile's largest magnitude is found, and written as fragments.  Latency-bound: one round trip each way.
-__global__ __launch_bounds__(ST) void split_weights_kernel(const SplitPrepArgs) {
+__global__ __launch_bounds__(PT) void split_weights_kernel(const SplitPrepArgs) {
     const SplitPrepArgs& P = kernel_args<SplitPrepArgs>();
-    __shared__ float red[SW];
+    __shared__ float red[PT / 64];
     const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
     const int first = P.first[lane];
     const int pi = __builtin_amdgcn_readfirstlane(__popcll(__ballot(b >= first)) - 1);
@@ -130,7 +117,7 @@ __global__ __launch_bounds__(ST) void split_weights_kernel(const SplitPrepArgs) 
     const float* src = P.src[M.from] + M.src;
     float* dst = P.dst + M.dst;
     if (M.kind == SPLIT_VECTOR) {        // a vector padded with zeros to whole tiles
-        for (int i = tid; i < (N + 31) / 32 * 32; i += ST) dst[i] = i < N ? src[i] : 0.f;
+        for (int i = tid; i < (N + 31) / 32 * 32; i += PT) dst[i] = i < N ? src[i] : 0.f;
         return;
     }
     const int ks = (K + 31) >> 5, tiles = (N + 31) >> 5;
@@ -141,12 +128,12 @@ __global__ __launch_bounds__(ST) void split_weights_kernel(const SplitPrepArgs) 
         __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(src), 0, K * N * (int)sizeof(float), 0x00020000);
     // element (k, n) at k sk + n sn; what lies outside the matrix is requested outside the descriptor and reads as zero
     const int sk = trans ? 1 : N, sn = trans ? K : 1;
-    f32x4 v[4][2];
+    f32x4 v[PREP_ITEMS][2];
     float mx = 0.f;
 #pragma unroll
-    for (int it = 0; it < 4; ++it) {
-        if (it * ST >= items) break;
-        const int e = it * ST + tid;
+    for (int it = 0; it < PREP_ITEMS; ++it) {
+        if (it * PT >= items) break;
+        const int e = it * PT + tid;
         const int n = tile * 32 + ((e >> 6) & 1) * 16 + l15;
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
@@ -157,8 +144,8 @@ __global__ __launch_bounds__(ST) void split_weights_kernel(const SplitPrepArgs) 
     float bias = 0.f;
     if (tid < 32 && M.bias != SPLIT_NO_BIAS && tile * 32 + tid < N) bias = P.src[M.from][M.bias + tile * 32 + tid];
 #pragma unroll
-    for (int it = 0; it < 4; ++it) {
-        if (it * ST >= items) break;
+    for (int it = 0; it < PREP_ITEMS; ++it) {
+        if (it * PT >= items) break;
 #pragma unroll
         for (int i = 0; i < 8; ++i) mx = fmaxf(mx, fabsf(v[it][i >> 2][i & 3]));
     }
@@ -166,14 +153,14 @@ __global__ __launch_bounds__(ST) void split_weights_kernel(const SplitPrepArgs) 
     if (lane == 0) red[tid >> 6] = mx;
     __syncthreads();
 #pragma unroll
-    for (int w = 0; w < SW; ++w) mx = fmaxf(mx, red[w]);
+    for (int w = 0; w < PT / 64; ++w) mx = fmaxf(mx, red[w]);
     float inv;
     const float s = scale_for(mx, inv);
     u32x4* frag = reinterpret_cast<u32x4*>(dst) + (size_t)tile * ks * 256;
     float* tail = dst + (size_t)tiles * ks * 1024;
 #pragma unroll
-    for (int it = 0; it < 4; ++it) {
-        const int e = it * ST + tid;
+    for (int it = 0; it < PREP_ITEMS; ++it) {
+        const int e = it * PT + tid;
         if (e >= items) break;
         u32x4 hi, lo;
         split16x8(v[it][0], v[it][1], s, hi, lo);
@@ -197,7 +184,7 @@ hipError_t split_weights_launch(SplitPrepArgs& a, int kid, hipStream_t stream) {
     }
     if (blocks == 0) return hipSuccess;
     const ProfSlot ps = prof_slot();
-    PQL_LAUNCH(ps, split_weights_kernel, dim3(blocks), dim3(ST), 0, stream, a);
+    PQL_LAUNCH(ps, split_weights_kernel, dim3(blocks), dim3(PT), 0, stream, a);
     prof_commit(ps, kid, 0.0, kid == KID_SPLIT_WEIGHTS ? bytes : 0.0);
     return hipGetLastError();
 }
@@ -219,55 +206,81 @@ __device__ __forceinline__ u32x4* lds_units() { return reinterpret_cast<u32x4*>(
 // then lo terms.  base and plane in 16-byte units.
 struct Tile { int base, plane; };
 
-// The fragments of one k-step of a 32-column tile (4 KB): the requests run one step ahead of the matrix work, also from
-// one product to the next (over the epilogue and its barriers), so every product is told where the following one begins.
-struct Ahead { u32x4 w[4]; };
-__device__ __forceinline__ const u32x4* first_step(const MatView& W, int tile, int step) {
-    const int t = tile < W.tiles ? tile : 0, s = step < W.ks ? step : 0;       // an idle wavefront requests something valid
-    return W.frag + (size_t)(t * W.ks + s) * 256;
+// The fragments of two k-steps of a 32-column tile (4 KB each): the requests run two steps ahead of the matrix work, also
+// from one product to the next (over the epilogue and its barriers), so every product is told where the following one begins.
+struct Ahead { u32x4 w[2][4]; };
+struct Begin { const u32x4* first; const u32x4* second; };
+__device__ __forceinline__ Begin begin_of(const MatView& W, int tile, int s0, int ds) {
+    const int t = tile < W.tiles ? tile : 0, a = s0 < W.ks ? s0 : 0, b = s0 + ds < W.ks ? s0 + ds : a;     // (an idle wavefront requests something valid)
+    return {W.frag + (size_t)(t * W.ks + a) * 256, W.frag + (size_t)(t * W.ks + b) * 256};
 }
-__device__ __forceinline__ const u32x4* cur_valid(const float* mat) { return reinterpret_cast<const u32x4*>(mat); }
-__device__ __forceinline__ void request(Ahead& a, const u32x4* p, const Wv& T) {
-    const char* b = reinterpret_cast<const char*>(p);
+__device__ __forceinline__ Begin begin_at(const float* mat) {
+    return {reinterpret_cast<const u32x4*>(mat), reinterpret_cast<const u32x4*>(mat)};
+}
+__device__ __forceinline__ void request(Ahead& a, const Begin& p, const Wv& T) {
     const unsigned off = (unsigned)T.lane * 16u;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) a.w[i] = *reinterpret_cast<const u32x4*>(b + off + i * 1024);
+    for (int i = 0; i < 4; ++i) a.w[0][i] = *reinterpret_cast<const u32x4*>(reinterpret_cast<const char*>(p.first) + off + i * 1024);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) a.w[1][i] = *reinterpret_cast<const u32x4*>(reinterpret_cast<const char*>(p.second) + off + i * 1024);
 }
 
-// acc[m][n] += 16x16 products of weight columns 32 tile + 16 m .. with batch rows 16 n .., steps s0, s0 + ds, ...  `cur`
-// holds the first step's fragments and leaves with those at `next` (the fences keep the requests ahead of the MFMAs).
-__device__ __forceinline__ void mac_steps(f32x4 (&acc)[2][2], const MatView& W, int tile, const Tile& X, const Wv& T, int s0, int ds,
-                                 Ahead& cur, const u32x4* next) {
+// acc[m][n] = 16x16 products of weight columns 32 tile + 16 m .. with batch rows 16 n .., steps s0, s0 + ds, ...  `cur`
+// holds the first two steps' fragments and leaves with those at `next` (the fences keep the requests ahead of the MFMAs).
+// The cross products have sums of their own, 2^11 too large like their lo terms, which join at the end.
+// NB blocks of 16 rows (tiles of 32 rows: 2).
+template <int NB>
+__device__ __forceinline__ void mac_steps(f32x4 (&acc)[2][NB], const MatView& W, int tile, const Tile& X, const Wv& T, int s0, int ds,
+                                          Ahead& cur, const Begin& next) {
     const u32x4* p = W.frag + (size_t)tile * W.ks * 256;
+    f32x4 low[2][NB];
+#pragma unroll
+    for (int m = 0; m < 2; ++m)
+#pragma unroll
+        for (int n = 0; n < NB; ++n) { acc[m][n] = f32x4{0.f, 0.f, 0.f, 0.f}; low[m][n] = f32x4{0.f, 0.f, 0.f, 0.f}; }
     auto mac = [&](int s, const u32x4 (&w)[4]) {
-        const int at = X.base + (4 * s + T.q) * CS + T.l15;
-        u32x4 xh[2], xl[2];
+        const int at = X.base + (4 * s + T.q) * (16 * NB + 1) + T.l15;
+        f16x8 xh[NB], xl[NB];
 #pragma unroll
-        for (int n = 0; n < 2; ++n) { xh[n] = lds_units()[at + 16 * n]; xl[n] = lds_units()[at + X.plane + 16 * n]; }
+        for (int n = 0; n < NB; ++n) {
+            xh[n] = __builtin_bit_cast(f16x8, lds_units()[at + 16 * n]);
+            xl[n] = __builtin_bit_cast(f16x8, lds_units()[at + X.plane + 16 * n]);
+        }
 #pragma unroll
-        for (int c = 0; c < 3; ++c)          // smallest contributions first
+        for (int c = 0; c < 3; ++c)
 #pragma unroll
-            for (int m = 0; m < 2; ++m)
+            for (int m = 0; m < 2; ++m) {
+                const f16x8 a = __builtin_bit_cast(f16x8, c == 0 ? w[2 * m + 1] : w[2 * m]);
 #pragma unroll
-                for (int n = 0; n < 2; ++n)
-                    acc[m][n] = __builtin_amdgcn_mfma_f32_16x16x32_f16(
-                        __builtin_bit_cast(f16x8, c == 0 ? w[2 * m + 1] : w[2 * m]),
-                        __builtin_bit_cast(f16x8, c == 1 ? xl[n] : xh[n]), acc[m][n], 0, 0, 0);
+                for (int n = 0; n < NB; ++n) {
+                    if (c == 0) low[m][n] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a, xh[n], low[m][n], 0, 0, 0);
+                    if (c == 1) low[m][n] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a, xl[n], low[m][n], 0, 0, 0);
+                    if (c == 2) acc[m][n] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a, xh[n], acc[m][n], 0, 0, 0);
+                }
+            }
+    };
+    auto step = [&](int s, Ahead& have, Ahead& get) {      // steps s and s + ds from `have`, the two after them requested into `get`
+        const int s2 = s + 2 * ds, s3 = s + 3 * ds;
+        Begin b = next;
+        if (s2 < W.ks) b = {p + (size_t)s2 * 256, p + (size_t)(s3 < W.ks ? s3 : s2) * 256};
+        request(get, b, T);
+        __builtin_amdgcn_sched_barrier(0);
+        mac(s, have.w[0]);
+        if (s + ds < W.ks) mac(s + ds, have.w[1]);
+        __builtin_amdgcn_sched_barrier(0);
+        return s2 < W.ks;
     };
     Ahead other;
-    for (int s = s0; ; s += 2 * ds) {
-        const int s1 = s + ds, s2 = s + 2 * ds;
-        request(other, s1 < W.ks ? p + (size_t)s1 * 256 : next, T);
-        __builtin_amdgcn_sched_barrier(0);
-        mac(s, cur.w);
-        __builtin_amdgcn_sched_barrier(0);
-        if (s1 >= W.ks) { cur = other; break; }
-        request(cur, s2 < W.ks ? p + (size_t)s2 * 256 : next, T);
-        __builtin_amdgcn_sched_barrier(0);
-        mac(s1, other.w);
-        __builtin_amdgcn_sched_barrier(0);
-        if (s2 >= W.ks) break;
+    for (int s = s0; ; s += 4 * ds) {
+        if (!step(s, cur, other)) { cur = other; break; }
+        if (!step(s + 2 * ds, other, cur)) break;
     }
+#pragma unroll
+    for (int m = 0; m < 2; ++m)
+#pragma unroll
+        for (int n = 0; n < NB; ++n)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) acc[m][n][r] = __fmaf_rn(low[m][n][r], 1.f / PAIR_LO, acc[m][n][r]);
 }
 
 __device__ __forceinline__ void clear(f32x4 (&z)[2][2]) {
@@ -281,9 +294,10 @@ __device__ __forceinline__ void clear(f32x4 (&z)[2][2]) {
 // back in one burst when this one ends.)
 // The 32 x 32 results of one tile to / from a row-major [B][N] array: this lane's rows r0 + 16 n + l15, columns
 // 32 tile + 16 m + 4 q .. + 3.
-__device__ __forceinline__ void store_tile(float* g, int N, int tile, const f32x4 (&z)[2][2], int r0, int B, const Wv& T) {
+template <int NB = 2>
+__device__ __forceinline__ void store_tile(float* g, int N, int tile, const f32x4 (&z)[2][NB], int r0, int B, const Wv& T) {
 #pragma unroll
-    for (int n = 0; n < 2; ++n) {
+    for (int n = 0; n < NB; ++n) {
         const int row = r0 + 16 * n + T.l15;
         if (row >= B) continue;
         float* p = g + (size_t)row * (size_t)N;
@@ -300,10 +314,12 @@ __device__ __forceinline__ void store_tile(float* g, int N, int tile, const f32x
         }
     }
 }
-__device__ __forceinline__ void load_tile(const float* g, int N, int tile, f32x4 (&z)[2][2], int r0, int B, const Wv& T) {
-    clear(z);
+template <int NB = 2>
+__device__ __forceinline__ void load_tile(const float* g, int N, int tile, f32x4 (&z)[2][NB], int r0, int B, const Wv& T) {
 #pragma unroll
-    for (int n = 0; n < 2; ++n) {
+    for (int n = 0; n < NB; ++n) { z[0][n] = f32x4{0.f, 0.f, 0.f, 0.f}; z[1][n] = z[0][n]; }
+#pragma unroll
+    for (int n = 0; n < NB; ++n) {
         const int row = r0 + 16 * n + T.l15;
         if (row >= B) continue;
         const float* p = g + (size_t)row * (size_t)N;
@@ -335,19 +351,18 @@ __device__ __forceinline__ void store_colsum(float* out, int N, int tile, const 
 
 // Which of the workgroup's networks and output tiles a wavefront works on.
 struct Share { int net, slot, waves; };      // tiles slot, slot + waves, ...
-template <int TPW>
 __device__ __forceinline__ void load_ahead(const float* h, int N, f32x4 (&hv)[2][2], const Share& S, int r0, int B, const Wv& T) {
-    if (TPW == 1) load_tile(h, N, S.slot, hv, r0, B, T);
+    load_tile(h, N, S.slot, hv, r0, B, T);
 }
 
 // Small per-tile arrays in LDS (floats from `sm`).
 struct SmallMem {
-    int max, part, inv, logp, act;           // [512] row maxima, [512] head partials, [32] inverse scales of X, [32] log pi, [32][as] actions
+    int max, part, inv, logp, act;           // [256] row maxima, [256] head partials, [32] inverse scales of X, [32] log pi, [32][as] actions
     int as;
 };
 __device__ __forceinline__ SmallMem small_mem(int sm, int as) {
     SmallMem m;
-    m.max = sm; m.part = sm + 512; m.inv = sm + 1024; m.logp = sm + 1056; m.act = sm + 1088; m.as = as;
+    m.max = sm; m.part = sm + 256; m.inv = sm + 512; m.logp = sm + 544; m.act = sm + 576; m.as = as;
     return m;
 }
 
@@ -377,11 +392,11 @@ __device__ __forceinline__ void put_tile(const f32x4 (&z)[TPW][2][2], int tiles,
 #pragma unroll
     for (int n = 0; n < 2; ++n) {
         const f32x4* src = reinterpret_cast<const f32x4*>(smem) + (M.max + (S.net * 32 + 16 * n + T.l15) * S.waves) / 4;
-        f32x4 a = src[0], b = src[1];
-        float m = fmaxf(fmaxf(fmaxf(a[0], a[1]), fmaxf(a[2], a[3])), fmaxf(fmaxf(b[0], b[1]), fmaxf(b[2], b[3])));
-        if (S.waves > 8) {
-            a = src[2]; b = src[3];
-            m = fmaxf(m, fmaxf(fmaxf(fmaxf(a[0], a[1]), fmaxf(a[2], a[3])), fmaxf(fmaxf(b[0], b[1]), fmaxf(b[2], b[3]))));
+        f32x4 a = src[0];
+        float m = fmaxf(fmaxf(a[0], a[1]), fmaxf(a[2], a[3]));
+        if (S.waves > 4) {
+            a = src[1];
+            m = fmaxf(m, fmaxf(fmaxf(a[0], a[1]), fmaxf(a[2], a[3])));
         }
         sc[n] = scale_for(m, inv[n]);
     }
@@ -405,7 +420,7 @@ __device__ __forceinline__ void put_tile(const f32x4 (&z)[TPW][2][2], int tiles,
 // z = ELU(X W + b) for this wavefront's tiles; inv = inverse row scales of the input tile.
 template <int TPW>
 __device__ __forceinline__ void forward(f32x4 (&z)[TPW][2][2], const MatView& W, const Tile& X, const Share& S, const float (&inv)[2],
-                               const Wv& T, Ahead& cur, const u32x4* next) {
+                               const Wv& T, Ahead& cur, const Begin& next) {
     if (S.slot >= W.tiles) request(cur, next, T);
 #pragma unroll
     for (int t = 0; t < TPW; ++t) {
@@ -417,24 +432,24 @@ __device__ __forceinline__ void forward(f32x4 (&z)[TPW][2][2], const MatView& W,
         for (int m = 0; m < 2; ++m) b[m] = *reinterpret_cast<const f32x4*>(W.bias + 32 * tile + 16 * m + 4 * T.q);
         const float iw = W.inv[tile];
         f32x4 acc[2][2];
-        clear(acc);
-        mac_steps(acc, W, tile, X, T, 0, 1, cur, more ? first_step(W, tile + S.waves, 0) : next);
+        mac_steps<2>(acc, W, tile, X, T, 0, 1, cur, more ? begin_of(W, tile + S.waves, 0, 1) : next);
+        const float f[2] = {inv[0] * iw, inv[1] * iw};
 #pragma unroll
         for (int m = 0; m < 2; ++m)
 #pragma unroll
             for (int n = 0; n < 2; ++n)
 #pragma unroll
-                for (int r = 0; r < 4; ++r) z[t][m][n][r] = elu_f(__fmaf_rn(acc[m][n][r] * inv[n], iw, b[m][r]));
+                for (int r = 0; r < 4; ++r) z[t][m][n][r] = elu_f(__fmaf_rn(acc[m][n][r], f[n], b[m][r]));
     }
 }
 
 // z = (D W^T) * ELU'(.) with the activations h [B][N] read back from memory (each lane reads what it wrote in the forward
-// pass: with one tile per wavefront the caller has requested them into hv before the deltas were put into the tile, with
-// two there are no registers for that); the deltas go to d_out and their column sums to col_out where given.
+// pass: those of the first tile the caller has requested into hv before the deltas were put into the tile); the deltas go to
+// d_out and their column sums to col_out where given.
 template <int TPW>
 __device__ __forceinline__ void backward(f32x4 (&z)[TPW][2][2], const MatView& W, const Tile& X, const Share& S, const float (&inv)[2],
                                 const float* h, float* d_out, float* col_out, int N, int r0, int B, const Wv& T, Ahead& cur,
-                                const u32x4* next, f32x4 (&hv)[2][2]) {
+                                const Begin& next, f32x4 (&hv)[2][2]) {
     if (S.slot >= W.tiles) request(cur, next, T);
 #pragma unroll
     for (int t = 0; t < TPW; ++t) {
@@ -443,15 +458,15 @@ __device__ __forceinline__ void backward(f32x4 (&z)[TPW][2][2], const MatView& W
         const bool more = t + 1 < TPW && tile + S.waves < W.tiles;
         f32x4 acc[2][2];
         const float iw = W.inv[tile];
-        if (TPW > 1) load_tile(h, N, tile, hv, r0, B, T);
-        clear(acc);
-        mac_steps(acc, W, tile, X, T, 0, 1, cur, more ? first_step(W, tile + S.waves, 0) : next);
+        if (t > 0) load_tile(h, N, tile, hv, r0, B, T);
+        mac_steps<2>(acc, W, tile, X, T, 0, 1, cur, more ? begin_of(W, tile + S.waves, 0, 1) : next);
+        const float f[2] = {inv[0] * iw, inv[1] * iw};
 #pragma unroll
         for (int m = 0; m < 2; ++m)
 #pragma unroll
             for (int n = 0; n < 2; ++n)
 #pragma unroll
-                for (int r = 0; r < 4; ++r) z[t][m][n][r] = acc[m][n][r] * inv[n] * iw * delu_h(hv[m][n][r]);
+                for (int r = 0; r < 4; ++r) z[t][m][n][r] = acc[m][n][r] * f[n] * delu_h(hv[m][n][r]);
         if (d_out != nullptr) store_tile(d_out, N, tile, z[t], r0, B, T);
         if (col_out != nullptr) {
             const f32x4 cs[2] = {z[t][0][0] + z[t][0][1], z[t][1][0] + z[t][1][1]};
@@ -461,8 +476,8 @@ __device__ __forceinline__ void backward(f32x4 (&z)[TPW][2][2], const MatView& W
 }
 
 // ---- input rows --------------------------------------------------------------------------------------------
-// Rows r0 .. r0 + 31 of concat(obs[o], act[a]) as a tile: half a wavefront per row, so that its largest magnitude is found
-// without leaving the registers.  `floor`: lower bound of that magnitude (actions in [-1, 1] that are inserted later must
+// Rows r0 .. r0 + 31 of concat(obs[o], act[a]) as a tile: half a wavefront takes two rows, one after the other, so that their
+// largest magnitudes are found without leaving the registers.  `floor`: lower bound of that magnitude (actions in [-1, 1] that are inserted later must
 // fit the row's scale).  Up to 256 columns are requested ahead of time into v.
 struct InputRows { __amdgpu_buffer_rsrc_t obs, act, mean, rstd; int o, a, act_lds, as; bool norm; };   // act_lds >= 0: actions in LDS
 constexpr int XV = 8;
@@ -498,18 +513,24 @@ __device__ __forceinline__ float input_action(const InputRows& in, int row, int 
     }
     return buf_load(in.act, (unsigned)(live ? (row * in.a + c) * 4 : NOWHERE), 0);
 }
-__device__ __forceinline__ void request_rows(float (&v)[XV], const InputRows& in, int steps, const Wv& T) {
+struct Rows { float v[2][XV]; };
+__device__ __forceinline__ int input_row(const Wv& T, int i) { return 2 * T.wave + (T.lane >> 5) + 16 * i; }
+__device__ __forceinline__ void request_rows(Rows& x, const InputRows& in, int steps, const Wv& T) {
     if (steps > XV) return;
-    const int row = 2 * T.wave + (T.lane >> 5), c = T.lane & 31;
+    const int c = T.lane & 31;
     const int j0 = in.o >> 5;                 // at most 32 action columns: they lie in the steps j0 and j0 + 1
 #pragma unroll
-    for (int j = 0; j < XV; ++j) v[j] = input_value(in, row, c + 32 * j);
-    if (in.a > 0) {
-        const float y0 = input_action(in, row, c + 32 * j0), y1 = input_action(in, row, c + 32 * j0 + 32);
+    for (int i = 0; i < 2; ++i) {
+        const int row = input_row(T, i);
 #pragma unroll
-        for (int j = 0; j < XV; ++j) {
-            const bool live = c + 32 * j >= in.o;
-            v[j] = live ? (j == j0 ? y0 : (j == j0 + 1 ? y1 : 0.f)) : v[j];
+        for (int j = 0; j < XV; ++j) x.v[i][j] = input_value(in, row, c + 32 * j);
+        if (in.a > 0) {
+            const float y0 = input_action(in, row, c + 32 * j0), y1 = input_action(in, row, c + 32 * j0 + 32);
+#pragma unroll
+            for (int j = 0; j < XV; ++j) {
+                const bool live = c + 32 * j >= in.o;
+                x.v[i][j] = live ? (j == j0 ? y0 : (j == j0 + 1 ? y1 : 0.f)) : x.v[i][j];
+            }
         }
     }
 }
@@ -528,25 +549,29 @@ __device__ __forceinline__ void put_value(const Tile& X, int row, int k, float x
     h[at] = hi;
     h[at + X.plane * 8] = lo;
 }
-__device__ __forceinline__ void put_rows(const float (&v)[XV], const InputRows& in, int steps, const Tile& X, int inv_at, float floor_,
-                                const Wv& T) {
-    const int row = 2 * T.wave + (T.lane >> 5), c = T.lane & 31;
-    float mx = floor_;
-    if (steps <= XV) {
+__device__ __forceinline__ void put_rows(const Rows& x, const InputRows& in, int steps, const Tile& X, int inv_at, float floor_,
+                                         const Wv& T) {
+    const int c = T.lane & 31;
 #pragma unroll
-        for (int j = 0; j < XV; ++j) mx = fmaxf(mx, fabsf(v[j]));
-    } else {
-        for (int j = 0; j < steps; ++j) mx = fmaxf(mx, fabsf(input_any(in, row, c + 32 * j)));
-    }
-    float inv;
-    const float s = scale_for(half_max(mx), inv);
-    if (c == 0) smem[inv_at + row] = inv;
-    if (steps <= XV) {
+    for (int i = 0; i < 2; ++i) {
+        const int row = input_row(T, i);
+        float mx = floor_;
+        if (steps <= XV) {
 #pragma unroll
-        for (int j = 0; j < XV; ++j)
-            if (j < steps) put_value(X, row, c + 32 * j, v[j], s);
-    } else {
-        for (int j = 0; j < steps; ++j) put_value(X, row, c + 32 * j, input_any(in, row, c + 32 * j), s);
+            for (int j = 0; j < XV; ++j) mx = fmaxf(mx, fabsf(x.v[i][j]));
+        } else {
+            for (int j = 0; j < steps; ++j) mx = fmaxf(mx, fabsf(input_any(in, row, c + 32 * j)));
+        }
+        float inv;
+        const float s = scale_for(half_max(mx), inv);
+        if (c == 0) smem[inv_at + row] = inv;
+        if (steps <= XV) {
+#pragma unroll
+            for (int j = 0; j < XV; ++j)
+                if (j < steps) put_value(X, row, c + 32 * j, x.v[i][j], s);
+        } else {
+            for (int j = 0; j < steps; ++j) put_value(X, row, c + 32 * j, input_any(in, row, c + 32 * j), s);
+        }
     }
 }
 __device__ __forceinline__ void row_inv(float (&inv)[2], int at, const Wv& T) {
@@ -580,7 +605,7 @@ __device__ __forceinline__ void scaled(f32x4 (&acc)[2][2], const float (&inv)[2]
 #pragma unroll
         for (int n = 0; n < 2; ++n)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) acc[m][n][r] = acc[m][n][r] * inv[n] * iw;
+            for (int r = 0; r < 4; ++r) acc[m][n][r] *= inv[n] * iw;
 }
 
 // A sample of the tanh-Gaussian policy for element (row, col) of the output tile; the 32 lanes of a row add their shares of
@@ -605,12 +630,12 @@ __device__ __forceinline__ float sample_action(int at, int parts, int row, int c
     return lp;
 }
 
-// The policy's hidden layers on the tile (all sixteen wavefronts on one network), its output layer as partial tiles.
+// The policy's hidden layers on the tile (all wavefronts on one network), its output layer as partial tiles.
 // keep: h_l go to hA[l]; returns the number of partial tiles at H.
 template <int TPW>
 __device__ __forceinline__ int policy_forward(const SplitShape& P, const float* const* mats, const Tile& X, const Tile& H, const SmallMem& M,
                                      bool keep, float* const* hA, int aw, int r0, int B, const Wv& T, Ahead& cur,
-                                     const u32x4* next) {
+                                     const Begin& next) {
     const Share S = {0, T.wave, SW};
     float inv[2];
     row_inv(inv, M.inv, T);
@@ -619,7 +644,7 @@ __device__ __forceinline__ int policy_forward(const SplitShape& P, const float* 
         const int N = P.H[l];
         const MatView W = mat_view(mats[l], l == 0 ? P.o : P.H[l - 1], N);
         const MatView V = mat_view(mats[l + 1], N, l + 1 < P.L ? P.H[l + 1] : aw);
-        forward<TPW>(z, W, l == 0 ? X : H, S, inv, T, cur, l + 1 < P.L ? first_step(V, S.slot, 0) : first_step(V, 0, T.wave));
+        forward<TPW>(z, W, l == 0 ? X : H, S, inv, T, cur, l + 1 < P.L ? begin_of(V, S.slot, 0, 1) : begin_of(V, 0, T.wave, SW));
         if (keep) {
 #pragma unroll
             for (int t = 0; t < TPW; ++t)
@@ -630,7 +655,7 @@ __device__ __forceinline__ int policy_forward(const SplitShape& P, const float* 
     const MatView W = mat_view(mats[P.L], P.H[P.L - 1], aw);
     f32x4 acc[2][2];
     clear(acc);
-    if (T.wave < W.ks) mac_steps(acc, W, 0, H, T, T.wave, SW, cur, next);
+    if (T.wave < W.ks) mac_steps<2>(acc, W, 0, H, T, T.wave, SW, cur, next);
     else request(cur, next, T);
     scaled(acc, inv, W.inv[0]);
     const int parts = W.ks < SW ? W.ks : SW;
@@ -661,8 +686,8 @@ __device__ __forceinline__ void head_values(const f32x4 (&z)[TPW][2][2], const f
 #pragma unroll
         for (int n = 0; n < 2; ++n) {
             const f32x4* src = reinterpret_cast<const f32x4*>(smem) + (M.part + (i * 32 + 16 * n + T.l15) * S.waves) / 4;
-            f32x4 v = src[0] + src[1];
-            if (S.waves > 8) v += src[2] + src[3];
+            f32x4 v = src[0];
+            if (S.waves > 4) v += src[1];
             q[i][n] = (v[0] + v[1]) + (v[2] + v[3]) + bias[i];
         }
 }
@@ -682,14 +707,14 @@ template <int NN, int TPW>
 __device__ __forceinline__ void critic_forward(f32x4 (&z)[TPW][2][2], const SplitShape& P, const float* const (*mats)[PQL_MAX_HIDDEN + 1],
                                       int net, const Tile& X, const Tile& H, const Share& S, const SmallMem& M, int kept,
                                       float* const (*h)[PQL_MAX_HIDDEN + 1], int r0, int B, const Wv& T, Ahead& cur,
-                                      const u32x4* next, float (&xv)[XV], const InputRows& following, bool fetch) {
+                                      const Begin& next, Rows& xv, const InputRows& following, bool fetch) {
     float inv[2];
     row_inv(inv, M.inv, T);
     for (int l = 0; l < P.L; ++l) {
         const int N = P.H[l];
         const MatView W = mat_view(mats[net][l], l == 0 ? P.o + P.a : P.H[l - 1], N);
-        const u32x4* n = next;
-        if (l + 1 < P.L) n = first_step(mat_view(mats[net][l + 1], N, P.H[l + 1]), S.slot, 0);
+        Begin n = next;
+        if (l + 1 < P.L) n = begin_of(mat_view(mats[net][l + 1], N, P.H[l + 1]), S.slot, 0, 1);
         forward<TPW>(z, W, l == 0 ? X : H, S, inv, T, cur, n);
         if (l == 0 && fetch) request_rows(xv, following, (P.o + P.a + 31) >> 5, T);    // the next chain's input
         if (l < kept) {
@@ -703,16 +728,18 @@ __device__ __forceinline__ void critic_forward(f32x4 (&z)[TPW][2][2], const Spli
 
 // ---- distributional critics (PQL-D) on the tile ------------------------------------------------------------------------
 // Logits of a network from its last hidden tile: atoms <= 64 columns in two 32-column tiles, the wavefronts of a network take
-// one tile and every fourth k-step; the partial tiles go to LDS over the activations.  A row is then handled by one
+// one tile and every second k-step; the partial tiles go to LDS over the activations.  A row is then handled by one
 // wavefront, lane = atom.
-constexpr int DIST_PARTS = 8;        // partial tiles per network: (k-step mod 4) * 2 + tile
+constexpr int DIST_PARTS = 4;        // partial tiles per network: (k-step mod 2) * 2 + tile
+constexpr int LOGIT_STEP = 2;
+constexpr int DR = 32 / SW;          // rows per wavefront
 __device__ __forceinline__ void put_logits(const MatView& W, const Tile& H, int at, const Share& S, const float (&inv)[2], const Wv& T,
-                                  Ahead& cur, const u32x4* next) {
+                                  Ahead& cur, const Begin& next) {
     const int tile = S.slot & 1, part = S.slot >> 1;
     f32x4 acc[2][2];
     clear(acc);
     if (tile < W.tiles && part < W.ks) {
-        mac_steps(acc, W, tile, H, T, part, 4, cur, next);
+        mac_steps<2>(acc, W, tile, H, T, part, LOGIT_STEP, cur, next);
         scaled(acc, inv, W.inv[tile]);
     } else {
         request(cur, next, T);
@@ -723,7 +750,7 @@ __device__ __forceinline__ float logit(int at, int net, int row, int k) {
     const int col = k & 31;
     const int e = (((col >> 4) * 2 + (row >> 4)) * 64 + ((col >> 2) & 3) * 16 + (row & 15)) * 4 + (col & 3);
     const int p = at * 4 + (net * DIST_PARTS + (k >> 5)) * 1024 + e;
-    return (smem[p] + smem[p + 2048]) + (smem[p + 4096] + smem[p + 6144]);
+    return smem[p] + smem[p + 2048];
 }
 __device__ __forceinline__ float wave_max(float x) {
     x = fmaxf(x, dpp_move<0x128>(x));
@@ -739,15 +766,15 @@ __device__ __forceinline__ float lane_softmax(float x, bool live, float& logp) {
     logp = live ? (x - mx) - logf(s) : 0.f;
     return e / s;
 }
-// The gradients at the logits (two rows per wavefront, both networks) as a two-step tile per network at `at`, each row with
+// The gradients at the logits (DR rows per wavefront, both networks) as a two-step tile per network at `at`, each row with
 // its own scale (inverse scales to smem[inv_at + 32 net + row]).
 __device__ __forceinline__ Tile logit_tile(int at, int net) { return Tile{at + net * 2 * 8 * CS, 8 * CS}; }
-__device__ __forceinline__ void put_dlogits(const float (&dl)[2][2], int at, int inv_at, const Wv& T) {
+__device__ __forceinline__ void put_dlogits(const float (&dl)[2][DR], int at, int inv_at, const Wv& T) {
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int rr = 0; rr < 2; ++rr) {
-            const int row = 2 * T.wave + rr;
+        for (int rr = 0; rr < DR; ++rr) {
+            const int row = DR * T.wave + rr;
             float inv;
             const float s = scale_for(wave_max(fabsf(dl[i][rr])), inv);
             put_value(logit_tile(at, i), row, T.lane, dl[i][rr], s);
@@ -775,18 +802,18 @@ __device__ __forceinline__ void critic_step(const SplitCriticArgs& A) {
     const int B = A.B, L = P.L, a = P.a, HL = P.H[L - 1];
     const int r0 = blockIdx.x * 32, wg = blockIdx.x, nwg = gridDim.x;
     const int aw = SAC ? 2 * a : a;
-    const Share S = NN == 2 ? Share{T.wave >> 3, T.wave & 7, 8} : Share{0, T.wave, SW};
+    const Share S = NN == 2 ? Share{T.wave >> 2, T.wave & 3, 4} : Share{0, T.wave, SW};
     const Tile X = {P.x0, P.xplane}, H0 = {P.h0, P.hplane};
     const Tile H = {P.h0 + S.net * 2 * P.hplane, P.hplane};
     const SmallMem M = small_mem(P.sm, P.as);
     const int steps = (P.o + a + 31) >> 5;
-    float xv[XV];
+    Rows xv;
     InputRows in = input_rows(A.next_obs, P.o, nullptr, -1, a, P.as, r0, B);
     request_rows(xv, in, steps, T);
     Ahead cur;
-    request(cur, first_step(mat_view(A.pi[0], P.o, P.H[0]), T.wave, 0), T);
+    request(cur, begin_of(mat_view(A.pi[0], P.o, P.H[0]), T.wave, 0, 1), T);
     auto critic_begin = [&](const float* const (&mats)[2][PQL_MAX_HIDDEN + 1], int net) {
-        return first_step(mat_view(mats[net][0], P.o + a, P.H[0]), S.slot, 0);
+        return begin_of(mat_view(mats[net][0], P.o + a, P.H[0]), S.slot, 0, 1);
     };
     float ret[2], boot[2];
 #pragma unroll
@@ -799,20 +826,24 @@ __device__ __forceinline__ void critic_step(const SplitCriticArgs& A) {
     lds_barrier();
     // ---- a' from the lagged policy
     {
-        const int parts = policy_forward<NN == 2 ? (TPW + 1) / 2 : TPW>(P, A.pi, X, H0, M, false, nullptr, aw, r0, B, T,
+        const int parts = policy_forward<NN == 2 ? TPW / 2 : TPW>(P, A.pi, X, H0, M, false, nullptr, aw, r0, B, T,
                                                                              cur, critic_begin(A.qt, S.net));
-        const int row = T.tid >> 5, col = T.tid & 31;
-        float act = 0.f;
-        if (SAC) {      // a' ~ pi^v(.|s') with its log-density (soft target)
-            float eps, raw;
-            const float lp = sample_action(H0.base, parts, row, col, a, A.pi_bias, r0, A.sac, act, eps, raw);
-            if (col == 0) smem[M.logp + row] = lp;
-        } else if (col < a) {
-            act = tanhf(sum_partials(H0.base, parts, row, col) + A.pi_bias[col]);
-        }
-        if (col < a) {
-            if (P.alias) smem[M.act + row * M.as + col] = act;
-            else put_value(X, row, P.o + col, act, __uint_as_float(0x7F000000u - __float_as_uint(smem[M.inv + row])));
+        const int col = T.tid & 31;
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+            const int row = (T.tid >> 5) + 16 * e;
+            float act = 0.f;
+            if (SAC) {      // a' ~ pi^v(.|s') with its log-density (soft target)
+                float eps, raw;
+                const float lp = sample_action(H0.base, parts, row, col, a, A.pi_bias, r0, A.sac, act, eps, raw);
+                if (col == 0) smem[M.logp + row] = lp;
+            } else if (col < a) {
+                act = tanhf(sum_partials(H0.base, parts, row, col) + A.pi_bias[col]);
+            }
+            if (col < a) {
+                if (P.alias) smem[M.act + row * M.as + col] = act;
+                else put_value(X, row, P.o + col, act, __uint_as_float(0x7F000000u - __float_as_uint(smem[M.inv + row])));
+            }
         }
         lds_barrier();
         if (SAC) {      // y = ret + boot (min Q' - alpha log pi): the entropy term joins the reward part here
@@ -824,12 +855,12 @@ __device__ __forceinline__ void critic_step(const SplitCriticArgs& A) {
     // ---- target critics, y
     f32x4 z[TPW][2][2], wo[TPW][2];
     const int tilesL = (HL + 31) >> 5;
-    float y[2], mass[2];                     // TD target of this lane's rows / projected target distribution of this wavefront's (lane = atom)
+    float y[2], mass[DR];                     // TD target of this lane's rows / projected target distribution of this wavefront's (lane = atom)
     const int atoms = DIST ? A.atoms : 2;
     const bool live = T.lane < atoms;
     const float dz = (A.v_max - A.v_min) / (float)(atoms - 1), zk = A.v_min + (float)T.lane * dz;
     auto dist_begin = [&](const float* const (&mats)[2][PQL_MAX_HIDDEN + 1]) {
-        return first_step(mat_view(mats[S.net][L], HL, atoms), S.slot & 1, S.slot >> 1);
+        return begin_of(mat_view(mats[S.net][L], HL, atoms), S.slot & 1, S.slot >> 1, LOGIT_STEP);
     };
     const InputRows online = input_rows(A.obs, P.o, A.act, -1, a, P.as, r0, B);
     {
@@ -856,8 +887,8 @@ __device__ __forceinline__ void critic_step(const SplitCriticArgs& A) {
                 put_logits(mat_view(A.qt[net][L], HL, atoms), H, H0.base, S, inv, T, cur, critic_begin(A.q, S.net));
                 const float b0 = live ? A.bo_t[0][T.lane] : 0.f, b1 = live ? A.bo_t[1][T.lane] : 0.f;
 #pragma unroll
-                for (int rr = 0; rr < 2; ++rr) {
-                    const int row = 2 * T.wave + rr;
+                for (int rr = 0; rr < DR; ++rr) {
+                    const int row = DR * T.wave + rr;
                     float unused;
                     const float t0 = lane_softmax(logit(H0.base, 0, row, T.lane) + b0, live, unused);
                     const float t1 = lane_softmax(logit(H0.base, 1, row, T.lane) + b1, live, unused);
@@ -902,8 +933,8 @@ __device__ __forceinline__ void critic_step(const SplitCriticArgs& A) {
         }
         lds_barrier();
         if (!DIST) head_weights<TPW>(wo, A.wo_q[net], tilesL, S, T);
-        const u32x4* after = NN == 1 && ni == 0 ? critic_begin(A.q, 1) : cur_valid(A.q[0][0]);
-        const u32x4* back = L > 1 ? first_step(mat_view(A.qT[net][L - 1], HL, P.H[L - 2]), S.slot, 0) : after;
+        const Begin after = NN == 1 && ni == 0 ? critic_begin(A.q, 1) : begin_at(A.q[0][0]);
+        const Begin back = L > 1 ? begin_of(mat_view(A.qT[net][L - 1], HL, P.H[L - 2]), S.slot, 0, 1) : after;
         critic_forward<NN, TPW>(z, P, A.q, net, X, H, S, M, DIST ? L : L - 1, A.h, r0, B, T, cur, DIST ? dist_begin(A.q) : back, xv, in,
                                 false);
         if (DIST) {
@@ -911,14 +942,14 @@ __device__ __forceinline__ void critic_step(const SplitCriticArgs& A) {
             float inv[2];
             const MatView WT = mat_view(A.qT[net][L], atoms, HL);
             put_tile<TPW>(z, tilesL, H, S, M, inv, T);
-            put_logits(mat_view(A.q[net][L], HL, atoms), H, H0.base, S, inv, T, cur, first_step(WT, S.slot, 0));
-            float dl[2][2], lsum[2] = {0.f, 0.f}, dsum[2] = {0.f, 0.f};
+            put_logits(mat_view(A.q[net][L], HL, atoms), H, H0.base, S, inv, T, cur, begin_of(WT, S.slot, 0, 1));
+            float dl[2][DR], lsum[2] = {0.f, 0.f}, dsum[2] = {0.f, 0.f};
 #pragma unroll
             for (int i = 0; i < 2; ++i) {
                 const float b = live ? A.bo_q[i][T.lane] : 0.f;
 #pragma unroll
-                for (int rr = 0; rr < 2; ++rr) {
-                    const int row = 2 * T.wave + rr;
+                for (int rr = 0; rr < DR; ++rr) {
+                    const int row = DR * T.wave + rr;
                     const bool rv = r0 + row < B;
                     float lp;
                     const float p = lane_softmax(logit(H0.base, i, row, T.lane) + b, live, lp);
@@ -931,10 +962,10 @@ __device__ __forceinline__ void critic_step(const SplitCriticArgs& A) {
             }
             lds_barrier();                                   // the partial tiles have been read
             put_dlogits(dl, H0.base, M.part, T);
-            float* sums = &smem[(H0.base + 4 * 8 * CS) * 4];  // [2][16][64] output-bias gradients, behind the two tiles
+            float* sums = &smem[(H0.base + 4 * 8 * CS) * 4];  // [2][SW][64] output-bias gradients, behind the two tiles
             sums[T.wave * 64 + T.lane] = dsum[0];
             sums[(SW + T.wave) * 64 + T.lane] = dsum[1];
-            if (T.lane == 0) { smem[M.part + 64 + T.wave] = lsum[0]; smem[M.part + 80 + T.wave] = lsum[1]; }
+            if (T.lane == 0) { smem[M.part + 64 + T.wave] = lsum[0]; smem[M.part + 64 + SW + T.wave] = lsum[1]; }
             lds_barrier();
             if (T.tid < 128) {
                 const int i = T.tid >> 6, k = T.tid & 63;
@@ -944,12 +975,12 @@ __device__ __forceinline__ void critic_step(const SplitCriticArgs& A) {
             } else if (T.tid < 130) {
                 const int i = T.tid - 128;
                 float s = 0.f;
-                for (int w = 0; w < SW; ++w) s += smem[M.part + 64 + 16 * i + w];
+                for (int w = 0; w < SW; ++w) s += smem[M.part + 64 + SW * i + w];
                 A.p_loss[i * nwg + wg] = s;
             }
             row_inv(inv, M.part + 32 * net, T);
             f32x4 hl[2][2];
-            load_ahead<TPW>(A.h[net][L], HL, hl, S, r0, B, T);
+            load_ahead(A.h[net][L], HL, hl, S, r0, B, T);
             backward<TPW>(z, WT, logit_tile(H0.base, net), S, inv, A.h[net][L], A.d[net][L], A.col[net][L] + (size_t)wg * HL, HL, r0, B, T,
                           cur, back, hl);
         } else {
@@ -997,11 +1028,11 @@ __device__ __forceinline__ void critic_step(const SplitCriticArgs& A) {
         f32x4 hv[2][2];
         for (int l = L; l >= 2; --l) {
             const int Hl = P.H[l - 1], Hp = P.H[l - 2];
-            load_ahead<TPW>(A.h[net][l - 1], Hp, hv, S, r0, B, T);
+            load_ahead(A.h[net][l - 1], Hp, hv, S, r0, B, T);
             put_tile<TPW>(z, (Hl + 31) >> 5, H, S, M, inv, T);
             const MatView W = mat_view(A.qT[net][l - 1], Hl, Hp);
             backward<TPW>(z, W, H, S, inv, A.h[net][l - 1], A.d[net][l - 1], A.col[net][l - 1] + (size_t)wg * Hp, Hp, r0, B, T, cur,
-                          l > 2 ? first_step(mat_view(A.qT[net][l - 2], Hp, P.H[l - 3]), S.slot, 0) : after, hv);
+                          l > 2 ? begin_of(mat_view(A.qT[net][l - 2], Hp, P.H[l - 3]), S.slot, 0, 1) : after, hv);
         }
     }
 }
@@ -1015,38 +1046,43 @@ __device__ __forceinline__ void policy_step(const SplitPolicyArgs& A) {
     constexpr bool SAC = VAR == VAR_SAC, DIST = VAR == VAR_DIST;
     const Wv T = wave_of();
     const SplitShape& P = A.shape;
-    constexpr int TPA = NN == 2 ? (TPW + 1) / 2 : TPW;       // the policy's tiles per wavefront
+    constexpr int TPA = NN == 2 ? TPW / 2 : TPW;       // the policy's tiles per wavefront
     const int B = A.B, L = P.L, a = P.a, HL = P.H[L - 1], H1 = P.H[0];
     const int r0 = blockIdx.x * 32, wg = blockIdx.x;
     const int aw = SAC ? 2 * a : a;
-    const Share S = NN == 2 ? Share{T.wave >> 3, T.wave & 7, 8} : Share{0, T.wave, SW};
+    const Share S = NN == 2 ? Share{T.wave >> 2, T.wave & 3, 4} : Share{0, T.wave, SW};
     const Tile X = {P.x0, P.xplane}, H0 = {P.h0, P.hplane};
     const Tile H = {P.h0 + S.net * 2 * P.hplane, P.hplane};
     const SmallMem M = small_mem(P.sm, P.as);
     const int atoms = DIST ? A.atoms : 2;
     const int steps = (P.o + a + 31) >> 5;
-    const int row = T.tid >> 5, col = T.tid & 31;            // this thread's element of an action-wide tile
-    float xv[XV];
+    const int col = T.tid & 31;                              // this thread's elements of an action-wide tile: rows row_of(0), row_of(1)
+    auto row_of = [&](int e) { return (T.tid >> 5) + 16 * e; };
+    Rows xv;
     InputRows in = input_rows(A.obs, P.o, nullptr, -1, a, P.as, r0, B);
     request_rows(xv, in, steps, T);
     Ahead cur;
-    request(cur, first_step(mat_view(A.pi[0], P.o, P.H[0]), T.wave, 0), T);
-    auto critic_begin = [&](int net) { return first_step(mat_view(A.q[net][0], P.o + a, P.H[0]), S.slot, 0); };
+    request(cur, begin_of(mat_view(A.pi[0], P.o, P.H[0]), T.wave, 0, 1), T);
+    auto critic_begin = [&](int net) { return begin_of(mat_view(A.q[net][0], P.o + a, P.H[0]), S.slot, 0, 1); };
     // the first of the backward products of critic `net`: from its last hidden layer down, or its action gradient
-    auto action_begin = [&](int net) { return first_step(mat_view(A.w1aT[net], H1, a), 0, S.slot); };
+    auto action_begin = [&](int net) { return begin_of(mat_view(A.w1aT[net], H1, a), 0, S.slot, S.waves); };
     auto back_begin = [&](int net) {
-        return L > 1 ? first_step(mat_view(A.qT[net][L - 1], HL, P.H[L - 2]), S.slot, 0) : action_begin(net);
+        return L > 1 ? begin_of(mat_view(A.qT[net][L - 1], HL, P.H[L - 2]), S.slot, 0, 1) : action_begin(net);
     };
     put_rows(xv, in, steps, X, M.inv, 1.f, T);
     lds_barrier();
-    float act = 0.f, eps = 0.f, raw = 0.f, logp = 0.f;
+    float act[2] = {0.f, 0.f}, eps[2] = {0.f, 0.f}, raw[2] = {0.f, 0.f}, logp[2] = {0.f, 0.f};
     {
         const int parts = policy_forward<TPA>(P, A.pi, X, H0, M, true, A.hA, aw, r0, B, T, cur, critic_begin(S.net));
-        if (SAC) logp = sample_action(H0.base, parts, row, col, a, A.pi_bias, r0, A.sac, act, eps, raw);
-        else if (col < a) act = tanhf(sum_partials(H0.base, parts, row, col) + A.pi_bias[col]);
-        if (col < a) {
-            if (P.alias) smem[M.act + row * M.as + col] = act;
-            else put_value(X, row, P.o + col, act, __uint_as_float(0x7F000000u - __float_as_uint(smem[M.inv + row])));
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+            const int row = row_of(e);
+            if (SAC) logp[e] = sample_action(H0.base, parts, row, col, a, A.pi_bias, r0, A.sac, act[e], eps[e], raw[e]);
+            else if (col < a) act[e] = tanhf(sum_partials(H0.base, parts, row, col) + A.pi_bias[col]);
+            if (col < a) {
+                if (P.alias) smem[M.act + row * M.as + col] = act[e];
+                else put_value(X, row, P.o + col, act[e], __uint_as_float(0x7F000000u - __float_as_uint(smem[M.inv + row])));
+            }
         }
         lds_barrier();
     }
@@ -1065,7 +1101,7 @@ __device__ __forceinline__ void policy_step(const SplitPolicyArgs& A) {
         }
         if (!DIST) head_weights<TPW>(wo, A.wo[net], tilesL, S, T);
         critic_forward<NN, TPW>(z, P, A.q, net, X, H, S, M, NN == 2 && !DIST ? L - 1 : L, A.h, r0, B, T, cur,
-                                DIST ? first_step(mat_view(A.q[net][L], HL, atoms), S.slot & 1, S.slot >> 1)
+                                DIST ? begin_of(mat_view(A.q[net][L], HL, atoms), S.slot & 1, S.slot >> 1, LOGIT_STEP)
                                      : (NN == 1 && ni == 0 ? critic_begin(1) : back_begin(S.net)), xv, in, false);
         if (DIST) continue;
         float bias[NN], q[NN][2];
@@ -1090,12 +1126,12 @@ __device__ __forceinline__ void policy_step(const SplitPolicyArgs& A) {
         float inv[2];
         const MatView WT = mat_view(A.qT[net][L], atoms, HL);
         put_tile<TPW>(z, tilesL, H, S, M, inv, T);
-        put_logits(mat_view(A.q[net][L], HL, atoms), H, H0.base, S, inv, T, cur, first_step(WT, S.slot, 0));
+        put_logits(mat_view(A.q[net][L], HL, atoms), H, H0.base, S, inv, T, cur, begin_of(WT, S.slot, 0, 1));
         const float b0 = live ? A.bo[0][T.lane] : 0.f, b1 = live ? A.bo[1][T.lane] : 0.f;
-        float dl[2][2];
+        float dl[2][DR];
 #pragma unroll
-        for (int rr = 0; rr < 2; ++rr) {
-            const int tr = 2 * T.wave + rr;
+        for (int rr = 0; rr < DR; ++rr) {
+            const int tr = DR * T.wave + rr;
             const bool rv = r0 + tr < B;
             float unused;
             const float p0 = lane_softmax(logit(H0.base, 0, tr, T.lane) + b0, live, unused);
@@ -1118,7 +1154,7 @@ __device__ __forceinline__ void policy_step(const SplitPolicyArgs& A) {
         }
         row_inv(inv, M.part + 32 * net, T);
         f32x4 hl[2][2];
-        load_ahead<TPW>(A.h[net][L], HL, hl, S, r0, B, T);
+        load_ahead(A.h[net][L], HL, hl, S, r0, B, T);
         backward<TPW>(z, WT, logit_tile(H0.base, net), S, inv, A.h[net][L], nullptr, nullptr, HL, r0, B, T, cur, back_begin(net), hl);
     }
 #pragma unroll
@@ -1159,18 +1195,18 @@ __device__ __forceinline__ void policy_step(const SplitPolicyArgs& A) {
         f32x4 hv[2][2];
         for (int l = L; l >= 2; --l) {
             const int Hl = P.H[l - 1], Hp = P.H[l - 2];
-            load_ahead<TPW>(A.h[net][l - 1], Hp, hv, S, r0, B, T);
+            load_ahead(A.h[net][l - 1], Hp, hv, S, r0, B, T);
             put_tile<TPW>(z, (Hl + 31) >> 5, H, S, M, inv, T);
             const MatView W = mat_view(A.qT[net][l - 1], Hl, Hp);
             backward<TPW>(z, W, H, S, inv, A.h[net][l - 1], nullptr, nullptr, Hp, r0, B, T, cur,
-                          l > 2 ? first_step(mat_view(A.qT[net][l - 2], Hp, P.H[l - 3]), S.slot, 0) : action_begin(net), hv);
+                          l > 2 ? begin_of(mat_view(A.qT[net][l - 2], Hp, P.H[l - 3]), S.slot, 0, 1) : action_begin(net), hv);
         }
         put_tile<TPW>(z, (H1 + 31) >> 5, H, S, M, inv, T);
         const MatView W = mat_view(A.w1aT[net], H1, a);
-        const u32x4* after = NN == 1 && ni == 0 ? back_begin(1) : first_step(mat_view(A.waT[L], aw, HL), T.wave, 0);
+        const Begin after = NN == 1 && ni == 0 ? back_begin(1) : begin_of(mat_view(A.waT[L], aw, HL), T.wave, 0, 1);
         f32x4 acc[2][2];
         clear(acc);
-        if (S.slot < W.ks) mac_steps(acc, W, 0, H, T, S.slot, S.waves, cur, after);
+        if (S.slot < W.ks) mac_steps<2>(acc, W, 0, H, T, S.slot, S.waves, cur, after);
         else request(cur, after, T);
         scaled(acc, inv, W.inv[0]);
 #pragma unroll
@@ -1181,37 +1217,42 @@ __device__ __forceinline__ void policy_step(const SplitPolicyArgs& A) {
     const int ks1 = (H1 + 31) >> 5;
     const int per = ks1 < S.waves ? ks1 : S.waves;           // partial tiles per network
     put_partial(da, H0.base, S.net * per + S.slot, S.slot < per, T);
-    float g = 0.f, g2 = 0.f;                                 // gradient at the output layer: column col, and a + col (raw)
-    {
+    float g[2] = {0.f, 0.f}, g2[2] = {0.f, 0.f};             // gradient at the output layer: column col, and a + col (raw)
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+        const int row = row_of(e);
         const bool rv = r0 + row < B;
         const float s = col < a ? sum_partials(H0.base, NN * per, row, col) : 0.f;
         if (!SAC) {
-            g = (col < a && rv) ? s * (1.f - act * act) : 0.f;
+            g[e] = (col < a && rv) ? s * (1.f - act[e] * act[e]) : 0.f;
         } else if (col < a && rv) {
             // J = mean(alpha log pi - min Q): dJ/dmu = dJ/du = g + (alpha/B) 2a; dJ/draw = dJ/du sigma eps - alpha/B
             // inside the clip of log sigma, 0 outside
             const float ab = expf(A.sac.log_alpha[0]) / (float)B;
-            const float ls = fminf(fmaxf(raw, SAC_LOG_STD_MIN), SAC_LOG_STD_MAX);
-            g = s * (1.f - act * act) + ab * 2.f * act;
-            g2 = (raw > SAC_LOG_STD_MIN && raw < SAC_LOG_STD_MAX) ? g * expf(ls) * eps - ab : 0.f;
+            const float ls = fminf(fmaxf(raw[e], SAC_LOG_STD_MIN), SAC_LOG_STD_MAX);
+            g[e] = s * (1.f - act[e] * act[e]) + ab * 2.f * act[e];
+            g2[e] = (raw[e] > SAC_LOG_STD_MIN && raw[e] < SAC_LOG_STD_MAX) ? g[e] * expf(ls) * eps[e] - ab : 0.f;
         }
         if (col < a && rv) {
-            A.dPre[(size_t)(r0 + row) * aw + col] = g;
-            if (SAC) A.dPre[(size_t)(r0 + row) * aw + a + col] = g2;
+            A.dPre[(size_t)(r0 + row) * aw + col] = g[e];
+            if (SAC) A.dPre[(size_t)(r0 + row) * aw + a + col] = g2[e];
         }
     }
     lds_barrier();                                         // the partial tiles have been read
     // one k-step of 32 columns at the place of the activations, with its own row scales; column sums for the output bias
     const Tile D = {P.h0, 4 * CS};
     float* sums = &smem[P.h0 * 4 + 2 * 4 * CS * 4];          // [32][33] behind that tile
-    {
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+        const int row = row_of(e);
         float inv_d;
-        const float s = scale_for(half_max(fmaxf(fabsf(g), fabsf(g2))), inv_d);
+        const float s = scale_for(half_max(fmaxf(fabsf(g[e]), fabsf(g2[e]))), inv_d);
         if (col == 0) smem[M.inv + row] = inv_d;
-        if (!SAC || col < a || col >= aw) put_value(D, row, col, g, s);
-        if (SAC && col < a) put_value(D, row, a + col, g2, s);
-        if (!SAC || col < a) sums[row * 33 + col] = g;
-        if (SAC && col < a) sums[row * 33 + a + col] = g2;
+        if (!SAC || col < a || col >= aw) put_value(D, row, col, g[e], s);
+        if (SAC && col < a) put_value(D, row, a + col, g2[e], s);
+        if (!SAC || col < a) sums[row * 33 + col] = g[e];
+        if (SAC && col < a) sums[row * 33 + a + col] = g2[e];
+        if (SAC && col == 0) smem[M.logp + row] = r0 + row < B ? logp[e] : 0.f;
     }
     lds_barrier();
     if (T.tid < aw) {
@@ -1219,29 +1260,24 @@ __device__ __forceinline__ void policy_step(const SplitPolicyArgs& A) {
         for (int r = 0; r < 32; ++r) s += sums[r * 33 + T.tid];
         A.colA[L + 1][(size_t)wg * aw + T.tid] = s;
     }
-    if (SAC) {
-        const float lp = col == 0 && r0 + row < B ? logp : 0.f;
-        if (col == 0) smem[M.logp + row] = lp;
-        lds_barrier();
-        if (T.tid == 0) {
-            float s = 0.f;
-            for (int r = 0; r < 32; ++r) s += smem[M.logp + r];
-            A.p_logp[wg] = s;
-        }
+    if (SAC && T.tid == 64) {
+        float s = 0.f;
+        for (int r = 0; r < 32; ++r) s += smem[M.logp + r];
+        A.p_logp[wg] = s;
     }
     // ---- back through the policy
     {
         const Share SA = {0, T.wave, SW};
         f32x4 za[TPA][2][2], hv[2][2];
         row_inv(inv, M.inv, T);
-        load_ahead<TPA>(A.hA[L], HL, hv, SA, r0, B, T);
+        load_ahead(A.hA[L], HL, hv, SA, r0, B, T);
         for (int l = L; l >= 1; --l) {
             const int N = P.H[l - 1];
             const MatView W = mat_view(A.waT[l], l == L ? aw : P.H[l], N);
             backward<TPA>(za, W, l == L ? D : H0, SA, inv, A.hA[l], A.dA[l], A.colA[l] + (size_t)wg * N, N, r0, B, T, cur,
-                          l > 1 ? first_step(mat_view(A.waT[l - 1], N, P.H[l - 2]), T.wave, 0) : cur_valid(A.pi[0]), hv);
+                          l > 1 ? begin_of(mat_view(A.waT[l - 1], N, P.H[l - 2]), T.wave, 0, 1) : begin_at(A.pi[0]), hv);
             if (l > 1) {
-                load_ahead<TPA>(A.hA[l - 1], P.H[l - 2], hv, SA, r0, B, T);
+                load_ahead(A.hA[l - 1], P.H[l - 2], hv, SA, r0, B, T);
                 put_tile<TPA>(za, W.tiles, H0, SA, M, inv, T);
             }
         }
@@ -1261,7 +1297,7 @@ __device__ __forceinline__ void act_step(const SplitActArgs& A) {
     const Tile X = {P.x0, P.xplane}, H = {P.h0, P.hplane};
     const SmallMem M = small_mem(P.sm, P.as);
     const int steps = (P.o + 31) >> 5;
-    float xv[XV];
+    Rows xv;
     InputRows in = input_rows(A.obs, P.o, nullptr, -1, 0, P.as, r0, B);
     if (A.nmean != nullptr) {
         in.norm = true;
@@ -1269,28 +1305,32 @@ __device__ __forceinline__ void act_step(const SplitActArgs& A) {
     }
     request_rows(xv, in, steps, T);
     Ahead cur;
-    request(cur, first_step(mat_view(A.pi[0], P.o, P.H[0]), T.wave, 0), T);
+    request(cur, begin_of(mat_view(A.pi[0], P.o, P.H[0]), T.wave, 0, 1), T);
     put_rows(xv, in, steps, X, M.inv, 0.f, T);
     lds_barrier();
-    const int parts = policy_forward<TPW>(P, A.pi, X, H, M, false, nullptr, aw, r0, B, T, cur, cur_valid(A.pi[0]));
-    const int row = T.tid >> 5, col = T.tid & 31, env = r0 + row;
-    if (SAC) {
-        float act, eps, raw;
-        (void)sample_action(H.base, parts, row, col, a, A.pi_bias, r0, A.sac, act, eps, raw);
-        if (col < a && env < B) A.act_out[(size_t)env * a + col] = act;
-    } else if (col < a && env < B) {
-        const GemmNoise& nz = A.noise;
-        uint32_t w0, w1;
-        philox4x32_10_f((uint32_t)(env * a + col), 2u, nz.ctr2, nz.ctr3, nz.key0, nz.key1, w0, w1);
-        // double precision: (w >> 8) + 0.5 needs 25 significant bits
-        const double u1 = ((double)(w0 >> 8) + 0.5) * 0x1p-24;
-        const double u2 = ((double)(w1 >> 8) + 0.5) * 0x1p-24;
-        const double e = sqrt(-2.0 * log(u1)) * cos(6.283185307179586476925286766559 * u2);
-        double sigma = (double)nz.sigma_min;
-        if (nz.sigma_rows > 1)
-            sigma += ((double)env / (double)(nz.sigma_rows - 1)) * ((double)nz.sigma_max - (double)nz.sigma_min);
-        const float x = tanhf(sum_partials(H.base, parts, row, col) + A.pi_bias[col]) + (float)(sigma * e);
-        A.act_out[(size_t)env * a + col] = fminf(fmaxf(x, -1.f), 1.f);
+    const int parts = policy_forward<TPW>(P, A.pi, X, H, M, false, nullptr, aw, r0, B, T, cur, begin_at(A.pi[0]));
+    const int col = T.tid & 31;
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+        const int row = (T.tid >> 5) + 16 * e, env = r0 + row;
+        if (SAC) {
+            float act, eps, raw;
+            (void)sample_action(H.base, parts, row, col, a, A.pi_bias, r0, A.sac, act, eps, raw);
+            if (col < a && env < B) A.act_out[(size_t)env * a + col] = act;
+        } else if (col < a && env < B) {
+            const GemmNoise& nz = A.noise;
+            uint32_t w0, w1;
+            philox4x32_10_f((uint32_t)(env * a + col), 2u, nz.ctr2, nz.ctr3, nz.key0, nz.key1, w0, w1);
+            // double precision: (w >> 8) + 0.5 needs 25 significant bits
+            const double u1 = ((double)(w0 >> 8) + 0.5) * 0x1p-24;
+            const double u2 = ((double)(w1 >> 8) + 0.5) * 0x1p-24;
+            const double eps = sqrt(-2.0 * log(u1)) * cos(6.283185307179586476925286766559 * u2);
+            double sigma = (double)nz.sigma_min;
+            if (nz.sigma_rows > 1)
+                sigma += ((double)env / (double)(nz.sigma_rows - 1)) * ((double)nz.sigma_max - (double)nz.sigma_min);
+            const float x = tanhf(sum_partials(H.base, parts, row, col) + A.pi_bias[col]) + (float)(sigma * eps);
+            A.act_out[(size_t)env * a + col] = fminf(fmaxf(x, -1.f), 1.f);
+        }
     }
 }
 
@@ -1304,9 +1344,9 @@ static size_t plan_lds(SplitShape& p, int nets, int in_cols, bool dist = false) 
     p.xplane = (in_cols + 31) / 32 * 4 * CS;
     p.as = p.a | 1;
     const int h_units = nets * 2 * p.hplane;
-    const size_t small = sizeof(float) * (size_t)(1088 + 32 * p.as);
+    const size_t small = sizeof(float) * (size_t)(576 + 32 * p.as);
     // the policy step's output-layer tile and its column sums also live in the place of the activations
-    // (distributional critics: sixteen partial tiles of logits)
+    // (distributional critics: eight partial tiles of logits)
     const int least = dist ? 2 * DIST_PARTS * 256 : 2 * 4 * CS + 32 * 33 / 4;
     p.h0 = 0; p.x0 = h_units < least ? least : h_units; p.alias = 0;
     size_t units = (size_t)p.x0 + 2 * (size_t)p.xplane;
@@ -1338,24 +1378,24 @@ bool split_shape_ok(int o, int a, int aw, const int* H, int L, bool dist) {
 }
 
 // ---- kernels ------------------------------------------------------------------------------------------------------
-// fused_*: every layer at most 256 wide; chain_*: a widest layer of 512 (two output tiles per wavefront); split_*: the
+// fused_*: every layer at most 256 wide; chain_*: a widest layer of 512 (four output tiles per wavefront); split_*: the
 // other shapes, layers above 512 with the critics one after the other.
 template <int VAR>
-__global__ __launch_bounds__(ST) void fused_critic_kernel(const SplitCriticArgs) { critic_step<2, 1, VAR>(kernel_args<SplitCriticArgs>()); }
+__global__ __launch_bounds__(ST) void fused_critic_kernel(const SplitCriticArgs) { critic_step<2, 2, VAR>(kernel_args<SplitCriticArgs>()); }
 template <int VAR>
-__global__ __launch_bounds__(ST) void chain_critic_kernel(const SplitCriticArgs) { critic_step<2, 2, VAR>(kernel_args<SplitCriticArgs>()); }
+__global__ __launch_bounds__(ST) void chain_critic_kernel(const SplitCriticArgs) { critic_step<2, 4, VAR>(kernel_args<SplitCriticArgs>()); }
 template <int NN, int TPW, int VAR>
 __global__ __launch_bounds__(ST) void split_critic_kernel(const SplitCriticArgs) { critic_step<NN, TPW, VAR>(kernel_args<SplitCriticArgs>()); }
 template <int VAR>
-__global__ __launch_bounds__(ST) void fused_policy_kernel(const SplitPolicyArgs) { policy_step<2, 1, VAR>(kernel_args<SplitPolicyArgs>()); }
+__global__ __launch_bounds__(ST) void fused_policy_kernel(const SplitPolicyArgs) { policy_step<2, 2, VAR>(kernel_args<SplitPolicyArgs>()); }
 template <int VAR>
-__global__ __launch_bounds__(ST) void chain_policy_kernel(const SplitPolicyArgs) { policy_step<2, 2, VAR>(kernel_args<SplitPolicyArgs>()); }
+__global__ __launch_bounds__(ST) void chain_policy_kernel(const SplitPolicyArgs) { policy_step<2, 4, VAR>(kernel_args<SplitPolicyArgs>()); }
 template <int NN, int TPW, int VAR>
 __global__ __launch_bounds__(ST) void split_policy_kernel(const SplitPolicyArgs) { policy_step<NN, TPW, VAR>(kernel_args<SplitPolicyArgs>()); }
 template <int VAR>
 __global__ __launch_bounds__(ST) void fused_act_kernel(const SplitActArgs) { act_step<1, VAR>(kernel_args<SplitActArgs>()); }
 template <int VAR>
-__global__ __launch_bounds__(ST) void chain_act_kernel(const SplitActArgs) { act_step<1, VAR>(kernel_args<SplitActArgs>()); }
+__global__ __launch_bounds__(ST) void chain_act_kernel(const SplitActArgs) { act_step<2, VAR>(kernel_args<SplitActArgs>()); }
 
 #define SPLIT_LAUNCH(KERNEL, KID)                                                                                  \
     do {                                                                                                           \
@@ -1372,9 +1412,9 @@ __global__ __launch_bounds__(ST) void chain_act_kernel(const SplitActArgs) { act
     do {                                                                                                           \
         if (kind == SPLIT_FUSED) SPLIT_LAUNCH((fused_##STEP##_kernel<VAR>), fused_kid);                            \
         if (kind == SPLIT_CHAIN && VAR == VAR_PLAIN) SPLIT_LAUNCH((chain_##STEP##_kernel<VAR_PLAIN>), chain_kid);  \
-        if (w <= 256) SPLIT_LAUNCH((split_##STEP##_kernel<2, 1, VAR>), split_kid);                                 \
-        if (w <= 512) SPLIT_LAUNCH((split_##STEP##_kernel<2, 2, VAR>), split_kid);                                 \
-        if (VAR != VAR_DIST) SPLIT_LAUNCH((split_##STEP##_kernel<1, 2, VAR == VAR_DIST ? VAR_PLAIN : VAR>), split_kid); \
+        if (w <= 256) SPLIT_LAUNCH((split_##STEP##_kernel<2, 2, VAR>), split_kid);                                 \
+        if (w <= 512) SPLIT_LAUNCH((split_##STEP##_kernel<2, 4, VAR>), split_kid);                                 \
+        if (VAR != VAR_DIST) SPLIT_LAUNCH((split_##STEP##_kernel<1, 4, VAR == VAR_DIST ? VAR_PLAIN : VAR>), split_kid); \
     } while (0)
 
 static bool kind_fits(int kind, int w) {

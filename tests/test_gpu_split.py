@@ -109,3 +109,40 @@ def test_rows_and_weights_of_very_different_size(hidden):
     for x, y in zip(run(bad), q):
         assert np.isnan(x[5]) and not np.isfinite(x[40])
         assert np.array_equal(x[others], y[others])
+
+
+@pytest.mark.parametrize("batch,hidden", [(40, (64, 64)), (333, (96, 40)), (8192, (256, 256))])
+def test_weight_gradients_of_columns_that_grow_and_differ(batch, hidden):
+    """The weight-gradient kernel's column scales come from a column's first rows: states that grow by 1e7 over the batch
+    (the sums are rescaled on the way), columns in units from 1e-3 to 1e4, a column of zeros, one that starts with zeros.
+    Every row of dW_1 (one state column) to 1e-5 of its own largest entry, against float64 on the deltas of the oracle."""
+    import torch
+    w = workload(hidden, 21, 3, batch)
+    s, ring = session(w), oracle_ring(w)
+    fill_both(s, ring, w, w.nstep + 3)
+    s.sample(batch)
+    rng = np.random.default_rng(5)
+    b = {k: getattr(s.batch, k)[:batch].cpu().numpy().copy() for k in ("obs", "act", "ret", "next_obs", "boot")}
+    b["obs"] = (rng.standard_normal((batch, w.obs_dim)) * 10.0 ** (7.0 * np.arange(batch) / batch - 5)[:, None]
+                * 10.0 ** (np.arange(w.obs_dim) % 8 - 3)).astype(np.float32)
+    b["obs"][:, 4] = 0.0
+    b["obs"][:batch // 2, 8] = 0.0
+    b["boot"][:] = 0.0
+    for k in ("obs", "boot"):
+        getattr(s.batch, k)[:batch].copy_(torch.from_numpy(b[k]))
+    # small first-layer weights: the hidden layers stay of order 1
+    c = s.critic_init.copy()
+    for h in (0, c.size // 2):
+        c[h:h + w.obs_dim * hidden[0]] *= (1e-3 / np.repeat(10.0 ** (np.arange(w.obs_dim) % 8 - 3), hidden[0])).astype(np.float32)
+    s.critic.copy_(torch.from_numpy(c))
+    s.critic_update(batch)
+    y = b["ret"].astype(np.float64)
+    _, g = O.critic_loss_and_grads(c, w.critic_dims(), b, y)
+    got, n = s.c_g.cpu().numpy().astype(np.float64), w.obs_dim * hidden[0]
+    for h in (0, c.size // 2):
+        ref, x = g[h:h + n].reshape(w.obs_dim, -1), got[h:h + n].reshape(w.obs_dim, -1)
+        assert np.all(x[4] == 0.0)
+        err = np.abs(x - ref).max(1) / np.maximum(np.abs(ref).max(1), 1e-300)
+        err[4] = 0.0
+        print(batch, hidden, "worst column", int(err.argmax()), "%.2e" % err.max(), flush=True)
+        assert err.max() <= TOL
