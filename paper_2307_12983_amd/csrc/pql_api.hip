@@ -310,25 +310,33 @@ int act_family(const pql_config* c, int rows) {
     const bool narrow = split_shape_ok(c->obs_dim, c->act_dim, actor_out(c), c->hidden, c->n_hidden);
     return narrow && chain_shape_ok(c) && (rows + FUSED_BM - 1) / FUSED_BM >= CHAIN_MIN_TILES ? FAM_CHAIN : FAM_LAYERED;
 }
-// Floats of prepared weights that one call can need (the critic step's or the policy step's, whichever is larger).
-size_t split_floats(const pql_config* c) {
+// Whether a layer's matrix is prepared for layer_rowtile_kernel.
+bool layer_prepared(int K, int N) { return K <= SPLIT_MAXK && N >= 128 && N <= 0xffff; }
+// Floats of prepared weights that one call can need (the critic step's or the policy step's, whichever is larger), on the
+// one-launch kernels or layer by layer; 0: none (offsets within the block are 32-bit).
+size_t prepared_floats(const pql_config* c) {
     const int L = c->n_hidden, o = c->obs_dim, a = c->act_dim, aw = actor_out(c);
-    size_t pi = up(split_mat_floats(o, c->hidden[0])), q = up(split_mat_floats(o + a, c->hidden[0])), qT = 0;
-    size_t waT = up(split_mat_floats(aw, c->hidden[L - 1]));
+    const bool all = split_ok(c);
+    auto mat = [&](int K, int N) { return all || layer_prepared(K, N) ? up(split_mat_floats(K, N)) : 0; };
+    size_t pi = mat(o, c->hidden[0]), q = mat(o + a, c->hidden[0]), qT = 0, waT = mat(aw, c->hidden[L - 1]);
     for (int l = 1; l < L; ++l) {
-        const size_t f = up(split_mat_floats(c->hidden[l - 1], c->hidden[l])), b = up(split_mat_floats(c->hidden[l], c->hidden[l - 1]));
+        const size_t f = mat(c->hidden[l - 1], c->hidden[l]), b = mat(c->hidden[l], c->hidden[l - 1]);
         pi += f; q += f; qT += b; waT += b;
     }
-    pi += up(split_mat_floats(c->hidden[L - 1], aw));
-    size_t vec = up((size_t)c->hidden[L - 1] + 31);       // output weights of a scalar critic, padded
-    if (distributional(c)) {
-        q += up(split_mat_floats(c->hidden[L - 1], c->num_atoms));
-        qT += up(split_mat_floats(c->num_atoms, c->hidden[L - 1]));
-        vec = 0;
+    size_t vec = 0, w1aT = 0;
+    if (all) {
+        pi += mat(c->hidden[L - 1], aw);
+        w1aT = mat(c->hidden[0], a);
+        if (distributional(c)) {
+            q += mat(c->hidden[L - 1], c->num_atoms);
+            qT += mat(c->num_atoms, c->hidden[L - 1]);
+        } else {
+            vec = up((size_t)c->hidden[L - 1] + 31);       // output weights of a scalar critic, padded
+        }
     }
-    const size_t critic = pi + 4 * q + 2 * qT + 4 * vec;
-    const size_t policy = pi + waT + 2 * (q + qT + up(split_mat_floats(c->hidden[0], a)) + vec);
-    return critic > policy ? critic : policy;
+    const size_t critic = pi + 4 * q + 2 * qT + 4 * vec, policy = pi + waT + 2 * (q + qT + w1aT + vec);
+    const size_t need = critic > policy ? critic : policy;
+    return need < ((size_t)1 << 30) ? need : 0;
 }
 
 inline long dw_tiles(int M, int N) { return (long)((M + 63) / 64) * ((N + 63) / 64); }
@@ -379,17 +387,19 @@ void make_layout(const pql_config* c, Layout& w, bool with_split = true) {
             w.colQ[i][l] = take(crow * h);
         }
     }
-    // the target critics' activations (layer-by-layer path) and the prepared weights (row-tile kernels on fp16 pairs) are
-    // never needed by the same call: they share their place
+    // Prepared weights.  Where every call takes the fused kernels they share their place with the target critics'
+    // activations, which only the layer-by-layer path has.
     {
         const size_t at = off;
         for (int l = 1; l <= L; ++l)
             for (int i = 0; i < 2; ++i) w.hT[i][l] = take(B * (size_t)c->hidden[l - 1]);
+        const size_t need = with_split ? prepared_floats(c) : 0;
         w.split = 0;
-        if (with_split && split_ok(c)) {
+        if (need > 0 && fused_ok(c)) {
             w.split = at;
-            const size_t need = split_floats(c);
             if (off - at < need) off = at + up(need);
+        } else if (need > 0) {
+            w.split = take(need);
         }
     }
     w.colA[L + 1] = take(crow * (size_t)actor_out(c));
@@ -817,7 +827,7 @@ int32_t pql_gather_nstep(pql_ctx* c, pql_replay_storage st, const int64_t* idx, 
 // ---------------------------------------------------------------------------------------------
 // Forward passes of the policy (hidden layers), shared by act / critic update / policy update.
 static hipError_t actor_hidden_forward(pql_ctx* c, const float* params, const float* obs, int B, float* ws,
-                                       const Layout& w, hipStream_t st) {
+                                       const Layout& w, const float* const* frag, hipStream_t st) {
     const int L = c->L;
     for (int l = 1; l <= L; ++l) {
         std::vector<GemmProb> ps;
@@ -826,6 +836,7 @@ static hipError_t actor_hidden_forward(pql_ctx* c, const float* params, const fl
         if (l == 1) add_seg(p, obs, c->cfg.obs_dim, params + c->a_w[0], H, c->cfg.obs_dim);
         else add_seg(p, ws + w.hA[l - 1], c->cfg.hidden[l - 2], params + c->a_w[l - 1], H, c->cfg.hidden[l - 2]);
         p.bias = params + c->a_b[l - 1];
+        p.frag = frag[l - 1];
         ps.push_back(p);
         const hipError_t e = run_auto(GEMM_NN, ps, st);
         if (e != hipSuccess) return e;
@@ -866,7 +877,7 @@ static hipError_t stochastic_policy_sample(pql_ctx* c, const float* params, int 
 
 // One hidden layer of a critic as a forward problem.
 static GemmProb critic_layer(pql_ctx* c, const float* params, int l, const float* s, const float* a, int lda_a,
-                             const float* h_prev, float* h_out, int B) {
+                             const float* h_prev, float* h_out, int B, const float* const* frag) {
     const int H = c->cfg.hidden[l - 1];
     GemmProb p = prob(B, H, h_out, H, EPI_BIAS_ELU);
     if (l == 1) {
@@ -877,6 +888,7 @@ static GemmProb critic_layer(pql_ctx* c, const float* params, int l, const float
         add_seg(p, h_prev, c->cfg.hidden[l - 2], params + c->c_w[l - 1], H, c->cfg.hidden[l - 2]);
     }
     p.bias = params + c->c_b[l - 1];
+    p.frag = frag[l - 1];
     return p;
 }
 
@@ -905,6 +917,26 @@ static void add_critic_back(const pql_ctx* c, SplitPrep& prep, int from, int64_t
         out[l] = prep.add(from, base + c->c_w[l], SPLIT_NO_BIAS, c->cfg.hidden[l], c->cfg.hidden[l - 1], SPLIT_TRANSPOSED);
     if (distributional(&c->cfg))
         out[c->L] = prep.add(from, base + c->c_w[c->L], SPLIT_NO_BIAS, c->cfg.num_atoms, c->cfg.hidden[c->L - 1], SPLIT_TRANSPOSED);
+}
+// The same for a launch per layer: the hidden layers that layer_rowtile_kernel takes (NULL for the others).  Launches of up to
+// three networks share their row tiles, so nothing is prepared for batches below a third of the 256 tiles it asks for.
+struct LayerFrags { const float* l[PQL_MAX_HIDDEN + 1]; };
+static bool layers_prepared(const Layout& w, int rows, int networks) {
+    return w.split != 0 && (int64_t)networks * ((rows + FUSED_BM - 1) / FUSED_BM) >= LAYERED_MIN_TILES;
+}
+static void add_layers(const pql_ctx* c, SplitPrep& prep, int from, int64_t base, bool policy, LayerFrags& out) {
+    for (int l = 0; l < c->L; ++l) {
+        const int K = l > 0 ? c->cfg.hidden[l - 1] : c->cfg.obs_dim + (policy ? 0 : c->cfg.act_dim), N = c->cfg.hidden[l];
+        const int64_t w = policy ? c->a_w[l] : c->c_w[l], b = policy ? c->a_b[l] : c->c_b[l];
+        if (layer_prepared(K, N)) out.l[l] = prep.add(from, base + w, base + b, K, N, SPLIT_PLAIN);
+    }
+}
+// Transposes of layers 1..L-1 (the policy's also of its output layer L).
+static void add_layers_back(const pql_ctx* c, SplitPrep& prep, int from, int64_t base, bool policy, LayerFrags& out) {
+    for (int l = 1; l < c->L + (policy ? 1 : 0); ++l) {
+        const int K = l < c->L ? c->cfg.hidden[l] : actor_out(&c->cfg), N = c->cfg.hidden[l - 1];
+        if (layer_prepared(K, N)) out.l[l] = prep.add(from, base + (policy ? c->a_w[l] : c->c_w[l]), SPLIT_NO_BIAS, K, N, SPLIT_TRANSPOSED);
+    }
 }
 // The output weights of a scalar critic, padded with zeros to whole tiles.
 static const float* add_output(const pql_ctx* c, SplitPrep& prep, int from, int64_t base) {
@@ -977,7 +1009,14 @@ int32_t pql_actor_act(pql_ctx* c, const float* actor_params, const float* obs, i
         if (e != hipSuccess) return E.hip(e, "pql_actor_act");
         obs = ws + w.xn;
     }
-    e = actor_hidden_forward(c, actor_params, obs, num, ws, w, st);
+    LayerFrags fp = {};
+    if (layers_prepared(w, num, 1)) {
+        SplitPrep prep(ws + w.split);
+        prep.args.src[0] = actor_params;
+        add_layers(c, prep, 0, 0, true, fp);
+        if ((e = split_weights_launch(prep.args, KID_SPLIT_WEIGHTS, st)) != hipSuccess) return E.hip(e, "pql_actor_act");
+    }
+    e = actor_hidden_forward(c, actor_params, obs, num, ws, w, fp.l, st);
     if (e != hipSuccess) return E.hip(e, "pql_actor_act");
     if (c->cfg.stochastic_policy) {     // exploration is the policy's own randomness; the sigma schedule does not apply
         e = stochastic_policy_sample(c, actor_params, num, ws, w, act_out, nullptr, nullptr, 2u, c->acts, st);
@@ -1035,14 +1074,11 @@ static int32_t critic_update_run(pql_ctx* c, float* critic_params, const float* 
     std::memset(&adm, 0, sizeof(adm));
     int head_parts = 0;
     const bool dist = distributional(&c->cfg);
-    // Transposed weights: from the caller's cache when it holds those of this parameter vector (then the
-    // optimiser kernel refreshes them at the end of the call), else transposed into the workspace here.
+    // A cache that holds the transposed weights of this parameter vector is kept up by the optimiser kernel at the end.
     const int fam = w.split != 0 ? family(&c->cfg, B) : FAM_LAYERED;
     const bool cached = c->wcache != nullptr && c->wcache_critic == critic_params;
     CacheLayout cl;
     make_cache_layout(&c->cfg, cl);
-    auto WT = [&](int i, int l) { return cached ? c->wcache + cl.wT[i][l] : ws + w.wT[i][l]; };
-    auto WOT = [&](int i) { return cached ? c->wcache + cl.woT[i] : ws + w.woT[i]; };
     if (fam != FAM_LAYERED) {
         // The weights into fragment order, then one launch per row tile: target path, forward, heads, backward data path.
         SplitCriticArgs sa;
@@ -1078,6 +1114,18 @@ static int32_t critic_update_run(pql_ctx* c, float* critic_params, const float* 
                 red(adm, i * Pc + c->c_b[l - 1], ws + w.colQ[i][l], c->cfg.hidden[l - 1], head_parts, c->cfg.hidden[l - 1]);
         for (int i = 0; i < 2 && dist; ++i) red(adm, i * Pc + c->c_b[L - 1], ws + w.colQ[i][L], HL, head_parts, HL);
     } else {
+        LayerFrags fp = {}, ft[2] = {}, fq[2] = {}, fb[2] = {};
+        if (layers_prepared(w, B, 3)) {
+            SplitPrep prep(ws + w.split);
+            prep.args.src[0] = actor_target_params; prep.args.src[1] = critic_target_params; prep.args.src[2] = critic_params;
+            add_layers(c, prep, 0, 0, true, fp);
+            for (int i = 0; i < 2; ++i) {
+                add_layers(c, prep, 1, i * Pc, false, ft[i]);
+                add_layers(c, prep, 2, i * Pc, false, fq[i]);
+                add_layers_back(c, prep, 2, i * Pc, false, fb[i]);
+            }
+            if ((e = split_weights_launch(prep.args, KID_SPLIT_WEIGHTS, st)) != hipSuccess) return E.hip(e, who);
+        }
         // 1. lagged policy pi^v on s' (hidden layers) together with the online critics on (s, a)
         for (int l = 1; l <= L; ++l) {
             std::vector<GemmProb> ps;
@@ -1086,10 +1134,11 @@ static int32_t critic_update_run(pql_ctx* c, float* critic_params, const float* 
             if (l == 1) add_seg(p, batch.next_obs, o, actor_target_params + c->a_w[0], H, o);
             else add_seg(p, ws + w.hA[l - 1], c->cfg.hidden[l - 2], actor_target_params + c->a_w[l - 1], H, c->cfg.hidden[l - 2]);
             p.bias = actor_target_params + c->a_b[l - 1];
+            p.frag = fp.l[l - 1];
             ps.push_back(p);
             for (int i = 0; i < 2; ++i)
                 ps.push_back(critic_layer(c, critic_params + i * Pc, l, batch.obs, batch.act, ad,
-                                          l > 1 ? ws + w.hQ[i][l - 1] : nullptr, ws + w.hQ[i][l], B));
+                                          l > 1 ? ws + w.hQ[i][l - 1] : nullptr, ws + w.hQ[i][l], B, fq[i].l));
             if ((e = run_auto(GEMM_NN, ps, st)) != hipSuccess) return E.hip(e, who);
         }
         // 2. a' = tanh(output layer of pi^v), or a sample a' ~ pi^v(.|s') with its log-density
@@ -1110,7 +1159,7 @@ static int32_t critic_update_run(pql_ctx* c, float* critic_params, const float* 
             std::vector<GemmProb> ps;
             for (int i = 0; i < 2; ++i)
                 ps.push_back(critic_layer(c, critic_target_params + i * Pc, l, batch.next_obs, ws + w.aOut, ad,
-                                          l > 1 ? ws + w.hT[i][l - 1] : nullptr, ws + w.hT[i][l], B));
+                                          l > 1 ? ws + w.hT[i][l - 1] : nullptr, ws + w.hT[i][l], B, ft[i].l));
             if ((e = run_auto(GEMM_NN, ps, st)) != hipSuccess) return E.hip(e, who);
         }
         if (dist) {
@@ -1166,9 +1215,7 @@ static int32_t critic_update_run(pql_ctx* c, float* critic_params, const float* 
         }
 
         // 5. backward data path: delta_{l-1} = (delta_l W_l^T) * ELU'(z_{l-1}), bias grads as column sums
-        // Wide layers run on row tiles with W^T as a row-major B operand (transposed once per call);
-        // the others take the LDS-tiled kernel on W itself.
-        bool transposed = cached;
+        // Wide layers run on row tiles with W^T in fragment order; the others take the LDS-tiled kernel on W itself.
         for (int l = L; l >= 2; --l) {
             std::vector<GemmProb> ps, pt;
             const int Hl = c->cfg.hidden[l - 1], Hp = c->cfg.hidden[l - 2];
@@ -1178,23 +1225,12 @@ static int32_t critic_update_run(pql_ctx* c, float* critic_params, const float* 
                 p.colsum = ws + w.colQ[i][l - 1];
                 GemmProb q = p;
                 add_seg(p, ws + w.dQ[i][l], Hl, critic_params + i * Pc + c->c_w[l - 1], Hl, Hl);
-                add_seg(q, ws + w.dQ[i][l], Hl, WT(i, l - 1), Hp, Hl);
+                add_seg(q, ws + w.dQ[i][l], Hl, nullptr, Hp, Hl);
+                q.frag = fb[i].l[l - 1];
                 ps.push_back(p); pt.push_back(q);
             }
             int parts;
             if (takes_row_tiles(pt)) {
-                if (!transposed) {
-                    TransposeArgs tr;
-                    tr.n = 0;
-                    for (int i = 0; i < 2; ++i)
-                        for (int k = 1; k < L; ++k) {
-                            TransposeArgs::Mat& mt = tr.m[tr.n++];
-                            mt.src = critic_params + i * Pc + c->c_w[k]; mt.dst = ws + w.wT[i][k];
-                            mt.rows = c->cfg.hidden[k - 1]; mt.cols = c->cfg.hidden[k];
-                        }
-                    if ((e = transpose_launch(tr, st)) != hipSuccess) return E.hip(e, who);
-                    transposed = true;
-                }
                 if ((e = run(GEMM_NN, TILE_64x64, pt, nullptr, st)) != hipSuccess) return E.hip(e, who);
                 parts = (B + FUSED_BM - 1) / FUSED_BM;
             } else {
@@ -1341,16 +1377,14 @@ int32_t pql_actor_update(pql_ctx* c, float* actor_params, const float* critic_pa
     const int aw = actor_out(&c->cfg);                          // width of the policy's output layer
     const float* d_top = sac ? ws + w.dOut : ws + w.dPre;       // gradient at that layer
     int logp_parts = (B + SAC_ROWS - 1) / SAC_ROWS;             // partial sums of log pi (stochastic policy)
-    // Transposed weights from the caller's cache where it holds those of these parameter vectors
+    // Transposed action rows of the critics' first layer from the caller's cache where it holds those of this vector (what
+    // else the cache holds of the vectors is kept up by the optimiser kernel)
     const int fam = w.split != 0 ? family(&c->cfg, B) : FAM_LAYERED;
     const bool cached_q = c->wcache != nullptr && c->wcache_critic == critic_params;
     const bool cached_a = c->wcache != nullptr && c->wcache_actor == actor_params;
     CacheLayout cl;
     make_cache_layout(&c->cfg, cl);
-    auto WT = [&](int i, int l) { return cached_q ? c->wcache + cl.wT[i][l] : ws + w.wT[i][l]; };
     auto W1AT = [&](int i) { return cached_q ? c->wcache + cl.w1aT[i] : ws + w.w1aT[i]; };
-    auto WOT = [&](int i) { return cached_q ? c->wcache + cl.woT[i] : ws + w.woT[i]; };
-    auto WAT = [&](int l) { return cached_a ? c->wcache + cl.waT[l] : ws + w.waT[l]; };
     if (fam != FAM_LAYERED) {
         SplitPolicyArgs sa;
         std::memset(&sa, 0, sizeof(sa));
@@ -1387,8 +1421,20 @@ int32_t pql_actor_update(pql_ctx* c, float* actor_params, const float* critic_pa
         red(adm, c->a_b[L], ws + w.colA[L + 1], aw, loss_parts, aw);
         for (int l = 1; l <= L; ++l) red(adm, c->a_b[l - 1], ws + w.colA[l], c->cfg.hidden[l - 1], loss_parts, c->cfg.hidden[l - 1]);
     } else {
+        LayerFrags fp = {}, fpb = {}, fq[2] = {}, fb[2] = {};
+        if (layers_prepared(w, B, 2)) {
+            SplitPrep prep(ws + w.split);
+            prep.args.src[0] = actor_params; prep.args.src[1] = critic_params;
+            add_layers(c, prep, 0, 0, true, fp);
+            add_layers_back(c, prep, 0, 0, true, fpb);
+            for (int i = 0; i < 2; ++i) {
+                add_layers(c, prep, 1, i * Pc, false, fq[i]);
+                add_layers_back(c, prep, 1, i * Pc, false, fb[i]);
+            }
+            if ((e = split_weights_launch(prep.args, KID_SPLIT_WEIGHTS, st)) != hipSuccess) return E.hip(e, who);
+        }
         // 1. a = pi(s), or the reparameterised sample a = tanh(mu + sigma eps)
-        if ((e = actor_hidden_forward(c, actor_params, obs, B, ws, w, st)) != hipSuccess) return E.hip(e, who);
+        if ((e = actor_hidden_forward(c, actor_params, obs, B, ws, w, fp.l, st)) != hipSuccess) return E.hip(e, who);
         if (sac) {
             if ((e = stochastic_policy_sample(c, actor_params, B, ws, w, ws + w.aOut, ws + w.logp, ws + w.epsb, 5u,
                                               c->actor_t, st)) != hipSuccess)
@@ -1406,7 +1452,7 @@ int32_t pql_actor_update(pql_ctx* c, float* actor_params, const float* critic_pa
             std::vector<GemmProb> ps;
             for (int i = 0; i < 2; ++i)
                 ps.push_back(critic_layer(c, critic_params + i * Pc, l, obs, ws + w.aOut, ad,
-                                          l > 1 ? ws + w.hQ[i][l - 1] : nullptr, ws + w.hQ[i][l], B));
+                                          l > 1 ? ws + w.hQ[i][l - 1] : nullptr, ws + w.hQ[i][l], B, fq[i].l));
             if ((e = run_auto(GEMM_NN, ps, st)) != hipSuccess) return E.hip(e, who);
         }
         if (distributional(&c->cfg)) {
@@ -1448,9 +1494,8 @@ int32_t pql_actor_update(pql_ctx* c, float* actor_params, const float* critic_pa
             if ((e = policy_head_launch(h, st)) != hipSuccess) return E.hip(e, who);
             loss_parts = h.nwg;
         }
-        // 4. critic backward data path down to layer 1 (wide layers on row tiles with W^T as a
-        //    row-major B operand, transposed once per call; the others on the LDS-tiled kernel)
-        bool transposed_q = cached_q;
+        // 4. critic backward data path down to layer 1 (wide layers on row tiles with W^T in fragment order; the others on
+        //    the LDS-tiled kernel)
         for (int l = L; l >= 2; --l) {
             std::vector<GemmProb> ps, pt;
             const int Hl = c->cfg.hidden[l - 1], Hp = c->cfg.hidden[l - 2];
@@ -1459,26 +1504,13 @@ int32_t pql_actor_update(pql_ctx* c, float* actor_params, const float* critic_pa
                 p.aux = ws + w.hQ[i][l - 1]; p.ldaux = Hp;
                 GemmProb q = p;
                 add_seg(p, ws + w.dQ[i][l], Hl, critic_params + i * Pc + c->c_w[l - 1], Hl, Hl);
-                add_seg(q, ws + w.dQ[i][l], Hl, WT(i, l - 1), Hp, Hl);
+                add_seg(q, ws + w.dQ[i][l], Hl, nullptr, Hp, Hl);
+                q.frag = fb[i].l[l - 1];
                 ps.push_back(p); pt.push_back(q);
             }
-            if (takes_row_tiles(pt)) {
-                if (!transposed_q) {
-                    TransposeArgs tr;
-                    tr.n = 0;
-                    for (int i = 0; i < 2; ++i)
-                        for (int k = 1; k < L; ++k) {
-                            TransposeArgs::Mat& mt = tr.m[tr.n++];
-                            mt.src = critic_params + i * Pc + c->c_w[k]; mt.dst = ws + w.wT[i][k];
-                            mt.rows = c->cfg.hidden[k - 1]; mt.cols = c->cfg.hidden[k];
-                        }
-                    if ((e = transpose_launch(tr, st)) != hipSuccess) return E.hip(e, who);
-                    transposed_q = true;
-                }
-                if ((e = run(GEMM_NN, TILE_64x64, pt, nullptr, st)) != hipSuccess) return E.hip(e, who);
-            } else {
-                if ((e = run_auto(GEMM_NT, ps, st)) != hipSuccess) return E.hip(e, who);
-            }
+            if (takes_row_tiles(pt)) e = run(GEMM_NN, TILE_64x64, pt, nullptr, st);
+            else e = run_auto(GEMM_NT, ps, st);
+            if (e != hipSuccess) return E.hip(e, who);
         }
         // 5. gradient w.r.t. the action input of both critics, through tanh'
         {
@@ -1519,7 +1551,6 @@ int32_t pql_actor_update(pql_ctx* c, float* actor_params, const float* critic_pa
             red(adm, c->a_b[L], ws + w.p_sc, aw, (B + SAC_ROWS - 1) / SAC_ROWS, aw);
         }
         // 6. policy backward data path
-        bool transposed_a = cached_a;
         for (int l = L + 1; l >= 2; --l) {
             std::vector<GemmProb> ps, pt;
             const int Hl = (l == L + 1) ? aw : c->cfg.hidden[l - 1], Hp = c->cfg.hidden[l - 2];
@@ -1528,21 +1559,11 @@ int32_t pql_actor_update(pql_ctx* c, float* actor_params, const float* critic_pa
             p.colsum = ws + w.colA[l - 1];
             GemmProb q = p;
             add_seg(p, (l == L + 1) ? d_top : ws + w.dA[l], Hl, actor_params + c->a_w[l - 1], Hl, Hl);
-            add_seg(q, (l == L + 1) ? d_top : ws + w.dA[l], Hl, WAT(l - 1), Hp, Hl);
+            add_seg(q, (l == L + 1) ? d_top : ws + w.dA[l], Hl, nullptr, Hp, Hl);
+            q.frag = fpb.l[l - 1];
             ps.push_back(p); pt.push_back(q);
             int parts;
             if (takes_row_tiles(pt)) {
-                if (!transposed_a) {
-                    TransposeArgs tr;
-                    tr.n = 0;
-                    for (int k = 1; k <= L; ++k) {
-                        TransposeArgs::Mat& mt = tr.m[tr.n++];
-                        mt.src = actor_params + c->a_w[k]; mt.dst = ws + w.waT[k];
-                        mt.rows = c->cfg.hidden[k - 1]; mt.cols = k < L ? c->cfg.hidden[k] : aw;
-                    }
-                    if ((e = transpose_launch(tr, st)) != hipSuccess) return E.hip(e, who);
-                    transposed_a = true;
-                }
                 if ((e = run(GEMM_NN, TILE_64x64, pt, nullptr, st)) != hipSuccess) return E.hip(e, who);
                 parts = (B + FUSED_BM - 1) / FUSED_BM;
             } else {

@@ -98,6 +98,7 @@ struct GemmProb {
     int ldc;
     float* C;
     const float* bias;
+    const float* frag;      // the B matrix of all segments in fragment order (layer_rowtile_kernel), or NULL
     const float* aux;
     float* colsum;          // optional per-wave-row column sums of C: [tiles_m * waves_m][N]
     int ldaux;
@@ -327,7 +328,8 @@ bool act16_ok(const FusedActArgs& a);
 hipError_t fused_act16_launch(const FusedActArgs& a, hipStream_t stream);
 
 // ---- row-tile kernels on fp16 pairs (pql_split.hip) -----------------------------------------
-constexpr int SPLIT_MAXW = 1024;             // widest layer and input
+constexpr int SPLIT_MAXW = 1024;             // widest layer and input of the one-launch kernels
+constexpr int SPLIT_MAXK = 1280;             // longest contraction of a prepared matrix
 constexpr size_t SPLIT_LDS = 160 * 1024;
 enum SplitKind : int { SPLIT_PLAIN = 0, SPLIT_TRANSPOSED = 1, SPLIT_VECTOR = 2 };
 // Matrices (K x N) to bring into fragment order: element (k, n) is src[k * N + n], or src[n * K + k] (transposed); a vector
@@ -424,7 +426,7 @@ struct TransposeArgs {
 };
 hipError_t transpose_launch(TransposeArgs& a, hipStream_t stream);
 
-// Forward layers too wide for the chained kernels, on row tiles (pql_fused.hip).
+// One layer of a list of networks on row tiles (pql_split.hip); every problem needs its matrix in fragment order.
 bool layer_rowtile_ok(const GemmGroup& g);
 hipError_t layer_rowtile_launch(GemmGroup& g, hipStream_t stream);
 // Action-wide products (at most 32 columns) of the layered path on row tiles.

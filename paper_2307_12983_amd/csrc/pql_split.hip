@@ -35,7 +35,7 @@ enum Variant : int { VAR_PLAIN = 0, VAR_SAC = 1, VAR_DIST = 2 };
 constexpr int SW = 8;                // wavefronts per workgroup
 constexpr int ST = 64 * SW;          // threads per workgroup
 constexpr int PT = 1024;             // threads per workgroup of the preparation
-constexpr int PREP_ITEMS = SPLIT_MAXW / 256;   // pieces of eight values per thread
+constexpr int PREP_ITEMS = SPLIT_MAXK / 256;   // pieces of eight values per thread
 constexpr int CS = 33;               // 16-byte units per k-chunk of a tile: 32 rows and one of padding against bank conflicts
 
 // ---- layouts ----------------------------------------------------------------------------------------
@@ -178,7 +178,7 @@ hipError_t split_weights_launch(SplitPrepArgs& a, int kid, hipStream_t stream) {
     for (int i = 0; i < 64; ++i) {
         a.first[i] = i < a.n ? blocks : 0x7fffffff;
         if (i >= a.n) continue;
-        if (a.m[i].kind != SPLIT_VECTOR && a.m[i].K > SPLIT_MAXW) return hipErrorInvalidValue;
+        if (a.m[i].kind != SPLIT_VECTOR && a.m[i].K > SPLIT_MAXK) return hipErrorInvalidValue;
         blocks += a.m[i].kind == SPLIT_VECTOR ? 1 : (a.m[i].N + 31) / 32;
         bytes += 8.0 * a.m[i].K * a.m[i].N;
     }
@@ -1332,6 +1332,187 @@ __device__ __forceinline__ void act_step(const SplitActArgs& A) {
             A.act_out[(size_t)env * a + col] = fminf(fmaxf(x, -1.f), 1.f);
         }
     }
+}
+
+// =============================================================================================
+// One wide layer for a list of networks (networks too wide or batches too large for the one-launch kernels; the twin
+// critics, the target critics and the policy share launches): Y = ELU(X W + b), X W + b, or (D W^T) * ELU'(.) with column
+// sums.  A workgroup brings 16 NB input rows into LDS as pairs, each row with its own scale, and its eight wavefronts sweep
+// the output columns, 32 each per pass, the weights streaming from L2 in fragment order.  64 rows where they fit (inputs up
+// to 512 wide) read the weights half as often: at 32 rows they take twice the time of the matrix work, at 64 about as long.
+// =============================================================================================
+constexpr int LAYER_PIECES = 4;      // 16-byte pieces a lane brings in per row at once (1024 columns per half wavefront)
+template <int NB>
+__device__ __forceinline__ void layer_rows(const GemmProb& P, int K, int ks, int r0, int plane, float* inv_rows, const Wv& T) {
+    const int K0 = P.seg[0].K, K1 = K - K0, c0 = T.lane & 31, chunks = 4 * ks;
+    const int rows = P.M - r0 < 16 * NB ? P.M - r0 : 16 * NB;
+    const __amdgpu_buffer_rsrc_t s0 = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(P.seg[0].A) + (size_t)r0 * (size_t)K0, 0,
+                                                                        rows * K0 * (int)sizeof(float), 0x00020000);
+    const __amdgpu_buffer_rsrc_t s1 = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(P.seg[K1 > 0 ? 1 : 0].A) + (size_t)r0 * (size_t)(K1 > 0 ? K1 : K0), 0,
+                                                                        K1 > 0 ? rows * K1 * (int)sizeof(float) : 0, 0x00020000);
+    const bool vec = K1 == 0 && (K0 & 3) == 0 && (reinterpret_cast<uintptr_t>(P.seg[0].A) & 15) == 0;
+    auto piece = [&](int row, int chunk, f32x4 (&v)[2]) {      // chunk 4 step + q: columns k_slot(step, q, 0..7)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int k = k_slot(chunk >> 2, chunk & 3, 4 * h);
+            if (vec) {
+                v[h] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(s0, k < K0 ? (row * K0 + k) * 4 : NOWHERE, 0, 0));
+            } else {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int c = k + i - K0;
+                    const float x = buf_load(s0, (unsigned)(c < 0 ? (row * K0 + k + i) * 4 : NOWHERE), 0);
+                    const float y = K1 > 0 ? buf_load(s1, (unsigned)(c >= 0 && c < K1 ? (row * K1 + c) * 4 : NOWHERE), 0) : 0.f;
+                    v[h][i] = c < 0 ? x : y;
+                }
+            }
+        }
+    };
+    for (int i = 0; i < NB; ++i) {                               // 2 SW = 16 rows at a time
+        const int row = 16 * i + 2 * T.wave + (T.lane >> 5);
+        f32x4 v[LAYER_PIECES][2];
+        float mx = 0.f;
+        for (int p0 = 0; p0 < chunks; p0 += 32 * LAYER_PIECES) {
+#pragma unroll
+            for (int p = 0; p < LAYER_PIECES; ++p)
+                if (p0 + 32 * p < chunks) piece(row, p0 + 32 * p + c0, v[p]);
+#pragma unroll
+            for (int p = 0; p < LAYER_PIECES; ++p)
+                if (p0 + 32 * p < chunks) {
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) mx = fmaxf(mx, fabsf(v[p][e >> 2][e & 3]));
+                }
+        }
+        float inv;
+        const float s = scale_for(half_max(mx), inv);
+        if (c0 == 0) inv_rows[row] = inv;
+        for (int p0 = 0; p0 < chunks; p0 += 32 * LAYER_PIECES) {
+            const bool again = chunks > 32 * LAYER_PIECES;       // rows of more than 1024 columns come twice
+#pragma unroll
+            for (int p = 0; p < LAYER_PIECES; ++p) {
+                const int chunk = p0 + 32 * p + c0;
+                if (p0 + 32 * p >= chunks) continue;
+                if (again) piece(row, chunk, v[p]);
+                if (chunk >= chunks) continue;
+                u32x4 hi, lo;
+                split16x8(v[p][0], v[p][1], s, hi, lo);
+                lds_units()[chunk * (16 * NB + 1) + row] = hi;
+                lds_units()[plane + chunk * (16 * NB + 1) + row] = lo;
+            }
+        }
+    }
+}
+
+template <int NB>
+__global__ __launch_bounds__(ST) void layer_rowtile_kernel(const GemmGroup) {
+    const GemmGroup& G = kernel_args<GemmGroup>();
+    const Wv T = wave_of();
+    const int b = blockIdx.x;
+    int pi = 0;
+    for (int i = 1; i < G.nprob; ++i)
+        if (b >= G.p[i].tile_begin) pi = i;
+    const GemmProb& P = G.p[pi];
+    const int K = P.seg[0].K + (P.nseg > 1 ? P.seg[1].K : 0), N = P.N, M = P.M;
+    const int r0 = (b - P.tile_begin) * 16 * NB;
+    const MatView W = mat_view(P.frag, K, N);
+    const Tile X = {0, W.ks * 4 * (16 * NB + 1)};
+    float* inv_rows = &smem[2 * X.plane * 4];
+    Ahead cur;
+    request(cur, begin_of(W, T.wave, 0, 1), T);
+    layer_rows<NB>(P, K, W.ks, r0, X.plane, inv_rows, T);
+    lds_barrier();
+    float inv[NB];
+#pragma unroll
+    for (int n = 0; n < NB; ++n) inv[n] = inv_rows[16 * n + T.l15];
+    const int epi = P.epi;
+    for (int tile = T.wave; tile < W.tiles; tile += SW) {
+        f32x4 acc[2][NB], hv[2][NB], bias[2];
+        const float iw = W.inv[tile];
+#pragma unroll
+        for (int m = 0; m < 2; ++m) bias[m] = *reinterpret_cast<const f32x4*>(W.bias + 32 * tile + 16 * m + 4 * T.q);
+        mac_steps<NB>(acc, W, tile, X, T, 0, 1, cur, begin_of(W, tile + SW, 0, 1));
+        if (epi == EPI_MUL_DELU) load_tile<NB>(P.aux, N, tile, hv, r0, M, T);
+#pragma unroll
+        for (int n = 0; n < NB; ++n) {
+            const float f = inv[n] * iw;
+#pragma unroll
+            for (int m = 0; m < 2; ++m)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    if (epi == EPI_MUL_DELU) {
+                        acc[m][n][r] = acc[m][n][r] * f * delu_h(hv[m][n][r]);
+                    } else {
+                        const float x = __fmaf_rn(acc[m][n][r], f, bias[m][r]);
+                        acc[m][n][r] = epi == EPI_BIAS_ELU ? elu_f(x) : x;
+                    }
+                }
+        }
+        store_tile<NB>(P.C, N, tile, acc, r0, M, T);
+        if (P.colsum != nullptr) {      // one partial row per 32 batch rows
+#pragma unroll
+            for (int h = 0; h < NB / 2; ++h)
+                if (r0 + 32 * h < M) {
+                    const f32x4 cs[2] = {acc[0][2 * h] + acc[0][2 * h + 1], acc[1][2 * h] + acc[1][2 * h + 1]};
+                    store_colsum(P.colsum + (size_t)(r0 / 32 + h) * (size_t)N, N, tile, cs, T);
+                }
+        }
+    }
+}
+
+// LDS of a layer's input tile of `rows` rows.
+static size_t layer_lds(const GemmProb& p, int rows) {
+    const int K = p.seg[0].K + (p.nseg > 1 ? p.seg[1].K : 0);
+    return 2 * (size_t)((K + 31) / 32 * 4) * (rows + 1) * 16 + rows * sizeof(float);
+}
+
+bool layer_rowtile_ok(const GemmGroup& g) {
+    long wgs = 0;
+    for (int i = 0; i < g.nprob; ++i) {
+        const GemmProb& p = g.p[i];
+        if (p.frag == nullptr) return false;
+        if (p.epi != EPI_BIAS_ELU && p.epi != EPI_BIAS && p.epi != EPI_MUL_DELU) return false;
+        if (p.epi == EPI_MUL_DELU ? (p.aux == nullptr || p.ldaux != p.N) : (p.bias == nullptr || p.colsum != nullptr)) return false;
+        if (p.nseg < 1 || p.nseg > 2 || p.ldc != p.N) return false;
+        if (p.N < 128 || p.M < 1) return false;
+        for (int s = 0; s < p.nseg; ++s)
+            if (p.seg[s].K < 1 || p.seg[s].lda != p.seg[s].K) return false;
+        if (layer_lds(p, 32) > SPLIT_LDS) return false;
+        wgs += (p.M + 31) / 32;
+    }
+    return wgs >= 256;
+}
+
+hipError_t layer_rowtile_launch(GemmGroup& g, hipStream_t stream) {
+    if (!layer_rowtile_ok(g)) return hipErrorInvalidValue;
+    long wgs64 = 0;
+    bool fits = true;
+    for (int i = 0; i < g.nprob; ++i) {
+        wgs64 += (g.p[i].M + 63) / 64;
+        if (layer_lds(g.p[i], 64) > SPLIT_LDS) fits = false;
+    }
+    const int rows = fits && wgs64 >= 256 ? 64 : 32;             // (a workgroup for every compute unit comes first)
+    int total = 0;
+    size_t lds = 0;
+    double flops = 0.0;
+    for (int i = 0; i < g.nprob; ++i) {
+        GemmProb& p = g.p[i];
+        p.tile_begin = total;
+        p.tiles_m = (p.M + rows - 1) / rows; p.tiles_n = 1; p.splits = 1; p.k_chunk = 0;
+        total += p.tiles_m;
+        for (int s = 0; s < p.nseg; ++s) flops += 2.0 * p.M * (double)p.N * p.seg[s].K;
+        const size_t bytes = layer_lds(p, rows);
+        if (bytes > lds) lds = bytes;
+    }
+    g.total_tiles = total;
+    static LdsLimit configured, configured64;
+    const hipError_t e = rows == 64 ? set_lds_limit(reinterpret_cast<const void*>(layer_rowtile_kernel<4>), lds, configured64)
+                                    : set_lds_limit(reinterpret_cast<const void*>(layer_rowtile_kernel<2>), lds, configured);
+    if (e != hipSuccess) return e;
+    const ProfSlot ps = prof_slot();
+    if (rows == 64) PQL_LAUNCH(ps, layer_rowtile_kernel<4>, dim3(total), dim3(ST), lds, stream, g);
+    else            PQL_LAUNCH(ps, layer_rowtile_kernel<2>, dim3(total), dim3(ST), lds, stream, g);
+    prof_commit(ps, KID_LAYER_ROWTILE, ps.on ? flops : 0.0, 0.0);
+    return hipGetLastError();
 }
 
 // ---- host side ------------------------------------------------------------------------------------------------

@@ -64,6 +64,36 @@ def test_gradients_at_the_edges(case):
     print(case, "critic grad", e, "actor grad", ea, flush=True)
 
 
+LAYERS = {          # what the layer kernel's tiles and loads depend on: 64 / 32 rows, rows of more than 1024 columns, segments
+    "tiles_of_64_and_32_rows": workload((640, 150), 30, 5, 8225),
+    "rows_brought_in_twice": workload((1156, 204, 130), 33, 4, 4161),
+    "wide_odd_input": workload((136, 128), 603, 17, 8193),
+    "matrix_on_the_tiled_kernel": workload((1312, 128), 20, 3, 8192),
+}
+
+
+@pytest.mark.parametrize("case", list(LAYERS))
+def test_layers_at_the_edges(case):
+    w = LAYERS[case]
+    print(case, w.hidden, "B", w.batch, flush=True)
+    s, ring = session(w), oracle_ring(w)
+    fill_both(s, ring, w, w.nstep + 3)
+    L = oracle_learner(w, s.actor_init, s.critic_init)
+    s.sample(w.batch)
+    batch = oracle_batch(ring, w, w.batch, 0, None)
+    s.ctx.pql_profile_begin(200)
+    s.critic_update(w.batch)
+    losses, g = L.critic_update(batch)
+    s.actor_update(None, w.batch)
+    names = {k["name"] for k in s.ctx.pql_profile_end()}
+    assert "layer_rowtile_kernel" in names and not {n for n in names if n.startswith(("split_critic", "split_policy"))}
+    _, ga = L.actor_update(batch["obs"])
+    assert rel_err(s.critic_loss.cpu().numpy(), losses) <= TOL
+    e = assert_params_close(s.c_g.cpu().numpy(), g, w.critic_dims(), 2, TOL, "critic grad")
+    ea = assert_params_close(s.a_g.cpu().numpy(), ga, w.actor_dims(), 1, TOL, "actor grad")
+    print(case, "critic grad", e, "actor grad", ea, flush=True)
+
+
 @pytest.mark.parametrize("hidden", [(256, 256), (512, 96), (40, 100)])
 def test_rows_and_weights_of_very_different_size(hidden):
     """Every row of a batch has its own scale, every 32 columns of a matrix theirs: states between 1e-2 and 1e6 in one batch,
