@@ -576,14 +576,12 @@ __device__ inline void tn_stream_tile(const GemmProb& P, int split, int m0, int 
     else                tn_sum_store<TM, 3>(acc, red, lane, l32, half, C, P.M, P.N, P.ldc, m0, n0);
 }
 
-__global__ __launch_bounds__(NTHREADS, 3) void gemm_tn_stream_kernel(const GemmGroup g) {
+__global__ __launch_bounds__(NTHREADS, 3) void gemm_tn_stream_kernel(const GemmGroup) {
+    const GemmGroup& g = kernel_args<GemmGroup>();
     __shared__ float red[3][4096];
     __shared__ float rows[4][64];
     const int bid = xcd_remap(blockIdx.x, gridDim.x);
-    int pi = 0;
-    for (int i = 1; i < g.nprob; ++i)
-        if (bid >= g.p[i].tile_begin) pi = i;
-    const GemmProb& P = g.p[pi];
+    const GemmProb& P = g.p[record_of(g.p, &GemmProb::tile_begin, g.nprob, bid)];
     int local = bid - P.tile_begin;
     const int per_split = P.tiles_m * P.tiles_n;
     const int split = local / per_split;

@@ -42,6 +42,22 @@ void prof_commit(const ProfSlot& s, int kid, double flops, double bytes);
             hipLaunchKernelGGL(kernel, grid, block, lds, stream, __VA_ARGS__);                               \
     } while (0)
 
+// The kernel's argument block, read in place.  As an ordinary by-value parameter it is copied to private memory as soon as
+// one of its arrays is indexed with a run-time layer number; through the segment pointer every access is a scalar load.
+template <typename ARGS>
+__device__ __forceinline__ const ARGS& kernel_args() {
+    return *(const ARGS*)__builtin_amdgcn_kernarg_segment_ptr();
+}
+
+// Which of n records (at most 64, their first workgroups in ascending order from 0) workgroup b belongs to.  One lane reads
+// one record: a loop over them is a chain of scalar loads, about 0.1 us each.
+template <typename REC>
+__device__ __forceinline__ int record_of(const REC* r, int REC::*first, int n, int b) {
+    const int lane = threadIdx.x & 63;
+    const int begin = lane < n ? r[lane].*first : 0x7fffffff;
+    return __builtin_amdgcn_readfirstlane(__popcll(__ballot(b >= begin)) - 1);
+}
+
 // Largest dynamic-LDS size granted so far to one kernel, per device (the attribute belongs to the device's
 // copy of the function).  The grant only grows, under a lock, so that launches of the same kernel from several
 // threads with different tile sizes never see it shrink between their request and their launch.

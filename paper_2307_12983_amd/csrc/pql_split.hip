@@ -96,13 +96,6 @@ __device__ __forceinline__ float half_max(float x) {          // over the 32 lan
     return fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
 }
 
-// The kernel's argument block, read in place.  As an ordinary by-value parameter it is copied to private memory as soon as
-// one of its arrays is indexed with a run-time layer number; through the segment pointer every access is a scalar load.
-template <typename ARGS>
-__device__ __forceinline__ const ARGS& kernel_args() {
-    return *(const ARGS*)__builtin_amdgcn_kernarg_segment_ptr();
-}
-
 // ---- weights into fragment order ------------------------------------------------------------------------
 // One workgroup per 32-column tile: every element is read once (all requests in flight together), kept in registers while
 // the tile's largest magnitude is found, and written as fragments.  Latency-bound: one round trip each way.
@@ -1408,10 +1401,7 @@ __global__ __launch_bounds__(ST) void layer_rowtile_kernel(const GemmGroup) {
     const GemmGroup& G = kernel_args<GemmGroup>();
     const Wv T = wave_of();
     const int b = blockIdx.x;
-    int pi = 0;
-    for (int i = 1; i < G.nprob; ++i)
-        if (b >= G.p[i].tile_begin) pi = i;
-    const GemmProb& P = G.p[pi];
+    const GemmProb& P = G.p[record_of(G.p, &GemmProb::tile_begin, G.nprob, b)];
     const int K = P.seg[0].K + (P.nseg > 1 ? P.seg[1].K : 0), N = P.N, M = P.M;
     const int r0 = (b - P.tile_begin) * 16 * NB;
     const MatView W = mat_view(P.frag, K, N);

@@ -176,3 +176,23 @@ def test_weight_gradients_of_columns_that_grow_and_differ(batch, hidden):
         err[4] = 0.0
         print(batch, hidden, "worst column", int(err.argmax()), "%.2e" % err.max(), flush=True)
         assert err.max() <= TOL
+
+
+@pytest.mark.parametrize("hidden", [(24,), (512, 512)])
+def test_clipped_step_inside_the_ball_is_the_plain_step(hidden):
+    """adam_clip_kernel with one workgroup per 256 parameters and with several elements per thread (above 2^18 parameters):
+    a bound that no gradient reaches changes nothing, and the norm is the gradient's."""
+    import torch
+    w = workload(hidden, 20, 4, 64)
+    got = []
+    for bound in (0.0, 1e6):
+        s = session(w.replace(max_grad_norm=bound))
+        fill_both(s, oracle_ring(w), w, w.nstep + 3)
+        s.sample(w.batch)
+        s.critic_update(w.batch)
+        got.append([x.cpu().numpy() for x in (s.critic, s.c_m, s.c_v, s.c_g)] + [float(s.critic_grad_norm.cpu()[0])])
+    for a, b in zip(got[0][:4], got[1][:4]):
+        assert np.abs(a - b).max() <= 2e-7 * np.abs(a).max()
+    norm = np.sqrt((got[1][3].astype(np.float64) ** 2).sum())
+    assert abs(got[1][4] - norm) <= 1e-6 * norm
+    print(hidden, "parameters", got[0][0].size, "norm", norm, flush=True)
