@@ -789,6 +789,7 @@ __device__ __forceinline__ Wv wave_of() {
 // =============================================================================================
 template <int NN, int TPW, int VAR>
 __device__ __forceinline__ void critic_step(const SplitCriticArgs& A) {
+    warm_args<SplitCriticArgs>();
     constexpr bool SAC = VAR == VAR_SAC, DIST = VAR == VAR_DIST;
     const Wv T = wave_of();
     const SplitShape& P = A.shape;
@@ -1036,6 +1037,7 @@ __device__ __forceinline__ void critic_step(const SplitCriticArgs& A) {
 // =============================================================================================
 template <int NN, int TPW, int VAR>
 __device__ __forceinline__ void policy_step(const SplitPolicyArgs& A) {
+    warm_args<SplitPolicyArgs>();
     constexpr bool SAC = VAR == VAR_SAC, DIST = VAR == VAR_DIST;
     const Wv T = wave_of();
     const SplitShape& P = A.shape;
@@ -1282,6 +1284,7 @@ __device__ __forceinline__ void policy_step(const SplitPolicyArgs& A) {
 // =============================================================================================
 template <int TPW, int VAR>
 __device__ __forceinline__ void act_step(const SplitActArgs& A) {
+    warm_args<SplitActArgs>();
     constexpr bool SAC = VAR == VAR_SAC;
     const Wv T = wave_of();
     const SplitShape& P = A.shape;
