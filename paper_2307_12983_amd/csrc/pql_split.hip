@@ -1364,7 +1364,42 @@ __device__ __forceinline__ void layer_rows(const GemmProb& P, int K, int ks, int
             }
         }
     };
-    for (int i = 0; i < NB; ++i) {                               // 2 SW = 16 rows at a time
+    // 2 SW = 16 rows at a time; rows of up to RP pieces per lane: all NB rows' requests go out together (one row after the
+    // other, a workgroup waited NB times before its first product)
+    constexpr int RP = 4 * LAYER_PIECES / (2 * NB);              // NB = 4: 512 columns, NB = 2: 1024
+    if (chunks <= 32 * RP) {
+        f32x4 v[NB][RP][2];
+#pragma unroll
+        for (int i = 0; i < NB; ++i)
+#pragma unroll
+            for (int p = 0; p < RP; ++p)
+                if (32 * p < chunks) piece(16 * i + 2 * T.wave + (T.lane >> 5), 32 * p + c0, v[i][p]);
+#pragma unroll
+        for (int i = 0; i < NB; ++i) {
+            const int row = 16 * i + 2 * T.wave + (T.lane >> 5);
+            float mx = 0.f;
+#pragma unroll
+            for (int p = 0; p < RP; ++p)
+                if (32 * p < chunks) {
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) mx = fmaxf(mx, fabsf(v[i][p][e >> 2][e & 3]));
+                }
+            float inv;
+            const float s = scale_for(half_max(mx), inv);
+            if (c0 == 0) inv_rows[row] = inv;
+#pragma unroll
+            for (int p = 0; p < RP; ++p) {
+                const int chunk = 32 * p + c0;
+                if (chunk >= chunks) continue;
+                u32x4 hi, lo;
+                split16x8(v[i][p][0], v[i][p][1], s, hi, lo);
+                lds_units()[chunk * (16 * NB + 1) + row] = hi;
+                lds_units()[plane + chunk * (16 * NB + 1) + row] = lo;
+            }
+        }
+        return;
+    }
+    for (int i = 0; i < NB; ++i) {
         const int row = 16 * i + 2 * T.wave + (T.lane >> 5);
         f32x4 v[LAYER_PIECES][2];
         float mx = 0.f;
@@ -1423,8 +1458,9 @@ __global__ __launch_bounds__(ST) void layer_rowtile_kernel(const GemmGroup) {
         const float iw = W.inv[tile];
 #pragma unroll
         for (int m = 0; m < 2; ++m) bias[m] = *reinterpret_cast<const f32x4*>(W.bias + 32 * tile + 16 * m + 4 * T.q);
+        if (NB == 2 && epi == EPI_MUL_DELU) load_tile<NB>(P.aux, N, tile, hv, r0, M, T);      // (64 rows: too many registers)
         mac_steps<NB>(acc, W, tile, X, T, 0, 1, cur, begin_of(W, tile + SW, 0, 1));
-        if (epi == EPI_MUL_DELU) load_tile<NB>(P.aux, N, tile, hv, r0, M, T);
+        if (NB != 2 && epi == EPI_MUL_DELU) load_tile<NB>(P.aux, N, tile, hv, r0, M, T);
 #pragma unroll
         for (int n = 0; n < NB; ++n) {
             const float f = inv[n] * iw;
