@@ -336,9 +336,9 @@ int32_t pql_soft_update(pql_ctx* ctx, const float* src, float* dst, int64_t coun
 #define PQL_TRACK_LAGGED_POLICY  1
 int32_t pql_track_attach(pql_ctx* ctx, int32_t which, float* dst, float tau);
 
-/* The backward products delta * W^T read transposed copies of the online critics' and the policy's weight
- * matrices.  Without a cache every update transposes them into its workspace first (one small launch per
- * call).  With a caller-owned [device] block of pql_weight_cache_bytes(cfg) bytes, 256-byte aligned,
+/* Transposed copies of the online critics' and the policy's weight matrices.  Most products read weights that
+ * every call prepares for itself; the action gradient of the layer-by-layer path reads these copies, and without
+ * a cache such an update transposes them into its workspace first (one small launch per call).  With a caller-owned [device] block of pql_weight_cache_bytes(cfg) bytes, 256-byte aligned,
  * attached, the copies live there between calls: pql_weight_cache_refresh(ctx, critic_params, actor_params)
  * fills it from the given vectors (either may be NULL) and remembers their addresses; a later
  * pql_critic_update / pql_actor_update whose critic_params / actor_params argument is that same address

@@ -1,7 +1,7 @@
 // C interface of libpql: context, argument validation, workspace layout and the launch
-// sequences of the learner steps.  All device work is done by the kernels in pql_fused.hip and
-// pql_chain.hip (row-tile kernels: one launch per learner step), pql_act16.hip (Actor step on 16-row
-// tiles), pql_gemm.hip (LDS-tiled GEMMs, streaming weight gradients) and pql_kernels.hip (replay,
+// sequences of the learner steps.  All device work is done by the kernels in pql_split.hip (row-tile kernels on fp16 pairs:
+// one launch per learner step, or one per wide layer), pql_fused.hip (action-wide products), pql_act16.hip (Actor step on
+// 16-row tiles), pql_gemm.hip (LDS-tiled GEMMs, streaming weight gradients) and pql_kernels.hip (replay,
 // heads, optimiser, statistics); this file only decides which problems go into which launch.
 #include <cmath>
 #include <cstdio>
@@ -249,7 +249,7 @@ struct Layout {
     size_t colA[PQL_MAX_HIDDEN + 2];                                  // bias-grad partials of actor layer l (1..L+1)
     size_t aOut, dPre, y, q[2];
     size_t p_dw[2], p_dbh[2], p_db[2], p_loss;
-    size_t wT[2][PQL_MAX_HIDDEN + 1];                                 // transposed critic weights, layer l = 1..L-1
+    size_t wT[2][PQL_MAX_HIDDEN + 1];                                 // (no longer read: it and waT, woT keep the workspace the size it was)
     size_t w1aT[2];                                                   // transposed action rows of the critics' first layer
     size_t waT[PQL_MAX_HIDDEN + 1];                                   // transposed policy weights, layer l = 1..L
     size_t splitk;
@@ -270,11 +270,12 @@ int max_hidden(const pql_config* c) {
 // kernels, whatever the batch.  A widest layer of 512, scalar critics, deterministic policy, and a row tile for at least
 // half the compute units: the chain kernels.  Other shapes (any widths up to 1024) run in one launch per step as well,
 // between two bounds.  Below, the launch has too few workgroups: each streams all weights by itself (about 50 GB/s), where a
-// launch per layer spreads them over the chip.  Measured per critic update, one launch against a launch per layer:
-// 1024-512-256 at 64 / 520 / 2048 / 8000 rows 399 / 415 / 450 / 685 us against 276 / 309 / 466 / 1029; 512-512-512
-// 290 / 304 / 342 / 498 against 260 / 276 / 400 / 839; 300-136-128 118 / 123 / 130 / 187 against 147 / 154 / 174 / 260: the
-// line is at 2048 rows, and at no batch for critics of up to 2^18 weights.  Above (256 row tiles), every layer's launch has
-// enough work of its own, unless the variant has steps that only the one-launch kernels have on the 16-bit matrix cores.
+// launch per layer spreads them over the chip.  Measured per critic update, one launch against a launch per layer, at
+// 64 / 520 / 1024 / 2048 / 4096 / 8000 rows: 1024-512-256 335 / 341 / 341 / 351 / 380 / 493 us against 263 / 288 / 312 / 413 /
+// 358 / 616; 512-512-512 254 / 259 / 261 / 276 / 293 / 373 against 249 / 258 / 279 / 353 / 314 / 516; 300-136-128 93 / 99 /
+// 100 / 102 / 110 / 131 against 137 / 143 / 147 / 165 / 141 / 212: the line is at 2048 rows, and at no batch for critics of up
+// to 2^18 weights.  Above (256 row tiles), every layer's launch has enough work of its own, unless the variant has steps that
+// only the one-launch kernels have on the 16-bit matrix cores.
 constexpr int CHAIN_MIN_TILES = 128;
 constexpr int LAYERED_MIN_TILES = 256;
 constexpr int SPLIT_MIN_TILES = 64;

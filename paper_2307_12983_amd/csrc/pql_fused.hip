@@ -8,7 +8,7 @@ namespace pql {
 // Action-wide products of the layered path (at most 32 output columns): the policy's output layer
 // (with the Actor's exploration noise where asked for) and the gradient with respect to the action.  One wavefront's 32 columns already cover the
 // output, so the eight wavefronts of a row tile split the contraction instead (every eighth chunk
-// of 32 k-values each, as in the chained kernels' narrow layers) and their partial tiles meet in
+// of 32 k-values each, as in the one-launch kernels' narrow layers) and their partial tiles meet in
 // LDS.  Segments (the twin critics' first-layer deltas) pass through the same input tile one after
 // the other.  B operands are row-major [K][N].
 // =============================================================================================
