@@ -369,6 +369,11 @@ int gemm_waves_m(int tile) { return tile == TILE_128x32 ? 4 : 2; }
 // chunk with room for values 2^8 larger; a chunk that holds a larger one still rescales the sums (rare: the check is eight
 // comparisons).  Products: lo hi + hi lo + hi hi, v_mfma_f32_32x32x16_f16, fp32 sums; with three roundings per 16 rows where the
 // fp32 MFMAs of a 32x32x2 kernel make eight, the result is the closer one.
+//
+// us per launch on fp32 MFMAs / so: critics 60+8-256-256 at 8192 rows 34.5 / 23.2, 512-256-128 81 / 48.5, 1024-512-256 at
+// 32768 rows 973 / 622 (188 TFLOP/s).  Bound by the latency of its loads (one chunk ahead): the vector units are busy a third of
+// the time with the splitting, the matrix cores a quarter.  128 x 128 tiles shared through LDS (every value read and split once
+// per workgroup) took 622 - 679 and 28: twelve wavefronts that never wait for each other hide more than eight in step.
 // TM = 32-row tiles of the output per wavefront (1 for outputs of at most 32 rows).
 // =============================================================================================
 __device__ inline float tn_load(__amdgpu_buffer_rsrc_t r, int voff, int soff) {

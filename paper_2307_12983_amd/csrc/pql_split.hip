@@ -1336,7 +1336,9 @@ __device__ __forceinline__ void act_step(const SplitActArgs& A) {
 // critics, the target critics and the policy share launches): Y = ELU(X W + b), X W + b, or (D W^T) * ELU'(.) with column
 // sums.  A workgroup brings 16 NB input rows into LDS as pairs, each row with its own scale, and its eight wavefronts sweep
 // the output columns, 32 each per pass, the weights streaming from L2 in fragment order.  64 rows where they fit (inputs up
-// to 512 wide) read the weights half as often: at 32 rows they take twice the time of the matrix work, at 64 about as long.
+// to about 600 wide) read the weights half as often: at 32 rows they take twice the time of the matrix work, at 64 about as
+// long.  Eight launches of 1024-512-256 at 32768 rows: 427 us each on fp32 MFMAs, 220 so, 212 with the requests of all rows
+// together (222 TFLOP/s); one workgroup fits a compute unit, so what it reads first and writes last overlaps little.
 // =============================================================================================
 constexpr int LAYER_PIECES = 4;      // 16-byte pieces a lane brings in per row at once (1024 columns per half wavefront)
 template <int NB>
