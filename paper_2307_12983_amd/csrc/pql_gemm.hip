@@ -382,8 +382,10 @@ __device__ inline float tn_load(__amdgpu_buffer_rsrc_t r, int voff, int soff) {
 
 constexpr int TNS = 8;            // row pairs per chunk: one MFMA contracts the chunk's 16 rows
 
-// One column's scale: s and its inverse, and the largest magnitude that s still fits.
-struct ColumnScale { float s, inv, limit; };
+// One column's scale s = 2^e and the largest magnitude that it still fits.  The sums are brought from one scale to another, and
+// to none at the end, by adding exponents: a product of two columns' factors can leave fp32's range where the sum does not
+// (a column of values below 1e-32 beside one below 0.01: the factor is infinite, the sum still zero).
+struct ColumnScale { float s, limit; int e; };
 
 // Eight values of a column as pairs.
 __device__ __forceinline__ void tn_split(const float (&x)[TNS], float s, u32x4 (&t)[2]) {
@@ -400,15 +402,17 @@ __device__ __forceinline__ float tn_max(const float (&x)[TNS]) {
     return m;
 }
 // New scale of a column whose chunk exceeds the old one's limit (the halves of the wavefront hold the same column); returns
-// the factor by which the sums so far are to be multiplied.
-__device__ __forceinline__ float tn_rescale(ColumnScale& c, float m) {
+// the power of two by which the sums so far are to be multiplied.
+__device__ __forceinline__ int tn_rescale(ColumnScale& c, float m) {
     auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(m), __float_as_uint(m), false, false);
     m = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
-    if (!(m > c.limit)) return 1.f;
-    const float old = c.inv;
-    c.s = scale_for<7>(m, c.inv);
-    c.limit = 32768.f * c.inv;
-    return old * c.s;
+    if (!(m > c.limit)) return 0;
+    const int old = c.e;
+    float inv;
+    c.s = scale_for<7>(m, inv);
+    c.e = (int)(__float_as_uint(c.s) >> 23) - 127;
+    c.limit = 32768.f * inv;
+    return c.e - old;
 }
 __device__ __forceinline__ floatx16 mfma_f16(u32x4 a, u32x4 b, floatx16 c) {
     return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
@@ -446,7 +450,7 @@ __device__ inline void tn_sum_store(const floatx16 (&acc)[TM][2], float (*red)[4
 }
 
 template <int TM>
-__device__ inline void tn_stream_tile(const GemmProb& P, int split, int m0, int n0, float (*red)[4096], float (*rows)[64]) {
+__device__ inline void tn_stream_tile(const GemmProb& P, int split, int m0, int n0, float (*red)[4096], int (*rows)[64]) {
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l32 = lane & 31, half = lane >> 5;
@@ -479,11 +483,11 @@ __device__ inline void tn_stream_tile(const GemmProb& P, int split, int m0, int 
     float xa[TM][TNS], xb[2][TNS];
     ColumnScale ca[TM], cb[2];
 #pragma unroll
-    for (int i = 0; i < TM; ++i) ca[i] = ColumnScale{1.f, 1.f, 0.f};
+    for (int i = 0; i < TM; ++i) ca[i] = ColumnScale{1.f, 0.f, 0};
 #pragma unroll
-    for (int j = 0; j < 2; ++j) cb[j] = ColumnScale{1.f, 1.f, 0.f};
-    // factors of the output rows (columns of A) to all lanes that hold a part of them; only this wavefront's own LDS words
-    auto spread = [&](const float (&f)[TM], float (&out)[TM][16]) {
+    for (int j = 0; j < 2; ++j) cb[j] = ColumnScale{1.f, 0.f, 0};
+    // exponents of the output rows (columns of A) to all lanes that hold a part of them; only this wavefront's own LDS words
+    auto spread = [&](const int (&f)[TM], int (&out)[TM][16]) {
         __builtin_amdgcn_wave_barrier();
 #pragma unroll
         for (int i = 0; i < TM; ++i)
@@ -495,15 +499,15 @@ __device__ inline void tn_stream_tile(const GemmProb& P, int split, int m0, int 
             for (int r = 0; r < 16; ++r) out[i][r] = rows[wave][32 * i + 8 * (r >> 2) + 4 * half + (r & 3)];
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
     };
-    auto multiply = [&](const float (&fa)[TM], const float (&fb)[2]) {
-        float fr[TM][16];
+    auto multiply = [&](const int (&fa)[TM], const int (&fb)[2]) {
+        int fr[TM][16];
         spread(fa, fr);
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
             for (int j = 0; j < 2; ++j)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) acc[i][j][r] *= fr[i][r] * fb[j];
+                for (int r = 0; r < 16; ++r) acc[i][j][r] = __builtin_amdgcn_ldexpf(acc[i][j][r], fr[i][r] + fb[j]);
     };
     auto load_a = [&](int c, int i) {
         const int row = 2 * TNS * (c < nch ? c : 0);          // relative to the wavefront's first row
@@ -529,7 +533,7 @@ __device__ inline void tn_stream_tile(const GemmProb& P, int split, int m0, int 
 #pragma unroll
             for (int i = 0; i < TM; ++i) { ma[i] = tn_max(xa[i]); over |= ma[i] > ca[i].limit; }
             if (__ballot(over) != 0) {
-                float fa[TM], fb[2];
+                int fa[TM], fb[2];
 #pragma unroll
                 for (int i = 0; i < TM; ++i) fa[i] = tn_rescale(ca[i], ma[i]);
 #pragma unroll
@@ -558,11 +562,11 @@ __device__ inline void tn_stream_tile(const GemmProb& P, int split, int m0, int 
                 for (int j = 0; j < 2; ++j) acc[i][j] = mfma_f16(ta[0], tb[j][0], acc[i][j]);
             }
         }
-        float fa[TM], fb[2];
+        int fa[TM], fb[2];
 #pragma unroll
-        for (int i = 0; i < TM; ++i) fa[i] = ca[i].inv;
+        for (int i = 0; i < TM; ++i) fa[i] = -ca[i].e;
 #pragma unroll
-        for (int j = 0; j < 2; ++j) fb[j] = cb[j].inv;
+        for (int j = 0; j < 2; ++j) fb[j] = -cb[j].e;
         multiply(fa, fb);
     }
     // The four partial tiles meet in LDS.  Every wavefront owns a quarter of the tile's accumulator registers
@@ -584,7 +588,7 @@ __device__ inline void tn_stream_tile(const GemmProb& P, int split, int m0, int 
 __global__ __launch_bounds__(NTHREADS, 3) void gemm_tn_stream_kernel(const GemmGroup) {
     const GemmGroup& g = kernel_args<GemmGroup>();
     __shared__ float red[3][4096];
-    __shared__ float rows[4][64];
+    __shared__ int rows[4][64];
     const int bid = xcd_remap(blockIdx.x, gridDim.x);
     const GemmProb& P = g.p[record_of(g.p, &GemmProb::tile_begin, g.nprob, bid)];
     int local = bid - P.tile_begin;

@@ -196,3 +196,43 @@ def test_clipped_step_inside_the_ball_is_the_plain_step(hidden):
     norm = np.sqrt((got[1][3].astype(np.float64) ** 2).sum())
     assert abs(got[1][4] - norm) <= 1e-6 * norm
     print(hidden, "parameters", got[0][0].size, "norm", norm, flush=True)
+
+
+@pytest.mark.parametrize("batch,hidden", [(40, (64, 64)), (333, (96, 40)), (8192, (256, 256))])
+def test_weight_gradients_of_tiny_columns(batch, hidden):
+    """State columns far below 1 beside deltas far below 1: the powers of two by which the sums are rescaled multiply to more
+    than fp32 holds (1e-29 and deltas of 1e-7: 2^(7 + 96) times 2^(7 + 23)) while the sums are zero or ordinary.  A column of
+    1e-29 throughout, one of subnormals, one that is tiny in the first half and ordinary after it: finite everywhere, every row
+    of dW_1 to 1e-5 of its own largest entry (subnormals: to the spacing of fp32 results near zero, 2^-149 a term)."""
+    import torch
+    w = workload(hidden, 21, 3, batch)
+    s, ring = session(w), oracle_ring(w)
+    fill_both(s, ring, w, w.nstep + 3)
+    s.sample(batch)
+    rng = np.random.default_rng(6)
+    b = {k: getattr(s.batch, k)[:batch].cpu().numpy().copy() for k in ("obs", "act", "ret", "next_obs", "boot")}
+    b["obs"] = rng.standard_normal((batch, w.obs_dim)).astype(np.float32)
+    b["obs"][:, 4] *= np.float32(1e-29)
+    b["obs"][:, 8] = (b["obs"][:, 8].astype(np.float64) * 1e-40).astype(np.float32)
+    b["obs"][:batch // 2, 9] *= np.float32(1e-33)
+    b["boot"][:] = 0.0
+    b["ret"] = (b["ret"] * np.float32(1e-3)).astype(np.float32)
+    for k in ("obs", "ret", "boot"):
+        getattr(s.batch, k)[:batch].copy_(torch.from_numpy(b[k]))
+    c = s.critic_init.copy()
+    dims = w.critic_dims()
+    out = sum(i * o + o for i, o in dims[:-1])
+    for h in (0, c.size // 2):
+        c[h + out:h + c.size // 2] *= np.float32(0.1)             # small output weights: small deltas
+    s.critic.copy_(torch.from_numpy(c))
+    s.critic_update(batch)
+    _, g = O.critic_loss_and_grads(c, dims, b, b["ret"].astype(np.float64))
+    got, n = s.c_g.cpu().numpy().astype(np.float64), w.obs_dim * hidden[0]
+    assert np.isfinite(got).all()
+    for h in (0, c.size // 2):
+        ref, x = g[h:h + n].reshape(w.obs_dim, -1), got[h:h + n].reshape(w.obs_dim, -1)
+        assert np.abs(x[8] - ref[8]).max() <= batch * 2.0 ** -149
+        err = np.abs(x - ref).max(1) / np.abs(ref).max(1)
+        err[8] = 0.0
+        print(batch, hidden, "worst column", int(err.argmax()), "%.2e" % err.max(), flush=True)
+        assert err.max() <= TOL
