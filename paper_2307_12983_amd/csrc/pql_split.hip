@@ -866,8 +866,8 @@ __device__ __forceinline__ void critic_step(const SplitCriticArgs& A) {
         float tq[2][2];
         for (int ni = 0; ni < (NN == 2 ? 1 : 2); ++ni) {
             const int net = NN == 2 ? S.net : ni;
+            if (ni > 0) lds_barrier();      // every wavefront has read the other critic's head partials (and activations)
             if (P.alias) {      // the input tile shares its place with the activations: bring the rows in again
-                if (ni > 0) lds_barrier();
                 in.act_lds = M.act;
                 request_rows(xv, in, steps, T);
                 put_rows(xv, in, steps, X, M.inv, 1.f, T);
@@ -1092,8 +1092,8 @@ __device__ __forceinline__ void policy_step(const SplitPolicyArgs& A) {
     float qv[2][2];
     for (int ni = 0; ni < (NN == 2 ? 1 : 2); ++ni) {
         const int net = NN == 2 ? S.net : ni;
+        if (ni > 0) lds_barrier();          // every wavefront has read the other critic's head partials (and activations)
         if (P.alias) {
-            if (ni > 0) lds_barrier();
             in.act_lds = M.act;
             request_rows(xv, in, steps, T);
             put_rows(xv, in, steps, X, M.inv, 1.f, T);

@@ -36,6 +36,8 @@ CASES = {
     "pair_two_tiles_odd": workload((300, 136, 24), 33, 1, 65),
     "odd_widths_sac": workload((100, 200), 45, 11, 31, sac=True),
     "one_layer_sac": workload((40,), 7, 3, 33, sac=True),
+    "one_layer_single": workload((1024,), 20, 4, 97),                   # no barrier but the heads' own between the two critics
+    "one_layer_single_sac": workload((640,), 20, 4, 2049, sac=True),
     "one_layer_atoms": workload((24,), 7, 3, 33, num_atoms=51),
     "few_atoms_wide": workload((512, 72), 19, 5, 97, num_atoms=11, v_min=-2.0, v_max=3.0),
     "deep": workload((40, 72, 100, 24, 200, 8, 64, 33), 5, 2, 64),
