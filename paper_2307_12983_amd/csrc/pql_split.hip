@@ -40,21 +40,21 @@ constexpr int PREP_ITEMS = SPLIT_MAXK / 256;   // pieces of eight values per thr
 constexpr int CS = 33;               // 16-byte units per k-chunk of a tile: 32 rows and one of padding against bank conflicts
 
 // ---- layouts ----------------------------------------------------------------------------------------
-// A prepared matrix (K x N): fragments [N/32][K/32][16-column half][hi, lo][lane] of 16 bytes, then the inverse scale of
-// every 32-column tile (64 floats reserved), then the bias padded with zeros to whole tiles.  Lane (l15 = lane & 15,
+// A prepared matrix (K x N): fragments [N/32][K/32][16-column half][hi, lo][lane] of 16 bytes, then the bias padded with
+// zeros to whole tiles, then the inverse scale of every 32-column tile.  Lane (l15 = lane & 15,
 // q = lane >> 4) holds column 16 half + l15 for the eight k-values k_slot(step, q, i).
 __host__ __device__ __forceinline__ int k_slot(int step, int q, int i) { return 32 * step + 16 * (i >> 2) + 4 * q + (i & 3); }
 size_t split_mat_floats(int K, int N) {
     const size_t ks = (size_t)((K + 31) / 32), tiles = (size_t)((N + 31) / 32);
-    return tiles * ks * 1024 + 64 + tiles * 32;
+    return tiles * ks * 1024 + tiles * 33;
 }
 struct MatView { const u32x4* frag; const float* inv; const float* bias; int ks, tiles; };
 __device__ __forceinline__ MatView mat_view(const float* base, int K, int N) {
     MatView m;
     m.ks = (K + 31) >> 5; m.tiles = (N + 31) >> 5;
     m.frag = reinterpret_cast<const u32x4*>(base);
-    m.inv = base + (size_t)m.tiles * m.ks * 1024;
-    m.bias = m.inv + 64;
+    m.bias = base + (size_t)m.tiles * m.ks * 1024;
+    m.inv = m.bias + (size_t)m.tiles * 32;
     return m;
 }
 
@@ -162,8 +162,8 @@ __global__ __launch_bounds__(PT) void split_weights_kernel(const SplitPrepArgs) 
         d[0] = hi;
         d[64] = lo;
     }
-    if (tid == 0) tail[tile] = inv;
-    if (tid < 32) tail[64 + tile * 32 + tid] = bias;
+    if (tid == 0) tail[tiles * 32 + tile] = inv;
+    if (tid < 32) tail[tile * 32 + tid] = bias;
 }
 
 hipError_t split_weights_launch(SplitPrepArgs& a, int kid, hipStream_t stream) {

@@ -70,6 +70,8 @@ LAYERS = {          # what the layer kernel's tiles and loads depend on: 64 / 32
     "tiles_of_64_and_32_rows": workload((640, 150), 30, 5, 8225),
     "rows_brought_in_twice": workload((1156, 204, 130), 33, 4, 4161),
     "wide_odd_input": workload((136, 128), 603, 17, 8193),
+    "scales_of_65_tiles": workload((2080, 64), 20, 3, 8192),          # one column tile more than 64
+    "scales_of_128_tiles": workload((128, 4096, 128), 20, 3, 4100),   # both directions: the second layer's transpose has 4096 rows
     "matrix_on_the_tiled_kernel": workload((1312, 128), 20, 3, 8192),
 }
 
