@@ -312,7 +312,7 @@ int act_family(const pql_config* c, int rows) {
     return narrow && chain_shape_ok(c) && (rows + FUSED_BM - 1) / FUSED_BM >= CHAIN_MIN_TILES ? FAM_CHAIN : FAM_LAYERED;
 }
 // Whether a layer's matrix is prepared for layer_rowtile_kernel.
-bool layer_prepared(int K, int N) { return K <= SPLIT_MAXK && N >= 128 && N <= 0xffff; }
+bool layer_prepared(int K, int N) { return K <= SPLIT_MAXK && N >= 128; }
 // Floats of prepared weights that one call can need (the critic step's or the policy step's, whichever is larger), on the
 // one-launch kernels or layer by layer; 0: none (offsets within the block are 32-bit).
 size_t prepared_floats(const pql_config* c) {
@@ -466,17 +466,15 @@ void make_cache_layout(const pql_config* c, CacheLayout& w) {
     w.total = off;
 }
 
-// Collects the matrices a call needs in fragment order; their places run through the workspace block for them.  Sources
-// are named by the parameter vector they lie in (`from`) and an offset.
+// Collects the matrices a call needs in fragment order; their places run through the workspace block for them.
 struct SplitPrep {
     SplitPrepArgs args;
     float* block;
     int at;
-    explicit SplitPrep(float* b) : block(b), at(0) { args.n = 0; args.dst = b; args.src[0] = args.src[1] = args.src[2] = nullptr; }
-    const float* add(int from, int64_t src, int64_t bias, int K, int N, int kind) {
+    explicit SplitPrep(float* b) : block(b), at(0) { args.n = 0; args.dst = b; }
+    const float* add(const float* src, const float* bias, int K, int N, int kind) {
         SplitPrepArgs::Mat& m = args.m[args.n++];
-        m.src = (int)src; m.bias = (int)bias; m.dst = at; m.K = (uint16_t)K; m.N = (uint16_t)N;
-        m.kind = (uint8_t)kind; m.from = (uint8_t)from; m.pad_ = 0;
+        m.src = src; m.bias = bias; m.dst = at; m.K = K; m.N = N; m.kind = kind;
         at += (int)up(kind == SPLIT_VECTOR ? (size_t)(N + 31) / 32 * 32 : split_mat_floats(K, N));
         return block + m.dst;
     }
@@ -897,27 +895,27 @@ static void fill_shape(const pql_ctx* c, SplitShape& p) {
     p.o = c->cfg.obs_dim; p.a = c->cfg.act_dim; p.L = c->L;
     for (int l = 0; l < c->L; ++l) p.H[l] = c->cfg.hidden[l];
 }
-// The policy's layers 0..L and a critic's hidden layers 0..L-1 in fragment order (`base`: where the critic begins).
-static void add_policy(const pql_ctx* c, SplitPrep& prep, int from, const float** out) {
+// The policy's layers 0..L and a critic's hidden layers 0..L-1 in fragment order (`p`: where the network begins).
+static void add_policy(const pql_ctx* c, SplitPrep& prep, const float* p, const float** out) {
     for (int l = 0; l <= c->L; ++l) {
         const int K = l == 0 ? c->cfg.obs_dim : c->cfg.hidden[l - 1], N = l < c->L ? c->cfg.hidden[l] : actor_out(&c->cfg);
-        out[l] = prep.add(from, c->a_w[l], c->a_b[l], K, N, SPLIT_PLAIN);
+        out[l] = prep.add(p + c->a_w[l], p + c->a_b[l], K, N, SPLIT_PLAIN);
     }
 }
-static void add_critic(const pql_ctx* c, SplitPrep& prep, int from, int64_t base, const float** out) {
+static void add_critic(const pql_ctx* c, SplitPrep& prep, const float* p, const float** out) {
     for (int l = 0; l < c->L; ++l) {
         const int K = l == 0 ? c->cfg.obs_dim + c->cfg.act_dim : c->cfg.hidden[l - 1], N = c->cfg.hidden[l];
-        out[l] = prep.add(from, base + c->c_w[l], base + c->c_b[l], K, N, SPLIT_PLAIN);
+        out[l] = prep.add(p + c->c_w[l], p + c->c_b[l], K, N, SPLIT_PLAIN);
     }
     if (distributional(&c->cfg))
-        out[c->L] = prep.add(from, base + c->c_w[c->L], SPLIT_NO_BIAS, c->cfg.hidden[c->L - 1], c->cfg.num_atoms, SPLIT_PLAIN);
+        out[c->L] = prep.add(p + c->c_w[c->L], nullptr, c->cfg.hidden[c->L - 1], c->cfg.num_atoms, SPLIT_PLAIN);
 }
 // The transposes of its layers 1..L-1 (with distributional critics also L) for the backward products.
-static void add_critic_back(const pql_ctx* c, SplitPrep& prep, int from, int64_t base, const float** out) {
+static void add_critic_back(const pql_ctx* c, SplitPrep& prep, const float* p, const float** out) {
     for (int l = 1; l < c->L; ++l)
-        out[l] = prep.add(from, base + c->c_w[l], SPLIT_NO_BIAS, c->cfg.hidden[l], c->cfg.hidden[l - 1], SPLIT_TRANSPOSED);
+        out[l] = prep.add(p + c->c_w[l], nullptr, c->cfg.hidden[l], c->cfg.hidden[l - 1], SPLIT_TRANSPOSED);
     if (distributional(&c->cfg))
-        out[c->L] = prep.add(from, base + c->c_w[c->L], SPLIT_NO_BIAS, c->cfg.num_atoms, c->cfg.hidden[c->L - 1], SPLIT_TRANSPOSED);
+        out[c->L] = prep.add(p + c->c_w[c->L], nullptr, c->cfg.num_atoms, c->cfg.hidden[c->L - 1], SPLIT_TRANSPOSED);
 }
 // The same for a launch per layer: the hidden layers that layer_rowtile_kernel takes (NULL for the others).  Launches of up to
 // three networks share their row tiles, so nothing is prepared for batches below a third of the 256 tiles it asks for.
@@ -925,24 +923,24 @@ struct LayerFrags { const float* l[PQL_MAX_HIDDEN + 1]; };
 static bool layers_prepared(const Layout& w, int rows, int networks) {
     return w.split != 0 && (int64_t)networks * ((rows + FUSED_BM - 1) / FUSED_BM) >= LAYERED_MIN_TILES;
 }
-static void add_layers(const pql_ctx* c, SplitPrep& prep, int from, int64_t base, bool policy, LayerFrags& out) {
+static void add_layers(const pql_ctx* c, SplitPrep& prep, const float* p, bool policy, LayerFrags& out) {
     for (int l = 0; l < c->L; ++l) {
         const int K = l > 0 ? c->cfg.hidden[l - 1] : c->cfg.obs_dim + (policy ? 0 : c->cfg.act_dim), N = c->cfg.hidden[l];
         const int64_t w = policy ? c->a_w[l] : c->c_w[l], b = policy ? c->a_b[l] : c->c_b[l];
-        if (layer_prepared(K, N)) out.l[l] = prep.add(from, base + w, base + b, K, N, SPLIT_PLAIN);
+        if (layer_prepared(K, N)) out.l[l] = prep.add(p + w, p + b, K, N, SPLIT_PLAIN);
     }
 }
 // Transposes of layers 1..L-1 (the policy's also of its output layer L).
-static void add_layers_back(const pql_ctx* c, SplitPrep& prep, int from, int64_t base, bool policy, LayerFrags& out) {
+static void add_layers_back(const pql_ctx* c, SplitPrep& prep, const float* p, bool policy, LayerFrags& out) {
     for (int l = 1; l < c->L + (policy ? 1 : 0); ++l) {
         const int K = l < c->L ? c->cfg.hidden[l] : actor_out(&c->cfg), N = c->cfg.hidden[l - 1];
-        if (layer_prepared(K, N)) out.l[l] = prep.add(from, base + (policy ? c->a_w[l] : c->c_w[l]), SPLIT_NO_BIAS, K, N, SPLIT_TRANSPOSED);
+        if (layer_prepared(K, N)) out.l[l] = prep.add(p + (policy ? c->a_w[l] : c->c_w[l]), nullptr, K, N, SPLIT_TRANSPOSED);
     }
 }
 // The output weights of a scalar critic, padded with zeros to whole tiles.
-static const float* add_output(const pql_ctx* c, SplitPrep& prep, int from, int64_t base) {
+static const float* add_output(const pql_ctx* c, SplitPrep& prep, const float* p) {
     if (distributional(&c->cfg)) return nullptr;
-    return prep.add(from, base + c->c_w[c->L], SPLIT_NO_BIAS, 1, c->cfg.hidden[c->L - 1], SPLIT_VECTOR);
+    return prep.add(p + c->c_w[c->L], nullptr, 1, c->cfg.hidden[c->L - 1], SPLIT_VECTOR);
 }
 
 int32_t pql_actor_act(pql_ctx* c, const float* actor_params, const float* obs, int32_t num, float sigma_min,
@@ -985,8 +983,7 @@ int32_t pql_actor_act(pql_ctx* c, const float* actor_params, const float* obs, i
         std::memset(&sa, 0, sizeof(sa));
         fill_shape(c, sa.shape);
         SplitPrep prep(ws + w.split);
-        prep.args.src[0] = actor_params;
-        add_policy(c, prep, 0, sa.pi);
+        add_policy(c, prep, actor_params, sa.pi);
         sa.B = num; sa.pi_bias = actor_params + c->a_b[c->L];
         sa.obs = obs; sa.act_out = act_out;
         if (c->obs_norm) {
@@ -1013,8 +1010,7 @@ int32_t pql_actor_act(pql_ctx* c, const float* actor_params, const float* obs, i
     LayerFrags fp = {};
     if (layers_prepared(w, num, 1)) {
         SplitPrep prep(ws + w.split);
-        prep.args.src[0] = actor_params;
-        add_layers(c, prep, 0, 0, true, fp);
+        add_layers(c, prep, actor_params, true, fp);
         if ((e = split_weights_launch(prep.args, KID_SPLIT_WEIGHTS, st)) != hipSuccess) return E.hip(e, "pql_actor_act");
     }
     e = actor_hidden_forward(c, actor_params, obs, num, ws, w, fp.l, st);
@@ -1087,16 +1083,15 @@ static int32_t critic_update_run(pql_ctx* c, float* critic_params, const float* 
         fill_shape(c, sa.shape);
         sa.B = B;
         SplitPrep prep(ws + w.split);
-        prep.args.src[0] = actor_target_params; prep.args.src[1] = critic_target_params; prep.args.src[2] = critic_params;
-        add_policy(c, prep, 0, sa.pi);
+        add_policy(c, prep, actor_target_params, sa.pi);
         sa.pi_bias = actor_target_params + c->a_b[L];
         for (int i = 0; i < 2; ++i) {
             const float *qt = critic_target_params + i * Pc, *q = critic_params + i * Pc;
-            add_critic(c, prep, 1, i * Pc, sa.qt[i]);
-            add_critic(c, prep, 2, i * Pc, sa.q[i]);
-            add_critic_back(c, prep, 2, i * Pc, sa.qT[i]);
-            sa.wo_t[i] = add_output(c, prep, 1, i * Pc);
-            sa.wo_q[i] = add_output(c, prep, 2, i * Pc);
+            add_critic(c, prep, qt, sa.qt[i]);
+            add_critic(c, prep, q, sa.q[i]);
+            add_critic_back(c, prep, q, sa.qT[i]);
+            sa.wo_t[i] = add_output(c, prep, qt);
+            sa.wo_q[i] = add_output(c, prep, q);
             sa.bo_t[i] = qt + c->c_b[L]; sa.bo_q[i] = q + c->c_b[L];
             for (int l = 1; l <= L; ++l) { sa.h[i][l] = ws + w.hQ[i][l]; sa.d[i][l] = ws + w.dQ[i][l]; sa.col[i][l] = ws + w.colQ[i][l]; }
             sa.q_out[i] = ws + w.q[i];
@@ -1118,12 +1113,11 @@ static int32_t critic_update_run(pql_ctx* c, float* critic_params, const float* 
         LayerFrags fp = {}, ft[2] = {}, fq[2] = {}, fb[2] = {};
         if (layers_prepared(w, B, 3)) {
             SplitPrep prep(ws + w.split);
-            prep.args.src[0] = actor_target_params; prep.args.src[1] = critic_target_params; prep.args.src[2] = critic_params;
-            add_layers(c, prep, 0, 0, true, fp);
+            add_layers(c, prep, actor_target_params, true, fp);
             for (int i = 0; i < 2; ++i) {
-                add_layers(c, prep, 1, i * Pc, false, ft[i]);
-                add_layers(c, prep, 2, i * Pc, false, fq[i]);
-                add_layers_back(c, prep, 2, i * Pc, false, fb[i]);
+                add_layers(c, prep, critic_target_params + i * Pc, false, ft[i]);
+                add_layers(c, prep, critic_params + i * Pc, false, fq[i]);
+                add_layers_back(c, prep, critic_params + i * Pc, false, fb[i]);
             }
             if ((e = split_weights_launch(prep.args, KID_SPLIT_WEIGHTS, st)) != hipSuccess) return E.hip(e, who);
         }
@@ -1392,21 +1386,20 @@ int32_t pql_actor_update(pql_ctx* c, float* actor_params, const float* critic_pa
         fill_shape(c, sa.shape);
         sa.B = B;
         SplitPrep prep(ws + w.split);
-        prep.args.src[0] = actor_params; prep.args.src[1] = critic_params;
-        add_policy(c, prep, 0, sa.pi);
+        add_policy(c, prep, actor_params, sa.pi);
         sa.pi_bias = actor_params + c->a_b[L];
         for (int l = 1; l <= L; ++l) {
             const int K = l < L ? c->cfg.hidden[l] : aw;
-            sa.waT[l] = prep.add(0, c->a_w[l], SPLIT_NO_BIAS, K, c->cfg.hidden[l - 1], SPLIT_TRANSPOSED);
+            sa.waT[l] = prep.add(actor_params + c->a_w[l], nullptr, K, c->cfg.hidden[l - 1], SPLIT_TRANSPOSED);
             sa.hA[l] = ws + w.hA[l]; sa.dA[l] = ws + w.dA[l]; sa.colA[l] = ws + w.colA[l];
         }
         sa.colA[L + 1] = ws + w.colA[L + 1];
         for (int i = 0; i < 2; ++i) {
             const float* q = critic_params + i * Pc;
-            add_critic(c, prep, 1, i * Pc, sa.q[i]);
-            add_critic_back(c, prep, 1, i * Pc, sa.qT[i]);
-            sa.w1aT[i] = prep.add(1, i * Pc + c->c_w[0] + (int64_t)o * H1, SPLIT_NO_BIAS, H1, ad, SPLIT_TRANSPOSED);
-            sa.wo[i] = add_output(c, prep, 1, i * Pc);
+            add_critic(c, prep, q, sa.q[i]);
+            add_critic_back(c, prep, q, sa.qT[i]);
+            sa.w1aT[i] = prep.add(q + c->c_w[0] + (int64_t)o * H1, nullptr, H1, ad, SPLIT_TRANSPOSED);
+            sa.wo[i] = add_output(c, prep, q);
             sa.bo[i] = q + c->c_b[L];
             for (int l = 1; l <= L; ++l) sa.h[i][l] = ws + w.hQ[i][l];
             sa.q_out[i] = ws + w.q[i];
@@ -1425,12 +1418,11 @@ int32_t pql_actor_update(pql_ctx* c, float* actor_params, const float* critic_pa
         LayerFrags fp = {}, fpb = {}, fq[2] = {}, fb[2] = {};
         if (layers_prepared(w, B, 2)) {
             SplitPrep prep(ws + w.split);
-            prep.args.src[0] = actor_params; prep.args.src[1] = critic_params;
-            add_layers(c, prep, 0, 0, true, fp);
-            add_layers_back(c, prep, 0, 0, true, fpb);
+            add_layers(c, prep, actor_params, true, fp);
+            add_layers_back(c, prep, actor_params, true, fpb);
             for (int i = 0; i < 2; ++i) {
-                add_layers(c, prep, 1, i * Pc, false, fq[i]);
-                add_layers_back(c, prep, 1, i * Pc, false, fb[i]);
+                add_layers(c, prep, critic_params + i * Pc, false, fq[i]);
+                add_layers_back(c, prep, critic_params + i * Pc, false, fb[i]);
             }
             if ((e = split_weights_launch(prep.args, KID_SPLIT_WEIGHTS, st)) != hipSuccess) return E.hip(e, who);
         }

@@ -359,19 +359,17 @@ constexpr int SPLIT_MAXW = 1024;             // widest layer and input of the on
 constexpr int SPLIT_MAXK = 1280;             // longest contraction of a prepared matrix
 constexpr size_t SPLIT_LDS = 160 * 1024;
 enum SplitKind : int { SPLIT_PLAIN = 0, SPLIT_TRANSPOSED = 1, SPLIT_VECTOR = 2 };
-// Matrices (K x N) to bring into fragment order: element (k, n) is src[k * N + n], or src[n * K + k] (transposed); a vector
-// of N floats is only padded with zeros to a multiple of 32.  Records are kept small and their first workgroups apart: a
+// Matrices (K x N) to bring into fragment order: element (k, n) is src[k * N + n], or src[n * K + k] (transposed), the bias
+// (NULL: zeros) that of a layer's N outputs; a vector of N floats is only padded with zeros to a multiple of 32.  Records are kept small and their first workgroups apart: a
 // workgroup finds its record with one load per lane, not by walking the list.
 // Most entries: critic step with PQL_MAX_HIDDEN = 8 layers and distributional critics: policy 9, four critics 9 each, 8
 // transposes for each online critic.
 constexpr int SPLIT_MAX_MATS = 9 + 4 * 9 + 2 * 8;
-constexpr int SPLIT_NO_BIAS = -1;
 struct SplitPrepArgs {
-    const float* src[3];                 // the parameter vectors the records' offsets refer to
     float* dst;
     int n;
     int first[64];                       // first workgroup of each record, filled by the launch function
-    struct Mat { int src, bias, dst; uint16_t K, N; uint8_t kind, from; uint16_t pad_; } m[SPLIT_MAX_MATS];   // offsets in floats
+    struct Mat { const float *src, *bias; int dst, K, N, kind; } m[SPLIT_MAX_MATS];     // dst: offset in floats
 };
 static_assert(SPLIT_MAX_MATS <= 64, "a wavefront looks its record up with one lane each");
 size_t split_mat_floats(int K, int N);

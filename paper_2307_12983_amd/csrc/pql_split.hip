@@ -108,7 +108,7 @@ __global__ __launch_bounds__(PT) void split_weights_kernel(const SplitPrepArgs) 
     const int pi = __builtin_amdgcn_readfirstlane(__popcll(__ballot(b >= first)) - 1);
     const SplitPrepArgs::Mat M = P.m[pi];
     const int tile = b - __builtin_amdgcn_readlane(first, pi), K = M.K, N = M.N;
-    const float* src = P.src[M.from] + M.src;
+    const float* src = M.src;
     float* dst = P.dst + M.dst;
     if (M.kind == SPLIT_VECTOR) {        // a vector padded with zeros to whole tiles
         for (int i = tid; i < (N + 31) / 32 * 32; i += PT) dst[i] = i < N ? src[i] : 0.f;
@@ -136,7 +136,7 @@ __global__ __launch_bounds__(PT) void split_weights_kernel(const SplitPrepArgs) 
         }
     }
     float bias = 0.f;
-    if (tid < 32 && M.bias != SPLIT_NO_BIAS && tile * 32 + tid < N) bias = P.src[M.from][M.bias + tile * 32 + tid];
+    if (tid < 32 && M.bias != nullptr && tile * 32 + tid < N) bias = M.bias[tile * 32 + tid];
 #pragma unroll
     for (int it = 0; it < PREP_ITEMS; ++it) {
         if (it * PT >= items) break;
