@@ -30,6 +30,8 @@
 #include "pql_pairs.h"
 #include "pql_rowtile.h"
 
+#include <float.h>
+
 namespace pql {
 
 enum Variant : int { VAR_PLAIN = 0, VAR_SAC = 1, VAR_DIST = 2 };
@@ -143,11 +145,29 @@ __global__ __launch_bounds__(PT) void split_weights_kernel(const SplitPrepArgs) 
 #pragma unroll
         for (int i = 0; i < 8; ++i) mx = fmaxf(mx, fabsf(v[it][i >> 2][i & 3]));
     }
-    mx = quarters_max(half_max(mx));
-    if (lane == 0) red[tid >> 6] = mx;
-    __syncthreads();
+    // element i of piece e of this tile
+    auto offset = [&](int e, int i) {
+        const int k = k_slot(e >> 7, (e >> 4) & 3, i), n = tile * 32 + ((e >> 6) & 1) * 16 + (e & 15);
+        return k < K && n < N ? (unsigned)(k * sk + n * sn) * 4u : 0x7ffffffcu;
+    };
+    bool infinite = false;
+    while (true) {
+        mx = quarters_max(half_max(mx));
+        if (lane == 0) red[tid >> 6] = mx;
+        __syncthreads();
 #pragma unroll
-    for (int w = 0; w < PT / 64; ++w) mx = fmaxf(mx, red[w]);
+        for (int w = 0; w < PT / 64; ++w) mx = fmaxf(mx, red[w]);
+        if (infinite || !(mx > FLT_MAX)) break;
+        // an infinite weight: the scale is that of the finite ones, so that the columns beside it keep their values
+        infinite = true;
+        mx = 0.f;
+#pragma unroll 1
+        for (int j = tid; j < items * 8; j += PT) {
+            const float x = fabsf(buf_load(rs, offset(j >> 3, j & 7), 0));
+            mx = fmaxf(mx, x <= FLT_MAX ? x : 0.f);
+        }
+        __syncthreads();
+    }
     float inv;
     const float s = scale_for(mx, inv);
     u32x4* frag = reinterpret_cast<u32x4*>(dst) + (size_t)tile * ks * 256;
@@ -161,6 +181,19 @@ __global__ __launch_bounds__(PT) void split_weights_kernel(const SplitPrepArgs) 
         u32x4* d = frag + (size_t)(e >> 6) * 128 + lane;
         d[0] = hi;
         d[64] = lo;
+    }
+    if (infinite) {          // as hi = 0, lo = +-inf: one product with the sign of x_hi, none with x_lo
+#pragma unroll 1
+        for (int e = tid; e < items; e += PT)                    // (the pieces this thread has just written)
+#pragma unroll 1
+            for (int i = 0; i < 8; ++i) {
+                const float x = buf_load(rs, offset(e, i), 0);
+                if (!(fabsf(x) > FLT_MAX)) continue;
+                char* d = reinterpret_cast<char*>(frag + (size_t)(e >> 6) * 128 + lane) + 2 * i;
+                const uint16_t hi = 0, lo = x > 0.f ? 0x7c00 : 0xfc00;
+                __builtin_memcpy(d, &hi, 2);
+                __builtin_memcpy(d + 64 * 16, &lo, 2);
+            }
     }
     if (tid == 0) tail[tiles * 32 + tile] = inv;
     if (tid < 32) tail[tile * 32 + tid] = bias;
@@ -477,7 +510,7 @@ __device__ __forceinline__ void backward(f32x4 (&z)[TPW][2][2], const MatView& W
 // Rows r0 .. r0 + 31 of concat(obs[o], act[a]) as a tile: half a wavefront takes two rows, one after the other, so that their
 // largest magnitudes are found without leaving the registers.  `floor`: lower bound of that magnitude (actions in [-1, 1] that are inserted later must
 // fit the row's scale).  Up to 256 columns are requested ahead of time into v.
-struct InputRows { __amdgpu_buffer_rsrc_t obs, act, mean, rstd; int o, a, act_lds, as; bool norm; };   // act_lds >= 0: actions in LDS
+struct InputRows { __amdgpu_buffer_rsrc_t obs, act, mean, rstd; int o, a, act_lds, as, last; bool norm; };   // act_lds >= 0: actions in LDS; last: last row
 constexpr int XV = 8;
 constexpr int NOWHERE = 0x7ffffffc;          // a buffer offset past any descriptor used here: the load returns zero
 
@@ -489,11 +522,12 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t rows_of(const float* p, int co
 __device__ __forceinline__ InputRows input_rows(const float* obs, int o, const float* act, int act_lds, int a, int as, int r0, int B) {
     InputRows in;
     in.obs = rows_of(obs, o, r0, B); in.act = rows_of(act, a, r0, B); in.mean = in.obs; in.rstd = in.obs;
-    in.o = o; in.a = a; in.act_lds = act_lds; in.as = as; in.norm = false;
+    in.o = o; in.a = a; in.act_lds = act_lds; in.as = as; in.last = (B - r0 < 32 ? B - r0 : 32) - 1; in.norm = false;
     return in;
 }
-// Column c + 32 j of the concatenated row.  Branch-free: what a descriptor does not hold reads as zero (rows beyond the
-// batch, columns beyond the row).
+// Column c + 32 j of the concatenated row.  Branch-free: what a descriptor does not hold reads as zero (columns beyond the row).
+// Places of rows beyond the batch hold its last row: their results go nowhere, but enter sums with a factor of zero, so they
+// have to be finite where those of the batch are (a row of zeros is not, at an infinite weight).
 __device__ __forceinline__ float input_value(const InputRows& in, int row, int col) {
     float x = buf_load(in.obs, (unsigned)(col < in.o ? (row * in.o + col) * 4 : NOWHERE), 0);
     if (in.norm) {
@@ -513,13 +547,14 @@ __device__ __forceinline__ float input_action(const InputRows& in, int row, int 
 }
 struct Rows { float v[2][XV]; };
 __device__ __forceinline__ int input_row(const Wv& T, int i) { return 2 * T.wave + (T.lane >> 5) + 16 * i; }
+__device__ __forceinline__ int source_row(const InputRows& in, int row) { return row < in.last ? row : in.last; }
 __device__ __forceinline__ void request_rows(Rows& x, const InputRows& in, int steps, const Wv& T) {
     if (steps > XV) return;
     const int c = T.lane & 31;
     const int j0 = in.o >> 5;                 // at most 32 action columns: they lie in the steps j0 and j0 + 1
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
-        const int row = input_row(T, i);
+        const int row = source_row(in, input_row(T, i));
 #pragma unroll
         for (int j = 0; j < XV; ++j) x.v[i][j] = input_value(in, row, c + 32 * j);
         if (in.a > 0) {
@@ -558,7 +593,7 @@ __device__ __forceinline__ void put_rows(const Rows& x, const InputRows& in, int
 #pragma unroll
             for (int j = 0; j < XV; ++j) mx = fmaxf(mx, fabsf(x.v[i][j]));
         } else {
-            for (int j = 0; j < steps; ++j) mx = fmaxf(mx, fabsf(input_any(in, row, c + 32 * j)));
+            for (int j = 0; j < steps; ++j) mx = fmaxf(mx, fabsf(input_any(in, source_row(in, row), c + 32 * j)));
         }
         float inv;
         const float s = scale_for(half_max(mx), inv);
@@ -568,7 +603,7 @@ __device__ __forceinline__ void put_rows(const Rows& x, const InputRows& in, int
             for (int j = 0; j < XV; ++j)
                 if (j < steps) put_value(X, row, c + 32 * j, x.v[i][j], s);
         } else {
-            for (int j = 0; j < steps; ++j) put_value(X, row, c + 32 * j, input_any(in, row, c + 32 * j), s);
+            for (int j = 0; j < steps; ++j) put_value(X, row, c + 32 * j, input_any(in, source_row(in, row), c + 32 * j), s);
         }
     }
 }

@@ -240,3 +240,70 @@ def test_weight_gradients_of_tiny_columns(batch, hidden):
         err[8] = 0.0
         print(batch, hidden, "worst column", int(err.argmax()), "%.2e" % err.max(), flush=True)
         assert err.max() <= TOL
+
+
+INFINITE = {        # widths, batch: one launch per update (two classes, critics one after the other), one launch per layer
+    "fused": ((64, 64), 65),
+    "pair": ((300, 136, 24), 97),
+    "single": ((640, 40), 65),
+    "layers": ((640, 150), 8225),
+}
+
+
+@pytest.mark.parametrize("case", list(INFINITE))
+def test_infinite_weight_stays_in_its_column(case):
+    """A weight of -inf on a state column that is positive throughout: its hidden unit is ELU(-inf) = -1 with slope 0 in every
+    row, as in any arithmetic, and the other 31 columns that share a scale with it are what they are without it."""
+    import torch
+    hidden, batch = INFINITE[case]
+    w = workload(hidden, 20, 4, batch)
+    s, ring = session(w), oracle_ring(w)
+    fill_both(s, ring, w, w.nstep + 3)
+    s.sample(batch)
+    s.batch.obs[:batch, 3].abs_().add_(0.1)
+    b = {k: getattr(s.batch, k)[:batch].cpu().numpy().copy() for k in ("obs", "act", "ret", "next_obs", "boot")}
+    c = s.critic_init.copy()
+    for h, unit in ((0, 5), (c.size // 2, hidden[0] - 1)):
+        c[h + 3 * hidden[0] + unit] = -np.inf
+    s.critic.copy_(torch.from_numpy(c))
+    # the targets stay finite
+    L = oracle_learner(w, s.actor_init, s.critic_init)
+    L.critic = c.astype(np.float64)
+    s.critic_update(batch)
+    losses, g = L.critic_update(b)
+    s.critic.copy_(torch.from_numpy(c))
+    L.critic = c.astype(np.float64)
+    s.actor_update(s.batch.obs, batch)
+    _, ga = L.actor_update(b["obs"])
+    assert np.isfinite(g).all() and np.isfinite(ga).all()
+    assert rel_err(s.critic_loss.cpu().numpy(), losses) <= TOL
+    e = assert_params_close(s.c_g.cpu().numpy(), g, w.critic_dims(), 2, TOL, "critic grad")
+    ea = assert_params_close(s.a_g.cpu().numpy(), ga, w.actor_dims(), 1, TOL, "actor grad")
+    print(case, "critic grad", e, "actor grad", ea, flush=True)
+
+
+@pytest.mark.parametrize("hidden", [(64, 64), (512, 256)])
+def test_infinite_output_weights_give_saturated_actions(hidden):
+    """The Actor step above 4096 environments: an action with an infinite output weight is +1 or -1 by the sign of its hidden
+    unit, the others are the oracle's."""
+    import torch
+    w = workload(hidden, 20, 4, 4128).replace(num_envs=4128, capacity=4128 * 4, sigma_min=0.0, sigma_max=0.0)
+    s = session(w)
+    p = s.actor_init.copy()
+    dims = w.actor_dims()
+    out = sum(i * o + o for i, o in dims[:-1])
+    p[out + 7 * 4 + 2] = np.inf
+    s.actor.copy_(torch.from_numpy(p))
+    obs = np.random.default_rng(8).standard_normal((4128, 20)).astype(np.float32)
+    got = s.act(torch.from_numpy(obs).cuda()).cpu().numpy()
+    finite = s.actor_init.astype(np.float64)
+    ref = O.actor_forward(finite, dims, obs.astype(np.float64))
+    others = [0, 1, 3]
+    assert np.abs(got[:, others] - ref[:, others]).max() <= TOL
+    x = obs.astype(np.float64)
+    for l, (i, o) in enumerate(dims[:-1]):
+        at = sum(a * b + b for a, b in dims[:l])
+        z = x @ finite[at:at + i * o].reshape(i, o) + finite[at + i * o:at + i * o + o]
+        x = np.where(z > 0, z, np.expm1(np.minimum(z, 0)))
+    clear = np.abs(x[:, 7]) > 1e-4
+    assert np.array_equal(got[clear, 2], np.sign(x[clear, 7]).astype(np.float32))
