@@ -355,7 +355,7 @@ bool act16_ok(const FusedActArgs& a);
 hipError_t fused_act16_launch(const FusedActArgs& a, hipStream_t stream);
 
 // ---- row-tile kernels on fp16 pairs (pql_split.hip) -----------------------------------------
-constexpr int SPLIT_MAXW = 1024;             // widest layer and input of the one-launch kernels
+constexpr int SPLIT_MAXW = 1024;             // widest layer and state of the one-launch kernels (actions, at most 32, come on top)
 constexpr int SPLIT_MAXK = 1280;             // longest contraction of a prepared matrix
 constexpr size_t SPLIT_LDS = 160 * 1024;
 enum SplitKind : int { SPLIT_PLAIN = 0, SPLIT_TRANSPOSED = 1, SPLIT_VECTOR = 2 };

@@ -1618,7 +1618,7 @@ static int widest(const SplitShape& p) {
 }
 
 bool split_shape_ok(int o, int a, int aw, const int* H, int L, bool dist) {
-    if (aw > FUSED_MAX_ACT || o + a > SPLIT_MAXW) return false;
+    if (aw > FUSED_MAX_ACT || o > SPLIT_MAXW) return false;
     SplitShape p;
     p.o = o; p.a = a; p.L = L;
     for (int l = 0; l < L; ++l) {

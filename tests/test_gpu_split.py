@@ -32,6 +32,7 @@ def workload(hidden, o, a, batch, **kw):
 
 CASES = {
     "single_two_pass_input": workload((1024, 40), 230, 32, 2049),
+    "widest_input": workload((200, 40), 1024, 32, 65),                  # 1056 columns: 33 k-steps
     "pair_shared_input_tile": workload((512, 512), 250, 10, 2050),
     "pair_two_tiles_odd": workload((300, 136, 24), 33, 1, 65),
     "odd_widths_sac": workload((100, 200), 45, 11, 31, sac=True),
