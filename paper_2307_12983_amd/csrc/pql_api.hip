@@ -249,15 +249,13 @@ struct Layout {
     size_t colA[PQL_MAX_HIDDEN + 2];                                  // bias-grad partials of actor layer l (1..L+1)
     size_t aOut, dPre, y, q[2];
     size_t p_dw[2], p_dbh[2], p_db[2], p_loss;
-    size_t wT[2][PQL_MAX_HIDDEN + 1];                                 // (no longer read: it and waT, woT keep the workspace the size it was)
     size_t w1aT[2];                                                   // transposed action rows of the critics' first layer
-    size_t waT[PQL_MAX_HIDDEN + 1];                                   // transposed policy weights, layer l = 1..L
-    size_t splitk;
-    size_t lgT[2], lgQ[2], p_dbo[2], woT[2];                          // distributional critics: logits, output-bias partials, W_out^T
+    size_t splitk;                                                    // weight-gradient slabs
+    size_t split;                                                     // weights in fragment order (0: none)
+    size_t lgT[2], lgQ[2], p_dbo[2];                                  // distributional critics: logits, output-bias partials
     size_t mu2a, logp, epsb, dOut, p_sc, p_lp;                        // stochastic policy: outputs, log pi, draws, gradient, partials
     size_t sqp;                                                       // per-workgroup sums of squared gradients
     size_t xn;                                                        // standardised Actor observations
-    size_t split;                                                     // weights in fragment order (row-tile kernels on fp16 pairs)
     size_t total;
 };
 
@@ -314,8 +312,10 @@ int act_family(const pql_config* c, int rows) {
 // Whether a layer's matrix is prepared for layer_rowtile_kernel.
 bool layer_prepared(int K, int N) { return K <= SPLIT_MAXK && N >= 128; }
 // Floats of prepared weights that one call can need (the critic step's or the policy step's, whichever is larger), on the
-// one-launch kernels or layer by layer; 0: none (offsets within the block are 32-bit).
+// one-launch kernels or layer by layer; 0: none (no batch of the context takes either; offsets within the block are 32-bit).
 size_t prepared_floats(const pql_config* c) {
+    if ((c->max_batch + FUSED_BM - 1) / FUSED_BM < SPLIT_MIN_TILES && !fused_ok(c) &&
+        (!split_ok(c) || pql_critic_param_count(c) > SPLIT_ANY_TILES_WEIGHTS)) return 0;
     const int L = c->n_hidden, o = c->obs_dim, a = c->act_dim, aw = actor_out(c);
     const bool all = split_ok(c);
     auto mat = [&](int K, int N) { return all || layer_prepared(K, N) ? up(split_mat_floats(K, N)) : 0; };
@@ -366,8 +366,7 @@ size_t splitk_floats(const pql_config* c, int B) {
     return sc > sa ? sc : sa;
 }
 
-// with_split = false: without room for prepared weights (the calls then take the other kernels).
-void make_layout(const pql_config* c, Layout& w, bool with_split = true) {
+void make_layout(const pql_config* c, Layout& w) {
     std::memset(&w, 0, sizeof(w));
     const int L = c->n_hidden;
     const size_t B = (size_t)c->max_batch;
@@ -388,21 +387,10 @@ void make_layout(const pql_config* c, Layout& w, bool with_split = true) {
             w.colQ[i][l] = take(crow * h);
         }
     }
-    // Prepared weights.  Where every call takes the fused kernels they share their place with the target critics'
-    // activations, which only the layer-by-layer path has.
-    {
-        const size_t at = off;
-        for (int l = 1; l <= L; ++l)
-            for (int i = 0; i < 2; ++i) w.hT[i][l] = take(B * (size_t)c->hidden[l - 1]);
-        const size_t need = with_split ? prepared_floats(c) : 0;
-        w.split = 0;
-        if (need > 0 && fused_ok(c)) {
-            w.split = at;
-            if (off - at < need) off = at + up(need);
-        } else if (need > 0) {
-            w.split = take(need);
-        }
-    }
+    const size_t targets = off;
+    for (int l = 1; l <= L; ++l)
+        for (int i = 0; i < 2; ++i) w.hT[i][l] = take(B * (size_t)c->hidden[l - 1]);
+    const size_t need = prepared_floats(c), targets_size = off - targets;
     w.colA[L + 1] = take(crow * (size_t)actor_out(c));
     w.aOut = take(B * c->act_dim);
     w.dPre = take(B * (size_t)actor_out(c));
@@ -415,12 +403,24 @@ void make_layout(const pql_config* c, Layout& w, bool with_split = true) {
         w.p_db[i] = take(nwg);
     }
     w.p_loss = take(2 * nwg);
-    for (int i = 0; i < 2; ++i) {
-        for (int l = 1; l < L; ++l) w.wT[i][l] = take((size_t)c->hidden[l - 1] * c->hidden[l]);
-        w.w1aT[i] = take((size_t)c->act_dim * c->hidden[0]);
+    for (int i = 0; i < 2; ++i) w.w1aT[i] = take((size_t)c->act_dim * c->hidden[0]);
+    // Prepared weights take the place of what no call holds at the same time: the target critics' activations where no batch
+    // of the context runs layer by layer, else the slabs of the weight gradients, which are written after the last product
+    // that reads the weights.  The slabs' room includes one transposed copy of every matrix behind a hidden layer; with it the
+    // prepared weights fit wherever the total nears the static scratch's 64 MiB, so that the configurations it takes are those
+    // of the kernels without prepared weights.
+    {
+        size_t copies = 0;
+        for (int l = 1; l <= L; ++l) {
+            if (l < L) copies += 2 * up((size_t)c->hidden[l - 1] * c->hidden[l]);
+            copies += up((size_t)c->hidden[l - 1] * (l < L ? c->hidden[l] : actor_out(c)));
+        }
+        if (distributional(c)) copies += 2 * up((size_t)c->num_atoms * c->hidden[L - 1]);
+        const size_t room = copies + up(splitk_floats(c, (int)B));
+        const bool beside = need <= targets_size && family(c, 1) != FAM_LAYERED && family(c, c->max_batch) != FAM_LAYERED;
+        w.splitk = take(beside || room > need ? room : need);
+        w.split = need == 0 ? 0 : (beside ? targets : w.splitk);
     }
-    for (int l = 1; l <= L; ++l) w.waT[l] = take((size_t)c->hidden[l - 1] * (l < L ? c->hidden[l] : actor_out(c)));
-    w.splitk = take(splitk_floats(c, (int)B));
     {
         const size_t pa = (size_t)pql_actor_param_count(c), pc = 2 * (size_t)pql_critic_param_count(c);
         w.sqp = take(adam_reduce_blocks_bound(pa > pc ? pa : pc, RED_MAX_TENSORS));
@@ -440,13 +440,12 @@ void make_layout(const pql_config* c, Layout& w, bool with_split = true) {
             w.lgT[i] = take(B * (size_t)c->num_atoms);
             w.lgQ[i] = take(B * (size_t)c->num_atoms);
             w.p_dbo[i] = take(nwg * (size_t)c->num_atoms);
-            w.woT[i] = take((size_t)c->num_atoms * c->hidden[L - 1]);
         }
     w.total = off;
 }
 
-// Transposed weights kept between calls (pql_weight_cache_*): the same matrices the workspace holds as
-// wT / w1aT / woT / waT, in a block of the caller's.
+// Transposed weights kept between calls (pql_weight_cache_*), in a block of the caller's: hidden layers of the critics, action
+// rows of their first layers, output layers of distributional critics, layers of the policy.
 struct CacheLayout {
     size_t wT[2][PQL_MAX_HIDDEN + 1], w1aT[2], woT[2], waT[PQL_MAX_HIDDEN + 1];
     size_t total;
@@ -1328,8 +1327,6 @@ int32_t pql_critic_update_static(pql_ctx* c, float* critic_params, const float* 
     if (rc != PQL_OK) return rc;
     Layout w;
     make_layout(&c->cfg, w);
-    // a configuration that fits without the prepared weights only runs on the kernels that need none
-    if (w.total * sizeof(float) > STATIC_SCRATCH_BYTES) make_layout(&c->cfg, w, false);
     if (w.total * sizeof(float) > STATIC_SCRATCH_BYTES) {
         char msg[192];
         std::snprintf(msg, sizeof(msg), "pql_critic_update_static: this configuration needs %zu bytes of scratch, the static "

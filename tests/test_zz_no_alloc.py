@@ -19,7 +19,7 @@ def _session(w):
     return LearnerSession(w)
 
 
-@pytest.mark.parametrize("case", ["row_tile", "layered"])
+@pytest.mark.parametrize("case", ["row_tile", "layered", "largest"])
 def test_static_scratch_entry_point_matches_workspace_entry_point(case):
     import torch
     if not torch.cuda.is_available():
@@ -27,10 +27,14 @@ def test_static_scratch_entry_point_matches_workspace_entry_point(case):
     base = W.WORKLOADS["ant"]
     if case == "row_tile":      # the chained row-tile kernels
         w = base.replace(name="static_a", num_envs=96, capacity=96 * 13, batch=1000)
-    else:                       # a layer wider than 256: the per-layer path with its many scratch buffers
+    elif case == "largest":     # a network with layers above 256 at the largest batch whose scratch fits
+        w = W.WORKLOADS["humanoid"].replace(name="static_l", num_envs=64, capacity=64 * 9, batch=1791)
+    else:                       # a layer wider than 256
         w = W.WORKLOADS["humanoid"].replace(name="static_h", num_envs=64, capacity=64 * 9, batch=777)
     a, b, ring = _session(w), _session(w), oracle_ring(w)
     assert a.ctx.workspace_bytes() <= a.ctx.static_scratch_bytes()
+    if case == "largest":
+        assert _session(w.replace(batch=1792)).ctx.workspace_bytes() > a.ctx.static_scratch_bytes()
     fill_both(a, ring, w, w.nstep + 4)
     fill_both(b, oracle_ring(w), w, w.nstep + 4)
     L = oracle_learner(w, a.actor_init, a.critic_init)
