@@ -364,11 +364,14 @@ int gemm_waves_m(int tile) { return tile == TILE_128x32 ? 4 : 2; }
 // zero): no LDS staging and no barrier inside the loop.  The four wavefronts of a workgroup each take a quarter of the
 // split's rows of the same tile (rows in chunks of 16); the partial tiles meet in LDS at the end.
 //
-// A lane holds eight rows of one column of each operand; it writes them as fp16 pairs (pql_pairs.h) scaled by a power of two
-// of that column's own, which stays the same over the rows as the contraction needs it to.  The scale comes from the first
-// chunk with room for values 2^8 larger; a chunk that holds a larger one still rescales the sums (rare: the check is eight
-// comparisons).  Products: lo hi + hi lo + hi hi, v_mfma_f32_32x32x16_f16, fp32 sums; with three roundings per 16 rows where the
-// fp32 MFMAs of a 32x32x2 kernel make eight, the result is the closer one.
+// A lane holds eight rows of one column of each operand; it writes them as fp16 pairs (pql_pairs.h, lo terms 2^11 too large)
+// scaled by a power of two of that column's own, which stays the same over the rows as the contraction needs it to.  The scale
+// comes from the first chunk with room for values 2^5 larger; a chunk that holds a larger one still rescales the sums (rare: the
+// check is eight comparisons).  Values down to 2^-24 of their column's largest so far keep their relative precision.
+// Products: lo hi + hi lo in a sum of the chunk's own, which joins the running sum, and hi hi; v_mfma_f32_32x32x16_f16, fp32
+// sums.  With two roundings of the running sum per 16 rows where the fp32 MFMAs of a 32x32x2 kernel make eight, the result is
+// the closer one.  (With unscaled lo terms, which need no sum of their own, values from 2^-9 of the column's largest down lose
+// bits: 5e-4 of a gradient where states of 2^20 in a few rows meet deltas of zero, 1e-6 so.)
 //
 // us per launch on fp32 MFMAs / so: critics 60+8-256-256 at 8192 rows 34.5 / 23.2, 512-256-128 81 / 48.5, 1024-512-256 at
 // 32768 rows 973 / 622 (188 TFLOP/s).  Bound by the latency of its loads (one chunk ahead): the vector units are busy a third of
@@ -381,17 +384,20 @@ __device__ inline float tn_load(__amdgpu_buffer_rsrc_t r, int voff, int soff) {
 }
 
 constexpr int TNS = 8;            // row pairs per chunk: one MFMA contracts the chunk's 16 rows
+constexpr int TN_TOP = 10;
 
-// One column's scale s = 2^e and the largest magnitude that it still fits.  The sums are brought from one scale to another, and
-// to none at the end, by adding exponents: a product of two columns' factors can leave fp32's range where the sum does not
-// (a column of values below 1e-32 beside one below 0.01: the factor is infinite, the sum still zero).
-struct ColumnScale { float s, limit; int e; };
+// A column's scale is held as the largest magnitude that it still fits, a power of two (0: no value other than zero seen yet):
+// limit * s = 2^15.  The sums are brought from one scale to another, and to none at the end, by adding exponents: a product of
+// two columns' factors can leave fp32's range where the sum does not (a column of values below 1e-32 beside one below 0.01: the
+// factor is infinite, the sum still zero).
+__device__ __forceinline__ float tn_scale(float limit) { return __uint_as_float((269u << 23) - __float_as_uint(limit)); }
+__device__ __forceinline__ int tn_exponent(float limit) { return limit > 0.f ? 142 - (int)(__float_as_uint(limit) >> 23) : 0; }
 
 // Eight values of a column as pairs.
 __device__ __forceinline__ void tn_split(const float (&x)[TNS], float s, u32x4 (&t)[2]) {
     unsigned h[4], l[4];
 #pragma unroll
-    for (int p = 0; p < 4; ++p) split16x2<false>(x[2 * p], x[2 * p + 1], s, h[p], l[p]);
+    for (int p = 0; p < 4; ++p) split16x2(x[2 * p], x[2 * p + 1], s, h[p], l[p]);
     t[0] = u32x4{h[0], h[1], h[2], h[3]};
     t[1] = u32x4{l[0], l[1], l[2], l[3]};
 }
@@ -401,18 +407,17 @@ __device__ __forceinline__ float tn_max(const float (&x)[TNS]) {
     for (int i = 1; i < TNS; ++i) m = fmaxf(m, fabsf(x[i]));
     return m;
 }
-// New scale of a column whose chunk exceeds the old one's limit (the halves of the wavefront hold the same column); returns
-// the power of two by which the sums so far are to be multiplied.
-__device__ __forceinline__ int tn_rescale(ColumnScale& c, float m) {
+// New scale of a column whose chunk exceeds the old one's limit (the halves of the wavefront hold the same column): its
+// largest magnitude goes to [2^TN_TOP, 2^(TN_TOP + 1)).  Returns the power of two by which the sums so far are to be multiplied.
+__device__ __forceinline__ int tn_rescale(float& limit, float m) {
     auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(m), __float_as_uint(m), false, false);
     m = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
-    if (!(m > c.limit)) return 0;
-    const int old = c.e;
-    float inv;
-    c.s = scale_for<7>(m, inv);
-    c.e = (int)(__float_as_uint(c.s) >> 23) - 127;
-    c.limit = 32768.f * inv;
-    return c.e - old;
+    if (!(m > limit)) return 0;
+    const int old = tn_exponent(limit);
+    int e = (int)(__float_as_uint(m) >> 23);
+    e = (e < 20 ? 20 : e) + 15 - TN_TOP;
+    limit = __uint_as_float((unsigned)(e > 255 ? 255 : e) << 23);
+    return tn_exponent(limit) - old;
 }
 __device__ __forceinline__ floatx16 mfma_f16(u32x4 a, u32x4 b, floatx16 c) {
     return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
@@ -481,11 +486,11 @@ __device__ inline void tn_stream_tile(const GemmProb& P, int split, int m0, int 
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
     float xa[TM][TNS], xb[2][TNS];
-    ColumnScale ca[TM], cb[2];
+    float ca[TM], cb[2];                                      // limits
 #pragma unroll
-    for (int i = 0; i < TM; ++i) ca[i] = ColumnScale{1.f, 0.f, 0};
+    for (int i = 0; i < TM; ++i) ca[i] = 0.f;
 #pragma unroll
-    for (int j = 0; j < 2; ++j) cb[j] = ColumnScale{1.f, 0.f, 0};
+    for (int j = 0; j < 2; ++j) cb[j] = 0.f;
     // exponents of the output rows (columns of A) to all lanes that hold a part of them; only this wavefront's own LDS words
     auto spread = [&](const int (&f)[TM], int (&out)[TM][16]) {
         __builtin_amdgcn_wave_barrier();
@@ -529,44 +534,49 @@ __device__ inline void tn_stream_tile(const GemmProb& P, int split, int m0, int 
             float ma[TM], mb[2];
             bool over = false;
 #pragma unroll
-            for (int j = 0; j < 2; ++j) { mb[j] = tn_max(xb[j]); over |= mb[j] > cb[j].limit; }
+            for (int j = 0; j < 2; ++j) { mb[j] = tn_max(xb[j]); over |= mb[j] > cb[j]; }
 #pragma unroll
-            for (int i = 0; i < TM; ++i) { ma[i] = tn_max(xa[i]); over |= ma[i] > ca[i].limit; }
+            for (int i = 0; i < TM; ++i) { ma[i] = tn_max(xa[i]); over |= ma[i] > ca[i]; }
             if (__ballot(over) != 0) {
                 int fa[TM], fb[2];
 #pragma unroll
                 for (int i = 0; i < TM; ++i) fa[i] = tn_rescale(ca[i], ma[i]);
 #pragma unroll
                 for (int j = 0; j < 2; ++j) fb[j] = tn_rescale(cb[j], mb[j]);
-                multiply(fa, fb);
+                if (c > 0) multiply(fa, fb);                     // (nothing summed yet)
             }
             // a value's registers are free once it is split: the same value of the next chunk is requested into
             // them at once (the fences keep the requests there) and has this chunk's matrix work to arrive
             u32x4 tb[2][2], ta[2];
 #pragma unroll
-            for (int j = 0; j < 2; ++j) tn_split(xb[j], cb[j].s, tb[j]);
+            for (int j = 0; j < 2; ++j) tn_split(xb[j], tn_scale(cb[j]), tb[j]);
             __builtin_amdgcn_sched_barrier(0);
             load_b(c + 1);
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int i = 0; i < TM; ++i) {
-                tn_split(xa[i], ca[i].s, ta);
+                tn_split(xa[i], tn_scale(ca[i]), ta);
                 __builtin_amdgcn_sched_barrier(0x008);
                 load_a(c + 1, i);
                 __builtin_amdgcn_sched_barrier(0x008);
 #pragma unroll
-                for (int j = 0; j < 2; ++j) acc[i][j] = mfma_f16(ta[1], tb[j][0], acc[i][j]);
+                for (int j = 0; j < 2; ++j) {
+                    floatx16 low;
 #pragma unroll
-                for (int j = 0; j < 2; ++j) acc[i][j] = mfma_f16(ta[0], tb[j][1], acc[i][j]);
+                    for (int r = 0; r < 16; ++r) low[r] = 0.f;
+                    low = mfma_f16(ta[1], tb[j][0], low);
+                    acc[i][j] = mfma_f16(ta[0], tb[j][0], acc[i][j]);
+                    low = mfma_f16(ta[0], tb[j][1], low);
 #pragma unroll
-                for (int j = 0; j < 2; ++j) acc[i][j] = mfma_f16(ta[0], tb[j][0], acc[i][j]);
+                    for (int r = 0; r < 16; ++r) acc[i][j][r] = __fmaf_rn(low[r], 1.f / PAIR_LO, acc[i][j][r]);
+                }
             }
         }
         int fa[TM], fb[2];
 #pragma unroll
-        for (int i = 0; i < TM; ++i) fa[i] = -ca[i].e;
+        for (int i = 0; i < TM; ++i) fa[i] = -tn_exponent(ca[i]);
 #pragma unroll
-        for (int j = 0; j < 2; ++j) fb[j] = -cb[j].e;
+        for (int j = 0; j < 2; ++j) fb[j] = -tn_exponent(cb[j]);
         multiply(fa, fb);
     }
     // The four partial tiles meet in LDS.  Every wavefront owns a quarter of the tile's accumulator registers

@@ -64,8 +64,8 @@ __device__ __forceinline__ void split16x8(const f32x4& a, const f32x4& b, float 
     unsigned h[4], l[4];
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
-        split16x2<true>(a[2 * i], a[2 * i + 1], s, h[i], l[i]);
-        split16x2<true>(b[2 * i], b[2 * i + 1], s, h[2 + i], l[2 + i]);
+        split16x2(a[2 * i], a[2 * i + 1], s, h[i], l[i]);
+        split16x2(b[2 * i], b[2 * i + 1], s, h[2 + i], l[2 + i]);
     }
     hi = u32x4{h[0], h[1], h[2], h[3]};
     lo = u32x4{l[0], l[1], l[2], l[3]};

@@ -308,3 +308,40 @@ def test_infinite_output_weights_give_saturated_actions(hidden):
         x = np.where(z > 0, z, np.expm1(np.minimum(z, 0)))
     clear = np.abs(x[:, 7]) > 1e-4
     assert np.array_equal(got[clear, 2], np.sign(x[clear, 7]).astype(np.float32))
+
+
+@pytest.mark.parametrize("batch,hidden", [(40, (64, 64)), (333, (96, 40)), (8192, (256, 256))])
+def test_weight_gradients_of_columns_with_outliers(batch, hidden):
+    """A column's scale is that of its largest value: states of 2^20 in some rows (the first a wavefront sees) and of order 1 in
+    the others, where the large ones meet a delta of exactly zero (the TD target of those rows is the critic's own Q value).
+    The small ones have to keep 32-bit precision: every row of critic 1's dW_1 to 1e-5 of its own largest entry."""
+    import torch
+    from test_gpu_parity import workspace_rows
+    w = workload(hidden, 21, 3, batch)
+    s, ring = session(w), oracle_ring(w)
+    fill_both(s, ring, w, w.nstep + 3)
+    s.sample(batch)
+    rng = np.random.default_rng(9)
+    b = {k: getattr(s.batch, k)[:batch].cpu().numpy().copy() for k in ("obs", "act", "ret", "next_obs", "boot")}
+    b["obs"] = rng.standard_normal((batch, w.obs_dim)).astype(np.float32)
+    large = np.arange(batch) % 64 == 0
+    cols = [2, 7, 20]
+    b["obs"][np.ix_(large, cols)] *= np.float32(2.0 ** 20)
+    b["boot"][:] = 0.0
+    c = s.critic_init.copy()
+    for h in (0, c.size // 2):
+        c[h:h + w.obs_dim * hidden[0]].reshape(w.obs_dim, -1)[cols] = 0.0       # the hidden layers do not see these columns
+    for _ in range(2):
+        for k in ("obs", "ret", "boot"):
+            getattr(s.batch, k)[:batch].copy_(torch.from_numpy(b[k]))
+        s.critic.copy_(torch.from_numpy(c))
+        s.critic_update(batch)
+        b["ret"][large] = workspace_rows(s, 1, batch)[large]
+    rest = {k: v[~large] for k, v in b.items()}
+    n, half = w.obs_dim * hidden[0], c.size // 2
+    _, g = O.critic_loss_and_grads(c, w.critic_dims(), rest, rest["ret"].astype(np.float64))
+    ref = g[:n].reshape(w.obs_dim, -1) * ((~large).sum() / batch)
+    x = s.c_g.cpu().numpy().astype(np.float64)[:n].reshape(w.obs_dim, -1)
+    err = np.abs(x - ref).max(1) / np.abs(ref).max(1)
+    print(batch, hidden, "columns with outliers %.2e" % err[cols].max(), "others %.2e" % np.delete(err, cols).max(), flush=True)
+    assert err.max() <= TOL
