@@ -387,10 +387,6 @@ void make_layout(const pql_config* c, Layout& w) {
             w.colQ[i][l] = take(crow * h);
         }
     }
-    const size_t targets = off;
-    for (int l = 1; l <= L; ++l)
-        for (int i = 0; i < 2; ++i) w.hT[i][l] = take(B * (size_t)c->hidden[l - 1]);
-    const size_t need = prepared_floats(c), targets_size = off - targets;
     w.colA[L + 1] = take(crow * (size_t)actor_out(c));
     w.aOut = take(B * c->act_dim);
     w.dPre = take(B * (size_t)actor_out(c));
@@ -404,23 +400,6 @@ void make_layout(const pql_config* c, Layout& w) {
     }
     w.p_loss = take(2 * nwg);
     for (int i = 0; i < 2; ++i) w.w1aT[i] = take((size_t)c->act_dim * c->hidden[0]);
-    // Prepared weights take the place of what no call holds at the same time: the target critics' activations where no batch
-    // of the context runs layer by layer, else the slabs of the weight gradients, which are written after the last product
-    // that reads the weights.  The slabs' room includes one transposed copy of every matrix behind a hidden layer; with it the
-    // prepared weights fit wherever the total nears the static scratch's 64 MiB, so that the configurations it takes are those
-    // of the kernels without prepared weights.
-    {
-        size_t copies = 0;
-        for (int l = 1; l <= L; ++l) {
-            if (l < L) copies += 2 * up((size_t)c->hidden[l - 1] * c->hidden[l]);
-            copies += up((size_t)c->hidden[l - 1] * (l < L ? c->hidden[l] : actor_out(c)));
-        }
-        if (distributional(c)) copies += 2 * up((size_t)c->num_atoms * c->hidden[L - 1]);
-        const size_t room = copies + up(splitk_floats(c, (int)B));
-        const bool beside = need <= targets_size && family(c, 1) != FAM_LAYERED && family(c, c->max_batch) != FAM_LAYERED;
-        w.splitk = take(beside || room > need ? room : need);
-        w.split = need == 0 ? 0 : (beside ? targets : w.splitk);
-    }
     {
         const size_t pa = (size_t)pql_actor_param_count(c), pc = 2 * (size_t)pql_critic_param_count(c);
         w.sqp = take(adam_reduce_blocks_bound(pa > pc ? pa : pc, RED_MAX_TENSORS));
@@ -441,6 +420,29 @@ void make_layout(const pql_config* c, Layout& w) {
             w.lgQ[i] = take(B * (size_t)c->num_atoms);
             w.p_dbo[i] = take(nwg * (size_t)c->num_atoms);
         }
+    // Prepared weights take the place of what no call holds at the same time: the slabs of the weight gradients, which are
+    // written after the last product that reads the weights, and where no batch of the context runs layer by layer also the
+    // target critics' activations before them.  The slabs' room includes one transposed copy of every matrix behind a hidden
+    // layer; with it the prepared weights fit wherever the total nears the static scratch's 64 MiB, so that the
+    // configurations it takes are those of the kernels without prepared weights.  (Narrow layers between wide ones, whose
+    // padding is large, can be the exception: they then run layer by layer without.)
+    const size_t targets = off, need = prepared_floats(c);
+    for (int l = 1; l <= L; ++l)
+        for (int i = 0; i < 2; ++i) w.hT[i][l] = take(B * (size_t)c->hidden[l - 1]);
+    w.splitk = off;
+    size_t copies = 0;
+    for (int l = 1; l <= L; ++l) {
+        if (l < L) copies += 2 * up((size_t)c->hidden[l - 1] * c->hidden[l]);
+        copies += up((size_t)c->hidden[l - 1] * (l < L ? c->hidden[l] : actor_out(c)));
+    }
+    if (distributional(c)) copies += 2 * up((size_t)c->num_atoms * c->hidden[L - 1]);
+    take(copies + up(splitk_floats(c, (int)B)));
+    const bool layered = family(c, 1) == FAM_LAYERED || family(c, c->max_batch) == FAM_LAYERED;
+    const size_t begin = layered ? w.splitk : targets, end = begin + up(need), limit = STATIC_SCRATCH_BYTES / sizeof(float);
+    if (need > 0 && (fused_ok(c) || end <= limit || off > limit)) {
+        w.split = begin;
+        off = end > off ? end : off;
+    }
     w.total = off;
 }
 
@@ -976,7 +978,7 @@ int32_t pql_actor_act(pql_ctx* c, const float* actor_params, const float* obs, i
             return PQL_OK;
         }
     }
-    const int fam = act_family(&c->cfg, num);
+    const int fam = w.split != 0 ? act_family(&c->cfg, num) : FAM_LAYERED;
     if (fam != FAM_LAYERED) {
         SplitActArgs sa;
         std::memset(&sa, 0, sizeof(sa));
@@ -993,7 +995,7 @@ int32_t pql_actor_act(pql_ctx* c, const float* actor_params, const float* obs, i
         sa.noise.key0 = (uint32_t)(c->cfg.seed & 0xffffffffu); sa.noise.key1 = (uint32_t)(c->cfg.seed >> 32);
         sa.noise.ctr2 = (uint32_t)((uint64_t)c->acts & 0xffffffffu); sa.noise.ctr3 = (uint32_t)((uint64_t)c->acts >> 32);
         sa.sac = fused_sac(c, 2u, c->acts, nullptr);
-        hipError_t se = split_weights_launch(prep.args, fam == FAM_CHAIN ? KID_CHAIN_ACT : KID_FUSED_ACT, st);
+        hipError_t se = split_weights_launch(prep.args, false, fam == FAM_CHAIN ? KID_CHAIN_ACT : KID_FUSED_ACT, st);
         if (se == hipSuccess) se = split_act_launch(sa, fam, st);
         if (se != hipSuccess) return E.hip(se, "pql_actor_act");
         c->acts += 1;
@@ -1010,7 +1012,7 @@ int32_t pql_actor_act(pql_ctx* c, const float* actor_params, const float* obs, i
     if (layers_prepared(w, num, 1)) {
         SplitPrep prep(ws + w.split);
         add_layers(c, prep, actor_params, true, fp);
-        if ((e = split_weights_launch(prep.args, KID_SPLIT_WEIGHTS, st)) != hipSuccess) return E.hip(e, "pql_actor_act");
+        if ((e = split_weights_launch(prep.args, true, KID_SPLIT_WEIGHTS, st)) != hipSuccess) return E.hip(e, "pql_actor_act");
     }
     e = actor_hidden_forward(c, actor_params, obs, num, ws, w, fp.l, st);
     if (e != hipSuccess) return E.hip(e, "pql_actor_act");
@@ -1101,7 +1103,7 @@ static int32_t critic_update_run(pql_ctx* c, float* critic_params, const float* 
         sa.y = ws + w.y; sa.p_loss = ws + w.p_loss;
         if (dist) { sa.atoms = c->cfg.num_atoms; sa.v_min = c->cfg.v_min; sa.v_max = c->cfg.v_max; }
         sa.sac = fused_sac(c, 4u, c->critic_t, c->temperature_v);
-        if ((e = split_weights_launch(prep.args, KID_SPLIT_WEIGHTS, st)) != hipSuccess) return E.hip(e, who);
+        if ((e = split_weights_launch(prep.args, true, KID_SPLIT_WEIGHTS, st)) != hipSuccess) return E.hip(e, who);
         if ((e = split_critic_launch(sa, fam, st)) != hipSuccess) return E.hip(e, who);
         head_parts = (B + FUSED_BM - 1) / FUSED_BM;
         for (int i = 0; i < 2; ++i)
@@ -1118,7 +1120,7 @@ static int32_t critic_update_run(pql_ctx* c, float* critic_params, const float* 
                 add_layers(c, prep, critic_params + i * Pc, false, fq[i]);
                 add_layers_back(c, prep, critic_params + i * Pc, false, fb[i]);
             }
-            if ((e = split_weights_launch(prep.args, KID_SPLIT_WEIGHTS, st)) != hipSuccess) return E.hip(e, who);
+            if ((e = split_weights_launch(prep.args, true, KID_SPLIT_WEIGHTS, st)) != hipSuccess) return E.hip(e, who);
         }
         // 1. lagged policy pi^v on s' (hidden layers) together with the online critics on (s, a)
         for (int l = 1; l <= L; ++l) {
@@ -1405,7 +1407,7 @@ int32_t pql_actor_update(pql_ctx* c, float* actor_params, const float* critic_pa
         sa.sac = fused_sac(c, 5u, c->actor_t, c->temperature);
         sa.p_logp = sac ? ws + w.p_lp : nullptr;
         if (distributional(&c->cfg)) { sa.atoms = c->cfg.num_atoms; sa.v_min = c->cfg.v_min; sa.v_max = c->cfg.v_max; }
-        if ((e = split_weights_launch(prep.args, KID_SPLIT_WEIGHTS, st)) != hipSuccess) return E.hip(e, who);
+        if ((e = split_weights_launch(prep.args, true, KID_SPLIT_WEIGHTS, st)) != hipSuccess) return E.hip(e, who);
         if ((e = split_policy_launch(sa, fam, st)) != hipSuccess) return E.hip(e, who);
         loss_parts = (B + FUSED_BM - 1) / FUSED_BM;
         logp_parts = loss_parts;
@@ -1421,7 +1423,7 @@ int32_t pql_actor_update(pql_ctx* c, float* actor_params, const float* critic_pa
                 add_layers(c, prep, critic_params + i * Pc, false, fq[i]);
                 add_layers_back(c, prep, critic_params + i * Pc, false, fb[i]);
             }
-            if ((e = split_weights_launch(prep.args, KID_SPLIT_WEIGHTS, st)) != hipSuccess) return E.hip(e, who);
+            if ((e = split_weights_launch(prep.args, true, KID_SPLIT_WEIGHTS, st)) != hipSuccess) return E.hip(e, who);
         }
         // 1. a = pi(s), or the reparameterised sample a = tanh(mu + sigma eps)
         if ((e = actor_hidden_forward(c, actor_params, obs, B, ws, w, fp.l, st)) != hipSuccess) return E.hip(e, who);

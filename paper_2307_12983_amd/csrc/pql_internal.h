@@ -367,14 +367,14 @@ enum SplitKind : int { SPLIT_PLAIN = 0, SPLIT_TRANSPOSED = 1, SPLIT_VECTOR = 2 }
 constexpr int SPLIT_MAX_MATS = 9 + 4 * 9 + 2 * 8;
 struct SplitPrepArgs {
     float* dst;
-    int n;
+    int n, both;                         // both: whether the other lo terms are wanted (filled by the launch function)
     int first[64];                       // first workgroup of each record, filled by the launch function
     struct Mat { const float *src, *bias; int dst, K, N, kind; } m[SPLIT_MAX_MATS];     // dst: offset in floats
 };
 static_assert(SPLIT_MAX_MATS <= 64, "a wavefront looks its record up with one lane each");
 size_t split_mat_floats(int K, int N);
 // kid: the class the launch is filed under (the Actor step counts its preparation as part of itself)
-hipError_t split_weights_launch(SplitPrepArgs& a, int kid, hipStream_t stream);
+hipError_t split_weights_launch(SplitPrepArgs& a, bool both, int kid, hipStream_t stream);
 
 struct SplitShape {
     int o, a, L;

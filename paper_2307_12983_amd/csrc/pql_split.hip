@@ -39,23 +39,25 @@ constexpr int SW = 8;                // wavefronts per workgroup
 constexpr int ST = 64 * SW;          // threads per workgroup
 constexpr int PT = 1024;             // threads per workgroup of the preparation
 constexpr int PREP_ITEMS = SPLIT_MAXK / 256;   // pieces of eight values per thread
+constexpr int STEP_UNITS = 384;      // 16-byte units of one k-step of a prepared 32-column tile
 constexpr int CS = 33;               // 16-byte units per k-chunk of a tile: 32 rows and one of padding against bank conflicts
 
 // ---- layouts ----------------------------------------------------------------------------------------
-// A prepared matrix (K x N): fragments [N/32][K/32][16-column half][hi, lo][lane] of 16 bytes, then the bias padded with
-// zeros to whole tiles, then the inverse scale of every 32-column tile.  Lane (l15 = lane & 15,
+// A prepared matrix (K x N): fragments [N/32][K/32][hi, lo, other lo][16-column half][lane] of 16 bytes (see
+// split_weights_kernel; workgroups with odd numbers read the other lo terms), then the bias padded with zeros to whole tiles,
+// then the inverse scale of every 32-column tile.  Lane (l15 = lane & 15,
 // q = lane >> 4) holds column 16 half + l15 for the eight k-values k_slot(step, q, i).
 __host__ __device__ __forceinline__ int k_slot(int step, int q, int i) { return 32 * step + 16 * (i >> 2) + 4 * q + (i & 3); }
 size_t split_mat_floats(int K, int N) {
     const size_t ks = (size_t)((K + 31) / 32), tiles = (size_t)((N + 31) / 32);
-    return tiles * ks * 1024 + tiles * 33;
+    return tiles * ks * (4 * STEP_UNITS) + tiles * 33;
 }
 struct MatView { const u32x4* frag; const float* inv; const float* bias; int ks, tiles; };
 __device__ __forceinline__ MatView mat_view(const float* base, int K, int N) {
     MatView m;
     m.ks = (K + 31) >> 5; m.tiles = (N + 31) >> 5;
     m.frag = reinterpret_cast<const u32x4*>(base);
-    m.bias = base + (size_t)m.tiles * m.ks * 1024;
+    m.bias = base + (size_t)m.tiles * m.ks * (4 * STEP_UNITS);
     m.inv = m.bias + (size_t)m.tiles * 32;
     return m;
 }
@@ -69,6 +71,14 @@ __device__ __forceinline__ void split16x8(const f32x4& a, const f32x4& b, float 
     }
     hi = u32x4{h[0], h[1], h[2], h[3]};
     lo = u32x4{l[0], l[1], l[2], l[3]};
+}
+
+// The lo terms of two values at the same distance from the exact remainders as the given ones, on the other side.
+__device__ __forceinline__ unsigned other_lo(float x0, float x1, float s, unsigned hi, unsigned lo) {
+    const f16x2 h = __builtin_bit_cast(f16x2, hi), l = __builtin_bit_cast(f16x2, lo);
+    const float r0 = __fmaf_rn((float)h[0], -PAIR_LO, x0 * s * PAIR_LO), r1 = __fmaf_rn((float)h[1], -PAIR_LO, x1 * s * PAIR_LO);
+    const f16x2 o = {(_Float16)__fmaf_rn(2.f, r0, -(float)l[0]), (_Float16)__fmaf_rn(2.f, r1, -(float)l[1])};
+    return __builtin_bit_cast(unsigned, o);
 }
 
 // Reductions across the four 16-lane rows of a wavefront (same l15) and inside one of them.
@@ -102,6 +112,14 @@ __device__ __forceinline__ float half_max(float x) {          // over the 32 lan
 // ---- weights into fragment order ------------------------------------------------------------------------
 // One workgroup per 32-column tile: every element is read once (all requests in flight together), kept in registers while
 // the tile's largest magnitude is found, and written as fragments.  Latency-bound: one round trip each way.
+//
+// Two fp16 terms and the sign of lo hold 23 of a weight's 24 significant bits; half of the weights whose lo is in its upper
+// octave lie exactly between two pairs.  Rounded the same way for all rows of a batch, those errors add up in the gradients,
+// where the errors of activations average out: 1.1e-7 of a policy gradient of 512-256-128 at 8192 rows where the fp32 MFMA
+// kernels were off by 0.9e-7.  So there are two sets of lo terms, the second rounded to the other neighbour (lo' =
+// fp16(2 r - lo), r the exact remainder), and every second row tile takes the second: on average over the batch the weights are
+// exact (0.7e-7).  Workgroups go round the eight XCDs, so an L2 still holds one set.  The Actor step, whose rows stand alone,
+// takes the first throughout.
 __global__ __launch_bounds__(PT) void split_weights_kernel(const SplitPrepArgs) {
     const SplitPrepArgs& P = kernel_args<SplitPrepArgs>();
     __shared__ float red[PT / 64];
@@ -170,17 +188,22 @@ __global__ __launch_bounds__(PT) void split_weights_kernel(const SplitPrepArgs) 
     }
     float inv;
     const float s = scale_for(mx, inv);
-    u32x4* frag = reinterpret_cast<u32x4*>(dst) + (size_t)tile * ks * 256;
-    float* tail = dst + (size_t)tiles * ks * 1024;
+    u32x4* frag = reinterpret_cast<u32x4*>(dst) + (size_t)tile * ks * STEP_UNITS;
+    float* tail = dst + (size_t)tiles * ks * (4 * STEP_UNITS);
+    auto place = [&](int e) { return frag + (size_t)(e >> 7) * STEP_UNITS + ((e >> 6) & 1) * 64 + lane; };       // piece e's hi terms
 #pragma unroll
     for (int it = 0; it < PREP_ITEMS; ++it) {
         const int e = it * PT + tid;
         if (e >= items) break;
-        u32x4 hi, lo;
+        u32x4 hi, lo, lo2;
         split16x8(v[it][0], v[it][1], s, hi, lo);
-        u32x4* d = frag + (size_t)(e >> 6) * 128 + lane;
+        u32x4* d = place(e);
         d[0] = hi;
-        d[64] = lo;
+        d[128] = lo;
+        if (!P.both) continue;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) lo2[i] = other_lo(v[it][i >> 1][2 * (i & 1)], v[it][i >> 1][2 * (i & 1) + 1], s, hi[i], lo[i]);
+        d[256] = lo2;
     }
     if (infinite) {          // as hi = 0, lo = +-inf: one product with the sign of x_hi, none with x_lo
 #pragma unroll 1
@@ -189,17 +212,19 @@ __global__ __launch_bounds__(PT) void split_weights_kernel(const SplitPrepArgs) 
             for (int i = 0; i < 8; ++i) {
                 const float x = buf_load(rs, offset(e, i), 0);
                 if (!(fabsf(x) > FLT_MAX)) continue;
-                char* d = reinterpret_cast<char*>(frag + (size_t)(e >> 6) * 128 + lane) + 2 * i;
+                char* d = reinterpret_cast<char*>(place(e)) + 2 * i;
                 const uint16_t hi = 0, lo = x > 0.f ? 0x7c00 : 0xfc00;
                 __builtin_memcpy(d, &hi, 2);
-                __builtin_memcpy(d + 64 * 16, &lo, 2);
+                __builtin_memcpy(d + 128 * 16, &lo, 2);
+                if (P.both) __builtin_memcpy(d + 256 * 16, &lo, 2);
             }
     }
     if (tid == 0) tail[tiles * 32 + tile] = inv;
     if (tid < 32) tail[tile * 32 + tid] = bias;
 }
 
-hipError_t split_weights_launch(SplitPrepArgs& a, int kid, hipStream_t stream) {
+hipError_t split_weights_launch(SplitPrepArgs& a, bool both, int kid, hipStream_t stream) {
+    a.both = both ? 1 : 0;
     int blocks = 0;
     double bytes = 0.0;
     for (int i = 0; i < 64; ++i) {
@@ -207,7 +232,7 @@ hipError_t split_weights_launch(SplitPrepArgs& a, int kid, hipStream_t stream) {
         if (i >= a.n) continue;
         if (a.m[i].kind != SPLIT_VECTOR && a.m[i].K > SPLIT_MAXK) return hipErrorInvalidValue;
         blocks += a.m[i].kind == SPLIT_VECTOR ? 1 : (a.m[i].N + 31) / 32;
-        bytes += 8.0 * a.m[i].K * a.m[i].N;
+        bytes += (both ? 10.0 : 8.0) * a.m[i].K * a.m[i].N;
     }
     if (blocks == 0) return hipSuccess;
     const ProfSlot ps = prof_slot();
@@ -217,7 +242,7 @@ hipError_t split_weights_launch(SplitPrepArgs& a, int kid, hipStream_t stream) {
 }
 
 // ---- a layer on the tile --------------------------------------------------------------------------------
-struct Wv { int tid, lane, wave, l15, q; };
+struct Wv { int tid, lane, wave, l15, q; unsigned hi, lo; };        // hi, lo: this lane's byte offsets into a k-step's fragments
 
 // Barrier for data in LDS only: __syncthreads() would also wait for every store to memory and every weight request that
 // is meant to stay in flight across it.
@@ -233,23 +258,26 @@ __device__ __forceinline__ u32x4* lds_units() { return reinterpret_cast<u32x4*>(
 // then lo terms.  base and plane in 16-byte units.
 struct Tile { int base, plane; };
 
-// The fragments of two k-steps of a 32-column tile (4 KB each): the requests run two steps ahead of the matrix work, also
+// The fragments of two k-steps of a 32-column tile (4 KB each, hi and lo of its halves): the requests run two steps ahead of the matrix work, also
 // from one product to the next (over the epilogue and its barriers), so every product is told where the following one begins.
 struct Ahead { u32x4 w[2][4]; };
 struct Begin { const u32x4* first; const u32x4* second; };
 __device__ __forceinline__ Begin begin_of(const MatView& W, int tile, int s0, int ds) {
     const int t = tile < W.tiles ? tile : 0, a = s0 < W.ks ? s0 : 0, b = s0 + ds < W.ks ? s0 + ds : a;     // (an idle wavefront requests something valid)
-    return {W.frag + (size_t)(t * W.ks + a) * 256, W.frag + (size_t)(t * W.ks + b) * 256};
+    return {W.frag + (size_t)(t * W.ks + a) * STEP_UNITS, W.frag + (size_t)(t * W.ks + b) * STEP_UNITS};
 }
 __device__ __forceinline__ Begin begin_at(const float* mat) {
     return {reinterpret_cast<const u32x4*>(mat), reinterpret_cast<const u32x4*>(mat)};
 }
 __device__ __forceinline__ void request(Ahead& a, const Begin& p, const Wv& T) {
-    const unsigned off = (unsigned)T.lane * 16u;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) a.w[0][i] = *reinterpret_cast<const u32x4*>(reinterpret_cast<const char*>(p.first) + off + i * 1024);
+    for (int st = 0; st < 2; ++st) {
+        const char* step = reinterpret_cast<const char*>(st == 0 ? p.first : p.second);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) a.w[1][i] = *reinterpret_cast<const u32x4*>(reinterpret_cast<const char*>(p.second) + off + i * 1024);
+        for (int m = 0; m < 2; ++m) a.w[st][m] = *reinterpret_cast<const u32x4*>(step + T.hi + m * 1024);
+#pragma unroll
+        for (int m = 0; m < 2; ++m) a.w[st][2 + m] = *reinterpret_cast<const u32x4*>(step + T.lo + m * 1024);
+    }
 }
 
 // acc[m][n] = 16x16 products of weight columns 32 tile + 16 m .. with batch rows 16 n .., steps s0, s0 + ds, ...  `cur`
@@ -259,7 +287,7 @@ __device__ __forceinline__ void request(Ahead& a, const Begin& p, const Wv& T) {
 template <int NB>
 __device__ __forceinline__ void mac_steps(f32x4 (&acc)[2][NB], const MatView& W, int tile, const Tile& X, const Wv& T, int s0, int ds,
                                           Ahead& cur, const Begin& next) {
-    const u32x4* p = W.frag + (size_t)tile * W.ks * 256;
+    const u32x4* p = W.frag + (size_t)tile * W.ks * STEP_UNITS;
     f32x4 low[2][NB];
 #pragma unroll
     for (int m = 0; m < 2; ++m)
@@ -277,7 +305,7 @@ __device__ __forceinline__ void mac_steps(f32x4 (&acc)[2][NB], const MatView& W,
         for (int c = 0; c < 3; ++c)
 #pragma unroll
             for (int m = 0; m < 2; ++m) {
-                const f16x8 a = __builtin_bit_cast(f16x8, c == 0 ? w[2 * m + 1] : w[2 * m]);
+                const f16x8 a = __builtin_bit_cast(f16x8, c == 0 ? w[2 + m] : w[m]);
 #pragma unroll
                 for (int n = 0; n < NB; ++n) {
                     if (c == 0) low[m][n] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a, xh[n], low[m][n], 0, 0, 0);
@@ -289,7 +317,7 @@ __device__ __forceinline__ void mac_steps(f32x4 (&acc)[2][NB], const MatView& W,
     auto step = [&](int s, Ahead& have, Ahead& get) {      // steps s and s + ds from `have`, the two after them requested into `get`
         const int s2 = s + 2 * ds, s3 = s + 3 * ds;
         Begin b = next;
-        if (s2 < W.ks) b = {p + (size_t)s2 * 256, p + (size_t)(s3 < W.ks ? s3 : s2) * 256};
+        if (s2 < W.ks) b = {p + (size_t)s2 * STEP_UNITS, p + (size_t)(s3 < W.ks ? s3 : s2) * STEP_UNITS};
         request(get, b, T);
         __builtin_amdgcn_sched_barrier(0);
         mac(s, have.w[0]);
@@ -815,10 +843,11 @@ __device__ __forceinline__ void put_dlogits(const float (&dl)[2][DR], int at, in
         }
 }
 
-__device__ __forceinline__ Wv wave_of() {
+__device__ __forceinline__ Wv wave_of(int other) {        // other: whether the workgroup reads the other lo terms
     Wv T;
     T.tid = threadIdx.x; T.lane = T.tid & 63; T.wave = __builtin_amdgcn_readfirstlane(T.tid >> 6);
     T.l15 = T.lane & 15; T.q = T.lane >> 4;
+    T.hi = (unsigned)T.lane * 16u; T.lo = T.hi + 2048u + (unsigned)other * 2048u;
     return T;
 }
 
@@ -831,7 +860,7 @@ template <int NN, int TPW, int VAR>
 __device__ __forceinline__ void critic_step(const SplitCriticArgs& A) {
     warm_args<SplitCriticArgs>();
     constexpr bool SAC = VAR == VAR_SAC, DIST = VAR == VAR_DIST;
-    const Wv T = wave_of();
+    const Wv T = wave_of(blockIdx.x & 1);
     const SplitShape& P = A.shape;
     const int B = A.B, L = P.L, a = P.a, HL = P.H[L - 1];
     const int r0 = blockIdx.x * 32, wg = blockIdx.x, nwg = gridDim.x;
@@ -1079,7 +1108,7 @@ template <int NN, int TPW, int VAR>
 __device__ __forceinline__ void policy_step(const SplitPolicyArgs& A) {
     warm_args<SplitPolicyArgs>();
     constexpr bool SAC = VAR == VAR_SAC, DIST = VAR == VAR_DIST;
-    const Wv T = wave_of();
+    const Wv T = wave_of(blockIdx.x & 1);
     const SplitShape& P = A.shape;
     constexpr int TPA = NN == 2 ? TPW / 2 : TPW;       // the policy's tiles per wavefront
     const int B = A.B, L = P.L, a = P.a, HL = P.H[L - 1], H1 = P.H[0];
@@ -1326,7 +1355,7 @@ template <int TPW, int VAR>
 __device__ __forceinline__ void act_step(const SplitActArgs& A) {
     warm_args<SplitActArgs>();
     constexpr bool SAC = VAR == VAR_SAC;
-    const Wv T = wave_of();
+    const Wv T = wave_of(0);
     const SplitShape& P = A.shape;
     const int B = A.B, a = P.a, r0 = blockIdx.x * 32;
     const int aw = SAC ? 2 * a : a;
@@ -1479,7 +1508,7 @@ __device__ __forceinline__ void layer_rows(const GemmProb& P, int K, int ks, int
 template <int NB>
 __global__ __launch_bounds__(ST) void layer_rowtile_kernel(const GemmGroup) {
     const GemmGroup& G = kernel_args<GemmGroup>();
-    const Wv T = wave_of();
+    const Wv T = wave_of(blockIdx.x & 1);
     const int b = blockIdx.x;
     const GemmProb& P = G.p[record_of(G.p, &GemmProb::tile_begin, G.nprob, b)];
     const int K = P.seg[0].K + (P.nseg > 1 ? P.seg[1].K : 0), N = P.N, M = P.M;
