@@ -1659,8 +1659,8 @@ bool split_shape_ok(int o, int a, int aw, const int* H, int L, bool dist) {
 }
 
 // ---- kernels ------------------------------------------------------------------------------------------------------
-// fused_*: every layer at most 256 wide; chain_*: a widest layer of 512 (four output tiles per wavefront); split_*: the
-// other shapes, layers above 512 with the critics one after the other.
+// fused_*: every layer at most 256 wide (two output tiles per wavefront); chain_*: at most 512, scalar critics and deterministic
+// policy (four); split_*: at most 512 with the other variants, and layers above 512 with the critics one after the other.
 template <int VAR>
 __global__ __launch_bounds__(ST) void fused_critic_kernel(const SplitCriticArgs) { critic_step<2, 2, VAR>(kernel_args<SplitCriticArgs>()); }
 template <int VAR>
@@ -1688,13 +1688,14 @@ __global__ __launch_bounds__(ST) void chain_act_kernel(const SplitActArgs) { act
         prof_commit(ps, KID, flops, 0.0);                                                                          \
         return hipGetLastError();                                                                                  \
     } while (0)
-// Picks the kernel of one step: class, shape and policy variant are fixed at compile time.
+// Picks the kernel of one step: shape and policy variant are fixed at compile time, one kernel for each pair that occurs (the
+// class only decides what a launch is filed under).
 #define SPLIT_PICK(STEP, VAR)                                                                                      \
     do {                                                                                                           \
-        if (kind == SPLIT_FUSED) SPLIT_LAUNCH((fused_##STEP##_kernel<VAR>), fused_kid);                            \
-        if (kind == SPLIT_CHAIN && VAR == VAR_PLAIN) SPLIT_LAUNCH((chain_##STEP##_kernel<VAR_PLAIN>), chain_kid);  \
-        if (w <= 256) SPLIT_LAUNCH((split_##STEP##_kernel<2, 2, VAR>), split_kid);                                 \
-        if (w <= 512) SPLIT_LAUNCH((split_##STEP##_kernel<2, 4, VAR>), split_kid);                                 \
+        if (w <= 256) SPLIT_LAUNCH((fused_##STEP##_kernel<VAR>), kind == SPLIT_FUSED ? fused_kid : split_kid);     \
+        if (w <= 512 && VAR == VAR_PLAIN)                                                                          \
+            SPLIT_LAUNCH((chain_##STEP##_kernel<VAR_PLAIN>), kind == SPLIT_CHAIN ? chain_kid : split_kid);         \
+        if (w <= 512) SPLIT_LAUNCH((split_##STEP##_kernel<2, 4, VAR == VAR_PLAIN ? VAR_SAC : VAR>), split_kid);    \
         if (VAR != VAR_DIST) SPLIT_LAUNCH((split_##STEP##_kernel<1, 4, VAR == VAR_DIST ? VAR_PLAIN : VAR>), split_kid); \
     } while (0)
 
