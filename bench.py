@@ -35,7 +35,9 @@ from paper_2307_12983_amd import profile_tools  # noqa: E402
 
 PEAK_FP32_MFMA_TFLOPS = 157.3     # MI355X dense fp32 matrix peak
 # Kernels that multiply fp32 values as fp16 pairs issue three fp16 products per fp32 one: their peak is a third of the dense
-# fp16 peak (2.5 PFLOP/s).  The power limit holds a register-only loop of such products with real data to 544.
+# fp16 peak (2.5 PFLOP/s).  What a register-only loop of such products sustains on non-trivial data (the power limit lowers the
+# clock to 1.6 GHz) is a stored constant, measured once with a stand-alone program and not in this run; the library's probe
+# (fp32_mfma_probe) runs fp32 MFMAs.
 PEAK_PAIRS_TFLOPS = 2516.6 / 3
 SUSTAINED_PAIRS_TFLOPS = 544.0
 FP32_MFMA_KERNELS = ("fused_act16_kernel", "narrow_rowtile_kernel", "gemm_grouped_")
@@ -350,6 +352,8 @@ def run_workload(w, args, steps, warmup, profile_steps, isolated, keep_rows, sch
                      "avg_launch_us": 1e3 * dom["total_ms"] / dom["launches"], "launches": dom["launches"],
                      "arithmetic": "fp32 as fp16 pairs, three products" if pairs else "fp32 MFMA",
                      "achievable_peak": achievable, "frac_of_achievable": achieved / achievable,
+                     "achievable_source": ("stored: stand-alone register-only loop, not this run" if pairs else
+                                           "register-only probe in this run"),
                      "fp32_mfma_probe": mfma_ceiling,
                      "all_gemm_tflops": tot_gemm_flops / (tot_gemm_ms * 1e-3) / 1e12},
         "hbm": {"peak_gbs": PEAK_HBM_GBS, "copy_gbs": hbm_copy_gbs, "copy_frac": hbm_copy_gbs / PEAK_HBM_GBS,

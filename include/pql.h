@@ -336,15 +336,15 @@ int32_t pql_soft_update(pql_ctx* ctx, const float* src, float* dst, int64_t coun
 #define PQL_TRACK_LAGGED_POLICY  1
 int32_t pql_track_attach(pql_ctx* ctx, int32_t which, float* dst, float tau);
 
-/* Transposed copies of the online critics' and the policy's weight matrices.  Most products read weights that
- * every call prepares for itself; the action gradient of the layer-by-layer path reads these copies, and without
- * a cache such an update transposes them into its workspace first (one small launch per call).  With a caller-owned [device] block of pql_weight_cache_bytes(cfg) bytes, 256-byte aligned,
- * attached, the copies live there between calls: pql_weight_cache_refresh(ctx, critic_params, actor_params)
- * fills it from the given vectors (either may be NULL) and remembers their addresses; a later
- * pql_critic_update / pql_actor_update whose critic_params / actor_params argument is that same address
- * reads the block instead of transposing, and the optimiser kernel writes the transposes of the parameters
- * it has just updated back into it.  Calls with other parameter vectors (a snapshot, another network) are
- * unaffected: they transpose into their workspace as before.
+/* Transposed copies of the online critics' and the policy's weight matrices, kept up to date between calls.  One
+ * call reads them: pql_actor_update, where it runs layer by layer at more than 8160 rows, takes the action rows of
+ * the critics' first layers from here instead of transposing them into its workspace (one small launch).  Every other product reads weights that each call prepares
+ * for itself.  With a caller-owned [device] block of pql_weight_cache_bytes(cfg) bytes, 256-byte aligned,
+ * attached, pql_weight_cache_refresh(ctx, critic_params, actor_params) fills it from the given vectors (either may
+ * be NULL) and remembers their addresses; a later pql_critic_update / pql_actor_update whose critic_params /
+ * actor_params argument is that same address leaves the transposes of the parameters it has just updated in the
+ * block (the optimiser kernel writes them).  Calls with other parameter vectors (a snapshot, another network) do
+ * not touch it.
  * The caller must call pql_weight_cache_refresh again after changing a remembered vector by any other
  * means (a copy into it, pql_adam_step, pql_soft_update with it as dst, loading a checkpoint) and before
  * the first update; attaching (also NULL, which detaches) forgets both vectors.  Results are the same with

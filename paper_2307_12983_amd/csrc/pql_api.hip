@@ -272,8 +272,13 @@ int max_hidden(const pql_config* c) {
 // 64 / 520 / 1024 / 2048 / 4096 / 8000 rows: 1024-512-256 335 / 341 / 341 / 351 / 380 / 493 us against 263 / 288 / 312 / 413 /
 // 358 / 616; 512-512-512 254 / 259 / 261 / 276 / 293 / 373 against 249 / 258 / 279 / 353 / 314 / 516; 300-136-128 93 / 99 /
 // 100 / 102 / 110 / 131 against 137 / 143 / 147 / 165 / 141 / 212: the line is at 2048 rows, and at no batch for critics of up
-// to 2^18 weights.  Above (256 row tiles), every layer's launch has enough work of its own, unless the variant has steps that
-// only the one-launch kernels have on the 16-bit matrix cores.
+// to 2^18 weights.
+// Above 256 row tiles the scalar deterministic variant goes layer by layer unless the chain kernels' shape rule takes it.  That
+// rule and the bound are older than the kernels they now choose between, and the measurements do not support them: per critic
+// update at 8192 / 16384 / 32768 rows, one launch against a launch per layer, 1024-512-256 with 60 states 500 / 998 / 1960 us
+// against 636 / 1172 / 2200, with 211 states 628 / 1220 / 2438 against 720 / 1310 / 2464; 512-512-512 389 / 726 / 1428 against
+// 499 / 880 / 1650; 480-480-256 306 / 597 / 1120 against 436 / 728 / 1342; 300-136-128 128 / 231 / 462 against 209 / 352 / 669;
+// 200-100 72 / 120 / 216 against 144 / 230 / 416.  (Networks with a layer above 1024 have no other path.)
 constexpr int CHAIN_MIN_TILES = 128;
 constexpr int LAYERED_MIN_TILES = 256;
 constexpr int SPLIT_MIN_TILES = 64;
@@ -303,7 +308,8 @@ int family(const pql_config* c, int rows) {
     return tiles < LAYERED_MIN_TILES || (!plain && max_hidden(c) <= 512) ? FAM_SPLIT : FAM_LAYERED;
 }
 // The Actor step where fused_act16_kernel (16-row tiles, up to 4096 environments) does not apply: the row-tile kernels on
-// prepared weights for the shapes of the fused and chain kernels, else layer by layer.
+// prepared weights for the shapes of the fused and chain kernels, else layer by layer (the row-tile kernels take any width up to
+// 512; which is faster for the other shapes has not been measured).
 int act_family(const pql_config* c, int rows) {
     if (fused_ok(c)) return FAM_FUSED;
     const bool narrow = split_shape_ok(c->obs_dim, c->act_dim, actor_out(c), c->hidden, c->n_hidden);
