@@ -374,11 +374,11 @@ int gemm_waves_m(int tile) { return tile == TILE_128x32 ? 4 : 2; }
 // bits: 5e-4 of a gradient where states of 2^20 in a few rows meet deltas of zero, 1e-6 so.)
 //
 // us per launch on fp32 MFMAs / so: critics 60+8-256-256 at 8192 rows 34.5 / 23, 512-256-128 81 / 48, 1024-512-256 at 32768 rows
-// 973 / 650 (180 TFLOP/s); with unscaled lo terms 22, 44 and 622.  Bound by the latency of its loads (one chunk ahead) and, a
-// third of the time, by the vector units' splitting and joining.  Slower: the cross products' sums kept over all chunks with
-// two chunks requested ahead, which leaves two workgroups per compute unit (25, 51, 645; with the split count chosen for those
-// 27, 47, 670); with lo unscaled, 128 x 128 tiles shared through LDS (every value read and split once per workgroup, 28 and
-// 622 - 679): wavefronts that never wait for each other hide more than eight in step.
+// 973 / 650 (180 TFLOP/s); with unscaled lo terms 22, 44 and 622.  Bound by the latency of its loads (one chunk ahead): matrix
+// instructions take 0.76 of a compute unit's busy cycles and vector instructions 0.61, of the four SIMDs' four.  Slower: the
+// cross products' sums kept over all chunks with two chunks requested ahead, which leaves two workgroups per compute unit (25, 51,
+// 645; with the split count chosen for those 27, 47, 670); with lo unscaled, 128 x 128 tiles shared through LDS (every value read
+// and split once per workgroup, 28 and 622 - 679): wavefronts that never wait for each other hide more than eight in step.
 // TM = 32-row tiles of the output per wavefront (1 for outputs of at most 32 rows).
 // =============================================================================================
 __device__ inline float tn_load(__amdgpu_buffer_rsrc_t r, int voff, int soff) {
