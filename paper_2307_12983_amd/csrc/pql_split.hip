@@ -59,8 +59,8 @@ __device__ __forceinline__ MatView mat_view(const float* base, int K, int N) {
     MatView m;
     m.ks = (K + 31) >> 5; m.tiles = (N + 31) >> 5;
     m.frag = reinterpret_cast<const u32x4*>(base);
-    m.bias = base + (size_t)m.tiles * m.ks * (4 * STEP_UNITS);
-    m.inv = m.bias + (size_t)m.tiles * 32;
+    m.bias = base + (unsigned)(m.tiles * m.ks * (4 * STEP_UNITS));
+    m.inv = m.bias + (unsigned)(m.tiles * 32);
     return m;
 }
 
@@ -245,6 +245,12 @@ hipError_t split_weights_launch(SplitPrepArgs& a, bool both, int kid, hipStream_
 
 // ---- a layer on the tile --------------------------------------------------------------------------------
 struct Wv { int tid, lane, wave, l15, q; unsigned hi, lo; };        // hi, lo: this lane's byte offsets into a k-step's fragments
+// R: what is rare is not compiled in (an input of more than XV steps or in the place of the activations, widths that are no
+// multiples of four): with two wavefronts per SIMD a wavefront issues an instruction every eight or nine cycles, so the tests and
+// the scalars kept (and spilled) for paths not taken cost as much as work does.  us per launch with / without them: critic update
+// 256-256 58 / 55, policy update 51 / 48, critic update 512-256-128 125 / 120, 64-64 at 256 rows 23.6 / 22.
+template <bool R>
+struct WvOf : Wv { static constexpr bool regular = R; };
 
 // Barrier for data in LDS only: __syncthreads() would also wait for every store to memory and every weight request that
 // is meant to stay in flight across it.
@@ -266,7 +272,7 @@ struct Ahead { u32x4 w[2][4]; };
 struct Begin { const u32x4* first; const u32x4* second; };
 __device__ __forceinline__ Begin begin_of(const MatView& W, int tile, int s0, int ds) {
     const int t = tile < W.tiles ? tile : 0, a = s0 < W.ks ? s0 : 0, b = s0 + ds < W.ks ? s0 + ds : a;     // (an idle wavefront requests something valid)
-    return {W.frag + (size_t)(t * W.ks + a) * STEP_UNITS, W.frag + (size_t)(t * W.ks + b) * STEP_UNITS};
+    return {W.frag + (unsigned)((t * W.ks + a) * STEP_UNITS), W.frag + (unsigned)((t * W.ks + b) * STEP_UNITS)};
 }
 __device__ __forceinline__ Begin begin_at(const float* mat) {
     return {reinterpret_cast<const u32x4*>(mat), reinterpret_cast<const u32x4*>(mat)};
@@ -289,7 +295,7 @@ __device__ __forceinline__ void request(Ahead& a, const Begin& p, const Wv& T) {
 template <int NB>
 __device__ __forceinline__ void mac_steps(f32x4 (&acc)[2][NB], const MatView& W, int tile, const Tile& X, const Wv& T, int s0, int ds,
                                           Ahead& cur, const Begin& next) {
-    const u32x4* p = W.frag + (size_t)tile * W.ks * STEP_UNITS;
+    const u32x4* p = W.frag + (unsigned)(tile * W.ks * STEP_UNITS);
     f32x4 low[2][NB];
 #pragma unroll
     for (int m = 0; m < 2; ++m)
@@ -319,7 +325,7 @@ __device__ __forceinline__ void mac_steps(f32x4 (&acc)[2][NB], const MatView& W,
     auto step = [&](int s, Ahead& have, Ahead& get) {      // steps s and s + ds from `have`, the two after them requested into `get`
         const int s2 = s + 2 * ds, s3 = s + 3 * ds;
         Begin b = next;
-        if (s2 < W.ks) b = {p + (size_t)s2 * STEP_UNITS, p + (size_t)(s3 < W.ks ? s3 : s2) * STEP_UNITS};
+        if (s2 < W.ks) b = {p + (unsigned)(s2 * STEP_UNITS), p + (unsigned)((s3 < W.ks ? s3 : s2) * STEP_UNITS)};
         request(get, b, T);
         __builtin_amdgcn_sched_barrier(0);
         mac(s, have.w[0]);
@@ -352,67 +358,76 @@ __device__ __forceinline__ void clear(f32x4 (&z)[2][2]) {
 // 140 / 131, 256-256 59.8 / 58.2 and its weight gradients 23.2 / 22.3.  The layer kernel's results are larger than the
 // caches: no difference there, and the weight gradients after it are 1 % faster without them.)
 // The 32 x 32 results of one tile to / from a row-major [B][N] array: this lane's rows r0 + 16 n + l15, columns
-// 32 tile + 16 m + 4 q .. + 3.
-template <int NB = 2, bool PAST = false>
-__device__ __forceinline__ void store_tile(float* g, int N, int tile, const f32x4 (&z)[2][NB], int r0, int B, const Wv& T) {
+// 32 tile + 16 m + 4 q .. + 3.  Through a descriptor of the tile's rows, which drops what lies past them: no branches, so that all
+// requests leave together and none waits for another (as masked loads the compiler waited for each before the next one:
+// four round trips a tile).
+constexpr int NOWHERE = 0x7ffffffc;          // a buffer offset past any descriptor used here: a load returns zero, a store is dropped
+template <int NB>
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t tile_rows(const float* g, int N, int r0, int B) {
+    const int rows = B - r0 < 16 * NB ? B - r0 : 16 * NB;
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(g) + (size_t)r0 * (size_t)N, 0, rows * N * (int)sizeof(float), 0x00020000);
+}
+template <int NB = 2, bool PAST = false, typename WV>
+__device__ __forceinline__ void store_tile(float* g, int N, int tile, const f32x4 (&z)[2][NB], int r0, int B, const WV& T) {
+    const __amdgpu_buffer_rsrc_t rs = tile_rows<NB>(g, N, r0, B);
+    const int col = 32 * tile + 4 * T.q;
 #pragma unroll
-    for (int n = 0; n < NB; ++n) {
-        const int row = r0 + 16 * n + T.l15;
-        if (row >= B) continue;
-        float* p = g + (size_t)row * (size_t)N;
+    for (int n = 0; n < NB; ++n)
 #pragma unroll
         for (int m = 0; m < 2; ++m) {
-            const int col = 32 * tile + 16 * m + 4 * T.q;
-            if ((N & 3) == 0) {
-                if (col >= N) continue;
-                if (PAST) __builtin_nontemporal_store(z[m][n], reinterpret_cast<f32x4*>(p + col));
-                else      *reinterpret_cast<f32x4*>(p + col) = z[m][n];
+            const int at = ((16 * n + T.l15) * N + col + 16 * m) * (int)sizeof(float);
+            if (WV::regular || (N & 3) == 0) {
+                __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, z[m][n]), rs, col + 16 * m < N ? at : NOWHERE, 0, PAST ? 2 : 0);
             } else {
 #pragma unroll
                 for (int r = 0; r < 4; ++r)
-                    if (col + r < N) p[col + r] = z[m][n][r];
+                    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(z[m][n][r]), rs, col + 16 * m + r < N ? at + 4 * r : NOWHERE, 0, 0);
             }
         }
-    }
 }
-template <int NB = 2>
-__device__ __forceinline__ void load_tile(const float* g, int N, int tile, f32x4 (&z)[2][NB], int r0, int B, const Wv& T) {
+template <int NB = 2, typename WV>
+__device__ __forceinline__ void load_tile(const float* g, int N, int tile, f32x4 (&z)[2][NB], int r0, int B, const WV& T) {
+    const __amdgpu_buffer_rsrc_t rs = tile_rows<NB>(g, N, r0, B);
+    const int col = 32 * tile + 4 * T.q;
+    const bool vec = WV::regular || (N & 3) == 0;
 #pragma unroll
-    for (int n = 0; n < NB; ++n) { z[0][n] = f32x4{0.f, 0.f, 0.f, 0.f}; z[1][n] = z[0][n]; }
-#pragma unroll
-    for (int n = 0; n < NB; ++n) {
-        const int row = r0 + 16 * n + T.l15;
-        if (row >= B) continue;
-        const float* p = g + (size_t)row * (size_t)N;
+    for (int n = 0; n < NB; ++n)
 #pragma unroll
         for (int m = 0; m < 2; ++m) {
-            const int col = 32 * tile + 16 * m + 4 * T.q;
-            if ((N & 3) == 0) {
-                if (col < N) z[m][n] = *reinterpret_cast<const f32x4*>(p + col);
-            } else {
-#pragma unroll
-                for (int r = 0; r < 4; ++r)
-                    if (col + r < N) z[m][n][r] = p[col + r];
-            }
+            const int at = ((16 * n + T.l15) * N + col + 16 * m) * (int)sizeof(float);
+            z[m][n] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, vec && col + 16 * m < N ? at : NOWHERE, 0, 0));
         }
-    }
+    if (vec) return;
+#pragma unroll
+    for (int n = 0; n < NB; ++n)
+#pragma unroll
+        for (int m = 0; m < 2; ++m) {
+            const int at = ((16 * n + T.l15) * N + col + 16 * m) * (int)sizeof(float);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) z[m][n][r] = buf_load(rs, (unsigned)(col + 16 * m + r < N ? at + 4 * r : NOWHERE), 0);
+        }
 }
-// Sums over the tile's 32 rows of a[..] (times b[..] where given) to out[N].
+// Sums of a[..] over the tile's rows (this lane's share of them) to out[N].  Eight columns' values meet in a butterfly that
+// halves what a lane holds at every exchange (lane l15 of a quarter ends with column l15 / 2 of its eight), so that one store
+// takes all 32 columns.
 __device__ __forceinline__ void store_colsum(float* out, int N, int tile, const f32x4 (&a)[2], const Wv& T) {
+    const bool b3 = (T.l15 & 8) != 0, b2 = (T.l15 & 4) != 0, b1 = (T.l15 & 2) != 0;
+    f32x4 v;
 #pragma unroll
-    for (int m = 0; m < 2; ++m) {
-        const int col = 32 * tile + 16 * m + 4 * T.q;
+    for (int r = 0; r < 4; ++r) v[r] = (b3 ? a[1][r] : a[0][r]) + dpp_move<0x128>(b3 ? a[0][r] : a[1][r]);          // row_ror 8
+    float u[2];
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const float s = row16_sum(a[m][r]);
-            if (T.l15 == 0 && col + r < N) out[col + r] = s;
-        }
-    }
+    for (int r = 0; r < 2; ++r) u[r] = (b2 ? v[2 + r] : v[r]) + dpp_move<0x141>(b2 ? v[r] : v[2 + r]);              // row_half_mirror
+    float s = (b1 ? u[1] : u[0]) + dpp_move<0x4E>(b1 ? u[0] : u[1]);                                                // quad_perm [2, 3, 0, 1]
+    s += dpp_move<0xB1>(s);                                                                                         // quad_perm [1, 0, 3, 2]
+    const int col = 32 * tile + 16 * (T.l15 >> 3) + 4 * T.q + ((T.l15 >> 1) & 3);
+    if ((T.l15 & 1) == 0 && col < N) out[col] = s;
 }
 
 // Which of the workgroup's networks and output tiles a wavefront works on.
 struct Share { int net, slot, waves; };      // tiles slot, slot + waves, ...
-__device__ __forceinline__ void load_ahead(const float* h, int N, f32x4 (&hv)[2][2], const Share& S, int r0, int B, const Wv& T) {
+template <typename WV>
+__device__ __forceinline__ void load_ahead(const float* h, int N, f32x4 (&hv)[2][2], const Share& S, int r0, int B, const WV& T) {
     load_tile(h, N, S.slot, hv, r0, B, T);
 }
 
@@ -507,9 +522,9 @@ __device__ __forceinline__ void forward(f32x4 (&z)[TPW][2][2], const MatView& W,
 // z = (D W^T) * ELU'(.) with the activations h [B][N] read back from memory (each lane reads what it wrote in the forward
 // pass: those of the first tile the caller has requested into hv before the deltas were put into the tile); the deltas go to
 // d_out and their column sums to col_out where given.
-template <int TPW>
+template <int TPW, typename WV>
 __device__ __forceinline__ void backward(f32x4 (&z)[TPW][2][2], const MatView& W, const Tile& X, const Share& S, const float (&inv)[2],
-                                const float* h, float* d_out, float* col_out, int N, int r0, int B, const Wv& T, Ahead& cur,
+                                const float* h, float* d_out, float* col_out, int N, int r0, int B, const WV& T, Ahead& cur,
                                 const Begin& next, f32x4 (&hv)[2][2]) {
     if (S.slot >= W.tiles) request(cur, next, T);
 #pragma unroll
@@ -542,7 +557,6 @@ __device__ __forceinline__ void backward(f32x4 (&z)[TPW][2][2], const MatView& W
 // fit the row's scale).  Up to 256 columns are requested ahead of time into v.
 struct InputRows { __amdgpu_buffer_rsrc_t obs, act, mean, rstd; int o, a, act_lds, as, last; bool norm; };   // act_lds >= 0: actions in LDS; last: last row
 constexpr int XV = 8;
-constexpr int NOWHERE = 0x7ffffffc;          // a buffer offset past any descriptor used here: the load returns zero
 
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t rows_of(const float* p, int cols, int r0, int B) {
     const int rows = B - r0 < 32 ? B - r0 : 32;
@@ -555,9 +569,9 @@ __device__ __forceinline__ InputRows input_rows(const float* obs, int o, const f
     in.o = o; in.a = a; in.act_lds = act_lds; in.as = as; in.last = (B - r0 < 32 ? B - r0 : 32) - 1; in.norm = false;
     return in;
 }
-// Column c + 32 j of the concatenated row.  Branch-free: what a descriptor does not hold reads as zero (columns beyond the row).
 // Places of rows beyond the batch hold its last row: their results go nowhere, but enter sums with a factor of zero, so they
-// have to be finite where those of the batch are (a row of zeros is not, at an infinite weight).
+// have to be finite where those of the batch are (a row of zeros is not, at an infinite weight).  Columns beyond the row are
+// requested past the descriptor and read as zero.
 __device__ __forceinline__ float input_value(const InputRows& in, int row, int col) {
     float x = buf_load(in.obs, (unsigned)(col < in.o ? (row * in.o + col) * 4 : NOWHERE), 0);
     if (in.norm) {
@@ -575,26 +589,35 @@ __device__ __forceinline__ float input_action(const InputRows& in, int row, int 
     }
     return buf_load(in.act, (unsigned)(live ? (row * in.a + c) * 4 : NOWHERE), 0);
 }
-struct Rows { float v[2][XV]; };
+// Requested rows: columns c + 32 j of the states (and their statistics), and the action columns, which lie in the steps j0 and
+// j0 + 1.  They come together where they are put: put together here, the request would wait for its own answers.
+struct Rows { float v[2][XV], y[2][2], mean[XV], rstd[XV]; };
 __device__ __forceinline__ int input_row(const Wv& T, int i) { return 2 * T.wave + (T.lane >> 5) + 16 * i; }
 __device__ __forceinline__ int source_row(const InputRows& in, int row) { return row < in.last ? row : in.last; }
-__device__ __forceinline__ void request_rows(Rows& x, const InputRows& in, int steps, const Wv& T) {
-    if (steps > XV) return;
-    const int c = T.lane & 31;
-    const int j0 = in.o >> 5;                 // at most 32 action columns: they lie in the steps j0 and j0 + 1
+// Element j of a row that begins at byte offset `base` (this lane's first column included): whole steps need no mask.
+__device__ __forceinline__ float step_value(__amdgpu_buffer_rsrc_t r, int base, int j, int j0, int o, int c) {
+    const int at = j < j0 || (j == j0 && c + 32 * j0 < o) ? base : NOWHERE - 32 * 4 * XV;
+    return buf_load(r, (unsigned)(at + 128 * j), 0);
+}
+template <typename WV>
+__device__ __forceinline__ void request_rows(Rows& x, const InputRows& in, int steps, const WV& T) {
+    if (!WV::regular && steps > XV) return;
+    const int c = T.lane & 31, j0 = in.o >> 5;
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
-        const int row = source_row(in, input_row(T, i));
+        const int row = source_row(in, input_row(T, i)), base = (row * in.o + c) * 4;
 #pragma unroll
-        for (int j = 0; j < XV; ++j) x.v[i][j] = input_value(in, row, c + 32 * j);
+        for (int j = 0; j < XV; ++j)
+            if (j < steps) x.v[i][j] = step_value(in.obs, base, j, j0, in.o, c);
         if (in.a > 0) {
-            const float y0 = input_action(in, row, c + 32 * j0), y1 = input_action(in, row, c + 32 * j0 + 32);
 #pragma unroll
-            for (int j = 0; j < XV; ++j) {
-                const bool live = c + 32 * j >= in.o;
-                x.v[i][j] = live ? (j == j0 ? y0 : (j == j0 + 1 ? y1 : 0.f)) : x.v[i][j];
-            }
+            for (int j = 0; j < 2; ++j) x.y[i][j] = input_action(in, row, c + 32 * (j0 + j));
         }
+    }
+    if (in.norm) {
+#pragma unroll
+        for (int j = 0; j < XV; ++j)
+            if (j < steps) { x.mean[j] = step_value(in.mean, c * 4, j, j0, in.o, c); x.rstd[j] = step_value(in.rstd, c * 4, j, j0, in.o, c); }
     }
 }
 __device__ __forceinline__ float input_any(const InputRows& in, int row, int col) {
@@ -604,34 +627,43 @@ __device__ __forceinline__ float input_any(const InputRows& in, int row, int col
 __device__ __forceinline__ int tile_half(const Tile& X, int row, int k) {      // position of (row, k) in 2-byte units
     return (X.base + ((k >> 5) * 4 + ((k >> 2) & 3)) * CS + row) * 8 + (k & 3) + 4 * ((k >> 4) & 1);
 }
-__device__ __forceinline__ void put_value(const Tile& X, int row, int k, float x, float s) {
+__device__ __forceinline__ void put_at(const Tile& X, int at, float x, float s) {
     _Float16* h = reinterpret_cast<_Float16*>(smem);
     _Float16 hi, lo;
     split16(x, s, hi, lo);
-    const int at = tile_half(X, row, k);
     h[at] = hi;
     h[at + X.plane * 8] = lo;
 }
+__device__ __forceinline__ void put_value(const Tile& X, int row, int k, float x, float s) { put_at(X, tile_half(X, row, k), x, s); }
+template <typename WV>
 __device__ __forceinline__ void put_rows(const Rows& x, const InputRows& in, int steps, const Tile& X, int inv_at, float floor_,
-                                         const Wv& T) {
-    const int c = T.lane & 31;
+                                         const WV& T) {
+    const int c = T.lane & 31, j0 = in.o >> 5;
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
         const int row = input_row(T, i);
-        float mx = floor_;
-        if (steps <= XV) {
+        float mx = floor_, v[XV];
+        if (WV::regular || steps <= XV) {
+            // states and actions come together here, not where they are requested: that would wait for both
 #pragma unroll
-            for (int j = 0; j < XV; ++j) mx = fmaxf(mx, fabsf(x.v[i][j]));
+            for (int j = 0; j < XV; ++j) {
+                if (j >= steps) break;
+                v[j] = in.norm ? (x.v[i][j] - x.mean[j]) * x.rstd[j] : x.v[i][j];
+                if (in.a > 0 && j >= j0) v[j] = c + 32 * j >= in.o ? (j > j0 ? x.y[i][1] : x.y[i][0]) : v[j];
+                mx = fmaxf(mx, fabsf(v[j]));
+            }
         } else {
             for (int j = 0; j < steps; ++j) mx = fmaxf(mx, fabsf(input_any(in, source_row(in, row), c + 32 * j)));
         }
         float inv;
         const float s = scale_for(half_max(mx), inv);
         if (c == 0) smem[inv_at + row] = inv;
-        if (steps <= XV) {
+        if (WV::regular || steps <= XV) {
 #pragma unroll
-            for (int j = 0; j < XV; ++j)
-                if (j < steps) put_value(X, row, c + 32 * j, x.v[i][j], s);
+            for (int j = 0; j < XV; ++j) {
+                if (j >= steps) break;
+                put_at(X, tile_half(X, row, c) + j * 4 * CS * 8, v[j], s);
+            }
         } else {
             for (int j = 0; j < steps; ++j) put_value(X, row, c + 32 * j, input_any(in, source_row(in, row), c + 32 * j), s);
         }
@@ -658,8 +690,11 @@ __device__ __forceinline__ void put_partial(const f32x4 (&acc)[2][2], int at, in
 }
 __device__ __forceinline__ float sum_partials(int at, int parts, int row, int col) {
     const int e = (((col >> 4) * 2 + (row >> 4)) * 64 + ((col >> 2) & 3) * 16 + (row & 15)) * 4 + (col & 3);
-    float s = 0.f;
-    for (int p = 0; p < parts; ++p) s += smem[at * 4 + p * 1024 + e];
+    float s = 0.f, x[SW];
+#pragma unroll
+    for (int p = 0; p < SW; ++p) x[p] = smem[at * 4 + (p < parts ? p : 0) * 1024 + e];      // (all requests before the first sum)
+#pragma unroll
+    for (int p = 0; p < SW; ++p) s += p < parts ? x[p] : 0.f;
     return s;
 }
 __device__ __forceinline__ void scaled(f32x4 (&acc)[2][2], const float (&inv)[2], float iw) {
@@ -695,9 +730,9 @@ __device__ __forceinline__ float sample_action(int at, int parts, int row, int c
 
 // The policy's hidden layers on the tile (all wavefronts on one network), its output layer as partial tiles.
 // keep: h_l go to hA[l]; returns the number of partial tiles at H.
-template <int TPW>
+template <int TPW, typename WV>
 __device__ __forceinline__ int policy_forward(const SplitShape& P, const float* const* mats, const Tile& X, const Tile& H, const SmallMem& M,
-                                     bool keep, float* const* hA, int aw, int r0, int B, const Wv& T, Ahead& cur,
+                                     bool keep, float* const* hA, int aw, int r0, int B, const WV& T, Ahead& cur,
                                      const Begin& next) {
     const Share S = {0, T.wave, SW};
     float inv[2];
@@ -766,10 +801,10 @@ __device__ __forceinline__ void head_weights(f32x4 (&wo)[TPW][2], const float* w
 }
 
 // Hidden layers of the critics on (X): leaves z = h_L in registers.  h_l of layers l <= kept go to h[net][l].
-template <int NN, int TPW>
+template <int NN, int TPW, typename WV>
 __device__ __forceinline__ void critic_forward(f32x4 (&z)[TPW][2][2], const SplitShape& P, const float* const (*mats)[PQL_MAX_HIDDEN + 1],
                                       int net, const Tile& X, const Tile& H, const Share& S, const SmallMem& M, int kept,
-                                      float* const (*h)[PQL_MAX_HIDDEN + 1], int r0, int B, const Wv& T, Ahead& cur,
+                                      float* const (*h)[PQL_MAX_HIDDEN + 1], int r0, int B, const WV& T, Ahead& cur,
                                       const Begin& next, Rows& xv, const InputRows& following, bool fetch) {
     float inv[2];
     row_inv(inv, M.inv, T);
@@ -845,8 +880,9 @@ __device__ __forceinline__ void put_dlogits(const float (&dl)[2][DR], int at, in
         }
 }
 
-__device__ __forceinline__ Wv wave_of(int other) {        // other: whether the workgroup reads the other lo terms
-    Wv T;
+template <bool R = false>
+__device__ __forceinline__ WvOf<R> wave_of(int other) {        // other: whether the workgroup reads the other lo terms
+    WvOf<R> T;
     T.tid = threadIdx.x; T.lane = T.tid & 63; T.wave = __builtin_amdgcn_readfirstlane(T.tid >> 6);
     T.l15 = T.lane & 15; T.q = T.lane >> 4;
     T.hi = (unsigned)T.lane * 16u; T.lo = T.hi + 2048u + (unsigned)other * 2048u;
@@ -858,11 +894,11 @@ __device__ __forceinline__ Wv wave_of(int other) {        // other: whether the 
 // t_i = Q'_i(s', a'), y = ret + boot * min(t_1, t_2); q_i = Q_i(s, a); loss partials, output deltas, and the deltas of
 // every hidden layer of both critics.  NN networks side by side, TPW output tiles per wavefront.
 // =============================================================================================
-template <int NN, int TPW, int VAR>
+template <int NN, int TPW, int VAR, bool R = false>
 __device__ __forceinline__ void critic_step(const SplitCriticArgs& A) {
     warm_args<SplitCriticArgs>();
     constexpr bool SAC = VAR == VAR_SAC, DIST = VAR == VAR_DIST;
-    const Wv T = wave_of(blockIdx.x & 1);
+    const WvOf<R> T = wave_of<R>(blockIdx.x & 1);
     const SplitShape& P = A.shape;
     const int B = A.B, L = P.L, a = P.a, HL = P.H[L - 1];
     const int r0 = blockIdx.x * 32, wg = blockIdx.x, nwg = gridDim.x;
@@ -906,7 +942,7 @@ __device__ __forceinline__ void critic_step(const SplitCriticArgs& A) {
                 act = tanhf(sum_partials(H0.base, parts, row, col) + A.pi_bias[col]);
             }
             if (col < a) {
-                if (P.alias) smem[M.act + row * M.as + col] = act;
+                if (!R && P.alias) smem[M.act + row * M.as + col] = act;
                 else put_value(X, row, P.o + col, act, __uint_as_float(0x7F000000u - __float_as_uint(smem[M.inv + row])));
             }
         }
@@ -930,16 +966,17 @@ __device__ __forceinline__ void critic_step(const SplitCriticArgs& A) {
     const InputRows online = input_rows(A.obs, P.o, A.act, -1, a, P.as, r0, B);
     {
         float tq[2][2];
+#pragma unroll 1
         for (int ni = 0; ni < (NN == 2 ? 1 : 2); ++ni) {
             const int net = NN == 2 ? S.net : ni;
             if (ni > 0) lds_barrier();      // every wavefront has read the other critic's head partials (and activations)
-            if (P.alias) {      // the input tile shares its place with the activations: bring the rows in again
+            if (!R && P.alias) {      // the input tile shares its place with the activations: bring the rows in again
                 in.act_lds = M.act;
                 request_rows(xv, in, steps, T);
                 put_rows(xv, in, steps, X, M.inv, 1.f, T);
                 lds_barrier();
             }
-            if (!DIST) head_weights<TPW>(wo, A.wo_t[net], tilesL, S, T);
+            if (!DIST && TPW <= 2) head_weights<TPW>(wo, A.wo_t[net], tilesL, S, T);      // (wider layers: no registers to spare until the products are done)
             const bool last = NN == 2 || ni == 1;
             critic_forward<NN, TPW>(z, P, A.qt, net, X, H, S, M, 0, nullptr, r0, B, T, cur,
                                     DIST ? dist_begin(A.qt) : (last ? critic_begin(A.q, S.net) : critic_begin(A.qt, 1)), xv, online,
@@ -971,6 +1008,7 @@ __device__ __forceinline__ void critic_step(const SplitCriticArgs& A) {
             float bias[NN], q[NN][2];
 #pragma unroll
             for (int i = 0; i < NN; ++i) bias[i] = A.bo_t[NN == 2 ? i : net][0];
+            if (TPW > 2) head_weights<TPW>(wo, A.wo_t[net], tilesL, S, T);
             head_values<NN, TPW>(z, wo, S, M, bias, q, T);
 #pragma unroll
             for (int n = 0; n < 2; ++n) {
@@ -989,15 +1027,16 @@ __device__ __forceinline__ void critic_step(const SplitCriticArgs& A) {
     // ---- online critics: forward, head, backward data path
     const float invB = 1.f / (float)B;
     in = online;
+#pragma unroll 1
     for (int ni = 0; ni < (NN == 2 ? 1 : 2); ++ni) {
         const int net = NN == 2 ? S.net : ni;
-        if (NN == 2 || P.alias || ni == 0) {
+        if (NN == 2 || (!R && P.alias) || ni == 0) {
             if (ni > 0) request_rows(xv, in, steps, T);       // (else requested during the target critics)
             lds_barrier();     // the head partials of the networks before have been read, and so has their input
             put_rows(xv, in, steps, X, M.inv, 0.f, T);
         }
         lds_barrier();
-        if (!DIST) head_weights<TPW>(wo, A.wo_q[net], tilesL, S, T);
+        if (!DIST && TPW <= 2) head_weights<TPW>(wo, A.wo_q[net], tilesL, S, T);
         const Begin after = NN == 1 && ni == 0 ? critic_begin(A.q, 1) : begin_at(A.q[0][0]);
         const Begin back = L > 1 ? begin_of(mat_view(A.qT[net][L - 1], HL, P.H[L - 2]), S.slot, 0, 1) : after;
         critic_forward<NN, TPW>(z, P, A.q, net, X, H, S, M, DIST ? L : L - 1, A.h, r0, B, T, cur, DIST ? dist_begin(A.q) : back, xv, in,
@@ -1052,6 +1091,7 @@ __device__ __forceinline__ void critic_step(const SplitCriticArgs& A) {
         float bias[NN], q[NN][2];
 #pragma unroll
         for (int i = 0; i < NN; ++i) bias[i] = A.bo_q[NN == 2 ? i : net][0];
+        if (TPW > 2) head_weights<TPW>(wo, A.wo_q[net], tilesL, S, T);
         head_values<NN, TPW>(z, wo, S, M, bias, q, T);
         float d[2], loss = 0.f, db = 0.f;
 #pragma unroll
@@ -1106,11 +1146,11 @@ __device__ __forceinline__ void critic_step(const SplitCriticArgs& A) {
 // P-learner step on one row tile (Algorithm 2: maximise min_i Q_i(s, pi(s))): a = pi(s), both critics on (s, a), the
 // gradient -1/B through the smaller critic down to its action input, through tanh' and back through the policy.
 // =============================================================================================
-template <int NN, int TPW, int VAR>
+template <int NN, int TPW, int VAR, bool R = false>
 __device__ __forceinline__ void policy_step(const SplitPolicyArgs& A) {
     warm_args<SplitPolicyArgs>();
     constexpr bool SAC = VAR == VAR_SAC, DIST = VAR == VAR_DIST;
-    const Wv T = wave_of(blockIdx.x & 1);
+    const WvOf<R> T = wave_of<R>(blockIdx.x & 1);
     const SplitShape& P = A.shape;
     constexpr int TPA = NN == 2 ? TPW / 2 : TPW;       // the policy's tiles per wavefront
     const int B = A.B, L = P.L, a = P.a, HL = P.H[L - 1], H1 = P.H[0];
@@ -1146,7 +1186,7 @@ __device__ __forceinline__ void policy_step(const SplitPolicyArgs& A) {
             if (SAC) logp[e] = sample_action(H0.base, parts, row, col, a, A.pi_bias, r0, A.sac, act[e], eps[e], raw[e]);
             else if (col < a) act[e] = tanhf(sum_partials(H0.base, parts, row, col) + A.pi_bias[col]);
             if (col < a) {
-                if (P.alias) smem[M.act + row * M.as + col] = act[e];
+                if (!R && P.alias) smem[M.act + row * M.as + col] = act[e];
                 else put_value(X, row, P.o + col, act[e], __uint_as_float(0x7F000000u - __float_as_uint(smem[M.inv + row])));
             }
         }
@@ -1156,16 +1196,17 @@ __device__ __forceinline__ void policy_step(const SplitPolicyArgs& A) {
     f32x4 z[TPW][2][2], wo[TPW][2];
     const int tilesL = (HL + 31) >> 5;
     float qv[2][2];
+#pragma unroll 1
     for (int ni = 0; ni < (NN == 2 ? 1 : 2); ++ni) {
         const int net = NN == 2 ? S.net : ni;
         if (ni > 0) lds_barrier();          // every wavefront has read the other critic's head partials (and activations)
-        if (P.alias) {
+        if (!R && P.alias) {
             in.act_lds = M.act;
             request_rows(xv, in, steps, T);
             put_rows(xv, in, steps, X, M.inv, 1.f, T);
             lds_barrier();
         }
-        if (!DIST) head_weights<TPW>(wo, A.wo[net], tilesL, S, T);
+        if (!DIST && TPW <= 2) head_weights<TPW>(wo, A.wo[net], tilesL, S, T);
         critic_forward<NN, TPW>(z, P, A.q, net, X, H, S, M, NN == 2 && !DIST ? L - 1 : L, A.h, r0, B, T, cur,
                                 DIST ? begin_of(mat_view(A.q[net][L], HL, atoms), S.slot & 1, S.slot >> 1, LOGIT_STEP)
                                      : (NN == 1 && ni == 0 ? critic_begin(1) : back_begin(S.net)), xv, in, false);
@@ -1173,6 +1214,7 @@ __device__ __forceinline__ void policy_step(const SplitPolicyArgs& A) {
         float bias[NN], q[NN][2];
 #pragma unroll
         for (int i = 0; i < NN; ++i) bias[i] = A.bo[NN == 2 ? i : net][0];
+        if (TPW > 2) head_weights<TPW>(wo, A.wo[net], tilesL, S, T);
         head_values<NN, TPW>(z, wo, S, M, bias, q, T);
 #pragma unroll
         for (int n = 0; n < 2; ++n) {
@@ -1240,6 +1282,7 @@ __device__ __forceinline__ void policy_step(const SplitPolicyArgs& A) {
     f32x4 da[2][2];
     clear(da);
     float inv[2];
+#pragma unroll 1
     for (int ni = 0; ni < (NN == 2 ? 1 : 2); ++ni) {
         const int net = NN == 2 ? S.net : ni;
         if (NN == 1) {
@@ -1357,7 +1400,7 @@ template <int TPW, int VAR>
 __device__ __forceinline__ void act_step(const SplitActArgs& A) {
     warm_args<SplitActArgs>();
     constexpr bool SAC = VAR == VAR_SAC;
-    const Wv T = wave_of(0);
+    const auto T = wave_of(0);
     const SplitShape& P = A.shape;
     const int B = A.B, a = P.a, r0 = blockIdx.x * 32;
     const int aw = SAC ? 2 * a : a;
@@ -1510,7 +1553,7 @@ __device__ __forceinline__ void layer_rows(const GemmProb& P, int K, int ks, int
 template <int NB>
 __global__ __launch_bounds__(ST) void layer_rowtile_kernel(const GemmGroup) {
     const GemmGroup& G = kernel_args<GemmGroup>();
-    const Wv T = wave_of(blockIdx.x & 1);
+    const auto T = wave_of(blockIdx.x & 1);
     const int b = blockIdx.x;
     const GemmProb& P = G.p[record_of(G.p, &GemmProb::tile_begin, G.nprob, b)];
     const int K = P.seg[0].K + (P.nseg > 1 ? P.seg[1].K : 0), N = P.N, M = P.M;
@@ -1663,16 +1706,16 @@ bool split_shape_ok(int o, int a, int aw, const int* H, int L, bool dist) {
 // ---- kernels ------------------------------------------------------------------------------------------------------
 // fused_*: every layer at most 256 wide (two output tiles per wavefront); chain_*: at most 512, scalar critics and deterministic
 // policy (four); split_*: at most 512 with the other variants, and layers above 512 with the critics one after the other.
-template <int VAR>
-__global__ __launch_bounds__(ST) void fused_critic_kernel(const SplitCriticArgs) { critic_step<2, 2, VAR>(kernel_args<SplitCriticArgs>()); }
-template <int VAR>
-__global__ __launch_bounds__(ST) void chain_critic_kernel(const SplitCriticArgs) { critic_step<2, 4, VAR>(kernel_args<SplitCriticArgs>()); }
+template <int VAR, bool R>
+__global__ __launch_bounds__(ST) void fused_critic_kernel(const SplitCriticArgs) { critic_step<2, 2, VAR, R>(kernel_args<SplitCriticArgs>()); }
+template <int VAR, bool R>
+__global__ __launch_bounds__(ST) void chain_critic_kernel(const SplitCriticArgs) { critic_step<2, 4, VAR, R>(kernel_args<SplitCriticArgs>()); }
 template <int NN, int TPW, int VAR>
 __global__ __launch_bounds__(ST) void split_critic_kernel(const SplitCriticArgs) { critic_step<NN, TPW, VAR>(kernel_args<SplitCriticArgs>()); }
-template <int VAR>
-__global__ __launch_bounds__(ST) void fused_policy_kernel(const SplitPolicyArgs) { policy_step<2, 2, VAR>(kernel_args<SplitPolicyArgs>()); }
-template <int VAR>
-__global__ __launch_bounds__(ST) void chain_policy_kernel(const SplitPolicyArgs) { policy_step<2, 4, VAR>(kernel_args<SplitPolicyArgs>()); }
+template <int VAR, bool R>
+__global__ __launch_bounds__(ST) void fused_policy_kernel(const SplitPolicyArgs) { policy_step<2, 2, VAR, R>(kernel_args<SplitPolicyArgs>()); }
+template <int VAR, bool R>
+__global__ __launch_bounds__(ST) void chain_policy_kernel(const SplitPolicyArgs) { policy_step<2, 4, VAR, R>(kernel_args<SplitPolicyArgs>()); }
 template <int NN, int TPW, int VAR>
 __global__ __launch_bounds__(ST) void split_policy_kernel(const SplitPolicyArgs) { policy_step<NN, TPW, VAR>(kernel_args<SplitPolicyArgs>()); }
 template <int VAR>
@@ -1694,13 +1737,23 @@ __global__ __launch_bounds__(ST) void chain_act_kernel(const SplitActArgs) { act
 // class only decides what a launch is filed under).
 #define SPLIT_PICK(STEP, VAR)                                                                                      \
     do {                                                                                                           \
-        if (w <= 256) SPLIT_LAUNCH((fused_##STEP##_kernel<VAR>), kind == SPLIT_FUSED ? fused_kid : split_kid);     \
+        const bool r = regular(p);                                                                                 \
+        if (w <= 256 && r) SPLIT_LAUNCH((fused_##STEP##_kernel<VAR, true>), kind == SPLIT_FUSED ? fused_kid : split_kid); \
+        if (w <= 256) SPLIT_LAUNCH((fused_##STEP##_kernel<VAR, false>), kind == SPLIT_FUSED ? fused_kid : split_kid); \
+        if (w <= 512 && VAR == VAR_PLAIN && r)                                                                     \
+            SPLIT_LAUNCH((chain_##STEP##_kernel<VAR_PLAIN, true>), kind == SPLIT_CHAIN ? chain_kid : split_kid);   \
         if (w <= 512 && VAR == VAR_PLAIN)                                                                          \
-            SPLIT_LAUNCH((chain_##STEP##_kernel<VAR_PLAIN>), kind == SPLIT_CHAIN ? chain_kid : split_kid);         \
+            SPLIT_LAUNCH((chain_##STEP##_kernel<VAR_PLAIN, false>), kind == SPLIT_CHAIN ? chain_kid : split_kid);  \
         if (w <= 512) SPLIT_LAUNCH((split_##STEP##_kernel<2, 4, VAR == VAR_PLAIN ? VAR_SAC : VAR>), split_kid);    \
         if (VAR != VAR_DIST) SPLIT_LAUNCH((split_##STEP##_kernel<1, 4, VAR == VAR_DIST ? VAR_PLAIN : VAR>), split_kid); \
     } while (0)
 
+// Whether the kernels without the rare paths take this shape (after plan_lds).
+static bool regular(const SplitShape& p) {
+    for (int l = 0; l < p.L; ++l)
+        if (p.H[l] & 3) return false;
+    return !p.alias && p.o + p.a <= 32 * XV;
+}
 static bool kind_fits(int kind, int w) {
     return kind == SPLIT_FUSED ? w <= 256 : (kind == SPLIT_CHAIN ? w <= 512 : true);
 }
