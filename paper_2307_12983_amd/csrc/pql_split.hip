@@ -268,7 +268,9 @@ struct Tile { int base, plane; };
 
 // The fragments of two k-steps of a 32-column tile (4 KB each, hi and lo of its halves): the requests run two steps ahead of the matrix work, also
 // from one product to the next (over the epilogue and its barriers), so every product is told where the following one begins.
-struct Ahead { u32x4 w[2][4]; };
+template <int D>
+struct AheadOf { u32x4 w[D][4]; };
+typedef AheadOf<2> Ahead;
 struct Begin { const u32x4* first; const u32x4* second; };
 __device__ __forceinline__ Begin begin_of(const MatView& W, int tile, int s0, int ds) {
     const int t = tile < W.tiles ? tile : 0, a = s0 < W.ks ? s0 : 0, b = s0 + ds < W.ks ? s0 + ds : a;     // (an idle wavefront requests something valid)
@@ -277,9 +279,10 @@ __device__ __forceinline__ Begin begin_of(const MatView& W, int tile, int s0, in
 __device__ __forceinline__ Begin begin_at(const float* mat) {
     return {reinterpret_cast<const u32x4*>(mat), reinterpret_cast<const u32x4*>(mat)};
 }
-__device__ __forceinline__ void request(Ahead& a, const Begin& p, const Wv& T) {
+template <int D>
+__device__ __forceinline__ void request(AheadOf<D>& a, const Begin& p, const Wv& T) {
 #pragma unroll
-    for (int st = 0; st < 2; ++st) {
+    for (int st = 0; st < D; ++st) {
         const char* step = reinterpret_cast<const char*>(st == 0 ? p.first : p.second);
 #pragma unroll
         for (int m = 0; m < 2; ++m) a.w[st][m] = *reinterpret_cast<const u32x4*>(step + T.hi + m * 1024);
@@ -291,10 +294,10 @@ __device__ __forceinline__ void request(Ahead& a, const Begin& p, const Wv& T) {
 // acc[m][n] = 16x16 products of weight columns 32 tile + 16 m .. with batch rows 16 n .., steps s0, s0 + ds, ...  `cur`
 // holds the first two steps' fragments and leaves with those at `next` (the fences keep the requests ahead of the MFMAs).
 // The cross products have sums of their own, 2^11 too large like their lo terms, which join at the end.
-// NB blocks of 16 rows (tiles of 32 rows: 2).
-template <int NB>
+// NB blocks of 16 rows (tiles of 32 rows: 2), D steps ahead.
+template <int NB, int D>
 __device__ __forceinline__ void mac_steps(f32x4 (&acc)[2][NB], const MatView& W, int tile, const Tile& X, const Wv& T, int s0, int ds,
-                                          Ahead& cur, const Begin& next) {
+                                          AheadOf<D>& cur, const Begin& next) {
     const u32x4* p = W.frag + (unsigned)(tile * W.ks * STEP_UNITS);
     f32x4 low[2][NB];
 #pragma unroll
@@ -322,21 +325,22 @@ __device__ __forceinline__ void mac_steps(f32x4 (&acc)[2][NB], const MatView& W,
                 }
             }
     };
-    auto step = [&](int s, Ahead& have, Ahead& get) {      // steps s and s + ds from `have`, the two after them requested into `get`
-        const int s2 = s + 2 * ds, s3 = s + 3 * ds;
+    // D steps from s on out of `have`, the D after them requested into `get`
+    auto step = [&](int s, AheadOf<D>& have, AheadOf<D>& get) {
+        const int s2 = s + D * ds, s3 = s + (2 * D - 1) * ds;
         Begin b = next;
         if (s2 < W.ks) b = {p + (unsigned)(s2 * STEP_UNITS), p + (unsigned)((s3 < W.ks ? s3 : s2) * STEP_UNITS)};
         request(get, b, T);
         __builtin_amdgcn_sched_barrier(0);
         mac(s, have.w[0]);
-        if (s + ds < W.ks) mac(s + ds, have.w[1]);
+        if (D > 1 && s + ds < W.ks) mac(s + ds, have.w[D - 1]);
         __builtin_amdgcn_sched_barrier(0);
         return s2 < W.ks;
     };
-    Ahead other;
-    for (int s = s0; ; s += 4 * ds) {
+    AheadOf<D> other;
+    for (int s = s0; ; s += 2 * D * ds) {
         if (!step(s, cur, other)) { cur = other; break; }
-        if (!step(s + 2 * ds, other, cur)) break;
+        if (!step(s + D * ds, other, cur)) break;
     }
 #pragma unroll
     for (int m = 0; m < 2; ++m)
@@ -346,11 +350,12 @@ __device__ __forceinline__ void mac_steps(f32x4 (&acc)[2][NB], const MatView& W,
             for (int r = 0; r < 4; ++r) acc[m][n][r] = __fmaf_rn(low[m][n][r], 1.f / PAIR_LO, acc[m][n][r]);
 }
 
-__device__ __forceinline__ void clear(f32x4 (&z)[2][2]) {
+template <int NB>
+__device__ __forceinline__ void clear(f32x4 (&z)[2][NB]) {
 #pragma unroll
     for (int m = 0; m < 2; ++m)
 #pragma unroll
-        for (int n = 0; n < 2; ++n) z[m][n] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int n = 0; n < NB; ++n) z[m][n] = f32x4{0.f, 0.f, 0.f, 0.f};
 }
 
 // (PAST: stores bypass the caches' retention.  The one-launch kernels leave their results in the caches, where a row's two
@@ -424,50 +429,61 @@ __device__ __forceinline__ void store_colsum(float* out, int N, int tile, const 
     if ((T.l15 & 1) == 0 && col < N) out[col] = s;
 }
 
+// The same of the sums over the row blocks.
+template <int NB>
+__device__ __forceinline__ void store_rowsum(float* out, int N, int tile, const f32x4 (&z)[2][NB], const Wv& T) {
+    f32x4 cs[2] = {z[0][0] + z[0][1], z[1][0] + z[1][1]};
+#pragma unroll
+    for (int n = 2; n < NB; ++n) { cs[0] += z[0][n]; cs[1] += z[1][n]; }
+    store_colsum(out, N, tile, cs, T);
+}
+
 // Which of the workgroup's networks and output tiles a wavefront works on.
 struct Share { int net, slot, waves; };      // tiles slot, slot + waves, ...
-template <typename WV>
-__device__ __forceinline__ void load_ahead(const float* h, int N, f32x4 (&hv)[2][2], const Share& S, int r0, int B, const WV& T) {
+template <int NB, typename WV>
+__device__ __forceinline__ void load_ahead(const float* h, int N, f32x4 (&hv)[2][NB], const Share& S, int r0, int B, const WV& T) {
     load_tile(h, N, S.slot, hv, r0, B, T);
 }
 
 // Small per-tile arrays in LDS (floats from `sm`).
 struct SmallMem {
-    int max, part, inv, logp, act;           // [256] row maxima, [256] head partials, [32] inverse scales of X, [32] log pi, [32][as] actions
+    int max, part, inv, logp, act;           // of 16 NB rows: row maxima and head partials of eight wavefronts, inverse scales of X, log pi, [as] actions
     int as;
 };
+__host__ __device__ constexpr int small_floats(int nb, int as) { return 288 * nb + 16 * nb * as; }
+template <int NB>
 __device__ __forceinline__ SmallMem small_mem(int sm, int as) {
     SmallMem m;
-    m.max = sm; m.part = sm + 256; m.inv = sm + 512; m.logp = sm + 544; m.act = sm + 576; m.as = as;
+    m.max = sm; m.part = sm + 128 * NB; m.inv = sm + 256 * NB; m.logp = sm + 272 * NB; m.act = sm + 288 * NB; m.as = as;
     return m;
 }
 
 // Puts the wavefronts' results (z, TPW tiles of 32 columns each) into the activation tile `out`, in place over the layer's
 // input: row maxima meet in LDS; the barrier they need is also the one after which nobody reads the input any more.
-template <int TPW>
-__device__ __forceinline__ void put_tile(const f32x4 (&z)[TPW][2][2], int tiles, const Tile& out, const Share& S, const SmallMem& M,
-                                float (&inv)[2], const Wv& T) {
-    float mx[2] = {0.f, 0.f};
+template <int TPW, int NB>
+__device__ __forceinline__ void put_tile(const f32x4 (&z)[TPW][2][NB], int tiles, const Tile& out, const Share& S, const SmallMem& M,
+                                float (&inv)[NB], const Wv& T) {
+    float mx[NB] = {};
 #pragma unroll
     for (int t = 0; t < TPW; ++t)
         if (S.slot + t * S.waves < tiles) {
 #pragma unroll
-            for (int n = 0; n < 2; ++n)
+            for (int n = 0; n < NB; ++n)
 #pragma unroll
                 for (int m = 0; m < 2; ++m)
 #pragma unroll
                     for (int r = 0; r < 4; ++r) mx[n] = fmaxf(mx[n], fabsf(z[t][m][n][r]));
         }
 #pragma unroll
-    for (int n = 0; n < 2; ++n) {
+    for (int n = 0; n < NB; ++n) {
         mx[n] = quarters_max(mx[n]);
-        if (T.q == 0) smem[M.max + (S.net * 32 + 16 * n + T.l15) * S.waves + S.slot] = mx[n];
+        if (T.q == 0) smem[M.max + (S.net * 16 * NB + 16 * n + T.l15) * S.waves + S.slot] = mx[n];
     }
     lds_barrier();
-    float sc[2];
+    float sc[NB];
 #pragma unroll
-    for (int n = 0; n < 2; ++n) {
-        const f32x4* src = reinterpret_cast<const f32x4*>(smem) + (M.max + (S.net * 32 + 16 * n + T.l15) * S.waves) / 4;
+    for (int n = 0; n < NB; ++n) {
+        const f32x4* src = reinterpret_cast<const f32x4*>(smem) + (M.max + (S.net * 16 * NB + 16 * n + T.l15) * S.waves) / 4;
         f32x4 a = src[0];
         float m = fmaxf(fmaxf(a[0], a[1]), fmaxf(a[2], a[3]));
         if (S.waves > 4) {
@@ -481,10 +497,10 @@ __device__ __forceinline__ void put_tile(const f32x4 (&z)[TPW][2][2], int tiles,
         const int tile = S.slot + t * S.waves;
         if (tile < tiles) {
 #pragma unroll
-            for (int n = 0; n < 2; ++n) {
+            for (int n = 0; n < NB; ++n) {
                 u32x4 hi, lo;
                 split16x8(z[t][0][n], z[t][1][n], sc[n], hi, lo);
-                const int at = out.base + (4 * tile + T.q) * CS + 16 * n + T.l15;
+                const int at = out.base + (4 * tile + T.q) * (16 * NB + 1) + 16 * n + T.l15;
                 lds_units()[at] = hi;
                 lds_units()[at + out.plane] = lo;
             }
@@ -494,9 +510,9 @@ __device__ __forceinline__ void put_tile(const f32x4 (&z)[TPW][2][2], int tiles,
 }
 
 // z = ELU(X W + b) for this wavefront's tiles; inv = inverse row scales of the input tile.
-template <int TPW>
-__device__ __forceinline__ void forward(f32x4 (&z)[TPW][2][2], const MatView& W, const Tile& X, const Share& S, const float (&inv)[2],
-                               const Wv& T, Ahead& cur, const Begin& next) {
+template <int TPW, int NB, int D>
+__device__ __forceinline__ void forward(f32x4 (&z)[TPW][2][NB], const MatView& W, const Tile& X, const Share& S, const float (&inv)[NB],
+                               const Wv& T, AheadOf<D>& cur, const Begin& next) {
     if (S.slot >= W.tiles) request(cur, next, T);
 #pragma unroll
     for (int t = 0; t < TPW; ++t) {
@@ -507,13 +523,15 @@ __device__ __forceinline__ void forward(f32x4 (&z)[TPW][2][2], const MatView& W,
 #pragma unroll
         for (int m = 0; m < 2; ++m) b[m] = *reinterpret_cast<const f32x4*>(W.bias + 32 * tile + 16 * m + 4 * T.q);
         const float iw = W.inv[tile];
-        f32x4 acc[2][2];
-        mac_steps<2>(acc, W, tile, X, T, 0, 1, cur, more ? begin_of(W, tile + S.waves, 0, 1) : next);
-        const float f[2] = {inv[0] * iw, inv[1] * iw};
+        f32x4 acc[2][NB];
+        mac_steps(acc, W, tile, X, T, 0, 1, cur, more ? begin_of(W, tile + S.waves, 0, 1) : next);
+        float f[NB];
+#pragma unroll
+        for (int n = 0; n < NB; ++n) f[n] = inv[n] * iw;
 #pragma unroll
         for (int m = 0; m < 2; ++m)
 #pragma unroll
-            for (int n = 0; n < 2; ++n)
+            for (int n = 0; n < NB; ++n)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) z[t][m][n][r] = elu_f(__fmaf_rn(acc[m][n][r], f[n], b[m][r]));
     }
@@ -522,51 +540,51 @@ __device__ __forceinline__ void forward(f32x4 (&z)[TPW][2][2], const MatView& W,
 // z = (D W^T) * ELU'(.) with the activations h [B][N] read back from memory (each lane reads what it wrote in the forward
 // pass: those of the first tile the caller has requested into hv before the deltas were put into the tile); the deltas go to
 // d_out and their column sums to col_out where given.
-template <int TPW, typename WV>
-__device__ __forceinline__ void backward(f32x4 (&z)[TPW][2][2], const MatView& W, const Tile& X, const Share& S, const float (&inv)[2],
-                                const float* h, float* d_out, float* col_out, int N, int r0, int B, const WV& T, Ahead& cur,
-                                const Begin& next, f32x4 (&hv)[2][2]) {
+template <int TPW, int NB, int D, typename WV>
+__device__ __forceinline__ void backward(f32x4 (&z)[TPW][2][NB], const MatView& W, const Tile& X, const Share& S, const float (&inv)[NB],
+                                const float* h, float* d_out, float* col_out, int N, int r0, int B, const WV& T, AheadOf<D>& cur,
+                                const Begin& next, f32x4 (&hv)[2][NB]) {
     if (S.slot >= W.tiles) request(cur, next, T);
 #pragma unroll
     for (int t = 0; t < TPW; ++t) {
         const int tile = S.slot + t * S.waves;
         if (tile >= W.tiles) { clear(z[t]); continue; }
         const bool more = t + 1 < TPW && tile + S.waves < W.tiles;
-        f32x4 acc[2][2];
+        f32x4 acc[2][NB];
         const float iw = W.inv[tile];
         if (t > 0) load_tile(h, N, tile, hv, r0, B, T);
-        mac_steps<2>(acc, W, tile, X, T, 0, 1, cur, more ? begin_of(W, tile + S.waves, 0, 1) : next);
-        const float f[2] = {inv[0] * iw, inv[1] * iw};
+        mac_steps(acc, W, tile, X, T, 0, 1, cur, more ? begin_of(W, tile + S.waves, 0, 1) : next);
+        float f[NB];
+#pragma unroll
+        for (int n = 0; n < NB; ++n) f[n] = inv[n] * iw;
 #pragma unroll
         for (int m = 0; m < 2; ++m)
 #pragma unroll
-            for (int n = 0; n < 2; ++n)
+            for (int n = 0; n < NB; ++n)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) z[t][m][n][r] = acc[m][n][r] * f[n] * delu_h(hv[m][n][r]);
         if (d_out != nullptr) store_tile(d_out, N, tile, z[t], r0, B, T);
-        if (col_out != nullptr) {
-            const f32x4 cs[2] = {z[t][0][0] + z[t][0][1], z[t][1][0] + z[t][1][1]};
-            store_colsum(col_out, N, tile, cs, T);
-        }
+        if (col_out != nullptr) store_rowsum(col_out, N, tile, z[t], T);
     }
 }
 
 // ---- input rows --------------------------------------------------------------------------------------------
-// Rows r0 .. r0 + 31 of concat(obs[o], act[a]) as a tile: half a wavefront takes two rows, one after the other, so that their
+// Rows r0 .. r0 + 16 NB - 1 of concat(obs[o], act[a]) as a tile: half a wavefront takes NB rows, one after the other, so that their
 // largest magnitudes are found without leaving the registers.  `floor`: lower bound of that magnitude (actions in [-1, 1] that are inserted later must
 // fit the row's scale).  Up to 256 columns are requested ahead of time into v.
 struct InputRows { __amdgpu_buffer_rsrc_t obs, act, mean, rstd; int o, a, act_lds, as, last; bool norm; };   // act_lds >= 0: actions in LDS; last: last row
 constexpr int XV = 8;
 
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t rows_of(const float* p, int cols, int r0, int B) {
-    const int rows = B - r0 < 32 ? B - r0 : 32;
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t rows_of(const float* p, int cols, int r0, int B, int most) {
+    const int rows = B - r0 < most ? B - r0 : most;
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p) + (size_t)r0 * (size_t)cols, 0,
                                              p != nullptr ? rows * cols * (int)sizeof(float) : 0, 0x00020000);
 }
+template <int NB>
 __device__ __forceinline__ InputRows input_rows(const float* obs, int o, const float* act, int act_lds, int a, int as, int r0, int B) {
     InputRows in;
-    in.obs = rows_of(obs, o, r0, B); in.act = rows_of(act, a, r0, B); in.mean = in.obs; in.rstd = in.obs;
-    in.o = o; in.a = a; in.act_lds = act_lds; in.as = as; in.last = (B - r0 < 32 ? B - r0 : 32) - 1; in.norm = false;
+    in.obs = rows_of(obs, o, r0, B, 16 * NB); in.act = rows_of(act, a, r0, B, 16 * NB); in.mean = in.obs; in.rstd = in.obs;
+    in.o = o; in.a = a; in.act_lds = act_lds; in.as = as; in.last = (B - r0 < 16 * NB ? B - r0 : 16 * NB) - 1; in.norm = false;
     return in;
 }
 // Places of rows beyond the batch hold its last row: their results go nowhere, but enter sums with a factor of zero, so they
@@ -591,7 +609,8 @@ __device__ __forceinline__ float input_action(const InputRows& in, int row, int 
 }
 // Requested rows: columns c + 32 j of the states (and their statistics), and the action columns, which lie in the steps j0 and
 // j0 + 1.  They come together where they are put: put together here, the request would wait for its own answers.
-struct Rows { float v[2][XV], y[2][2], mean[XV], rstd[XV]; };
+template <int NB>
+struct Rows { float v[NB][XV], y[NB][2], mean[XV], rstd[XV]; };
 __device__ __forceinline__ int input_row(const Wv& T, int i) { return 2 * T.wave + (T.lane >> 5) + 16 * i; }
 __device__ __forceinline__ int source_row(const InputRows& in, int row) { return row < in.last ? row : in.last; }
 // Element j of a row that begins at byte offset `base` (this lane's first column included): whole steps need no mask.
@@ -599,12 +618,12 @@ __device__ __forceinline__ float step_value(__amdgpu_buffer_rsrc_t r, int base, 
     const int at = j < j0 || (j == j0 && c + 32 * j0 < o) ? base : NOWHERE - 32 * 4 * XV;
     return buf_load(r, (unsigned)(at + 128 * j), 0);
 }
-template <typename WV>
-__device__ __forceinline__ void request_rows(Rows& x, const InputRows& in, int steps, const WV& T) {
+template <int NB, typename WV>
+__device__ __forceinline__ void request_rows(Rows<NB>& x, const InputRows& in, int steps, const WV& T) {
     if (!WV::regular && steps > XV) return;
     const int c = T.lane & 31, j0 = in.o >> 5;
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
+    for (int i = 0; i < NB; ++i) {
         const int row = source_row(in, input_row(T, i)), base = (row * in.o + c) * 4;
 #pragma unroll
         for (int j = 0; j < XV; ++j)
@@ -624,8 +643,9 @@ __device__ __forceinline__ float input_any(const InputRows& in, int row, int col
     const float x = input_value(in, row, col);
     return in.a > 0 && col >= in.o ? input_action(in, row, col) : x;
 }
+template <int NB>
 __device__ __forceinline__ int tile_half(const Tile& X, int row, int k) {      // position of (row, k) in 2-byte units
-    return (X.base + ((k >> 5) * 4 + ((k >> 2) & 3)) * CS + row) * 8 + (k & 3) + 4 * ((k >> 4) & 1);
+    return (X.base + ((k >> 5) * 4 + ((k >> 2) & 3)) * (16 * NB + 1) + row) * 8 + (k & 3) + 4 * ((k >> 4) & 1);
 }
 __device__ __forceinline__ void put_at(const Tile& X, int at, float x, float s) {
     _Float16* h = reinterpret_cast<_Float16*>(smem);
@@ -634,13 +654,14 @@ __device__ __forceinline__ void put_at(const Tile& X, int at, float x, float s) 
     h[at] = hi;
     h[at + X.plane * 8] = lo;
 }
-__device__ __forceinline__ void put_value(const Tile& X, int row, int k, float x, float s) { put_at(X, tile_half(X, row, k), x, s); }
-template <typename WV>
-__device__ __forceinline__ void put_rows(const Rows& x, const InputRows& in, int steps, const Tile& X, int inv_at, float floor_,
+template <int NB>
+__device__ __forceinline__ void put_value(const Tile& X, int row, int k, float x, float s) { put_at(X, tile_half<NB>(X, row, k), x, s); }
+template <int NB, typename WV>
+__device__ __forceinline__ void put_rows(const Rows<NB>& x, const InputRows& in, int steps, const Tile& X, int inv_at, float floor_,
                                          const WV& T) {
     const int c = T.lane & 31, j0 = in.o >> 5;
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
+    for (int i = 0; i < NB; ++i) {
         const int row = input_row(T, i);
         float mx = floor_, v[XV];
         if (WV::regular || steps <= XV) {
@@ -662,59 +683,64 @@ __device__ __forceinline__ void put_rows(const Rows& x, const InputRows& in, int
 #pragma unroll
             for (int j = 0; j < XV; ++j) {
                 if (j >= steps) break;
-                put_at(X, tile_half(X, row, c) + j * 4 * CS * 8, v[j], s);
+                put_at(X, tile_half<NB>(X, row, c) + j * 4 * (16 * NB + 1) * 8, v[j], s);
             }
         } else {
-            for (int j = 0; j < steps; ++j) put_value(X, row, c + 32 * j, input_any(in, source_row(in, row), c + 32 * j), s);
+            for (int j = 0; j < steps; ++j) put_value<NB>(X, row, c + 32 * j, input_any(in, source_row(in, row), c + 32 * j), s);
         }
     }
 }
-__device__ __forceinline__ void row_inv(float (&inv)[2], int at, const Wv& T) {
-    inv[0] = smem[at + T.l15];
-    inv[1] = smem[at + 16 + T.l15];
+template <int NB>
+__device__ __forceinline__ void row_inv(float (&inv)[NB], int at, const Wv& T) {
+#pragma unroll
+    for (int n = 0; n < NB; ++n) inv[n] = smem[at + 16 * n + T.l15];
 }
 
 // ---- action-wide products --------------------------------------------------------------------------------
-// At most 32 output columns: the wavefronts of a network split the contraction, every one leaves its partial 32 x 32 tile
+// At most 32 output columns: the wavefronts of a network split the contraction, every one leaves its partial tile
 // in LDS, over the input tile (hence the first barrier); afterwards element (row, col) is the sum of the partial tiles.
-__device__ __forceinline__ void put_partial(const f32x4 (&acc)[2][2], int at, int part, bool mine, const Wv& T) {
+template <int NB>
+__device__ __forceinline__ void put_partial(const f32x4 (&acc)[2][NB], int at, int part, bool mine, const Wv& T) {
     lds_barrier();
     if (mine) {
-        f32x4* p = reinterpret_cast<f32x4*>(smem) + at + part * 256 + T.lane;
+        f32x4* p = reinterpret_cast<f32x4*>(smem) + at + part * (128 * NB) + T.lane;
 #pragma unroll
         for (int m = 0; m < 2; ++m)
 #pragma unroll
-            for (int n = 0; n < 2; ++n) p[(2 * m + n) * 64] = acc[m][n];
+            for (int n = 0; n < NB; ++n) p[(NB * m + n) * 64] = acc[m][n];
     }
     lds_barrier();
 }
+template <int NB>
 __device__ __forceinline__ float sum_partials(int at, int parts, int row, int col) {
-    const int e = (((col >> 4) * 2 + (row >> 4)) * 64 + ((col >> 2) & 3) * 16 + (row & 15)) * 4 + (col & 3);
+    const int e = (((col >> 4) * NB + (row >> 4)) * 64 + ((col >> 2) & 3) * 16 + (row & 15)) * 4 + (col & 3);
     float s = 0.f, x[SW];
 #pragma unroll
-    for (int p = 0; p < SW; ++p) x[p] = smem[at * 4 + (p < parts ? p : 0) * 1024 + e];      // (all requests before the first sum)
+    for (int p = 0; p < SW; ++p) x[p] = smem[at * 4 + (p < parts ? p : 0) * (512 * NB) + e];      // (all requests before the first sum)
 #pragma unroll
     for (int p = 0; p < SW; ++p) s += p < parts ? x[p] : 0.f;
     return s;
 }
-__device__ __forceinline__ void scaled(f32x4 (&acc)[2][2], const float (&inv)[2], float iw) {
+template <int NB>
+__device__ __forceinline__ void scaled(f32x4 (&acc)[2][NB], const float (&inv)[NB], float iw) {
 #pragma unroll
     for (int m = 0; m < 2; ++m)
 #pragma unroll
-        for (int n = 0; n < 2; ++n)
+        for (int n = 0; n < NB; ++n)
 #pragma unroll
             for (int r = 0; r < 4; ++r) acc[m][n][r] *= inv[n] * iw;
 }
 
 // A sample of the tanh-Gaussian policy for element (row, col) of the output tile; the 32 lanes of a row add their shares of
 // log pi, which every lane returns.
+template <int NB>
 __device__ __forceinline__ float sample_action(int at, int parts, int row, int col, int a, const float* bias, int r0, const FusedSac& sc,
                                       float& act, float& eps, float& raw) {
     float lp = 0.f;
     act = 0.f; eps = 0.f; raw = 0.f;
     if (col < a) {
-        const float mu = sum_partials(at, parts, row, col) + bias[col];
-        raw = sum_partials(at, parts, row, col + a) + bias[col + a];
+        const float mu = sum_partials<NB>(at, parts, row, col) + bias[col];
+        raw = sum_partials<NB>(at, parts, row, col + a) + bias[col + a];
         eps = std_normal_f((uint32_t)((r0 + row) * a + col), sc);
         const float ls = fminf(fmaxf(raw, SAC_LOG_STD_MIN), SAC_LOG_STD_MAX);
         const float u = mu + expf(ls) * eps;
@@ -730,30 +756,30 @@ __device__ __forceinline__ float sample_action(int at, int parts, int row, int c
 
 // The policy's hidden layers on the tile (all wavefronts on one network), its output layer as partial tiles.
 // keep: h_l go to hA[l]; returns the number of partial tiles at H.
-template <int TPW, typename WV>
+template <int TPW, int NB, int D, typename WV>
 __device__ __forceinline__ int policy_forward(const SplitShape& P, const float* const* mats, const Tile& X, const Tile& H, const SmallMem& M,
-                                     bool keep, float* const* hA, int aw, int r0, int B, const WV& T, Ahead& cur,
+                                     bool keep, float* const* hA, int aw, int r0, int B, const WV& T, AheadOf<D>& cur,
                                      const Begin& next) {
     const Share S = {0, T.wave, SW};
-    float inv[2];
+    float inv[NB];
     row_inv(inv, M.inv, T);
-    f32x4 z[TPW][2][2];
+    f32x4 z[TPW][2][NB];
     for (int l = 0; l < P.L; ++l) {
         const int N = P.H[l];
         const MatView W = mat_view(mats[l], l == 0 ? P.o : P.H[l - 1], N);
         const MatView V = mat_view(mats[l + 1], N, l + 1 < P.L ? P.H[l + 1] : aw);
-        forward<TPW>(z, W, l == 0 ? X : H, S, inv, T, cur, l + 1 < P.L ? begin_of(V, S.slot, 0, 1) : begin_of(V, 0, T.wave, SW));
+        forward(z, W, l == 0 ? X : H, S, inv, T, cur, l + 1 < P.L ? begin_of(V, S.slot, 0, 1) : begin_of(V, 0, T.wave, SW));
         if (keep) {
 #pragma unroll
             for (int t = 0; t < TPW; ++t)
                 if (S.slot + t * SW < W.tiles) store_tile(hA[l + 1], N, S.slot + t * SW, z[t], r0, B, T);
         }
-        put_tile<TPW>(z, W.tiles, H, S, M, inv, T);
+        put_tile(z, W.tiles, H, S, M, inv, T);
     }
     const MatView W = mat_view(mats[P.L], P.H[P.L - 1], aw);
-    f32x4 acc[2][2];
+    f32x4 acc[2][NB];
     clear(acc);
-    if (T.wave < W.ks) mac_steps<2>(acc, W, 0, H, T, T.wave, SW, cur, next);
+    if (T.wave < W.ks) mac_steps(acc, W, 0, H, T, T.wave, SW, cur, next);
     else request(cur, next, T);
     scaled(acc, inv, W.inv[0]);
     const int parts = W.ks < SW ? W.ks : SW;
@@ -763,11 +789,11 @@ __device__ __forceinline__ int policy_forward(const SplitShape& P, const float* 
 
 // Scalar output head: partial dot products of this wavefront's tiles of the last hidden layer with the output weights meet in
 // LDS; q[i][n] = Q_i of this lane's rows (all networks the workgroup carries; one: q[0]).
-template <int NN, int TPW>
-__device__ __forceinline__ void head_values(const f32x4 (&z)[TPW][2][2], const f32x4 (&wo)[TPW][2], const Share& S, const SmallMem& M,
-                                   const float (&bias)[NN], float (&q)[NN][2], const Wv& T) {
+template <int NN, int TPW, int NB>
+__device__ __forceinline__ void head_values(const f32x4 (&z)[TPW][2][NB], const f32x4 (&wo)[TPW][2], const Share& S, const SmallMem& M,
+                                   const float (&bias)[NN], float (&q)[NN][NB], const Wv& T) {
 #pragma unroll
-    for (int n = 0; n < 2; ++n) {
+    for (int n = 0; n < NB; ++n) {
         float s = 0.f;
 #pragma unroll
         for (int t = 0; t < TPW; ++t)
@@ -776,14 +802,14 @@ __device__ __forceinline__ void head_values(const f32x4 (&z)[TPW][2][2], const f
 #pragma unroll
                 for (int r = 0; r < 4; ++r) s += z[t][m][n][r] * wo[t][m][r];
         s = quarters_sum(s);
-        if (T.q == 0) smem[M.part + (S.net * 32 + 16 * n + T.l15) * S.waves + S.slot] = s;
+        if (T.q == 0) smem[M.part + (S.net * 16 * NB + 16 * n + T.l15) * S.waves + S.slot] = s;
     }
     lds_barrier();
 #pragma unroll
     for (int i = 0; i < NN; ++i)
 #pragma unroll
-        for (int n = 0; n < 2; ++n) {
-            const f32x4* src = reinterpret_cast<const f32x4*>(smem) + (M.part + (i * 32 + 16 * n + T.l15) * S.waves) / 4;
+        for (int n = 0; n < NB; ++n) {
+            const f32x4* src = reinterpret_cast<const f32x4*>(smem) + (M.part + (i * 16 * NB + 16 * n + T.l15) * S.waves) / 4;
             f32x4 v = src[0];
             if (S.waves > 4) v += src[1];
             q[i][n] = (v[0] + v[1]) + (v[2] + v[3]) + bias[i];
@@ -801,26 +827,26 @@ __device__ __forceinline__ void head_weights(f32x4 (&wo)[TPW][2], const float* w
 }
 
 // Hidden layers of the critics on (X): leaves z = h_L in registers.  h_l of layers l <= kept go to h[net][l].
-template <int NN, int TPW, typename WV>
-__device__ __forceinline__ void critic_forward(f32x4 (&z)[TPW][2][2], const SplitShape& P, const float* const (*mats)[PQL_MAX_HIDDEN + 1],
+template <int NN, int TPW, int NB, int D, typename WV>
+__device__ __forceinline__ void critic_forward(f32x4 (&z)[TPW][2][NB], const SplitShape& P, const float* const (*mats)[PQL_MAX_HIDDEN + 1],
                                       int net, const Tile& X, const Tile& H, const Share& S, const SmallMem& M, int kept,
-                                      float* const (*h)[PQL_MAX_HIDDEN + 1], int r0, int B, const WV& T, Ahead& cur,
-                                      const Begin& next, Rows& xv, const InputRows& following, bool fetch) {
-    float inv[2];
+                                      float* const (*h)[PQL_MAX_HIDDEN + 1], int r0, int B, const WV& T, AheadOf<D>& cur,
+                                      const Begin& next, Rows<NB>& xv, const InputRows& following, bool fetch) {
+    float inv[NB];
     row_inv(inv, M.inv, T);
     for (int l = 0; l < P.L; ++l) {
         const int N = P.H[l];
         const MatView W = mat_view(mats[net][l], l == 0 ? P.o + P.a : P.H[l - 1], N);
         Begin n = next;
         if (l + 1 < P.L) n = begin_of(mat_view(mats[net][l + 1], N, P.H[l + 1]), S.slot, 0, 1);
-        forward<TPW>(z, W, l == 0 ? X : H, S, inv, T, cur, n);
+        forward(z, W, l == 0 ? X : H, S, inv, T, cur, n);
         if (l == 0 && fetch) request_rows(xv, following, (P.o + P.a + 31) >> 5, T);    // the next chain's input
         if (l < kept) {
 #pragma unroll
             for (int t = 0; t < TPW; ++t)
                 if (S.slot + t * S.waves < W.tiles) store_tile(h[net][l + 1], N, S.slot + t * S.waves, z[t], r0, B, T);
         }
-        if (l < P.L - 1) put_tile<TPW>(z, W.tiles, H, S, M, inv, T);
+        if (l < P.L - 1) put_tile(z, W.tiles, H, S, M, inv, T);
     }
 }
 
@@ -837,7 +863,7 @@ __device__ __forceinline__ void put_logits(const MatView& W, const Tile& H, int 
     f32x4 acc[2][2];
     clear(acc);
     if (tile < W.tiles && part < W.ks) {
-        mac_steps<2>(acc, W, tile, H, T, part, LOGIT_STEP, cur, next);
+        mac_steps(acc, W, tile, H, T, part, LOGIT_STEP, cur, next);
         scaled(acc, inv, W.inv[tile]);
     } else {
         request(cur, next, T);
@@ -875,7 +901,7 @@ __device__ __forceinline__ void put_dlogits(const float (&dl)[2][DR], int at, in
             const int row = DR * T.wave + rr;
             float inv;
             const float s = scale_for(wave_max(fabsf(dl[i][rr])), inv);
-            put_value(logit_tile(at, i), row, T.lane, dl[i][rr], s);
+            put_value<2>(logit_tile(at, i), row, T.lane, dl[i][rr], s);
             if (T.lane == 0) smem[inv_at + 32 * i + row] = inv;
         }
 }
@@ -898,7 +924,7 @@ template <int NN, int TPW, int VAR, bool R = false>
 __device__ __forceinline__ void critic_step(const SplitCriticArgs& A) {
     warm_args<SplitCriticArgs>();
     constexpr bool SAC = VAR == VAR_SAC, DIST = VAR == VAR_DIST;
-    const WvOf<R> T = wave_of<R>(blockIdx.x & 1);
+    const auto T = wave_of<R>(blockIdx.x & 1);
     const SplitShape& P = A.shape;
     const int B = A.B, L = P.L, a = P.a, HL = P.H[L - 1];
     const int r0 = blockIdx.x * 32, wg = blockIdx.x, nwg = gridDim.x;
@@ -906,10 +932,10 @@ __device__ __forceinline__ void critic_step(const SplitCriticArgs& A) {
     const Share S = NN == 2 ? Share{T.wave >> 2, T.wave & 3, 4} : Share{0, T.wave, SW};
     const Tile X = {P.x0, P.xplane}, H0 = {P.h0, P.hplane};
     const Tile H = {P.h0 + S.net * 2 * P.hplane, P.hplane};
-    const SmallMem M = small_mem(P.sm, P.as);
+    const SmallMem M = small_mem<2>(P.sm, P.as);
     const int steps = (P.o + a + 31) >> 5;
-    Rows xv;
-    InputRows in = input_rows(A.next_obs, P.o, nullptr, -1, a, P.as, r0, B);
+    Rows<2> xv;
+    InputRows in = input_rows<2>(A.next_obs, P.o, nullptr, -1, a, P.as, r0, B);
     request_rows(xv, in, steps, T);
     Ahead cur;
     request(cur, begin_of(mat_view(A.pi[0], P.o, P.H[0]), T.wave, 0, 1), T);
@@ -927,7 +953,7 @@ __device__ __forceinline__ void critic_step(const SplitCriticArgs& A) {
     lds_barrier();
     // ---- a' from the lagged policy
     {
-        const int parts = policy_forward<NN == 2 ? TPW / 2 : TPW>(P, A.pi, X, H0, M, false, nullptr, aw, r0, B, T,
+        const int parts = policy_forward<NN == 2 ? TPW / 2 : TPW, 2>(P, A.pi, X, H0, M, false, nullptr, aw, r0, B, T,
                                                                              cur, critic_begin(A.qt, S.net));
         const int col = T.tid & 31;
 #pragma unroll
@@ -936,14 +962,14 @@ __device__ __forceinline__ void critic_step(const SplitCriticArgs& A) {
             float act = 0.f;
             if (SAC) {      // a' ~ pi^v(.|s') with its log-density (soft target)
                 float eps, raw;
-                const float lp = sample_action(H0.base, parts, row, col, a, A.pi_bias, r0, A.sac, act, eps, raw);
+                const float lp = sample_action<2>(H0.base, parts, row, col, a, A.pi_bias, r0, A.sac, act, eps, raw);
                 if (col == 0) smem[M.logp + row] = lp;
             } else if (col < a) {
-                act = tanhf(sum_partials(H0.base, parts, row, col) + A.pi_bias[col]);
+                act = tanhf(sum_partials<2>(H0.base, parts, row, col) + A.pi_bias[col]);
             }
             if (col < a) {
                 if (!R && P.alias) smem[M.act + row * M.as + col] = act;
-                else put_value(X, row, P.o + col, act, __uint_as_float(0x7F000000u - __float_as_uint(smem[M.inv + row])));
+                else put_value<2>(X, row, P.o + col, act, __uint_as_float(0x7F000000u - __float_as_uint(smem[M.inv + row])));
             }
         }
         lds_barrier();
@@ -963,7 +989,7 @@ __device__ __forceinline__ void critic_step(const SplitCriticArgs& A) {
     auto dist_begin = [&](const float* const (&mats)[2][PQL_MAX_HIDDEN + 1]) {
         return begin_of(mat_view(mats[S.net][L], HL, atoms), S.slot & 1, S.slot >> 1, LOGIT_STEP);
     };
-    const InputRows online = input_rows(A.obs, P.o, A.act, -1, a, P.as, r0, B);
+    const InputRows online = input_rows<2>(A.obs, P.o, A.act, -1, a, P.as, r0, B);
     {
         float tq[2][2];
 #pragma unroll 1
@@ -978,14 +1004,14 @@ __device__ __forceinline__ void critic_step(const SplitCriticArgs& A) {
             }
             if (!DIST && TPW <= 2) head_weights<TPW>(wo, A.wo_t[net], tilesL, S, T);      // (wider layers: no registers to spare until the products are done)
             const bool last = NN == 2 || ni == 1;
-            critic_forward<NN, TPW>(z, P, A.qt, net, X, H, S, M, 0, nullptr, r0, B, T, cur,
+            critic_forward<NN>(z, P, A.qt, net, X, H, S, M, 0, nullptr, r0, B, T, cur,
                                     DIST ? dist_begin(A.qt) : (last ? critic_begin(A.q, S.net) : critic_begin(A.qt, 1)), xv, online,
                                     last);
             if (DIST) {
                 // the target critic with the smaller mean supplies the next-state distribution; its atoms move to
                 // clip(ret + boot z) and are projected back onto the support (lane k gathers atom k's mass)
                 float inv[2];
-                put_tile<TPW>(z, tilesL, H, S, M, inv, T);
+                put_tile(z, tilesL, H, S, M, inv, T);
                 put_logits(mat_view(A.qt[net][L], HL, atoms), H, H0.base, S, inv, T, cur, critic_begin(A.q, S.net));
                 const float b0 = live ? A.bo_t[0][T.lane] : 0.f, b1 = live ? A.bo_t[1][T.lane] : 0.f;
 #pragma unroll
@@ -1009,7 +1035,7 @@ __device__ __forceinline__ void critic_step(const SplitCriticArgs& A) {
 #pragma unroll
             for (int i = 0; i < NN; ++i) bias[i] = A.bo_t[NN == 2 ? i : net][0];
             if (TPW > 2) head_weights<TPW>(wo, A.wo_t[net], tilesL, S, T);
-            head_values<NN, TPW>(z, wo, S, M, bias, q, T);
+            head_values(z, wo, S, M, bias, q, T);
 #pragma unroll
             for (int n = 0; n < 2; ++n) {
                 if (NN == 2) { tq[0][n] = q[0][n]; tq[1][n] = q[NN - 1][n]; }
@@ -1039,13 +1065,13 @@ __device__ __forceinline__ void critic_step(const SplitCriticArgs& A) {
         if (!DIST && TPW <= 2) head_weights<TPW>(wo, A.wo_q[net], tilesL, S, T);
         const Begin after = NN == 1 && ni == 0 ? critic_begin(A.q, 1) : begin_at(A.q[0][0]);
         const Begin back = L > 1 ? begin_of(mat_view(A.qT[net][L - 1], HL, P.H[L - 2]), S.slot, 0, 1) : after;
-        critic_forward<NN, TPW>(z, P, A.q, net, X, H, S, M, DIST ? L : L - 1, A.h, r0, B, T, cur, DIST ? dist_begin(A.q) : back, xv, in,
+        critic_forward<NN>(z, P, A.q, net, X, H, S, M, DIST ? L : L - 1, A.h, r0, B, T, cur, DIST ? dist_begin(A.q) : back, xv, in,
                                 false);
         if (DIST) {
             // cross-entropy against the projected target, dLoss/dlogits, and through the output layer to h_L
             float inv[2];
             const MatView WT = mat_view(A.qT[net][L], atoms, HL);
-            put_tile<TPW>(z, tilesL, H, S, M, inv, T);
+            put_tile(z, tilesL, H, S, M, inv, T);
             put_logits(mat_view(A.q[net][L], HL, atoms), H, H0.base, S, inv, T, cur, begin_of(WT, S.slot, 0, 1));
             float dl[2][DR], lsum[2] = {0.f, 0.f}, dsum[2] = {0.f, 0.f};
 #pragma unroll
@@ -1085,14 +1111,14 @@ __device__ __forceinline__ void critic_step(const SplitCriticArgs& A) {
             row_inv(inv, M.part + 32 * net, T);
             f32x4 hl[2][2];
             load_ahead(A.h[net][L], HL, hl, S, r0, B, T);
-            backward<TPW>(z, WT, logit_tile(H0.base, net), S, inv, A.h[net][L], A.d[net][L], A.col[net][L] + (size_t)wg * HL, HL, r0, B, T,
+            backward(z, WT, logit_tile(H0.base, net), S, inv, A.h[net][L], A.d[net][L], A.col[net][L] + (size_t)wg * HL, HL, r0, B, T,
                           cur, back, hl);
         } else {
         float bias[NN], q[NN][2];
 #pragma unroll
         for (int i = 0; i < NN; ++i) bias[i] = A.bo_q[NN == 2 ? i : net][0];
         if (TPW > 2) head_weights<TPW>(wo, A.wo_q[net], tilesL, S, T);
-        head_values<NN, TPW>(z, wo, S, M, bias, q, T);
+        head_values(z, wo, S, M, bias, q, T);
         float d[2], loss = 0.f, db = 0.f;
 #pragma unroll
         for (int n = 0; n < 2; ++n) {
@@ -1134,9 +1160,9 @@ __device__ __forceinline__ void critic_step(const SplitCriticArgs& A) {
         for (int l = L; l >= 2; --l) {
             const int Hl = P.H[l - 1], Hp = P.H[l - 2];
             load_ahead(A.h[net][l - 1], Hp, hv, S, r0, B, T);
-            put_tile<TPW>(z, (Hl + 31) >> 5, H, S, M, inv, T);
+            put_tile(z, (Hl + 31) >> 5, H, S, M, inv, T);
             const MatView W = mat_view(A.qT[net][l - 1], Hl, Hp);
-            backward<TPW>(z, W, H, S, inv, A.h[net][l - 1], A.d[net][l - 1], A.col[net][l - 1] + (size_t)wg * Hp, Hp, r0, B, T, cur,
+            backward(z, W, H, S, inv, A.h[net][l - 1], A.d[net][l - 1], A.col[net][l - 1] + (size_t)wg * Hp, Hp, r0, B, T, cur,
                           l > 2 ? begin_of(mat_view(A.qT[net][l - 2], Hp, P.H[l - 3]), S.slot, 0, 1) : after, hv);
         }
     }
@@ -1150,7 +1176,7 @@ template <int NN, int TPW, int VAR, bool R = false>
 __device__ __forceinline__ void policy_step(const SplitPolicyArgs& A) {
     warm_args<SplitPolicyArgs>();
     constexpr bool SAC = VAR == VAR_SAC, DIST = VAR == VAR_DIST;
-    const WvOf<R> T = wave_of<R>(blockIdx.x & 1);
+    const auto T = wave_of<R>(blockIdx.x & 1);
     const SplitShape& P = A.shape;
     constexpr int TPA = NN == 2 ? TPW / 2 : TPW;       // the policy's tiles per wavefront
     const int B = A.B, L = P.L, a = P.a, HL = P.H[L - 1], H1 = P.H[0];
@@ -1159,13 +1185,13 @@ __device__ __forceinline__ void policy_step(const SplitPolicyArgs& A) {
     const Share S = NN == 2 ? Share{T.wave >> 2, T.wave & 3, 4} : Share{0, T.wave, SW};
     const Tile X = {P.x0, P.xplane}, H0 = {P.h0, P.hplane};
     const Tile H = {P.h0 + S.net * 2 * P.hplane, P.hplane};
-    const SmallMem M = small_mem(P.sm, P.as);
+    const SmallMem M = small_mem<2>(P.sm, P.as);
     const int atoms = DIST ? A.atoms : 2;
     const int steps = (P.o + a + 31) >> 5;
-    const int col = T.tid & 31;                              // this thread's elements of an action-wide tile: rows row_of(0), row_of(1)
+    const int col = T.tid & 31;                              // this thread's elements of an action-wide tile: rows row_of(e)
     auto row_of = [&](int e) { return (T.tid >> 5) + 16 * e; };
-    Rows xv;
-    InputRows in = input_rows(A.obs, P.o, nullptr, -1, a, P.as, r0, B);
+    Rows<2> xv;
+    InputRows in = input_rows<2>(A.obs, P.o, nullptr, -1, a, P.as, r0, B);
     request_rows(xv, in, steps, T);
     Ahead cur;
     request(cur, begin_of(mat_view(A.pi[0], P.o, P.H[0]), T.wave, 0, 1), T);
@@ -1179,15 +1205,15 @@ __device__ __forceinline__ void policy_step(const SplitPolicyArgs& A) {
     lds_barrier();
     float act[2] = {0.f, 0.f}, eps[2] = {0.f, 0.f}, raw[2] = {0.f, 0.f}, logp[2] = {0.f, 0.f};
     {
-        const int parts = policy_forward<TPA>(P, A.pi, X, H0, M, true, A.hA, aw, r0, B, T, cur, critic_begin(S.net));
+        const int parts = policy_forward<TPA, 2>(P, A.pi, X, H0, M, true, A.hA, aw, r0, B, T, cur, critic_begin(S.net));
 #pragma unroll
         for (int e = 0; e < 2; ++e) {
             const int row = row_of(e);
-            if (SAC) logp[e] = sample_action(H0.base, parts, row, col, a, A.pi_bias, r0, A.sac, act[e], eps[e], raw[e]);
-            else if (col < a) act[e] = tanhf(sum_partials(H0.base, parts, row, col) + A.pi_bias[col]);
+            if (SAC) logp[e] = sample_action<2>(H0.base, parts, row, col, a, A.pi_bias, r0, A.sac, act[e], eps[e], raw[e]);
+            else if (col < a) act[e] = tanhf(sum_partials<2>(H0.base, parts, row, col) + A.pi_bias[col]);
             if (col < a) {
                 if (!R && P.alias) smem[M.act + row * M.as + col] = act[e];
-                else put_value(X, row, P.o + col, act[e], __uint_as_float(0x7F000000u - __float_as_uint(smem[M.inv + row])));
+                else put_value<2>(X, row, P.o + col, act[e], __uint_as_float(0x7F000000u - __float_as_uint(smem[M.inv + row])));
             }
         }
         lds_barrier();
@@ -1207,7 +1233,7 @@ __device__ __forceinline__ void policy_step(const SplitPolicyArgs& A) {
             lds_barrier();
         }
         if (!DIST && TPW <= 2) head_weights<TPW>(wo, A.wo[net], tilesL, S, T);
-        critic_forward<NN, TPW>(z, P, A.q, net, X, H, S, M, NN == 2 && !DIST ? L - 1 : L, A.h, r0, B, T, cur,
+        critic_forward<NN>(z, P, A.q, net, X, H, S, M, NN == 2 && !DIST ? L - 1 : L, A.h, r0, B, T, cur,
                                 DIST ? begin_of(mat_view(A.q[net][L], HL, atoms), S.slot & 1, S.slot >> 1, LOGIT_STEP)
                                      : (NN == 1 && ni == 0 ? critic_begin(1) : back_begin(S.net)), xv, in, false);
         if (DIST) continue;
@@ -1215,7 +1241,7 @@ __device__ __forceinline__ void policy_step(const SplitPolicyArgs& A) {
 #pragma unroll
         for (int i = 0; i < NN; ++i) bias[i] = A.bo[NN == 2 ? i : net][0];
         if (TPW > 2) head_weights<TPW>(wo, A.wo[net], tilesL, S, T);
-        head_values<NN, TPW>(z, wo, S, M, bias, q, T);
+        head_values(z, wo, S, M, bias, q, T);
 #pragma unroll
         for (int n = 0; n < 2; ++n) {
             if (NN == 2) { qv[0][n] = q[0][n]; qv[1][n] = q[NN - 1][n]; }
@@ -1233,7 +1259,7 @@ __device__ __forceinline__ void policy_step(const SplitPolicyArgs& A) {
         const float zk = A.v_min + (float)T.lane * ((A.v_max - A.v_min) / (float)(atoms - 1));
         float inv[2];
         const MatView WT = mat_view(A.qT[net][L], atoms, HL);
-        put_tile<TPW>(z, tilesL, H, S, M, inv, T);
+        put_tile(z, tilesL, H, S, M, inv, T);
         put_logits(mat_view(A.q[net][L], HL, atoms), H, H0.base, S, inv, T, cur, begin_of(WT, S.slot, 0, 1));
         const float b0 = live ? A.bo[0][T.lane] : 0.f, b1 = live ? A.bo[1][T.lane] : 0.f;
         float dl[2][DR];
@@ -1263,7 +1289,7 @@ __device__ __forceinline__ void policy_step(const SplitPolicyArgs& A) {
         row_inv(inv, M.part + 32 * net, T);
         f32x4 hl[2][2];
         load_ahead(A.h[net][L], HL, hl, S, r0, B, T);
-        backward<TPW>(z, WT, logit_tile(H0.base, net), S, inv, A.h[net][L], nullptr, nullptr, HL, r0, B, T, cur, back_begin(net), hl);
+        backward(z, WT, logit_tile(H0.base, net), S, inv, A.h[net][L], nullptr, nullptr, HL, r0, B, T, cur, back_begin(net), hl);
     }
 #pragma unroll
     for (int n = 0; n < 2 && !DIST; ++n) {
@@ -1279,8 +1305,9 @@ __device__ __forceinline__ void policy_step(const SplitPolicyArgs& A) {
         if (T.lane == 0) A.p_loss[wg] = loss;
     }
     // ---- down to the critics' action input
-    f32x4 da[2][2];
-    clear(da);
+    const int ks1 = (H1 + 31) >> 5;
+    const int per = ks1 < S.waves ? ks1 : S.waves;           // partial tiles per network
+    float gs[2] = {0.f, 0.f};                                       // dJ/da of this thread's elements
     float inv[2];
 #pragma unroll 1
     for (int ni = 0; ni < (NN == 2 ? 1 : 2); ++ni) {
@@ -1305,33 +1332,30 @@ __device__ __forceinline__ void policy_step(const SplitPolicyArgs& A) {
         for (int l = L; l >= 2; --l) {
             const int Hl = P.H[l - 1], Hp = P.H[l - 2];
             load_ahead(A.h[net][l - 1], Hp, hv, S, r0, B, T);
-            put_tile<TPW>(z, (Hl + 31) >> 5, H, S, M, inv, T);
+            put_tile(z, (Hl + 31) >> 5, H, S, M, inv, T);
             const MatView W = mat_view(A.qT[net][l - 1], Hl, Hp);
-            backward<TPW>(z, W, H, S, inv, A.h[net][l - 1], nullptr, nullptr, Hp, r0, B, T, cur,
+            backward(z, W, H, S, inv, A.h[net][l - 1], nullptr, nullptr, Hp, r0, B, T, cur,
                           l > 2 ? begin_of(mat_view(A.qT[net][l - 2], Hp, P.H[l - 3]), S.slot, 0, 1) : action_begin(net), hv);
         }
-        put_tile<TPW>(z, (H1 + 31) >> 5, H, S, M, inv, T);
+        put_tile(z, (H1 + 31) >> 5, H, S, M, inv, T);
         const MatView W = mat_view(A.w1aT[net], H1, a);
         const Begin after = NN == 1 && ni == 0 ? back_begin(1) : begin_of(mat_view(A.waT[L], aw, HL), T.wave, 0, 1);
         f32x4 acc[2][2];
         clear(acc);
-        if (S.slot < W.ks) mac_steps<2>(acc, W, 0, H, T, S.slot, S.waves, cur, after);
+        if (S.slot < W.ks) mac_steps(acc, W, 0, H, T, S.slot, S.waves, cur, after);
         else request(cur, after, T);
         scaled(acc, inv, W.inv[0]);
+        put_partial(acc, H0.base, S.net * per + S.slot, S.slot < per, T);
 #pragma unroll
-        for (int m = 0; m < 2; ++m)
-#pragma unroll
-            for (int n = 0; n < 2; ++n) da[m][n] += acc[m][n];
+        for (int e = 0; e < 2; ++e)
+            if (col < a) gs[e] += sum_partials<2>(H0.base, NN * per, row_of(e), col);
     }
-    const int ks1 = (H1 + 31) >> 5;
-    const int per = ks1 < S.waves ? ks1 : S.waves;           // partial tiles per network
-    put_partial(da, H0.base, S.net * per + S.slot, S.slot < per, T);
     float g[2] = {0.f, 0.f}, g2[2] = {0.f, 0.f};             // gradient at the output layer: column col, and a + col (raw)
 #pragma unroll
     for (int e = 0; e < 2; ++e) {
         const int row = row_of(e);
         const bool rv = r0 + row < B;
-        const float s = col < a ? sum_partials(H0.base, NN * per, row, col) : 0.f;
+        const float s = gs[e];
         if (!SAC) {
             g[e] = (col < a && rv) ? s * (1.f - act[e] * act[e]) : 0.f;
         } else if (col < a && rv) {
@@ -1357,8 +1381,8 @@ __device__ __forceinline__ void policy_step(const SplitPolicyArgs& A) {
         float inv_d;
         const float s = scale_for(half_max(fmaxf(fabsf(g[e]), fabsf(g2[e]))), inv_d);
         if (col == 0) smem[M.inv + row] = inv_d;
-        if (!SAC || col < a || col >= aw) put_value(D, row, col, g[e], s);
-        if (SAC && col < a) put_value(D, row, a + col, g2[e], s);
+        if (!SAC || col < a || col >= aw) put_value<2>(D, row, col, g[e], s);
+        if (SAC && col < a) put_value<2>(D, row, a + col, g2[e], s);
         if (!SAC || col < a) sums[row * 33 + col] = g[e];
         if (SAC && col < a) sums[row * 33 + a + col] = g2[e];
         if (SAC && col == 0) smem[M.logp + row] = r0 + row < B ? logp[e] : 0.f;
@@ -1383,11 +1407,11 @@ __device__ __forceinline__ void policy_step(const SplitPolicyArgs& A) {
         for (int l = L; l >= 1; --l) {
             const int N = P.H[l - 1];
             const MatView W = mat_view(A.waT[l], l == L ? aw : P.H[l], N);
-            backward<TPA>(za, W, l == L ? D : H0, SA, inv, A.hA[l], A.dA[l], A.colA[l] + (size_t)wg * N, N, r0, B, T, cur,
+            backward(za, W, l == L ? D : H0, SA, inv, A.hA[l], A.dA[l], A.colA[l] + (size_t)wg * N, N, r0, B, T, cur,
                           l > 1 ? begin_of(mat_view(A.waT[l - 1], N, P.H[l - 2]), T.wave, 0, 1) : begin_at(A.pi[0]), hv);
             if (l > 1) {
                 load_ahead(A.hA[l - 1], P.H[l - 2], hv, SA, r0, B, T);
-                put_tile<TPA>(za, W.tiles, H0, SA, M, inv, T);
+                put_tile(za, W.tiles, H0, SA, M, inv, T);
             }
         }
     }
@@ -1396,36 +1420,36 @@ __device__ __forceinline__ void policy_step(const SplitPolicyArgs& A) {
 // =============================================================================================
 // Actor step on one row tile (Section 3.3, Algorithm 1): a = clip(pi(s) + sigma_i * eps, -1, 1).
 // =============================================================================================
-template <int TPW, int VAR>
+template <int TPW, int VAR, int NB = 2>
 __device__ __forceinline__ void act_step(const SplitActArgs& A) {
     warm_args<SplitActArgs>();
     constexpr bool SAC = VAR == VAR_SAC;
     const auto T = wave_of(0);
     const SplitShape& P = A.shape;
-    const int B = A.B, a = P.a, r0 = blockIdx.x * 32;
+    const int B = A.B, a = P.a, r0 = blockIdx.x * 16 * NB;
     const int aw = SAC ? 2 * a : a;
     const Tile X = {P.x0, P.xplane}, H = {P.h0, P.hplane};
-    const SmallMem M = small_mem(P.sm, P.as);
+    const SmallMem M = small_mem<NB>(P.sm, P.as);
     const int steps = (P.o + 31) >> 5;
-    Rows xv;
-    InputRows in = input_rows(A.obs, P.o, nullptr, -1, 0, P.as, r0, B);
+    Rows<NB> xv;
+    InputRows in = input_rows<NB>(A.obs, P.o, nullptr, -1, 0, P.as, r0, B);
     if (A.nmean != nullptr) {
         in.norm = true;
-        in.mean = rows_of(A.nmean, P.o, 0, 1); in.rstd = rows_of(A.nrstd, P.o, 0, 1);
+        in.mean = rows_of(A.nmean, P.o, 0, 1, 1); in.rstd = rows_of(A.nrstd, P.o, 0, 1, 1);
     }
     request_rows(xv, in, steps, T);
-    Ahead cur;
+    AheadOf<NB == 2 ? 2 : 1> cur;
     request(cur, begin_of(mat_view(A.pi[0], P.o, P.H[0]), T.wave, 0, 1), T);
     put_rows(xv, in, steps, X, M.inv, 0.f, T);
     lds_barrier();
-    const int parts = policy_forward<TPW>(P, A.pi, X, H, M, false, nullptr, aw, r0, B, T, cur, begin_at(A.pi[0]));
+    const int parts = policy_forward<TPW, NB>(P, A.pi, X, H, M, false, nullptr, aw, r0, B, T, cur, begin_at(A.pi[0]));
     const int col = T.tid & 31;
 #pragma unroll
-    for (int e = 0; e < 2; ++e) {
+    for (int e = 0; e < NB; ++e) {
         const int row = (T.tid >> 5) + 16 * e, env = r0 + row;
         if (SAC) {
             float act, eps, raw;
-            (void)sample_action(H.base, parts, row, col, a, A.pi_bias, r0, A.sac, act, eps, raw);
+            (void)sample_action<NB>(H.base, parts, row, col, a, A.pi_bias, r0, A.sac, act, eps, raw);
             if (col < a && env < B) A.act_out[(size_t)env * a + col] = act;
         } else if (col < a && env < B) {
             const GemmNoise& nz = A.noise;
@@ -1438,7 +1462,7 @@ __device__ __forceinline__ void act_step(const SplitActArgs& A) {
             double sigma = (double)nz.sigma_min;
             if (nz.sigma_rows > 1)
                 sigma += ((double)env / (double)(nz.sigma_rows - 1)) * ((double)nz.sigma_max - (double)nz.sigma_min);
-            const float x = tanhf(sum_partials(H.base, parts, row, col) + A.pi_bias[col]) + (float)(sigma * eps);
+            const float x = tanhf(sum_partials<NB>(H.base, parts, row, col) + A.pi_bias[col]) + (float)(sigma * eps);
             A.act_out[(size_t)env * a + col] = fminf(fmaxf(x, -1.f), 1.f);
         }
     }
@@ -1575,7 +1599,7 @@ __global__ __launch_bounds__(ST) void layer_rowtile_kernel(const GemmGroup) {
 #pragma unroll
         for (int m = 0; m < 2; ++m) bias[m] = *reinterpret_cast<const f32x4*>(W.bias + 32 * tile + 16 * m + 4 * T.q);
         if (NB == 2 && epi == EPI_MUL_DELU) load_tile<NB>(P.aux, N, tile, hv, r0, M, T);      // (64 rows: too many registers)
-        mac_steps<NB>(acc, W, tile, X, T, 0, 1, cur, begin_of(W, tile + SW, 0, 1));
+        mac_steps(acc, W, tile, X, T, 0, 1, cur, begin_of(W, tile + SW, 0, 1));
         if (NB != 2 && epi == EPI_MUL_DELU) load_tile<NB>(P.aux, N, tile, hv, r0, M, T);
 #pragma unroll
         for (int n = 0; n < NB; ++n) {
@@ -1663,17 +1687,17 @@ hipError_t layer_rowtile_launch(GemmGroup& g, hipStream_t stream) {
 // ---- host side ------------------------------------------------------------------------------------------------
 // LDS plan of a shape: the activation tiles of `nets` networks, the input tile behind them or, where that does not fit, in
 // their place, and the small arrays.  Returns the bytes, 0 if the shape does not fit at all.
-static size_t plan_lds(SplitShape& p, int nets, int in_cols, bool dist = false) {
+static size_t plan_lds(SplitShape& p, int nets, int in_cols, bool dist = false, int nb = 2) {
     int w = 0;
     for (int l = 0; l < p.L; ++l) w = p.H[l] > w ? p.H[l] : w;
-    p.hplane = (w + 31) / 32 * 4 * CS;
-    p.xplane = (in_cols + 31) / 32 * 4 * CS;
+    p.hplane = (w + 31) / 32 * 4 * (16 * nb + 1);
+    p.xplane = (in_cols + 31) / 32 * 4 * (16 * nb + 1);
     p.as = p.a | 1;
     const int h_units = nets * 2 * p.hplane;
-    const size_t small = sizeof(float) * (size_t)(576 + 32 * p.as);
+    const size_t small = sizeof(float) * (size_t)small_floats(nb, p.as);
     // the policy step's output-layer tile and its column sums also live in the place of the activations
     // (distributional critics: eight partial tiles of logits)
-    const int least = dist ? 2 * DIST_PARTS * 256 : 2 * 4 * CS + 32 * 33 / 4;
+    const int least = dist ? 2 * DIST_PARTS * 256 : 2 * 4 * (16 * nb + 1) + 16 * nb * 33 / 4;
     p.h0 = 0; p.x0 = h_units < least ? least : h_units; p.alias = 0;
     size_t units = (size_t)p.x0 + 2 * (size_t)p.xplane;
     if (units * 16 + small > SPLIT_LDS) {
@@ -1718,26 +1742,27 @@ template <int VAR, bool R>
 __global__ __launch_bounds__(ST) void chain_policy_kernel(const SplitPolicyArgs) { policy_step<2, 4, VAR, R>(kernel_args<SplitPolicyArgs>()); }
 template <int NN, int TPW, int VAR>
 __global__ __launch_bounds__(ST) void split_policy_kernel(const SplitPolicyArgs) { policy_step<NN, TPW, VAR>(kernel_args<SplitPolicyArgs>()); }
-template <int VAR>
-__global__ __launch_bounds__(ST) void fused_act_kernel(const SplitActArgs) { act_step<1, VAR>(kernel_args<SplitActArgs>()); }
-template <int VAR>
-__global__ __launch_bounds__(ST) void chain_act_kernel(const SplitActArgs) { act_step<2, VAR>(kernel_args<SplitActArgs>()); }
+template <int VAR, int NB>
+__global__ __launch_bounds__(ST) void fused_act_kernel(const SplitActArgs) { act_step<1, VAR, NB>(kernel_args<SplitActArgs>()); }
+template <int VAR, int NB>
+__global__ __launch_bounds__(ST) void chain_act_kernel(const SplitActArgs) { act_step<2, VAR, NB>(kernel_args<SplitActArgs>()); }
 
-#define SPLIT_LAUNCH(KERNEL, KID)                                                                                  \
+#define SPLIT_LAUNCH_ROWS(KERNEL, KID, ROWS)                                                                                  \
     do {                                                                                                           \
         static LdsLimit configured;                                                                                \
         const hipError_t le = set_lds_limit(reinterpret_cast<const void*>(KERNEL), lds, configured);               \
         if (le != hipSuccess) return le;                                                                           \
         const ProfSlot ps = prof_slot();                                                                           \
-        PQL_LAUNCH(ps, (KERNEL), dim3((a.B + 31) / 32), dim3(ST), lds, stream, a);                                 \
+        PQL_LAUNCH(ps, (KERNEL), dim3((a.B + (ROWS) - 1) / (ROWS)), dim3(ST), lds, stream, a);                     \
         prof_commit(ps, KID, flops, 0.0);                                                                          \
         return hipGetLastError();                                                                                  \
     } while (0)
+#define SPLIT_LAUNCH(KERNEL, KID) SPLIT_LAUNCH_ROWS(KERNEL, KID, 32)
 // Picks the kernel of one step: shape and policy variant are fixed at compile time, one kernel for each pair that occurs (the
 // class only decides what a launch is filed under).
 #define SPLIT_PICK(STEP, VAR)                                                                                      \
     do {                                                                                                           \
-        const bool r = regular(p);                                                                                 \
+        const bool r = regular(p) && !p.alias;                                                                                 \
         if (w <= 256 && r) SPLIT_LAUNCH((fused_##STEP##_kernel<VAR, true>), kind == SPLIT_FUSED ? fused_kid : split_kid); \
         if (w <= 256) SPLIT_LAUNCH((fused_##STEP##_kernel<VAR, false>), kind == SPLIT_FUSED ? fused_kid : split_kid); \
         if (w <= 512 && VAR == VAR_PLAIN && r)                                                                     \
@@ -1752,7 +1777,15 @@ __global__ __launch_bounds__(ST) void chain_act_kernel(const SplitActArgs) { act
 static bool regular(const SplitShape& p) {
     for (int l = 0; l < p.L; ++l)
         if (p.H[l] & 3) return false;
-    return !p.alias && p.o + p.a <= 32 * XV;
+    return p.o + p.a <= 32 * XV;
+}
+// Whether the Actor step takes tiles of 64 rows, which read the weights half as often: a tile takes five thirds of the time of one
+// of 32, one tile at a time fits a compute unit, and the launch takes as many rounds of 256 as it has tiles for.  us per call with 32
+// / 64 rows at 8193, 16384, 20000, 24576, 28000 and 32768 environments: 256-256 25.7 / 23.6, 28.0 / 24.4, 37.3 / 41.4, 38.0 / 41.3,
+// 47.1 / 41.3, 48.2 / 41.8; 512-256-128 41.4 / 36.1, 45.0 / 38.7, 62.6 / 66.6, 64.2 / 66.5, 81.3 / 67.1, 83.0 / 70.5.
+static bool takes_64_rows(int B) {
+    auto rounds = [&](int rows) { return ((B + rows - 1) / rows + 255) / 256; };
+    return 5 * rounds(64) < 3 * rounds(32);
 }
 static bool kind_fits(int kind, int w) {
     return kind == SPLIT_FUSED ? w <= 256 : (kind == SPLIT_CHAIN ? w <= 512 : true);
@@ -1796,16 +1829,22 @@ hipError_t split_act_launch(SplitActArgs& a, int kind, hipStream_t stream) {
     SplitShape& p = a.shape;
     const int w = widest(p), aw = a.sac.on ? 2 * p.a : p.a;
     if (!split_shape_ok(p.o, p.a, aw, p.H, p.L) || w > 512) return hipErrorInvalidValue;
-    const size_t lds = plan_lds(p, 1, p.o);
+    const bool rows64 = takes_64_rows(a.B) && regular(p);
+    const size_t lds = plan_lds(p, 1, p.o, false, rows64 ? 4 : 2);
     double pa = (double)p.o * p.H[0] + (double)p.H[p.L - 1] * aw;
     for (int l = 1; l < p.L; ++l) pa += (double)p.H[l - 1] * p.H[l];
     const double flops = 2.0 * a.B * pa;
+#define ACT_LAUNCH(KERNEL, VAR, KID)                                                                               \
+    do {                                                                                                           \
+        if (rows64) SPLIT_LAUNCH_ROWS((KERNEL<VAR, 4>), KID, 64);                                                  \
+        SPLIT_LAUNCH((KERNEL<VAR, 2>), KID);                                                                       \
+    } while (0)
     if (kind == SPLIT_FUSED) {
-        if (a.sac.on) SPLIT_LAUNCH(fused_act_kernel<VAR_SAC>, KID_FUSED_ACT);
-        SPLIT_LAUNCH(fused_act_kernel<VAR_PLAIN>, KID_FUSED_ACT);
+        if (a.sac.on) ACT_LAUNCH(fused_act_kernel, VAR_SAC, KID_FUSED_ACT);
+        ACT_LAUNCH(fused_act_kernel, VAR_PLAIN, KID_FUSED_ACT);
     }
-    if (a.sac.on) SPLIT_LAUNCH(chain_act_kernel<VAR_SAC>, KID_CHAIN_ACT);
-    SPLIT_LAUNCH(chain_act_kernel<VAR_PLAIN>, KID_CHAIN_ACT);
+    if (a.sac.on) ACT_LAUNCH(chain_act_kernel, VAR_SAC, KID_CHAIN_ACT);
+    ACT_LAUNCH(chain_act_kernel, VAR_PLAIN, KID_CHAIN_ACT);
 }
 
 }  // namespace pql

@@ -370,3 +370,32 @@ def test_policy_gradient_no_further_from_float64_than_fp32_products():
         errs.append(np.linalg.norm(s.a_g.cpu().numpy() - g) / np.linalg.norm(g))
     print("policy gradient 2-norm errors", errs, flush=True)
     assert np.mean(errs) <= 9e-8
+
+
+@pytest.mark.parametrize("case,num", [("narrow", 8193), ("narrow", 16384), ("one_step_inputs", 16321), ("widest", 8193), ("widest", 24577),
+                                      ("stochastic", 8200)])
+def test_actor_step_on_tiles_of_64_rows(case, num):
+    """The Actor step on tiles of 64 rows: a last tile of one row, full tiles, inputs of one step and of eight, standardised
+    observations.  To 1e-5 of the actions' scale of 1 (products to 1e-7, tanh and noise as on the other tiles)."""
+    import torch
+    w = {"narrow": workload((96, 64), 60, 8, num), "one_step_inputs": workload((64, 256, 32), 7, 3, num, obs_norm=True),
+         "widest": workload((512, 64, 256), 256, 32, num, obs_norm=True), "stochastic": workload((128, 96), 45, 11, num, sac=True)}[case]
+    print(case, w.hidden, "N", num, flush=True)
+    s = session(w)
+    rng = np.random.default_rng(17)
+    obs = (1.0 + 2.0 * rng.standard_normal((num, w.obs_dim))).astype(np.float32)
+    seen = obs
+    if w.obs_norm:
+        from parity_util import oracle_normalizer
+        nz = oracle_normalizer(w)
+        row = W.transition_rows(w, W.data_rng(w), 1)[0]
+        s.push(row)
+        nz.update(row["obs"])
+        seen = nz.normalize(obs)
+    lo, hi = float(np.float32(0.05)), float(np.float32(0.8))
+    got = s.act(torch.from_numpy(obs).cuda(), lo, hi).cpu().numpy().astype(np.float64)
+    ref = (O.sac_actor_act(s.actor_init, w.actor_dims(), seen, w.rng_seed, 0) if w.sac else
+           O.actor_act(s.actor_init, w.actor_dims(), seen, lo, hi, w.rng_seed, 0))
+    err = np.abs(got - ref).max()
+    print("max abs err %.2e" % err, flush=True)
+    assert err <= TOL
