@@ -22,10 +22,10 @@
 // wants them, so an epilogue packs its results with no exchange between lanes and writes them to LDS as 16-byte pieces,
 // and row maxima, output heads and their gradients come from registers.
 //
-// What bounds it: with 32 rows per workgroup the weights (4 bytes each, once per workgroup) come from L2 at 30 - 40 bytes
-// per clock and compute unit, about twice the time of the matrix work; a paired 256 x 256 layer takes 7.0 us with all
-// compute units running (5.4 us with 64 of them: the rest is the clock the power limit leaves), where the fp32 MFMA
-// kernels take 18.8 us.
+// What bounds it: with 32 rows per workgroup the weights (4 bytes each, once per workgroup) come from L2 at about 50 bytes per clock
+// and compute unit (a loop that only reads reaches 56 with all compute units running), more than twice the time of the matrix work: a
+// paired 256 x 256 layer takes 5 us, where the fp32 MFMA kernels take 18.8.  That is half of the launch; the other half is what
+// lies between the products, phases in which a wavefront waits for LDS, barriers and memory or issues one instruction every nine cycles.
 //
 // The weights are brought into fragment order by split_weights_kernel at the start of every call (zero-padded to whole
 // tiles, so any layer width works): a lane's operand is one 16-byte load, a wavefront's a contiguous kilobyte.
@@ -246,9 +246,11 @@ hipError_t split_weights_launch(SplitPrepArgs& a, bool both, int kid, hipStream_
 // ---- a layer on the tile --------------------------------------------------------------------------------
 struct Wv { int tid, lane, wave, l15, q; unsigned hi, lo; };        // hi, lo: this lane's byte offsets into a k-step's fragments
 // R: what is rare is not compiled in (an input of more than XV steps or in the place of the activations, widths that are no
-// multiples of four): with two wavefronts per SIMD a wavefront issues an instruction every eight or nine cycles, so the tests and
-// the scalars kept (and spilled) for paths not taken cost as much as work does.  us per launch with / without them: critic update
-// 256-256 58 / 55, policy update 51 / 48, critic update 512-256-128 125 / 120, 64-64 at 256 rows 23.6 / 22.
+// multiples of four): a wavefront issues an instruction every nine cycles (4.5 where two share a SIMD), and the tests, scalars and
+// registers kept (and spilled) for paths not taken lengthen every phase.  us per launch with / without them: critic update 256-256
+// 58 / 55, policy update 51 / 48, critic update 512-256-128 125 / 120, 64-64 at 256 rows 23.6 / 22; with the input in the place of
+// the activations critic update 1024-512-256 at 4096 rows 364 / 328, policy update 512-512-256 at 16384 385 / 373.
+enum Shapes : int { GENERAL = 0, REGULAR = 1, REGULAR_ALIAS = 2 };      // REGULAR_ALIAS: the input may lie in the place of the activations
 template <bool R>
 struct WvOf : Wv { static constexpr bool regular = R; };
 
@@ -920,11 +922,11 @@ __device__ __forceinline__ WvOf<R> wave_of(int other) {        // other: whether
 // t_i = Q'_i(s', a'), y = ret + boot * min(t_1, t_2); q_i = Q_i(s, a); loss partials, output deltas, and the deltas of
 // every hidden layer of both critics.  NN networks side by side, TPW output tiles per wavefront.
 // =============================================================================================
-template <int NN, int TPW, int VAR, bool R = false>
+template <int NN, int TPW, int VAR, int R>
 __device__ __forceinline__ void critic_step(const SplitCriticArgs& A) {
     warm_args<SplitCriticArgs>();
     constexpr bool SAC = VAR == VAR_SAC, DIST = VAR == VAR_DIST;
-    const auto T = wave_of<R>(blockIdx.x & 1);
+    const auto T = wave_of<R != GENERAL>(blockIdx.x & 1);
     const SplitShape& P = A.shape;
     const int B = A.B, L = P.L, a = P.a, HL = P.H[L - 1];
     const int r0 = blockIdx.x * 32, wg = blockIdx.x, nwg = gridDim.x;
@@ -968,7 +970,7 @@ __device__ __forceinline__ void critic_step(const SplitCriticArgs& A) {
                 act = tanhf(sum_partials<2>(H0.base, parts, row, col) + A.pi_bias[col]);
             }
             if (col < a) {
-                if (!R && P.alias) smem[M.act + row * M.as + col] = act;
+                if (R != REGULAR && P.alias) smem[M.act + row * M.as + col] = act;
                 else put_value<2>(X, row, P.o + col, act, __uint_as_float(0x7F000000u - __float_as_uint(smem[M.inv + row])));
             }
         }
@@ -996,7 +998,7 @@ __device__ __forceinline__ void critic_step(const SplitCriticArgs& A) {
         for (int ni = 0; ni < (NN == 2 ? 1 : 2); ++ni) {
             const int net = NN == 2 ? S.net : ni;
             if (ni > 0) lds_barrier();      // every wavefront has read the other critic's head partials (and activations)
-            if (!R && P.alias) {      // the input tile shares its place with the activations: bring the rows in again
+            if (R != REGULAR && P.alias) {      // the input tile shares its place with the activations: bring the rows in again
                 in.act_lds = M.act;
                 request_rows(xv, in, steps, T);
                 put_rows(xv, in, steps, X, M.inv, 1.f, T);
@@ -1056,7 +1058,7 @@ __device__ __forceinline__ void critic_step(const SplitCriticArgs& A) {
 #pragma unroll 1
     for (int ni = 0; ni < (NN == 2 ? 1 : 2); ++ni) {
         const int net = NN == 2 ? S.net : ni;
-        if (NN == 2 || (!R && P.alias) || ni == 0) {
+        if (NN == 2 || (R != REGULAR && P.alias) || ni == 0) {
             if (ni > 0) request_rows(xv, in, steps, T);       // (else requested during the target critics)
             lds_barrier();     // the head partials of the networks before have been read, and so has their input
             put_rows(xv, in, steps, X, M.inv, 0.f, T);
@@ -1172,11 +1174,11 @@ __device__ __forceinline__ void critic_step(const SplitCriticArgs& A) {
 // P-learner step on one row tile (Algorithm 2: maximise min_i Q_i(s, pi(s))): a = pi(s), both critics on (s, a), the
 // gradient -1/B through the smaller critic down to its action input, through tanh' and back through the policy.
 // =============================================================================================
-template <int NN, int TPW, int VAR, bool R = false>
+template <int NN, int TPW, int VAR, int R>
 __device__ __forceinline__ void policy_step(const SplitPolicyArgs& A) {
     warm_args<SplitPolicyArgs>();
     constexpr bool SAC = VAR == VAR_SAC, DIST = VAR == VAR_DIST;
-    const auto T = wave_of<R>(blockIdx.x & 1);
+    const auto T = wave_of<R != GENERAL>(blockIdx.x & 1);
     const SplitShape& P = A.shape;
     constexpr int TPA = NN == 2 ? TPW / 2 : TPW;       // the policy's tiles per wavefront
     const int B = A.B, L = P.L, a = P.a, HL = P.H[L - 1], H1 = P.H[0];
@@ -1212,7 +1214,7 @@ __device__ __forceinline__ void policy_step(const SplitPolicyArgs& A) {
             if (SAC) logp[e] = sample_action<2>(H0.base, parts, row, col, a, A.pi_bias, r0, A.sac, act[e], eps[e], raw[e]);
             else if (col < a) act[e] = tanhf(sum_partials<2>(H0.base, parts, row, col) + A.pi_bias[col]);
             if (col < a) {
-                if (!R && P.alias) smem[M.act + row * M.as + col] = act[e];
+                if (R != REGULAR && P.alias) smem[M.act + row * M.as + col] = act[e];
                 else put_value<2>(X, row, P.o + col, act[e], __uint_as_float(0x7F000000u - __float_as_uint(smem[M.inv + row])));
             }
         }
@@ -1226,7 +1228,7 @@ __device__ __forceinline__ void policy_step(const SplitPolicyArgs& A) {
     for (int ni = 0; ni < (NN == 2 ? 1 : 2); ++ni) {
         const int net = NN == 2 ? S.net : ni;
         if (ni > 0) lds_barrier();          // every wavefront has read the other critic's head partials (and activations)
-        if (!R && P.alias) {
+        if (R != REGULAR && P.alias) {
             in.act_lds = M.act;
             request_rows(xv, in, steps, T);
             put_rows(xv, in, steps, X, M.inv, 1.f, T);
@@ -1730,18 +1732,18 @@ bool split_shape_ok(int o, int a, int aw, const int* H, int L, bool dist) {
 // ---- kernels ------------------------------------------------------------------------------------------------------
 // fused_*: every layer at most 256 wide (two output tiles per wavefront); chain_*: at most 512, scalar critics and deterministic
 // policy (four); split_*: at most 512 with the other variants, and layers above 512 with the critics one after the other.
-template <int VAR, bool R>
+template <int VAR, int R>
 __global__ __launch_bounds__(ST) void fused_critic_kernel(const SplitCriticArgs) { critic_step<2, 2, VAR, R>(kernel_args<SplitCriticArgs>()); }
-template <int VAR, bool R>
+template <int VAR, int R>
 __global__ __launch_bounds__(ST) void chain_critic_kernel(const SplitCriticArgs) { critic_step<2, 4, VAR, R>(kernel_args<SplitCriticArgs>()); }
-template <int NN, int TPW, int VAR>
-__global__ __launch_bounds__(ST) void split_critic_kernel(const SplitCriticArgs) { critic_step<NN, TPW, VAR>(kernel_args<SplitCriticArgs>()); }
-template <int VAR, bool R>
+template <int NN, int TPW, int VAR, int R>
+__global__ __launch_bounds__(ST) void split_critic_kernel(const SplitCriticArgs) { critic_step<NN, TPW, VAR, R>(kernel_args<SplitCriticArgs>()); }
+template <int VAR, int R>
 __global__ __launch_bounds__(ST) void fused_policy_kernel(const SplitPolicyArgs) { policy_step<2, 2, VAR, R>(kernel_args<SplitPolicyArgs>()); }
-template <int VAR, bool R>
+template <int VAR, int R>
 __global__ __launch_bounds__(ST) void chain_policy_kernel(const SplitPolicyArgs) { policy_step<2, 4, VAR, R>(kernel_args<SplitPolicyArgs>()); }
-template <int NN, int TPW, int VAR>
-__global__ __launch_bounds__(ST) void split_policy_kernel(const SplitPolicyArgs) { policy_step<NN, TPW, VAR>(kernel_args<SplitPolicyArgs>()); }
+template <int NN, int TPW, int VAR, int R>
+__global__ __launch_bounds__(ST) void split_policy_kernel(const SplitPolicyArgs) { policy_step<NN, TPW, VAR, R>(kernel_args<SplitPolicyArgs>()); }
 template <int VAR, int NB>
 __global__ __launch_bounds__(ST) void fused_act_kernel(const SplitActArgs) { act_step<1, VAR, NB>(kernel_args<SplitActArgs>()); }
 template <int VAR, int NB>
@@ -1762,15 +1764,21 @@ __global__ __launch_bounds__(ST) void chain_act_kernel(const SplitActArgs) { act
 // class only decides what a launch is filed under).
 #define SPLIT_PICK(STEP, VAR)                                                                                      \
     do {                                                                                                           \
-        const bool r = regular(p) && !p.alias;                                                                                 \
-        if (w <= 256 && r) SPLIT_LAUNCH((fused_##STEP##_kernel<VAR, true>), kind == SPLIT_FUSED ? fused_kid : split_kid); \
-        if (w <= 256) SPLIT_LAUNCH((fused_##STEP##_kernel<VAR, false>), kind == SPLIT_FUSED ? fused_kid : split_kid); \
+        const bool r = regular(p);                                                                                 \
+        if (w <= 256 && r && !p.alias)                                                                             \
+            SPLIT_LAUNCH((fused_##STEP##_kernel<VAR, REGULAR>), kind == SPLIT_FUSED ? fused_kid : split_kid);      \
+        if (w <= 256) SPLIT_LAUNCH((fused_##STEP##_kernel<VAR, GENERAL>), kind == SPLIT_FUSED ? fused_kid : split_kid);\
+        if (w <= 512 && VAR == VAR_PLAIN && r && !p.alias)                                                         \
+            SPLIT_LAUNCH((chain_##STEP##_kernel<VAR_PLAIN, REGULAR>), kind == SPLIT_CHAIN ? chain_kid : split_kid);\
         if (w <= 512 && VAR == VAR_PLAIN && r)                                                                     \
-            SPLIT_LAUNCH((chain_##STEP##_kernel<VAR_PLAIN, true>), kind == SPLIT_CHAIN ? chain_kid : split_kid);   \
+            SPLIT_LAUNCH((chain_##STEP##_kernel<VAR_PLAIN, REGULAR_ALIAS>), kind == SPLIT_CHAIN ? chain_kid : split_kid);\
         if (w <= 512 && VAR == VAR_PLAIN)                                                                          \
-            SPLIT_LAUNCH((chain_##STEP##_kernel<VAR_PLAIN, false>), kind == SPLIT_CHAIN ? chain_kid : split_kid);  \
-        if (w <= 512) SPLIT_LAUNCH((split_##STEP##_kernel<2, 4, VAR == VAR_PLAIN ? VAR_SAC : VAR>), split_kid);    \
-        if (VAR != VAR_DIST) SPLIT_LAUNCH((split_##STEP##_kernel<1, 4, VAR == VAR_DIST ? VAR_PLAIN : VAR>), split_kid); \
+            SPLIT_LAUNCH((chain_##STEP##_kernel<VAR_PLAIN, GENERAL>), kind == SPLIT_CHAIN ? chain_kid : split_kid);\
+        constexpr int V2 = VAR == VAR_PLAIN ? VAR_SAC : VAR, V1 = VAR == VAR_DIST ? VAR_PLAIN : VAR;               \
+        if (w <= 512 && r) SPLIT_LAUNCH((split_##STEP##_kernel<2, 4, V2, REGULAR_ALIAS>), split_kid);              \
+        if (w <= 512) SPLIT_LAUNCH((split_##STEP##_kernel<2, 4, V2, GENERAL>), split_kid);                         \
+        if (VAR != VAR_DIST && r) SPLIT_LAUNCH((split_##STEP##_kernel<1, 4, V1, REGULAR_ALIAS>), split_kid);       \
+        if (VAR != VAR_DIST) SPLIT_LAUNCH((split_##STEP##_kernel<1, 4, V1, GENERAL>), split_kid);                  \
     } while (0)
 
 // Whether the kernels without the rare paths take this shape (after plan_lds).

@@ -399,3 +399,32 @@ def test_actor_step_on_tiles_of_64_rows(case, num):
     err = np.abs(got - ref).max()
     print("max abs err %.2e" % err, flush=True)
     assert err <= TOL
+
+
+RARE = {            # the kernels that keep what the others leave out: widths that are no multiples of four, inputs of more than eight steps
+    "odd_fused": workload((63, 30), 9, 3, 65),
+    "odd_pair": workload((301, 62), 33, 5, 97),
+    "odd_pair_sac": workload((301, 62), 33, 5, 97, sac=True),
+    "odd_pair_atoms": workload((301, 62), 33, 5, 97, num_atoms=21),
+    "odd_single_sac": workload((514, 31), 20, 4, 65, sac=True),
+    "nine_steps": workload((64, 32), 250, 7, 33),
+    "eight_steps": workload((512, 512), 248, 8, 2050),             # 256 columns: the widest regular input, in the place of the activations
+}
+
+
+@pytest.mark.parametrize("case", list(RARE))
+def test_gradients_of_rare_shapes(case):
+    w = RARE[case]
+    print(case, w.hidden, "B", w.batch, flush=True)
+    s, ring = session(w), oracle_ring(w)
+    fill_both(s, ring, w, w.nstep + 3)
+    L = oracle_learner(w, s.actor_init, s.critic_init)
+    s.sample(w.batch)
+    batch = oracle_batch(ring, w, w.batch, 0, None)
+    s.critic_update(w.batch)
+    losses, g = L.critic_update(batch)
+    s.actor_update(None, w.batch)
+    _, ga = L.actor_update(batch["obs"])
+    assert rel_err(s.critic_loss.cpu().numpy(), losses) <= TOL
+    assert_params_close(s.c_g.cpu().numpy(), g, w.critic_dims(), 2, TOL, "critic grad")
+    assert_params_close(s.a_g.cpu().numpy(), ga, w.actor_dims(), 1, TOL, "actor grad")
