@@ -950,6 +950,20 @@ static const float* add_output(const pql_ctx* c, SplitPrep& prep, const float* p
     return prep.add(p + c->c_w[c->L], nullptr, 1, c->cfg.hidden[c->L - 1], SPLIT_VECTOR);
 }
 
+// Not part of the interface: rows per tile of the Actor step's kernel on prepared weights, 0 where a launch per layer takes its place.
+int32_t pql_internal_act_tile_rows(const pql_config* cfg, int32_t num) {
+    const int rc = validate_cfg(cfg);
+    if (rc != PQL_OK) return rc;
+    if (num < 1 || num > cfg->max_batch) return PQL_ERR_INVALID_ARG;
+    Layout w;
+    make_layout(cfg, w);
+    if (w.split == 0 || act_family(cfg, num) == FAM_LAYERED) return 0;
+    SplitShape p;
+    p.o = cfg->obs_dim; p.a = cfg->act_dim; p.L = cfg->n_hidden;
+    for (int l = 0; l < p.L; ++l) p.H[l] = cfg->hidden[l];
+    return split_act_rows(p, num, cfg->stochastic_policy != 0);
+}
+
 int32_t pql_actor_act(pql_ctx* c, const float* actor_params, const float* obs, int32_t num, float sigma_min,
                       float sigma_max, float* act_out, void* workspace, void* stream) {
     if (!c) return PQL_ERR_NULL;

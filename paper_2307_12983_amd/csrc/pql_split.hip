@@ -1787,14 +1787,36 @@ static bool regular(const SplitShape& p) {
         if (p.H[l] & 3) return false;
     return p.o + p.a <= 32 * XV;
 }
+// Multiply-adds of the policy for one state.
+static double policy_weights(const SplitShape& p, int aw) {
+    double n = (double)p.o * p.H[0] + (double)p.H[p.L - 1] * aw;
+    for (int l = 1; l < p.L; ++l) n += (double)p.H[l - 1] * p.H[l];
+    return n;
+}
 // Whether the Actor step takes tiles of 64 rows, which read the weights half as often: a tile takes five thirds of the time of one
 // of 32, one tile at a time fits a compute unit, and the launch takes as many rounds of 256 as it has tiles for.  us per call with 32
 // / 64 rows at 8193, 16384, 20000, 24576, 28000 and 32768 environments: 256-256 25.7 / 23.6, 28.0 / 24.4, 37.3 / 41.4, 38.0 / 41.3,
 // 47.1 / 41.3, 48.2 / 41.8; 512-256-128 41.4 / 36.1, 45.0 / 38.7, 62.6 / 66.6, 64.2 / 66.5, 81.3 / 67.1, 83.0 / 70.5.
-static bool takes_64_rows(int B) {
+// What does not get cheaper is the output: a lane draws the noise of its action column for two or four rows, one after the other, and
+// each takes 0.6 - 0.8 us longer where a row has at most four.  With so few actions, or one narrow layer, that and the input are most
+// of a tile: 64 rows take 11 / 6 of the time of 32 (one narrow layer: twice), and a last round of a few tiles half a round.  us at
+// 8193, 16384, 24577, 32768, 40961, 49153, 57344 and 65537 environments: 250-64-4 18.8 / 22.2, 23.1 / 22.1, 34.5 / 37.3, 38.6 / 37.9,
+// 50.0 / 53.0, 58.2 / 59.3, 62.4 / 68.6, 73.7 / 74.4; 20-64-32-4 17.5 / 20.4, 22.2 / 20.5, 32.2 / 33.6, 36.2 / 33.9, 45.7 / 47.1,
+// 52.6 / 51.5, 57.4 / 60.6, 66.7 / 64.5.  The bounds on weights, at 8193: 60-256-256-4 (82 k) 25.7 / 26.4, 108-256-256-256-4 (160 k)
+// 35.3 / 34.4; stochastic, 20-64-32-4 (4 k) 19.7 / 20.8, 60-64-64-4 (8 k) 22.2 / 21.7.
+static bool takes_64_rows(const SplitShape& p, int B, bool sac) {
     auto rounds = [&](int rows) { return ((B + rows - 1) / rows + 255) / 256; };
-    return 5 * rounds(64) < 3 * rounds(32);
+    const bool narrow = p.L == 1 && p.H[0] <= 64, few = p.a <= 4;
+    const double weights = policy_weights(p, sac ? 2 * p.a : p.a);
+    if (!(few && (narrow || weights < (sac ? 4096 : 98304))) && !(narrow && !sac)) return 5 * rounds(64) < 3 * rounds(32);
+    auto halves = [&](int rows) {
+        const int tiles = (B + rows - 1) / rows, last = tiles % 256;
+        return 2 * (tiles / 256) + (last == 0 ? 0 : (last <= 32 ? 1 : 2));
+    };
+    return narrow ? 2 * halves(64) <= halves(32) : 11 * halves(64) < 6 * halves(32);
 }
+// Rows per tile of the Actor step.
+int split_act_rows(const SplitShape& p, int B, bool sac) { return takes_64_rows(p, B, sac) && regular(p) ? 64 : 32; }
 static bool kind_fits(int kind, int w) {
     return kind == SPLIT_FUSED ? w <= 256 : (kind == SPLIT_CHAIN ? w <= 512 : true);
 }
@@ -1837,11 +1859,9 @@ hipError_t split_act_launch(SplitActArgs& a, int kind, hipStream_t stream) {
     SplitShape& p = a.shape;
     const int w = widest(p), aw = a.sac.on ? 2 * p.a : p.a;
     if (!split_shape_ok(p.o, p.a, aw, p.H, p.L) || w > 512) return hipErrorInvalidValue;
-    const bool rows64 = takes_64_rows(a.B) && regular(p);
+    const bool rows64 = split_act_rows(p, a.B, a.sac.on != 0) == 64;
     const size_t lds = plan_lds(p, 1, p.o, false, rows64 ? 4 : 2);
-    double pa = (double)p.o * p.H[0] + (double)p.H[p.L - 1] * aw;
-    for (int l = 1; l < p.L; ++l) pa += (double)p.H[l - 1] * p.H[l];
-    const double flops = 2.0 * a.B * pa;
+    const double flops = 2.0 * a.B * policy_weights(p, aw);
 #define ACT_LAUNCH(KERNEL, VAR, KID)                                                                               \
     do {                                                                                                           \
         if (rows64) SPLIT_LAUNCH_ROWS((KERNEL<VAR, 4>), KID, 64);                                                  \
