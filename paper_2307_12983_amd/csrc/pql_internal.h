@@ -441,7 +441,7 @@ enum SplitClass : int { SPLIT_FUSED = 0, SPLIT_CHAIN = 1, SPLIT_OTHER = 2 };
 hipError_t split_critic_launch(SplitCriticArgs& a, int kind, hipStream_t stream);
 hipError_t split_policy_launch(SplitPolicyArgs& a, int kind, hipStream_t stream);
 hipError_t split_act_launch(SplitActArgs& a, int kind, hipStream_t stream);
-int split_act_rows(const SplitShape& p, int B, bool sac);      // rows per tile it takes
+int split_act_rows(SplitShape p, int B, bool sac);      // rows per tile it takes, 0 if none fits
 
 struct TransposeArgs {
     struct Mat { const float* src; float* dst; int rows, cols, block_begin, pad_; };

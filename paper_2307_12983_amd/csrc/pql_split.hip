@@ -1426,7 +1426,7 @@ template <int TPW, int VAR, int NB = 2>
 __device__ __forceinline__ void act_step(const SplitActArgs& A) {
     warm_args<SplitActArgs>();
     constexpr bool SAC = VAR == VAR_SAC;
-    const auto T = wave_of(0);
+    const auto T = wave_of<NB == 4>(0);          // tiles of 64 rows: states of up to XV steps
     const SplitShape& P = A.shape;
     const int B = A.B, a = P.a, r0 = blockIdx.x * 16 * NB;
     const int aw = SAC ? 2 * a : a;
@@ -1815,8 +1815,16 @@ static bool takes_64_rows(const SplitShape& p, int B, bool sac) {
     };
     return narrow ? 2 * halves(64) <= halves(32) : 11 * halves(64) < 6 * halves(32);
 }
-// Rows per tile of the Actor step.
-int split_act_rows(const SplitShape& p, int B, bool sac) { return takes_64_rows(p, B, sac) && regular(p) ? 64 : 32; }
+// Rows per tile of the Actor step (0: its tiles do not fit) and its LDS plan.  Its input is the states alone; the kernels on tiles of
+// 64 rows have no path for states of more than XV steps.
+static int plan_act(SplitShape& p, int B, bool sac, size_t& lds) {
+    if (p.o <= 32 * XV && takes_64_rows(p, B, sac) && (lds = plan_lds(p, 1, p.o, false, 4)) != 0) return 64;
+    return (lds = plan_lds(p, 1, p.o)) != 0 ? 32 : 0;
+}
+int split_act_rows(SplitShape p, int B, bool sac) {
+    size_t lds;
+    return plan_act(p, B, sac, lds);
+}
 static bool kind_fits(int kind, int w) {
     return kind == SPLIT_FUSED ? w <= 256 : (kind == SPLIT_CHAIN ? w <= 512 : true);
 }
@@ -1859,12 +1867,13 @@ hipError_t split_act_launch(SplitActArgs& a, int kind, hipStream_t stream) {
     SplitShape& p = a.shape;
     const int w = widest(p), aw = a.sac.on ? 2 * p.a : p.a;
     if (!split_shape_ok(p.o, p.a, aw, p.H, p.L) || w > 512) return hipErrorInvalidValue;
-    const bool rows64 = split_act_rows(p, a.B, a.sac.on != 0) == 64;
-    const size_t lds = plan_lds(p, 1, p.o, false, rows64 ? 4 : 2);
+    size_t lds;
+    const int rows = plan_act(p, a.B, a.sac.on != 0, lds);
+    if (rows == 0) return hipErrorInvalidValue;
     const double flops = 2.0 * a.B * policy_weights(p, aw);
 #define ACT_LAUNCH(KERNEL, VAR, KID)                                                                               \
     do {                                                                                                           \
-        if (rows64) SPLIT_LAUNCH_ROWS((KERNEL<VAR, 4>), KID, 64);                                                  \
+        if (rows == 64) SPLIT_LAUNCH_ROWS((KERNEL<VAR, 4>), KID, 64);                                                  \
         SPLIT_LAUNCH((KERNEL<VAR, 2>), KID);                                                                       \
     } while (0)
     if (kind == SPLIT_FUSED) {

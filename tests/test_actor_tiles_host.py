@@ -36,3 +36,10 @@ def test_few_actions_keep_32_rows_where_64_are_slower(num, rows):
 def test_one_narrow_layer_keeps_32_rows_where_64_are_slower(num, rows):
     for hidden, o, a, sac in (((64,), 20, 4, False), ((64,), 250, 4, False), ((32,), 200, 20, False), ((64,), 250, 4, True)):
         assert tile_rows(hidden, o, a, num, sac) == rows
+
+
+@pytest.mark.parametrize("hidden,o,rows", [((512, 64, 256), 256, 64), ((512, 64, 256), 224, 64), ((512, 64, 256), 257, 32), ((256, 256), 256, 64),
+                                           ((512, 512, 512, 256), 225, 64), ((256, 256), 1024, 32)])
+def test_states_alone_decide_not_the_actions_beside_them(hidden, o, rows):
+    for a in (5, 16, 32):
+        assert tile_rows(hidden, o, a, 8193) == rows
