@@ -373,14 +373,18 @@ def test_policy_gradient_no_further_from_float64_than_fp32_products():
 
 
 @pytest.mark.parametrize("case,num", [("narrow", 8193), ("narrow", 16384), ("one_step_inputs", 16321), ("widest", 8193), ("widest", 24577),
-                                      ("stochastic", 8200)])
+                                      ("wide", 8193), ("stochastic", 8200)])
 def test_actor_step_on_tiles_of_64_rows(case, num):
-    """The Actor step on tiles of 64 rows: a last tile of one row, full tiles, inputs of one step and of eight, standardised
-    observations.  To 1e-5 of the actions' scale of 1 (products to 1e-7, tanh and noise as on the other tiles)."""
+    """The Actor step on tiles of 64 rows: a last tile of one row, full tiles, inputs of one step and of eight (in the place of the
+    activations where a layer is 512 wide), standardised observations on both kernels.  To 1e-5 of the actions' scale of 1
+    (products to 1e-7, tanh and noise as on the other tiles)."""
     import torch
+    from test_actor_tiles_host import tile_rows
     w = {"narrow": workload((96, 64), 60, 8, num), "one_step_inputs": workload((64, 256, 32), 7, 3, num, obs_norm=True),
-         "widest": workload((512, 64, 256), 256, 32, num, obs_norm=True), "stochastic": workload((128, 96), 45, 11, num, sac=True)}[case]
+         "widest": workload((512, 64, 256), 256, 32, num, obs_norm=True), "wide": workload((512, 96), 20, 6, num, obs_norm=True),
+         "stochastic": workload((128, 96), 45, 11, num, sac=True)}[case]
     print(case, w.hidden, "N", num, flush=True)
+    assert tile_rows(w.hidden, w.obs_dim, w.act_dim, num, w.sac) == 64
     s = session(w)
     rng = np.random.default_rng(17)
     obs = (1.0 + 2.0 * rng.standard_normal((num, w.obs_dim))).astype(np.float32)
