@@ -1746,8 +1746,8 @@ template <int NN, int TPW, int VAR, int R>
 __global__ __launch_bounds__(ST) void split_policy_kernel(const SplitPolicyArgs) { policy_step<NN, TPW, VAR, R>(kernel_args<SplitPolicyArgs>()); }
 template <int VAR, int NB>
 __global__ __launch_bounds__(ST) void fused_act_kernel(const SplitActArgs) { act_step<1, VAR, NB>(kernel_args<SplitActArgs>()); }
-template <int VAR, int NB>
-__global__ __launch_bounds__(ST) void chain_act_kernel(const SplitActArgs) { act_step<2, VAR, NB>(kernel_args<SplitActArgs>()); }
+template <int NB>
+__global__ __launch_bounds__(ST) void chain_act_kernel(const SplitActArgs) { act_step<2, VAR_PLAIN, NB>(kernel_args<SplitActArgs>()); }
 
 #define SPLIT_LAUNCH_ROWS(KERNEL, KID, ROWS)                                                                                  \
     do {                                                                                                           \
@@ -1871,17 +1871,17 @@ hipError_t split_act_launch(SplitActArgs& a, int kind, hipStream_t stream) {
     const int rows = plan_act(p, a.B, a.sac.on != 0, lds);
     if (rows == 0) return hipErrorInvalidValue;
     const double flops = 2.0 * a.B * policy_weights(p, aw);
-#define ACT_LAUNCH(KERNEL, VAR, KID)                                                                               \
-    do {                                                                                                           \
-        if (rows == 64) SPLIT_LAUNCH_ROWS((KERNEL<VAR, 4>), KID, 64);                                                  \
-        SPLIT_LAUNCH((KERNEL<VAR, 2>), KID);                                                                       \
-    } while (0)
-    if (kind == SPLIT_FUSED) {
-        if (a.sac.on) ACT_LAUNCH(fused_act_kernel, VAR_SAC, KID_FUSED_ACT);
-        ACT_LAUNCH(fused_act_kernel, VAR_PLAIN, KID_FUSED_ACT);
+    if (kind != SPLIT_FUSED) {
+        if (a.sac.on) return hipErrorInvalidValue;          // (no class of stochastic policies takes this kernel)
+        if (rows == 64) SPLIT_LAUNCH_ROWS(chain_act_kernel<4>, KID_CHAIN_ACT, 64);
+        SPLIT_LAUNCH(chain_act_kernel<2>, KID_CHAIN_ACT);
     }
-    if (a.sac.on) ACT_LAUNCH(chain_act_kernel, VAR_SAC, KID_CHAIN_ACT);
-    ACT_LAUNCH(chain_act_kernel, VAR_PLAIN, KID_CHAIN_ACT);
+    if (a.sac.on) {
+        if (rows == 64) SPLIT_LAUNCH_ROWS((fused_act_kernel<VAR_SAC, 4>), KID_FUSED_ACT, 64);
+        SPLIT_LAUNCH((fused_act_kernel<VAR_SAC, 2>), KID_FUSED_ACT);
+    }
+    if (rows == 64) SPLIT_LAUNCH_ROWS((fused_act_kernel<VAR_PLAIN, 4>), KID_FUSED_ACT, 64);
+    SPLIT_LAUNCH((fused_act_kernel<VAR_PLAIN, 2>), KID_FUSED_ACT);
 }
 
 }  // namespace pql
