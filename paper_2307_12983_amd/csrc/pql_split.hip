@@ -431,19 +431,10 @@ __device__ __forceinline__ void store_colsum(float* out, int N, int tile, const 
     if ((T.l15 & 1) == 0 && col < N) out[col] = s;
 }
 
-// The same of the sums over the row blocks.
-template <int NB>
-__device__ __forceinline__ void store_rowsum(float* out, int N, int tile, const f32x4 (&z)[2][NB], const Wv& T) {
-    f32x4 cs[2] = {z[0][0] + z[0][1], z[1][0] + z[1][1]};
-#pragma unroll
-    for (int n = 2; n < NB; ++n) { cs[0] += z[0][n]; cs[1] += z[1][n]; }
-    store_colsum(out, N, tile, cs, T);
-}
-
 // Which of the workgroup's networks and output tiles a wavefront works on.
 struct Share { int net, slot, waves; };      // tiles slot, slot + waves, ...
-template <int NB, typename WV>
-__device__ __forceinline__ void load_ahead(const float* h, int N, f32x4 (&hv)[2][NB], const Share& S, int r0, int B, const WV& T) {
+template <typename WV>
+__device__ __forceinline__ void load_ahead(const float* h, int N, f32x4 (&hv)[2][2], const Share& S, int r0, int B, const WV& T) {
     load_tile(h, N, S.slot, hv, r0, B, T);
 }
 
@@ -542,31 +533,32 @@ __device__ __forceinline__ void forward(f32x4 (&z)[TPW][2][NB], const MatView& W
 // z = (D W^T) * ELU'(.) with the activations h [B][N] read back from memory (each lane reads what it wrote in the forward
 // pass: those of the first tile the caller has requested into hv before the deltas were put into the tile); the deltas go to
 // d_out and their column sums to col_out where given.
-template <int TPW, int NB, int D, typename WV>
-__device__ __forceinline__ void backward(f32x4 (&z)[TPW][2][NB], const MatView& W, const Tile& X, const Share& S, const float (&inv)[NB],
-                                const float* h, float* d_out, float* col_out, int N, int r0, int B, const WV& T, AheadOf<D>& cur,
-                                const Begin& next, f32x4 (&hv)[2][NB]) {
+template <int TPW, typename WV>
+__device__ __forceinline__ void backward(f32x4 (&z)[TPW][2][2], const MatView& W, const Tile& X, const Share& S, const float (&inv)[2],
+                                const float* h, float* d_out, float* col_out, int N, int r0, int B, const WV& T, Ahead& cur,
+                                const Begin& next, f32x4 (&hv)[2][2]) {
     if (S.slot >= W.tiles) request(cur, next, T);
 #pragma unroll
     for (int t = 0; t < TPW; ++t) {
         const int tile = S.slot + t * S.waves;
         if (tile >= W.tiles) { clear(z[t]); continue; }
         const bool more = t + 1 < TPW && tile + S.waves < W.tiles;
-        f32x4 acc[2][NB];
+        f32x4 acc[2][2];
         const float iw = W.inv[tile];
         if (t > 0) load_tile(h, N, tile, hv, r0, B, T);
         mac_steps(acc, W, tile, X, T, 0, 1, cur, more ? begin_of(W, tile + S.waves, 0, 1) : next);
-        float f[NB];
-#pragma unroll
-        for (int n = 0; n < NB; ++n) f[n] = inv[n] * iw;
+        const float f[2] = {inv[0] * iw, inv[1] * iw};
 #pragma unroll
         for (int m = 0; m < 2; ++m)
 #pragma unroll
-            for (int n = 0; n < NB; ++n)
+            for (int n = 0; n < 2; ++n)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) z[t][m][n][r] = acc[m][n][r] * f[n] * delu_h(hv[m][n][r]);
         if (d_out != nullptr) store_tile(d_out, N, tile, z[t], r0, B, T);
-        if (col_out != nullptr) store_rowsum(col_out, N, tile, z[t], T);
+        if (col_out != nullptr) {
+            const f32x4 cs[2] = {z[t][0][0] + z[t][0][1], z[t][1][0] + z[t][1][1]};
+            store_colsum(col_out, N, tile, cs, T);
+        }
     }
 }
 
@@ -791,11 +783,11 @@ __device__ __forceinline__ int policy_forward(const SplitShape& P, const float* 
 
 // Scalar output head: partial dot products of this wavefront's tiles of the last hidden layer with the output weights meet in
 // LDS; q[i][n] = Q_i of this lane's rows (all networks the workgroup carries; one: q[0]).
-template <int NN, int TPW, int NB>
-__device__ __forceinline__ void head_values(const f32x4 (&z)[TPW][2][NB], const f32x4 (&wo)[TPW][2], const Share& S, const SmallMem& M,
-                                   const float (&bias)[NN], float (&q)[NN][NB], const Wv& T) {
+template <int NN, int TPW>
+__device__ __forceinline__ void head_values(const f32x4 (&z)[TPW][2][2], const f32x4 (&wo)[TPW][2], const Share& S, const SmallMem& M,
+                                   const float (&bias)[NN], float (&q)[NN][2], const Wv& T) {
 #pragma unroll
-    for (int n = 0; n < NB; ++n) {
+    for (int n = 0; n < 2; ++n) {
         float s = 0.f;
 #pragma unroll
         for (int t = 0; t < TPW; ++t)
@@ -804,14 +796,14 @@ __device__ __forceinline__ void head_values(const f32x4 (&z)[TPW][2][NB], const 
 #pragma unroll
                 for (int r = 0; r < 4; ++r) s += z[t][m][n][r] * wo[t][m][r];
         s = quarters_sum(s);
-        if (T.q == 0) smem[M.part + (S.net * 16 * NB + 16 * n + T.l15) * S.waves + S.slot] = s;
+        if (T.q == 0) smem[M.part + (S.net * 32 + 16 * n + T.l15) * S.waves + S.slot] = s;
     }
     lds_barrier();
 #pragma unroll
     for (int i = 0; i < NN; ++i)
 #pragma unroll
-        for (int n = 0; n < NB; ++n) {
-            const f32x4* src = reinterpret_cast<const f32x4*>(smem) + (M.part + (i * 16 * NB + 16 * n + T.l15) * S.waves) / 4;
+        for (int n = 0; n < 2; ++n) {
+            const f32x4* src = reinterpret_cast<const f32x4*>(smem) + (M.part + (i * 32 + 16 * n + T.l15) * S.waves) / 4;
             f32x4 v = src[0];
             if (S.waves > 4) v += src[1];
             q[i][n] = (v[0] + v[1]) + (v[2] + v[3]) + bias[i];
@@ -829,12 +821,12 @@ __device__ __forceinline__ void head_weights(f32x4 (&wo)[TPW][2], const float* w
 }
 
 // Hidden layers of the critics on (X): leaves z = h_L in registers.  h_l of layers l <= kept go to h[net][l].
-template <int NN, int TPW, int NB, int D, typename WV>
-__device__ __forceinline__ void critic_forward(f32x4 (&z)[TPW][2][NB], const SplitShape& P, const float* const (*mats)[PQL_MAX_HIDDEN + 1],
+template <int NN, int TPW, typename WV>
+__device__ __forceinline__ void critic_forward(f32x4 (&z)[TPW][2][2], const SplitShape& P, const float* const (*mats)[PQL_MAX_HIDDEN + 1],
                                       int net, const Tile& X, const Tile& H, const Share& S, const SmallMem& M, int kept,
-                                      float* const (*h)[PQL_MAX_HIDDEN + 1], int r0, int B, const WV& T, AheadOf<D>& cur,
-                                      const Begin& next, Rows<NB>& xv, const InputRows& following, bool fetch) {
-    float inv[NB];
+                                      float* const (*h)[PQL_MAX_HIDDEN + 1], int r0, int B, const WV& T, Ahead& cur,
+                                      const Begin& next, Rows<2>& xv, const InputRows& following, bool fetch) {
+    float inv[2];
     row_inv(inv, M.inv, T);
     for (int l = 0; l < P.L; ++l) {
         const int N = P.H[l];
