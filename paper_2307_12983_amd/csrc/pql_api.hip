@@ -269,16 +269,18 @@ int max_hidden(const pql_config* c) {
 // half the compute units: the chain kernels.  Other shapes (any widths up to 1024) run in one launch per step as well,
 // between two bounds.  Below, the launch has too few workgroups: each streams all weights by itself (about 50 GB/s), where a
 // launch per layer spreads them over the chip.  Measured per critic update, one launch against a launch per layer, at
-// 64 / 520 / 1024 / 2048 / 4096 / 8000 rows: 1024-512-256 335 / 341 / 341 / 351 / 380 / 493 us against 263 / 288 / 312 / 413 /
-// 358 / 616; 512-512-512 254 / 259 / 261 / 276 / 293 / 373 against 249 / 258 / 279 / 353 / 314 / 516; 300-136-128 93 / 99 /
-// 100 / 102 / 110 / 131 against 137 / 143 / 147 / 165 / 141 / 212: the line is at 2048 rows, and at no batch for critics of up
-// to 2^18 weights.
+// 64 / 520 / 1024 / 2048 / 4096 / 8000 rows: 1024-512-256 with 60 states 307 / 314 / 311 / 319 / 355 / 479 us against 263 / 289 /
+// 313 / 416 / 378 / 644, with 211 states 366 / 374 / 378 / 399 / 442 / 600 against 280 / 312 / 346 / 482 / 440 / 724; 512-512-512
+// 233 / 239 / 240 / 252 / 282 / 372 against 249 / 259 / 281 / 355 / 328 / 539; 300-136-128 83 / 88 / 87 / 89 / 96 / 113 against
+// 138 / 144 / 148 / 167 / 145 / 217.  The line at 2048 rows, and at no batch for critics of up to 2^18 weights, is that of the widest
+// critics; narrower ones (512-512-512) and policy updates (1024-512-256 at 64 rows 271 us against 361) would gain below it too.
 // Above 256 row tiles the scalar deterministic variant goes layer by layer unless the chain kernels' shape rule takes it.  That
 // rule and the bound are older than the kernels they now choose between, and the measurements do not support them: per critic
-// update at 8192 / 16384 / 32768 rows, one launch against a launch per layer, 1024-512-256 with 60 states 500 / 998 / 1960 us
-// against 636 / 1172 / 2200, with 211 states 628 / 1220 / 2438 against 720 / 1310 / 2464; 512-512-512 389 / 726 / 1428 against
-// 499 / 880 / 1650; 480-480-256 306 / 597 / 1120 against 436 / 728 / 1342; 300-136-128 128 / 231 / 462 against 209 / 352 / 669;
-// 200-100 72 / 120 / 216 against 144 / 230 / 416.  (Networks with a layer above 1024 have no other path.)
+// update at 8192 / 16384 / 32768 rows, one launch against a launch per layer, 1024-512-256 with 60 states 489 / 952 / 1894 us
+// against 628 / 1179 / 2218, with 211 states 606 / 1171 / 2336 against 707 / 1309 / 2514; 512-512-512 383 / 739 / 1395 against
+// 485 / 892 / 1658; 480-480-256 299 / 594 / 1086 against 409 / 737 / 1339; 300-136-128 114 / 201 / 395 against 202 / 347 / 649;
+// 200-100 68 / 110 / 201 against 142 / 229 / 414; policy updates alike (1024-512-256 with 211 states at 32768 rows 1797 against 1907,
+// 200-100 163 against 337).  (Networks with a layer above 1024 have no other path.)
 constexpr int CHAIN_MIN_TILES = 128;
 constexpr int LAYERED_MIN_TILES = 256;
 constexpr int SPLIT_MIN_TILES = 64;

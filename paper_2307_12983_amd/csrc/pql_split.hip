@@ -16,7 +16,7 @@
 //
 // A workgroup (eight wavefronts, two per SIMD) owns 32 batch rows and carries them through a whole chain of layers, the
 // twin critics side by side (four wavefronts each) where the layers are at most 512 wide, one after the other up to 1024.
-// (Sixteen wavefronts of 128 registers spilled: 132 us for the update at 256-256 and batch 8192, 99.6 with eight.)  A
+// (Sixteen wavefronts of 128 registers, weights one step ahead: 68 us per launch at 256-256 and 8192 rows, 55 with eight.)  A
 // wavefront owns 32 output columns of one network.  The product is computed as W^T X^T (weights are the A operand): a lane
 // then holds four consecutive output columns of one batch row, which is the order in which the next layer's B operand
 // wants them, so an epilogue packs its results with no exchange between lanes and writes them to LDS as 16-byte pieces,
@@ -24,8 +24,9 @@
 //
 // What bounds it: with 32 rows per workgroup the weights (4 bytes each, once per workgroup) come from L2 at about 50 bytes per clock
 // and compute unit (a loop that only reads reaches 56 with all compute units running), more than twice the time of the matrix work: a
-// paired 256 x 256 layer takes 5 us, where the fp32 MFMA kernels take 18.8.  That is half of the launch; the other half is what
-// lies between the products, phases in which a wavefront waits for LDS, barriers and memory or issues one instruction every nine cycles.
+// paired 256 x 256 layer takes 5 us, where the fp32 MFMA kernels take 18.8.  That is a third of the launch (2.3 MB, 18 - 20 of 55 us at
+// 256-256 and 8192 rows); the rest is what lies between the products, phases in which a wavefront waits for LDS, barriers and memory or
+// issues one instruction every nine cycles.
 //
 // The weights are brought into fragment order by split_weights_kernel at the start of every call (zero-padded to whole
 // tiles, so any layer width works): a lane's operand is one 16-byte load, a wavefront's a contiguous kilobyte.
@@ -249,7 +250,9 @@ struct Wv { int tid, lane, wave, l15, q; unsigned hi, lo; };        // hi, lo: t
 // multiples of four): a wavefront issues an instruction every nine cycles (4.5 where two share a SIMD), and the tests, scalars and
 // registers kept (and spilled) for paths not taken lengthen every phase.  us per launch with / without them: critic update 256-256
 // 58 / 55, policy update 51 / 48, critic update 512-256-128 125 / 120, 64-64 at 256 rows 23.6 / 22; with the input in the place of
-// the activations critic update 1024-512-256 at 4096 rows 364 / 328, policy update 512-512-256 at 16384 385 / 373.
+// the activations critic update 1024-512-256 at 4096 rows 364 / 328, policy update 512-512-256 at 16384 385 / 373.  Kernels with the
+// critics one after the other still spill: 76 (critic) and 53 - 63 (policy) vector registers, 140 - 148 bytes of scratch a lane, and
+// with everything 191 - 204 and 181 - 197.
 enum Shapes : int { GENERAL = 0, REGULAR = 1, REGULAR_ALIAS = 2 };      // REGULAR_ALIAS: the input may lie in the place of the activations
 template <bool R>
 struct WvOf : Wv { static constexpr bool regular = R; };
@@ -367,7 +370,10 @@ __device__ __forceinline__ void clear(f32x4 (&z)[2][NB]) {
 // The 32 x 32 results of one tile to / from a row-major [B][N] array: this lane's rows r0 + 16 n + l15, columns
 // 32 tile + 16 m + 4 q .. + 3.  Through a descriptor of the tile's rows, which drops what lies past them: no branches, so that all
 // requests leave together and none waits for another (as masked loads the compiler waited for each before the next one:
-// four round trips a tile).
+// four round trips a tile).  Widths that are no multiples of four pay for the branch-free form with requests past the descriptor: with
+// masked loads policy updates of such networks above 512 wide were 3 - 5 % faster (514-31 at 4096 rows 115.5 / 118.8 us, 1023-510-255
+// 359 / 370, stochastic 641-201 at 3000 rows 175 / 184), all others slower (critic updates 127.4 / 126.3, 421 / 419, 191 / 186; 301-62
+// at 4096 rows critic 82.3 / 76.1, policy 76.0 / 72.1).
 constexpr int NOWHERE = 0x7ffffffc;          // a buffer offset past any descriptor used here: a load returns zero, a store is dropped
 template <int NB>
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t tile_rows(const float* g, int N, int r0, int B) {
@@ -1741,7 +1747,7 @@ __global__ __launch_bounds__(ST) void fused_act_kernel(const SplitActArgs) { act
 template <int NB>
 __global__ __launch_bounds__(ST) void chain_act_kernel(const SplitActArgs) { act_step<2, VAR_PLAIN, NB>(kernel_args<SplitActArgs>()); }
 
-#define SPLIT_LAUNCH_ROWS(KERNEL, KID, ROWS)                                                                                  \
+#define SPLIT_LAUNCH_ROWS(KERNEL, KID, ROWS)                                                                       \
     do {                                                                                                           \
         static LdsLimit configured;                                                                                \
         const hipError_t le = set_lds_limit(reinterpret_cast<const void*>(KERNEL), lds, configured);               \
